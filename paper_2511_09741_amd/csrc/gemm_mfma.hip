@@ -6,11 +6,8 @@
 //
 // One 256-thread workgroup (4 wavefronts, one per SIMD) owns a 256x256 output tile; each
 // wavefront owns 128x128 of it as 4x4 MFMA tiles (256 fp32 accumulators per lane).  K advances in
-// steps of 64 through a double-buffered LDS tile pair (2 x 64 KiB), filled through registers so the
-// next step's global loads are in flight while the current step multiplies.  That is the general
-// kernel (any K % 8 == 0).  Two pipelined kernels with direct global->LDS loads take the shapes the
-// layer has: 64-deep steps for the NT and NN forms when K % 64 == 0, 32-deep steps for TN and for
-// K % 32 == 0 (namespace v2 below).
+// steps of 64 (NT and NN) or 32 (TN) through an LDS ring filled by direct global->LDS loads.  Any K:
+// the last step's loads are clamped into the matrix and its fragments beyond K zeroed in registers.
 //
 // LDS layouts.  A K-contiguous operand is stored [row][64] with its 16-byte chunks XOR-swizzled by
 // (row>>1)&7: every MFMA operand (8 consecutive k of one row) is one ds_read_b128 and 16
@@ -22,6 +19,7 @@
 // Workgroup ids are remapped (gemm_tile_of_block) so that the 32 tiles an XCD works on at a time are an 8 x 4
 // block sharing operand panels in that XCD's L2, and the 256 tiles of the whole chip about a 16 x 16 block
 // sharing them in the memory-side cache.
+#include <string.h>
 #include <type_traits>
 
 #include "dev_common.h"
@@ -31,206 +29,8 @@ namespace taw {
 
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BM = 256, BN = 256;
 constexpr int kThreads = 256;
-constexpr int kTileElems = 256 * BK;               // one operand tile, either layout
-constexpr int kStageElems = 2 * kTileElems;        // A tile + B tile
-constexpr size_t kLdsBytes = 2 * (size_t)kStageElems * sizeof(bf16_t);  // 128 KiB
-
-typedef bf16_t __attribute__((address_space(3))) lds_bf16_t;
-
-__device__ __forceinline__ s16x4_t lds_read_tr(const bf16_t* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p));
-}
-
-// ---- global -> registers: 8 chunks of 16 bytes per thread and operand ------------------------
-// KC (K-contiguous): tile = 256 rows x 64 k.  thread -> chunk c = tid&7, rows (tid>>3) + 32 i.
-// NC (contiguous along the output dim): tile = 64 k x 256 cols.  thread -> chunk c = tid&31, k rows (tid>>5) + 8 i.
-template <bool KC>
-struct TileLoader {
-  const bf16_t* base;   // tile origin at k = 0
-  int off[8];           // per-chunk element offsets from base (rows/cols clamped into the matrix)
-  int64_t kstep;        // elements to advance per K step
-  int kfirst;           // KC: this thread's k offset inside a step; NC: first k row of this thread
-  __device__ __forceinline__ void init(const bf16_t* mat, int64_t ld, int64_t origin, int64_t extent, int tid) {
-    if (KC) {
-      const int c = tid & 7, r0 = tid >> 3;
-      base = mat + origin * ld;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        int64_t r = r0 + 32 * i;
-        if (origin + r >= extent) r = extent - 1 - origin;
-        off[i] = (int)(r * ld) + c * 8;
-      }
-      kstep = BK;
-      kfirst = c * 8;
-    } else {
-      const int c = tid & 31, k0 = tid >> 5;
-      int64_t col = origin + c * 8;
-      if (col >= extent) col = 0;
-      base = mat + col;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) off[i] = (int)((k0 + 8 * i) * ld);
-      kstep = BK * ld;
-      kfirst = k0;
-    }
-  }
-  // issues the loads of the step starting at k0 (addresses of chunks at or beyond K are redirected
-  // to a valid place); nothing here touches the loaded registers, so the loads stay in flight
-  // while the caller multiplies the previous step
-  __device__ __forceinline__ void load(u32x4_t (&regs)[8], int64_t k0, int64_t K) const {
-    const bf16_t* p = base + (k0 / BK) * kstep;
-    if (KC) {
-      const int adj = (k0 + kfirst < K) ? 0 : kfirst;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) regs[i] = *reinterpret_cast<const u32x4_t*>(p + (off[i] - adj));
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bool valid = k0 + kfirst + 8 * i < K;
-        regs[i] = *reinterpret_cast<const u32x4_t*>(valid ? p + off[i] : base);
-      }
-    }
-  }
-  // registers -> LDS tile of the step that started at k0; chunks at or beyond K are written as zeros
-  __device__ __forceinline__ void store(bf16_t* tile, const u32x4_t (&regs)[8], int tid, int64_t k0, int64_t K) const {
-    const u32x4_t zero = {0u, 0u, 0u, 0u};
-    if (KC) {
-      const int c = tid & 7, r0 = tid >> 3;
-      const bool valid = k0 + kfirst < K;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int r = r0 + 32 * i;
-        *reinterpret_cast<u32x4_t*>(tile + r * BK + ((c ^ ((r >> 1) & 7)) << 3)) = valid ? regs[i] : zero;
-      }
-    } else {
-      const int c = tid & 31, kr = tid >> 5;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int k = kr + 8 * i;
-        const bool valid = k0 + k < K;
-        *reinterpret_cast<u32x4_t*>(tile + k * 256 + ((c ^ ((k & 3) << 2)) << 3)) = valid ? regs[i] : zero;
-      }
-    }
-  }
-};
-
-// ---- LDS -> MFMA operand: 8 bf16 of k = 16 ks + 8 (lane>>5) + 0..7 for row/col x0 + (lane&31) ---
-template <bool KC>
-__device__ __forceinline__ bf16x8_t read_frag(const bf16_t* tile, int x0, int ks, int lane) {
-  if (KC) {
-    const int r = x0 + (lane & 31);
-    const int c = 2 * ks + (lane >> 5);
-    return *reinterpret_cast<const bf16x8_t*>(tile + r * BK + ((c ^ ((r >> 1) & 7)) << 3));
-  } else {
-    const int blk = lane >> 4, i = lane & 15;
-    const int n = x0 + 16 * (blk & 1) + 4 * (i & 3);
-    const int kb = 16 * ks + 8 * (blk >> 1) + (i >> 2);
-    union { s16x4_t h[2]; bf16x8_t v; } u;
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int k = kb + 4 * r;
-      u.h[r] = lds_read_tr(tile + k * 256 + (((n >> 3) ^ ((k & 3) << 2)) << 3) + (n & 7));
-    }
-    return u.v;
-  }
-}
-
-template <int MODE, bool C_F32>
-__global__ void __launch_bounds__(kThreads, 1)
-gemm_mfma_kernel(int64_t M, int64_t N, int64_t K, const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B,
-                 int64_t ldb, void* __restrict__ Cv, int64_t ldc, int accumulate, const void* __restrict__ Rv, int64_t ldr,
-                 int tiles_m, int tiles_n) {
-  constexpr bool A_KC = (MODE != GEMM_TN);
-  constexpr bool B_KC = (MODE == GEMM_NT);
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  bf16_t* lds = reinterpret_cast<bf16_t*>(lds_raw);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // ---- XCD-aware tile id
-  int tm, tn;
-  gemm_tile_of_block((int)blockIdx.x, tiles_m, tiles_n, &tm, &tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-
-  TileLoader<A_KC> la;
-  TileLoader<B_KC> lb;
-  la.init(A, lda, m0, M, tid);
-  lb.init(B, ldb, n0, N, tid);
-
-  const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  f32x16_t acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  u32x4_t ra[8], rb[8];
-  la.load(ra, 0, K);
-  lb.load(rb, 0, K);
-  la.store(lds, ra, tid, 0, K);
-  lb.store(lds + kTileElems, rb, tid, 0, K);
-  __syncthreads();
-
-  const int64_t nk = (K + BK - 1) / BK;
-  for (int64_t kt = 0; kt < nk; ++kt) {
-    const bf16_t* sa = lds + (kt & 1) * kStageElems;
-    const bf16_t* sb = sa + kTileElems;
-    const bool more = kt + 1 < nk;
-    if (more) {
-      la.load(ra, (kt + 1) * BK, K);
-      lb.load(rb, (kt + 1) * BK, K);
-    }
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      bf16x8_t fa[4], fb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) fa[i] = read_frag<A_KC>(sa, wm + 32 * i, ks, lane);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) fb[j] = read_frag<B_KC>(sb, wn + 32 * j, ks, lane);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);     // block (i, j) transposed, see stage_rows
-    }
-    if (more) {
-      bf16_t* da = lds + ((kt + 1) & 1) * kStageElems;
-      la.store(da, ra, tid, (kt + 1) * BK, K);
-      lb.store(da + kTileElems, rb, tid, (kt + 1) * BK, K);
-    }
-    __syncthreads();
-  }
-
-  // ---- epilogue: the blocks are transposed (see stage_rows): accumulator register r of lane l is
-  // C[row0 + (l&31)][col0 + 8 (r/4) + 4 (l>>5) + r%4]
-  const int lrow = lane & 31, lcol = 4 * (lane >> 5);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = m0 + wm + 32 * i + lrow;
-    if (row >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t col = n0 + wn + 32 * j + 8 * (r >> 2) + lcol + (r & 3);
-        if (col >= N) continue;
-        float v = acc[i][j][r];
-        if (C_F32) {
-          float* C = static_cast<float*>(Cv);
-          if (Rv) v += static_cast<const float*>(Rv)[row * ldr + col];
-          if (accumulate) v += C[row * ldc + col];
-          C[row * ldc + col] = v;
-        } else {
-          bf16_t* C = static_cast<bf16_t*>(Cv);
-          if (Rv) v += (float)static_cast<const bf16_t*>(Rv)[row * ldr + col];
-          if (accumulate) v += (float)C[row * ldc + col];
-          C[row * ldc + col] = (bf16_t)v;
-        }
-      }
-    }
-  }
-}
 
 // =============================================================================== pipelined kernel
 // Same tile shape and operand layouts, different data movement: K advances in steps of 32 through
@@ -246,7 +46,10 @@ gemm_mfma_kernel(int64_t M, int64_t N, int64_t K, const bf16_t* __restrict__ A, 
 // fragment read, 1 direct load}, each closed by a scheduling barrier: one wavefront per SIMD
 // issues in order, so the matrix pipe only stays busy if the LDS reads, the loads and their few
 // scalar instructions sit in the shadow of the MFMAs instead of in front of them.
-// Needs K % 32 == 0 (the launcher sends other K to the kernel above).
+// A K that is no multiple of the step: the rows / chunks of the last tile beyond K are loaded from its last
+// valid one (clamp_tail, before that tile's loads are issued) and zeroed in LDS once it has landed (zero_tail),
+// so no step is changed.  (A separate kernel staged through registers served these K before: 44 tiles of a
+// 4503-token weight gradient took 212 us in it.)
 namespace v2 {
 
 constexpr int BK2 = 32;
@@ -280,6 +83,11 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+// zeroes [from, to) bytes of LDS at p, in 16-byte pieces, all threads of the workgroup together
+__device__ __forceinline__ void zero_lds(unsigned char* p, int from, int to, int tid) {
+  for (int o = from + 16 * tid; o < to; o += 16 * kThreads) *reinterpret_cast<u32x4_t*>(p + o) = u32x4_t{0u, 0u, 0u, 0u};
 }
 
 // One operand of the tile: where its direct loads come from and where its MFMA fragments sit in LDS.
@@ -332,6 +140,17 @@ struct Operand {
       }
     }
   }
+  // the next loads are those of the last K step, of which only `rem` rows / columns of k exist
+  __device__ __forceinline__ void clamp_tail(int rem, int64_t ld, int lane, int wave) {
+    static_assert(!KC, "the 32-deep loop runs the TN form only");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = 2 * (4 * i + wave) + (lane >> 5);
+      if (k >= rem) goff[i] -= (unsigned)((k - (rem - 1)) * ld * 2);
+    }
+  }
+  // zeroes the k rows of the operand tile at op that are not among the first `rem`
+  static __device__ __forceinline__ void zero_tail(unsigned char* op, int rem, int tid) { zero_lds(op, rem * 512, kOpBytes, tid); }
   // direct load number i (0..3) of the current K step into the operand tile at LDS address lds_op
   __device__ __forceinline__ void dma(int i, unsigned lds_op, int wave) const { lds_dma16(base, goff[i], lds_op + (4 * i + wave) * 1024); }
   __device__ __forceinline__ void advance() { base += kstep; }
@@ -348,6 +167,26 @@ struct Operand {
     }
   }
 };
+
+// Zeroes the accumulators here (in the shadow of the first loads) and hides from the compiler that they are zero: known zeros are
+// kept in a second set of registers for the loop that may not run, and every accumulator is copied after it (0.4 us per tile).
+__device__ __forceinline__ void zero_acc(f32x16_t (&acc)[4][4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      asm volatile("" : "+a"(acc[i][j]));
+    }
+}
+
+// x == 0 as the compiler cannot know it (x uniform): a loop's exceptional trip, tested this way, stays a branch in the loop.  (Left
+// visible, the compiler peels that trip off and copies all 256 accumulators between registers on the way in and out.)
+__device__ __forceinline__ bool opaque_zero(int x) {
+  asm volatile("" : "+s"(x));
+  return x == 0;
+}
 
 // order in which a half step multiplies its 4 x 4 fragment pairs, two per group, and the fragment
 // each group reads for the following half step (0..3 = A fragment, 4..7 = B fragment): every
@@ -378,7 +217,7 @@ __device__ __forceinline__ void stage_rows(const f32x16_t& blk, float* stg_blk, 
 // Columns below rot_cols are heads of 128 whose adjacent pairs (2i, 2i+1) are rotated by the angle of
 // (row % S, i); table [S][64][2] fp32 of (cos, sin).  A lane holds 8 consecutive columns of a row here,
 // i.e. 4 whole pairs, in fp32: the fused qkv projection then needs no rotary pass of its own, and q, k
-// are rounded to bf16 once.  rot_cols is a multiple of the tile width, so a tile rotates wholly or not.
+// are rounded to bf16 once.  rot_cols is a multiple of 128.
 constexpr int kEpiNone = 0, kEpiRope = 1;
 struct EpiArgs {
   const float* table;
@@ -408,7 +247,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
     __builtin_amdgcn_wave_barrier();
     char* ci = cw + (int64_t)(32 * i) * ldc * ES;
     const char* ri = rw ? rw + (int64_t)(32 * i) * ldr * ES : nullptr;
-    const bool rotate = EPI == kEpiRope && n0 < ea.rot_cols;                                   // workgroup-uniform
+    const bool rotate = EPI == kEpiRope && n0 + wn < ea.rot_cols;                              // wavefront-uniform: 128 columns are one head
     const int pos0 = EPI == kEpiRope ? (int)((m0 + wm + 32 * i + rr0) % ea.S) : 0;             // this lane's row in pass 0
     const int pair0 = ((wn + ch * 8) & 127) >> 1;                                              // first of its 4 pairs inside the head
 #pragma unroll
@@ -425,7 +264,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
         if constexpr (EPI == kEpiRope) {
           if (rotate) {
             int pos = pos0 + it * RPP;
-            pos = pos >= ea.S ? pos - ea.S : pos;      // rows of a pass-group never span more than one sequence boundary (S >= 32)
+            pos = pos >= ea.S ? pos - ea.S : pos;      // 32 rows never span more than one sequence boundary (S >= 32)
             const float* tb = ea.table + ((int64_t)pos * 64 + pair0) * 2;
             const f32x4_t cs0 = *reinterpret_cast<const f32x4_t*>(tb), cs1 = *reinterpret_cast<const f32x4_t*>(tb + 4);
             const float cc[4] = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn[4] = {cs0[1], cs0[3], cs1[1], cs1[3]};
@@ -458,113 +297,101 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
   }
 }
 
-// ---- epilogue shared by the pipelined kernels: 32 x 128 accumulator blocks -> fp32 staging in LDS
-// ([32 rows][132] per wavefront, in the ring, which every wavefront has finished reading) ->
-// 16-byte accesses that cover whole row segments of C
+// the rotation of 4 or 8 consecutive columns col .. of row `row`, in place
+template <int V>
+__device__ __forceinline__ void rotate_chunk(float (&v)[V], int64_t row, int64_t col, const EpiArgs& ea) {
+  if (col >= ea.rot_cols) return;
+  const float* tb = ea.table + ((row % ea.S) * 64 + ((col & 127) >> 1)) * 2;
+#pragma unroll
+  for (int e = 0; e < V / 2; ++e) {
+    const float a = v[2 * e], b2 = v[2 * e + 1], c = tb[2 * e], sn = tb[2 * e + 1];
+    v[2 * e] = a * c - b2 * sn;
+    v[2 * e + 1] = a * sn + b2 * c;
+  }
+}
+
+// ---- epilogue of a wavefront's (32 TM) x (32 TN) block at (mw, nw), any part of it possibly outside C: 32-row slices -> fp32
+// staging rows in LDS (one region per wavefront, in the ring, which every wavefront has finished reading) -> 16-byte accesses that
+// cover whole row segments of C, four at a time so that what they read (residual, accumulated C) is fetched together; element by
+// element where C's or R's rows are not 16-byte aligned.  Loops over the staged slice stay loops: unrolled, this path of the 256 x 256
+// tile would be most of a kernel's code.
+template <bool C_F32, int TM, int TN, int EPI = kEpiNone>
+__device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
+                                              int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
+                                              const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
+  typedef typename std::conditional<C_F32, float, bf16_t>::type T;
+  constexpr int SLD = 32 * TN + 4, V = C_F32 ? 4 : 8, CPR = 32 * TN / V, U = CPR / 2 < 4 ? CPR / 2 : 4;      // CPR: chunks of V columns per row
+  float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
+  T* C = static_cast<T*>(Cv);
+  const T* R = static_cast<const T*>(Rv);
+  const bool vec = EPI != kEpiNone || ((N & (V - 1)) == 0 && (ldc & (V - 1)) == 0 && (!R || (ldr & (V - 1)) == 0));      // uniform
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) stage_rows<SLD>(acc[i][j], stg + 32 * j, lane);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+    const int64_t row0 = mw + 32 * i;
+    if (vec) {
+#pragma unroll 1
+      for (int it = 0; it < CPR / 2; it += U) {
+        Vec<T, V> r[U], c[U];
+        int64_t row[U], col[U];
+        bool in[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int idx = (it + u) * 64 + lane;
+          row[u] = row0 + idx / CPR;
+          col[u] = nw + idx % CPR * V;
+          in[u] = row[u] < M && col[u] < N;
+          if (in[u] && R) r[u].load(R + row[u] * ldr + col[u]);
+          if (in[u] && accumulate) c[u].load(C + row[u] * ldc + col[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (!in[u]) continue;
+          const int idx = (it + u) * 64 + lane;
+          const float* sp = stg + idx / CPR * SLD + idx % CPR * V;
+          float v[V];
+#pragma unroll
+          for (int e = 0; e < V; ++e) v[e] = sp[e];
+          if constexpr (EPI == kEpiRope) rotate_chunk(v, row[u], col[u], ea);
+          Vec<T, V> o;
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            if (R) v[e] += r[u].get(e);
+            if (accumulate) v[e] += c[u].get(e);
+            o.set(e, v[e]);
+          }
+          o.store(C + row[u] * ldc + col[u]);
+        }
+      }
+    } else {
+#pragma unroll 1
+      for (int e = lane; e < 32 * 32 * TN; e += 64) {
+        const int64_t row = row0 + e / (32 * TN), col = nw + e % (32 * TN);
+        if (row < M && col < N) {
+          float x = stg[e / (32 * TN) * SLD + e % (32 * TN)];
+          if (R) x += (float)R[row * ldr + col];
+          if (accumulate) x += (float)C[row * ldc + col];
+          C[row * ldc + col] = (T)x;
+        }
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// ---- epilogue of a 256 x 256 tile
 template <bool C_F32, int EPI = kEpiNone>
 __device__ __forceinline__ void store_tile(const f32x16_t (&acc)[4][4], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                            int wm, int wn, int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
-                                           const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0}) {
-  if constexpr (EPI != kEpiNone) {      // the host only asks for a fused epilogue when every tile lies inside the matrix
-    store_tile_full<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea);
-    return;
-  }
-  {
-    constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
-    const bool full = m0 + BM <= M && n0 + BN <= N && (ldc & V) == 0 && (!Rv || (ldr & V) == 0);    // workgroup-uniform
-    if (full) {
-      store_tile_full<C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr);
-      return;
-    }
-  }
-  if (C_F32) {
-    float* C = static_cast<float*>(Cv);
-    const float* R = static_cast<const float*>(Rv);
-    constexpr int SLD = 132;
-    float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
-    const bool vec_ok = (ldc & 3) == 0 && (!R || (ldr & 3) == 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) stage_rows<SLD>(acc[i][j], stg + 32 * j, lane);
-      __builtin_amdgcn_s_waitcnt(0xc07f);
-      __builtin_amdgcn_wave_barrier();
-      // 32 rows x 128 cols = 1024 chunks of 4 columns; lane -> (row = idx >> 5, chunk = idx & 31): half a
-      // wavefront covers 512 contiguous bytes of a row
-#pragma unroll
-      for (int it = 0; it < 16; ++it) {
-        const int idx = it * 64 + lane, rr = idx >> 5, ch = idx & 31;
-        const int64_t row = m0 + wm + 32 * i + rr, col = n0 + wn + ch * 4;
-        if (row < M && col < N) {
-          f32x4_t v = *reinterpret_cast<const f32x4_t*>(stg + rr * SLD + ch * 4);
-          float* cp = C + row * ldc + col;
-          if (col + 4 <= N && vec_ok) {
-            if (R) v += *reinterpret_cast<const f32x4_t*>(R + row * ldr + col);
-            if (accumulate) v += *reinterpret_cast<const f32x4_t*>(cp);
-            *reinterpret_cast<f32x4_t*>(cp) = v;
-          } else {
-            for (int e = 0; e < 4 && col + e < N; ++e) {
-              float x = v[e];
-              if (R) x += R[row * ldr + col + e];
-              if (accumulate) x += cp[e];
-              cp[e] = x;
-            }
-          }
-        }
-      }
-      __builtin_amdgcn_s_waitcnt(0xc07f);
-      __builtin_amdgcn_wave_barrier();
-    }
-  } else {
-    // fp32 staging in LDS ([32 rows][132] per wavefront), then 16-byte coalesced bf16 rows
-    bf16_t* C = static_cast<bf16_t*>(Cv);
-    const bf16_t* R = static_cast<const bf16_t*>(Rv);
-    constexpr int SLD = 132;
-    float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) stage_rows<SLD>(acc[i][j], stg + 32 * j, lane);
-      __builtin_amdgcn_s_waitcnt(0xc07f);
-      __builtin_amdgcn_wave_barrier();
-      // 32 rows x 128 cols = 512 chunks of 8 columns; lane -> (row = idx >> 4, chunk = idx & 15)
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int idx = it * 64 + lane, rr = idx >> 4, ch = idx & 15;
-        const int64_t row = m0 + wm + 32 * i + rr, col = n0 + wn + ch * 8;
-        if (row < M && col < N) {
-          const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(stg + rr * SLD + ch * 8);
-          const f32x4_t v1 = *reinterpret_cast<const f32x4_t*>(stg + rr * SLD + ch * 8 + 4);
-          float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-          if (col + 8 <= N && (ldc & 7) == 0 && (!R || (ldr & 7) == 0)) {
-            if (R) {
-              const bf16x8_t rv = *reinterpret_cast<const bf16x8_t*>(R + row * ldr + col);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] += (float)rv[e];
-            }
-            if (accumulate) {
-              const bf16x8_t cv = *reinterpret_cast<const bf16x8_t*>(C + row * ldc + col);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] += (float)cv[e];
-            }
-            bf16x8_t o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
-            *reinterpret_cast<bf16x8_t*>(C + row * ldc + col) = o;
-          } else {
-            for (int e = 0; e < 8 && col + e < N; ++e) {
-              float x = v[e];
-              if (R) x += (float)R[row * ldr + col + e];
-              if (accumulate) x += (float)C[row * ldc + col + e];
-              C[row * ldc + col + e] = (bf16_t)x;
-            }
-          }
-        }
-      }
-      __builtin_amdgcn_s_waitcnt(0xc07f);
-      __builtin_amdgcn_wave_barrier();
-    }
-  }
+                                           const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
+  constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
+  const bool full = m0 + BM <= M && n0 + BN <= N && (ldc & V) == 0 && (!Rv || (ldr & V) == 0) && (EPI == kEpiNone || ea.S >= 32);    // workgroup-uniform
+  if (full) store_tile_full<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea);
+  else store_checked<C_F32, 4, 4, EPI>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, Cv, ldc, accumulate, Rv, ldr, ea);
 }
 
 // one GEMM as the pipelined kernels take it
@@ -581,7 +408,7 @@ struct GemmArgs {
   int64_t ldr;
   int tiles_m, tiles_n;
   EpiArgs epi;            // fused epilogues only
-  // TN only: the contraction cut into `splits` ranges of k_chunk rows, one workgroup per (range, tile); range s writes its
+  // the contraction cut into `splits` ranges of k_chunk (a multiple of 64), one workgroup per (range, tile); range s writes its
   // partial product, dense [M][N] fp32, to part + s * M * N, and a second kernel sums the ranges into C in a fixed order
   int splits;
   int64_t k_chunk;
@@ -628,17 +455,13 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
-  f32x16_t acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int nk = (int)(K / BK2);
+  const int nk = (int)((K + BK2 - 1) / BK2), rem = (int)(K - (int64_t)(nk - 1) * BK2);     // rem: k rows of the last step
   // ---- prologue: tiles 0, 1, 2 in flight; tiles 0 and 1 landed and visible before the loop
   for (int t = 0; t < 3 && t < nk; ++t) {
+    if (t + 1 == nk) {
+      oa.clamp_tail(rem, lda, lane, wave);
+      ob.clamp_tail(rem, ldb, lane, wave);
+    }
     const unsigned st = lds0 + t * kStageBytes;
 #pragma unroll
     for (int i = 0; i < 4; ++i) oa.dma(i, st, wave);
@@ -647,8 +470,18 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
     oa.advance();
     ob.advance();
   }
+  f32x16_t acc[4][4];
+  zero_acc(acc);
   if (nk >= 3) wait_vmcnt<8>(); else wait_vmcnt<0>();
   stage_barrier();
+  auto zero_last = [&]() {
+    unsigned char* st = lds2 + ((nk - 1) & (kStages - 1)) * kStageBytes;
+    oa.zero_tail(st, rem, tid);
+    ob.zero_tail(st + kOpBytes, rem, tid);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    stage_barrier();
+  };
+  if (nk < 3 && rem != BK2) zero_last();
   __builtin_amdgcn_sched_barrier(0);
 
   bf16x8_t fa[2][4], fb[2][4];     // [MFMA k-step of the tile][fragment]
@@ -702,10 +535,21 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
   // compiler's lgkmcnt bookkeeping inside the loop only has the loop's own LDS reads to consider
   __builtin_amdgcn_s_waitcnt(0xc07f);
   int kt = 0;
-  for (; kt + 3 < nk; ++kt) step(kt, std::true_type{});
+  for (; kt + 3 < nk; ++kt) {
+    if (opaque_zero(kt + 4 - nk)) {      // this step loads the last tile
+      oa.clamp_tail(rem, lda, lane, wave);
+      ob.clamp_tail(rem, ldb, lane, wave);
+    }
+    step(kt, std::true_type{});
+  }
+  if (nk > 2 && rem != BK2) {      // the last tile, on its way, first has to land
+    wait_vmcnt<0>();
+    stage_barrier();
+    zero_last();
+  }
   for (; kt < nk; ++kt) step(kt, std::false_type{});
 
-  store_tile<C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, Cv, ldc, accumulate, Rv, ldr);
+  store_tile<C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, Cv, ldc, accumulate, Rv, ldr, ga.epi);
 }
 
 // =============================================================================== 64-deep K steps
@@ -727,21 +571,31 @@ constexpr int kOp64 = 256 * BK64 * 2;            // one operand tile: 32 KiB
 constexpr int kStage64 = 2 * kOp64;              // 64 KiB
 constexpr size_t kLds64 = 2 * (size_t)kStage64;  // 128 KiB
 
-template <bool KC>
+// R = rows (KC) or columns (NC) of the operand tile: 256, or 128 / 64 in the small-tile kernel below.
+template <bool KC, int R>
 struct Operand64 {
+  static constexpr int NL = R / 32;                // direct loads per wavefront and step
+  static constexpr int kBytes = R * BK64 * 2;      // one operand tile
+  static constexpr int kRow = KC ? BK64 * 2 : R * 2;                 // bytes of a tile row
+  static constexpr int kKpl = KC ? 0 : 512 / R;                      // NC: k rows covered by one load instruction
   uint64_t base;          // tile origin at the current K position (bytes); wavefront-uniform
   uint64_t kstep;         // bytes per K step
-  unsigned goff[8];       // per-lane byte offsets of the 8 loads of a step
+  unsigned goff[NL];      // per-lane byte offsets of the loads of a step
   // KC: rd[ks] for MFMA k-step ks, fragment i is 4096 i bytes further (32 rows)
-  // NC: rd[i] for fragment i; MFMA k-step ks adds 8192, the second transposing read of a fragment 2048
+  // NC: rd[i] for fragment i; MFMA k-step ks adds 16 tile rows, the second transposing read of a fragment 4
   unsigned rd[4];
+
+  // NC: which chunk of a k row sits where: 4 consecutive k rows x 64 bytes, what half a wavefront reads at a time, must fall into
+  // different banks.  Rows of 512 and 256 bytes all start at the same bank; of two 128-byte rows the second starts half way.
+  static __device__ __forceinline__ int swz(int k) { return R >= 128 ? (k & 3) << 2 : (k & 2) << 1; }
+  static __device__ __forceinline__ int k_of_load(int i, int lane, int wave) { return kKpl * (4 * i + wave) + lane / (R / 8); }
 
   __device__ __forceinline__ void init(const bf16_t* mat, int64_t ld, int64_t origin, int64_t extent, int w0, int lane, int wave) {
     if (KC) {
       base = (uint64_t)(mat + origin * ld);
       kstep = BK64 * 2;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < NL; ++i) {
         const int rt = 8 * (4 * i + wave) + (lane >> 3);      // row of the tile this lane's 16 bytes land in
         int64_t r = rt;
         if (origin + r >= extent) r = extent - 1 - origin;
@@ -755,9 +609,9 @@ struct Operand64 {
       base = (uint64_t)(mat + origin);
       kstep = (uint64_t)ld * (BK64 * 2);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int k = 2 * (4 * i + wave) + (lane >> 5);
-        int64_t col = ((lane & 31) ^ ((k & 3) << 2)) * 8;
+      for (int i = 0; i < NL; ++i) {
+        const int k = k_of_load(i, lane, wave);
+        int64_t col = ((lane & (R / 8 - 1)) ^ swz(k)) * 8;
         if (origin + col >= extent) col = extent - 8 - origin;
         goff[i] = (unsigned)((k * ld + col) * 2);
       }
@@ -766,12 +620,34 @@ struct Operand64 {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int n = w0 + 32 * i + 16 * (blk & 1) + 4 * (l16 & 3);
-        rd[i] = k * 512 + (((n >> 3) ^ ((k & 3) << 2)) << 4) + (n & 7) * 2;
+        rd[i] = k * kRow + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2;
       }
     }
   }
   __device__ __forceinline__ void dma(int i, unsigned lds_op, int wave) const { lds_dma16(base, goff[i], lds_op + (4 * i + wave) * 1024); }
   __device__ __forceinline__ void advance() { base += kstep; }
+  // the next loads are those of the last K step, of which only `rem` values of k exist (KC: a multiple of 8)
+  __device__ __forceinline__ void clamp_tail(int rem, int64_t ld, int lane, int wave) {
+    const int c = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);        // KC: the chunk this lane loads, the same in all its loads
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      if (KC) {
+        if (8 * c >= rem) goff[i] -= (unsigned)((c - (rem / 8 - 1)) * 16);
+      } else {
+        const int k = k_of_load(i, lane, wave);
+        if (k >= rem) goff[i] -= (unsigned)((k - (rem - 1)) * ld * 2);
+      }
+    }
+  }
+  // zeroes what the operand tile at op holds of k beyond the first `rem`
+  static __device__ __forceinline__ void zero_tail(unsigned char* op, int rem, int tid) {
+    if (KC) {
+      for (int r = tid; r < R; r += kThreads)
+        for (int c = rem / 8; c < 8; ++c) *reinterpret_cast<u32x4_t*>(op + r * kRow + ((c ^ ((r >> 1) & 7)) << 4)) = u32x4_t{0u, 0u, 0u, 0u};
+    } else {
+      zero_lds(op, rem * kRow, kBytes, tid);
+    }
+  }
   __device__ __forceinline__ bf16x8_t frag(const lds_u8_t* op, int i, int ks) const {
     if (KC) {
       return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(op + rd[ks] + 4096 * i);
@@ -779,7 +655,7 @@ struct Operand64 {
       union { s16x4_t h[2]; bf16x8_t v; } u;
 #pragma unroll
       for (int r = 0; r < 2; ++r)
-        u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + 8192 * ks + 2048 * r));
+        u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + (16 * ks + 4 * r) * kRow));
       return u.v;
     }
   }
@@ -787,12 +663,21 @@ struct Operand64 {
 
 template <int MODE, bool C_F32, int EPI = kEpiNone>
 __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) {
-  const int64_t M = ga.M, N = ga.N, K = ga.K, lda = ga.lda, ldb = ga.ldb, ldc = ga.ldc, ldr = ga.ldr;
+  const int64_t M = ga.M, N = ga.N, lda = ga.lda, ldb = ga.ldb;
+  int64_t K = ga.K;
   const bf16_t* __restrict__ A = ga.A;
   const bf16_t* __restrict__ B = ga.B;
-  void* __restrict__ Cv = ga.C;
-  const void* __restrict__ Rv = ga.R;
-  const int accumulate = ga.accumulate, tiles_m = ga.tiles_m, tiles_n = ga.tiles_n;
+  const int tiles_m = ga.tiles_m, tiles_n = ga.tiles_n;
+  int sp = 0;
+  if (ga.splits > 1) {      // workgroup-uniform: this workgroup's range of the contraction
+    const int ntl = tiles_m * tiles_n;
+    sp = block / ntl;
+    block -= sp * ntl;
+    const int64_t k0 = (int64_t)sp * ga.k_chunk;
+    A += k0;
+    B += MODE == GEMM_NT ? k0 : k0 * ldb;
+    K = K - k0 < ga.k_chunk ? K - k0 : ga.k_chunk;
+  }
   constexpr bool A_KC = (MODE != GEMM_TN);
   constexpr bool B_KC = (MODE == GEMM_NT);
   extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
@@ -807,28 +692,27 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  Operand64<A_KC> oa;
-  Operand64<B_KC> ob;
+  Operand64<A_KC, 256> oa;
+  Operand64<B_KC, 256> ob;
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
-  f32x16_t acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int nk = (int)(K / BK64);
+  const int nk = (int)((K + BK64 - 1) / BK64), rem = (int)(K - (int64_t)(nk - 1) * BK64);     // rem: k values of the last step
   // ---- prologue: stage 0 whole and the A half of stage 1 in flight; stage 0 landed and visible
+  if (nk == 1) {
+    oa.clamp_tail(rem, lda, lane, wave);
+    ob.clamp_tail(rem, ldb, lane, wave);
+  }
 #pragma unroll
   for (int i = 0; i < 8; ++i) oa.dma(i, lds0, wave);
 #pragma unroll
   for (int i = 0; i < 8; ++i) ob.dma(i, lds0 + kOp64, wave);
   oa.advance();
   ob.advance();
+  f32x16_t acc[4][4];
+  zero_acc(acc);
   if (nk > 1) {
+    if (nk == 2) oa.clamp_tail(rem, lda, lane, wave);
 #pragma unroll
     for (int i = 0; i < 8; ++i) oa.dma(i, lds0 + kStage64, wave);
     oa.advance();
@@ -837,6 +721,14 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
     wait_vmcnt<0>();
   }
   stage_barrier();
+  auto zero_last = [&](int t) {
+    unsigned char* st = lds2 + (t & 1) * kStage64;
+    oa.zero_tail(st, rem, tid);
+    ob.zero_tail(st + kOp64, rem, tid);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    stage_barrier();
+  };
+  if (nk == 1 && rem != BK64) zero_last(0);
   __builtin_amdgcn_sched_barrier(0);
 
   bf16x8_t fa[2][4], fb[2][4];     // [parity of the MFMA k-step][fragment]
@@ -886,39 +778,213 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
         __builtin_amdgcn_s_waitcnt(0xc07f);   // this wavefront's last reads of the stage have returned
         wait_vmcnt<0>();                      // and its share of the next stage has landed
         stage_barrier();
+        if (NEXT && !LA && rem != BK64) zero_last(kt + 1);      // stage kt + 1 is the last
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
   __builtin_amdgcn_s_waitcnt(0xc07f);
   int kt = 0;
-  for (; kt + 2 < nk; ++kt) step(kt, std::true_type{}, std::true_type{}, std::true_type{});
-  if (kt + 1 < nk) { step(kt, std::true_type{}, std::false_type{}, std::true_type{}); ++kt; }
+  for (; kt + 2 < nk; ++kt) {
+    if (opaque_zero(kt + 3 - nk)) oa.clamp_tail(rem, lda, lane, wave);      // this step loads the A half of the last stage
+    step(kt, std::true_type{}, std::true_type{}, std::true_type{});
+  }
+  if (kt + 1 < nk) {
+    ob.clamp_tail(rem, ldb, lane, wave);
+    step(kt, std::true_type{}, std::false_type{}, std::true_type{});
+    ++kt;
+  }
   step(kt, std::false_type{}, std::false_type{}, std::false_type{});
 
-  store_tile<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, Cv, ldc, accumulate, Rv, ldr, ga.epi);
+  if (ga.splits > 1)
+    store_tile<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.part + (int64_t)sp * M * N, N, 0, nullptr, 0, ga.epi);
+  else
+    store_tile<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
+}
+
+// =============================================================================== small tiles
+// Output tiles of (64 TM) x (64 TN), 4 wavefronts of (32 TM) x (32 TN) each, for problems whose 256 x 256 tiles would leave most of
+// the 256 compute units idle or in a nearly empty last round.  The operand layouts and the 64-deep K steps are those above; the ring has
+// NST stages; a step's fragments are read into registers one step ahead, while the MFMAs of the step before run.  NST = 4: the deep
+// prefetch a short grid needs (nothing else covers the latency of its loads); NST = 2: two workgroups share a compute unit.
+// What bounds them: the latency of a step's loads and, in a full chip, L2 bandwidth (a 128 x 128 tile reads twice the bytes per product
+// of a 256 x 256 one).  C[T, N] = A B^T, 256 x 256 tiles -> the shape picked: 1024 x 4096, K = 11008: 208 -> 98 us; 1024 x 1024, K = 1024:
+// 21.4 -> 6.0; 64 x 4096, K = 11008: 203 -> 22.5 (64 x 64, contraction in four ranges); 666 x 768, K = 256: 14.7 -> 4.0.  Reading the
+// fragments inside the step they are used in costs a third (64 x 64, K = 4096: 0.31 us per step instead of 0.26; 128 x 128: 0.70, 0.42).
+template <int MODE, bool C_F32, int TM, int TN, int NST, int EPI = kEpiNone>
+__device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
+  constexpr bool A_KC = (MODE != GEMM_TN);
+  constexpr bool B_KC = (MODE == GEMM_NT);
+  typedef Operand64<A_KC, 64 * TM> OpA;
+  typedef Operand64<B_KC, 64 * TN> OpB;
+  constexpr int kStage = OpA::kBytes + OpB::kBytes, LPS = OpA::NL + OpB::NL;      // LPS: loads per wavefront and step
+  const int64_t M = ga.M, N = ga.N, lda = ga.lda, ldb = ga.ldb;
+  int64_t K = ga.K;
+  const bf16_t* __restrict__ A = ga.A;
+  const bf16_t* __restrict__ B = ga.B;
+  int sp = 0;
+  if (ga.splits > 1) {      // workgroup-uniform: this workgroup's range of the contraction
+    const int ntl = ga.tiles_m * ga.tiles_n;
+    sp = block / ntl;
+    block -= sp * ntl;
+    const int64_t k0 = (int64_t)sp * ga.k_chunk;
+    A += A_KC ? k0 : k0 * lda;
+    B += B_KC ? k0 : k0 * ldb;
+    K = K - k0 < ga.k_chunk ? K - k0 : ga.k_chunk;
+  }
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
+  const lds_u8_t* lds = (const lds_u8_t*)lds2;
+  const unsigned lds0 = (unsigned)(size_t)lds;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  gemm_tile_of_block(block, ga.tiles_m, ga.tiles_n, &tm, &tn);
+  const int64_t m0 = (int64_t)tm * (64 * TM), n0 = (int64_t)tn * (64 * TN);
+  const int wm = (wave >> 1) * (32 * TM), wn = (wave & 1) * (32 * TN);
+  OpA oa;
+  OpB ob;
+  oa.init(A, lda, m0, M, wm, lane, wave);
+  ob.init(B, ldb, n0, N, wn, lane, wave);
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const int nk = (int)((K + BK64 - 1) / BK64), rem = (int)(K - (int64_t)(nk - 1) * BK64);     // rem: k values of the last step
+  auto dma = [&](int i, unsigned st) {      // load i (0 ... LPS - 1) of a stage
+    if (i < OpA::NL) oa.dma(i, st, wave);
+    else ob.dma(i - OpA::NL, st + OpA::kBytes, wave);
+  };
+  auto clamp_tail = [&]() {
+    oa.clamp_tail(rem, lda, lane, wave);
+    ob.clamp_tail(rem, ldb, lane, wave);
+  };
+  // at most `behind` (0 ... NST - 1) stages' loads are outstanding
+  auto wait_stages = [&](int behind) {
+    if (NST > 3 && behind >= 3) wait_vmcnt<3 * LPS>();
+    else if (NST > 2 && behind >= 2) wait_vmcnt<2 * LPS>();
+    else if (behind >= 1) wait_vmcnt<LPS>();
+    else wait_vmcnt<0>();
+  };
+  static_assert(NST >= 2 && NST <= 4 && (NST - 1) * LPS < 64, "wait_stages");
+#pragma unroll
+  for (int t = 0; t < NST; ++t)
+    if (t < nk) {
+      if (t + 1 == nk) clamp_tail();
+#pragma unroll
+      for (int i = 0; i < LPS; ++i) dma(i, lds0 + t * kStage);
+      oa.advance();
+      ob.advance();
+    }
+  wait_stages((nk < NST ? nk : NST) - 1);
+  stage_barrier();
+  auto zero_last = [&](int sl) {
+    oa.zero_tail(lds2 + sl * kStage, rem, tid);
+    ob.zero_tail(lds2 + sl * kStage + OpA::kBytes, rem, tid);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    stage_barrier();
+  };
+  if (nk == 1 && rem != BK64) zero_last(0);
+
+  // A step multiplies the fragments of stage kt, which sit in registers, and reads those of stage kt + 1 into a second set.  At its
+  // barrier stage kt + 1 has landed, and every wavefront has read stage kt, whose slot takes the loads of stage kt + NST.
+  struct Frags {
+    bf16x8_t a[4][TM], b[4][TN];      // [MFMA k-step]
+  } f0, f1;
+  constexpr int NF = 4 * (TM + TN), NM = 4 * TM * TN;      // fragments and MFMAs of a step
+  auto read = [&](Frags& f, const lds_u8_t* st, int e) {
+    const int ks = e / (TM + TN), i = e % (TM + TN);
+    if (i < TM) f.a[ks][i] = oa.frag(st, i, ks);
+    else f.b[ks][i - TM] = ob.frag(st + OpA::kBytes, i - TM, ks);
+  };
+#pragma unroll
+  for (int e = 0; e < NF; ++e) read(f0, lds, e);
+  int slot = 0;
+  auto step = [&](int kt, Frags& cur, Frags& nxt, auto load_c, auto next_c) {
+    constexpr bool LOAD = decltype(load_c)::value, NEXT = decltype(next_c)::value;
+    const unsigned fill = lds0 + slot * kStage;
+    slot = slot + 1 == NST ? 0 : slot + 1;
+    const lds_u8_t* st = lds + slot * kStage;
+    __builtin_amdgcn_s_waitcnt(0xc07f);                 // this wavefront has read stage kt
+    if (NEXT) {
+      if (LOAD) wait_vmcnt<(NST - 2) * LPS>();          // stages kt + 2 ... kt + NST - 1 may be outstanding
+      else wait_stages(nk - 2 - kt);
+      stage_barrier();
+      if (LOAD && opaque_zero(kt + NST + 1 - nk)) clamp_tail();
+      if (!LOAD && kt + 2 == nk && rem != BK64) zero_last(slot);      // stage kt + 1 is the last
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < NM; ++e) {
+      const int ks = e / (TM * TN), i = e % (TM * TN) / TN, j = e % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.b[ks][j], cur.a[ks][i], acc[i][j], 0, 0, 0);
+      if (NEXT) {
+#pragma unroll
+        for (int r = e * NF / NM; r < (e + 1) * NF / NM; ++r) read(nxt, st, r);
+      }
+      if (LOAD) {
+#pragma unroll
+        for (int r = e * LPS / NM; r < (e + 1) * LPS / NM; ++r) dma(r, fill);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (LOAD) {
+      oa.advance();
+      ob.advance();
+    }
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  int kt = 0;
+  for (; kt + NST + 1 < nk; kt += 2) {
+    step(kt, f0, f1, yes, yes);
+    step(kt + 1, f1, f0, yes, yes);
+  }
+  if (kt + NST < nk) {
+    step(kt, f0, f1, yes, yes);
+    f0 = f1;
+    ++kt;
+  }
+  for (; kt + 1 < nk; ++kt) {
+    step(kt, f0, f1, no, yes);
+    f0 = f1;
+  }
+  step(kt, f0, f1, no, no);
+  stage_barrier();                             // every wavefront has finished reading the ring: the epilogue stages through it
+  if (ga.splits > 1)
+    store_checked<true, TM, TN>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, ga.part + (int64_t)sp * M * N, N, 0, nullptr, 0, ga.epi);
+  else
+    store_checked<C_F32, TM, TN, EPI>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
 }
 
 // ---- kernels: one GEMM, or two independent ones in one grid (the first's tiles, then the second's)
-template <int MODE, bool C_F32, bool K64, int EPI = kEpiNone>
+template <int MODE, bool C_F32, int EPI = kEpiNone>
 __global__ void __launch_bounds__(kThreads, 1) gemm_pipe_kernel(GemmArgs g) {
-  static_assert(EPI == kEpiNone || K64, "fused epilogues exist for the 64-deep loop only");
-  if constexpr (K64) gemm_dlds64_body<MODE, C_F32, EPI>(g, (int)blockIdx.x);
+  if constexpr (MODE != GEMM_TN) gemm_dlds64_body<MODE, C_F32, EPI>(g, (int)blockIdx.x);
   else gemm_dlds_body<MODE, C_F32>(g, (int)blockIdx.x);
 }
 // The layer's backward has such pairs at every linear: the input gradient and the weight gradient
 // read the same incoming gradient and write different outputs.  Neither tile count is a multiple
 // of the 256 compute units for every width, so two launches leave two partly filled last rounds;
-// one grid leaves one.  The weight-gradient tiles (longer: they contract over all tokens) go first.
-template <int MODE0, bool F32_0, bool K64_0, int MODE1, bool F32_1, bool K64_1>
-__global__ void __launch_bounds__(kThreads, 1) gemm_dual_kernel(GemmArgs g0, GemmArgs g1, int n0) {
-  if ((int)blockIdx.x < n0) {
-    if (K64_0) gemm_dlds64_body<MODE0, F32_0>(g0, (int)blockIdx.x);
-    else gemm_dlds_body<MODE0, F32_0>(g0, (int)blockIdx.x);
-  } else {
-    if (K64_1) gemm_dlds64_body<MODE1, F32_1>(g1, (int)blockIdx.x - n0);
-    else gemm_dlds_body<MODE1, F32_1>(g1, (int)blockIdx.x - n0);
-  }
+// one grid leaves one.  n1 >= 0: the second's n1 workgroups go first (dual_order).
+__global__ void __launch_bounds__(kThreads, 1) gemm_dual_kernel(GemmArgs g0, GemmArgs g1, int n0, int n1) {
+  const int b = (int)blockIdx.x, b0 = n1 < 0 ? b : b - n1;      // this workgroup's index within the first problem, if it is one of its
+  if (b0 >= 0 && b0 < n0) gemm_dlds_body<GEMM_TN, true>(g0, b0);
+  else gemm_dlds64_body<GEMM_NN, false>(g1, n1 < 0 ? b - n0 : b);
+}
+template <int MODE, bool C_F32, int TM, int TN, int NST, int EPI = kEpiNone>
+__global__ void __launch_bounds__(kThreads, NST == 2 ? 2 : 1) gemm_small_kernel(GemmArgs g) {
+  gemm_small_body<MODE, C_F32, TM, TN, NST, EPI>(g, (int)blockIdx.x);
+}
+template <int TM, int TN, int NST>
+__global__ void __launch_bounds__(kThreads, NST == 2 ? 2 : 1) gemm_small_dual_kernel(GemmArgs g0, GemmArgs g1, int n0, int n1) {
+  const int b = (int)blockIdx.x, b0 = n1 < 0 ? b : b - n1;
+  if (b0 >= 0 && b0 < n0) gemm_small_body<GEMM_TN, true, TM, TN, NST>(g0, b0);
+  else gemm_small_body<GEMM_NN, false, TM, TN, NST>(g1, n1 < 0 ? b - n0 : b);
 }
 
 inline GemmArgs make_args(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
@@ -941,32 +1007,96 @@ inline GemmArgs make_args(int64_t M, int64_t N, int64_t K, const void* A, int64_
 
 static_assert(kLds64 == kLds2, "the two pipelined kernels share one LDS size");
 
-template <int MODE, bool C_F32, bool K64, int EPI = kEpiNone>
+template <int MODE, bool C_F32, int EPI = kEpiNone>
 int launch_pipe(const GemmArgs& g, hipStream_t st) {
-  TAW_SET_LDS_LIMIT_ONCE((gemm_pipe_kernel<MODE, C_F32, K64, EPI>), kLds2);
-  hipLaunchKernelGGL((gemm_pipe_kernel<MODE, C_F32, K64, EPI>), dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(kThreads), kLds2, st, g);
+  TAW_SET_LDS_LIMIT_ONCE((gemm_pipe_kernel<MODE, C_F32, EPI>), kLds2);
+  hipLaunchKernelGGL((gemm_pipe_kernel<MODE, C_F32, EPI>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(kThreads), kLds2, st, g);
   return (int)hipGetLastError();
 }
 
-template <int MODE0, bool F32_0, bool K64_0, int MODE1, bool F32_1, bool K64_1>
-int launch_dual(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st) {
-  TAW_SET_LDS_LIMIT_ONCE((gemm_dual_kernel<MODE0, F32_0, K64_0, MODE1, F32_1, K64_1>), kLds2);
-  const int n0 = g0.tiles_m * g0.tiles_n * g0.splits, n1 = g1.tiles_m * g1.tiles_n;
-  hipLaunchKernelGGL((gemm_dual_kernel<MODE0, F32_0, K64_0, MODE1, F32_1, K64_1>), dim3((unsigned)(n0 + n1)), dim3(kThreads), kLds2, st, g0, g1, n0);
+// -1: the first problem's workgroups go first; otherwise the second's n1 do: where they contract over more and are too few to
+// fill the chip, so that the last of them would run on alone (64 tiles of K = 22016 behind 1376 of K = 1024 cost 40 %).  With more of them
+// there is nothing to gain, and the weight gradient first is the faster order (3 % at 512 behind 1376).
+inline int dual_order(const GemmArgs& g0, const GemmArgs& g1, int n1) { return g0.k_chunk >= g1.k_chunk || n1 >= 256 ? -1 : n1; }
+
+inline int launch_dual(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st) {
+  TAW_SET_LDS_LIMIT_ONCE(gemm_dual_kernel, kLds2);
+  const int n0 = g0.tiles_m * g0.tiles_n * g0.splits, n1 = g1.tiles_m * g1.tiles_n * g1.splits;
+  hipLaunchKernelGGL(gemm_dual_kernel, dim3((unsigned)(n0 + n1)), dim3(kThreads), kLds2, st, g0, g1, n0, dual_order(g0, g1, n1));
   return (int)hipGetLastError();
+}
+
+template <int TM, int TN, int NST> constexpr size_t small_lds() { return (size_t)NST * (64 * TM + 64 * TN) * BK64 * 2; }
+
+template <int MODE, bool C_F32, int TM, int TN, int NST, int EPI = kEpiNone>
+int launch_small(const GemmArgs& g, hipStream_t st) {
+  TAW_SET_LDS_LIMIT_ONCE((gemm_small_kernel<MODE, C_F32, TM, TN, NST, EPI>), (small_lds<TM, TN, NST>()));
+  hipLaunchKernelGGL((gemm_small_kernel<MODE, C_F32, TM, TN, NST, EPI>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(kThreads),
+                     (small_lds<TM, TN, NST>()), st, g);
+  return (int)hipGetLastError();
+}
+
+template <int TM, int TN, int NST>
+int launch_small_dual(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st) {
+  TAW_SET_LDS_LIMIT_ONCE((gemm_small_dual_kernel<TM, TN, NST>), (small_lds<TM, TN, NST>()));
+  const int n0 = g0.tiles_m * g0.tiles_n * g0.splits, n1 = g1.tiles_m * g1.tiles_n * g1.splits;
+  hipLaunchKernelGGL((gemm_small_dual_kernel<TM, TN, NST>), dim3((unsigned)(n0 + n1)), dim3(kThreads), (small_lds<TM, TN, NST>()), st, g0, g1, n0, dual_order(g0, g1, n1));
+  return (int)hipGetLastError();
+}
+
+// C = (accumulate ? C : 0) + R + part[0] + part[1] + ... + part[splits - 1], the partial products in that order, with the rotation of the
+// fused epilogue where the GEMM asks for it; two GEMMs' worth in one grid, 8 columns per thread, blocks of the first first
+template <bool C_F32, bool ROPE>
+__device__ __forceinline__ void reduce_parts(const GemmArgs& g, int64_t first, int64_t stride) {
+  constexpr int V = C_F32 ? 4 : 8;
+  typedef typename std::conditional<C_F32, float, bf16_t>::type T;
+  const int64_t nv = g.N / V, total = g.M * nv;
+  for (int64_t i = first; i < total; i += stride) {
+    const int64_t r = i / nv, c = (i - r * nv) * V;
+    const float* pp = g.part + r * g.N + c;
+    float v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = 0.f;
+    for (int s = 0; s < g.splits; ++s, pp += g.M * g.N) {
+#pragma unroll
+      for (int e = 0; e < V; e += 4) {
+        const f32x4_t q = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(pp + e));
+        v[e] += q[0]; v[e + 1] += q[1]; v[e + 2] += q[2]; v[e + 3] += q[3];
+      }
+    }
+    if constexpr (ROPE) rotate_chunk(v, r, c, g.epi);
+    T* cp = static_cast<T*>(g.C) + r * g.ldc + c;
+    Vec<T, V> x;
+    if (g.R) {
+      x.load(static_cast<const T*>(g.R) + r * g.ldr + c);
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] += x.get(e);
+    }
+    if (g.accumulate) {
+      x.load(cp);
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] += x.get(e);
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) x.set(e, v[e]);
+    x.store(cp);
+  }
+}
+template <bool ROPE>
+__global__ void __launch_bounds__(256) splitk_reduce_bf16_kernel(GemmArgs g) {
+  reduce_parts<false, ROPE>(g, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+}
+__global__ void __launch_bounds__(256) splitk_reduce_dual_kernel(GemmArgs g0, GemmArgs g1, int n0) {
+  if ((int)blockIdx.x < n0) reduce_parts<true, false>(g0, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)n0 * 256);
+  else reduce_parts<false, false>(g1, (int64_t)(blockIdx.x - n0) * 256 + threadIdx.x, (int64_t)(gridDim.x - n0) * 256);
+}
+inline int reduce_blocks(const GemmArgs& g, int v) {
+  if (g.splits <= 1) return 0;
+  const int64_t n = (g.M * (g.N / v) + 255) / 256;
+  return (int)(n < 2048 ? n : 2048);
 }
 
 }  // namespace v2
-
-template <int MODE, bool C_F32>
-int launch_t(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
-             int accumulate, const void* R, int64_t ldr, hipStream_t st) {
-  TAW_SET_LDS_LIMIT_ONCE((gemm_mfma_kernel<MODE, C_F32>), kLdsBytes);
-  const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_mfma_kernel<MODE, C_F32>), dim3((unsigned)(tiles_m * tiles_n)), dim3(kThreads), kLdsBytes, st, M, N, K,
-                     (const bf16_t*)A, lda, (const bf16_t*)B, ldb, C, ldc, accumulate, R, ldr, tiles_m, tiles_n);
-  return (int)hipGetLastError();
-}
 
 }  // namespace
 
@@ -986,49 +1116,147 @@ bool gemm_mfma_supported(int dtype, int mode, int64_t M, int64_t N, int64_t K, i
   return true;
 }
 
-int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
-                     void* C, int64_t ldc, int c_dtype, int accumulate, const void* R, int64_t ldr, hipStream_t st) {
-  const bool f32 = c_dtype == DT_F32;
-  if (K % v2::BK2 != 0 || K < v2::BK2) {     // the pipelined kernel has no K tail
-    switch (mode) {
-      case GEMM_NT: return f32 ? launch_t<GEMM_NT, true>(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, st)
-                               : launch_t<GEMM_NT, false>(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, st);
-      case GEMM_NN: return f32 ? launch_t<GEMM_NN, true>(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, st)
-                               : launch_t<GEMM_NN, false>(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, st);
-      default: return f32 ? launch_t<GEMM_TN, true>(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, st)
-                          : launch_t<GEMM_TN, false>(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, st);
+// ---- which tile, and into how many ranges of the contraction
+struct GemmPlan {
+  int tile;          // 256, 192 (128 x 256), 128 or 64
+  int nst;           // stages of the small-tile ring
+  int splits[2];
+  int64_t chunk[2];
+  size_t part_floats;
+};
+
+// What a tile shape costs, in microseconds: `fixed` per workgroup, and per 64-deep step the larger of `lone` (one workgroup on a compute
+// unit: the latency of its loads) and `busy` x the workgroups that share the unit (`resident` at most).  Fitted over 1800
+// timings of the five shapes at 64 ... 8192 rows and 256 ... 22016 columns: 13 % off in the mean, and what it picks is 4 % slower than
+// the fastest of the shapes and cuts measured, 256 x 256 tiles alone 88 % (up to 9 times).
+struct TileCost {
+  int tile, tm, tn, nst, resident;
+  double fixed, lone, busy;
+};
+static const TileCost kTiles[] = {
+    {256, 256, 256, 2, 1, 6.8, 1.10, 1.17},
+    {192, 128, 256, 3, 1, 6.5, 0.63, 0.66},
+    {128, 128, 128, 4, 1, 4.1, 0.42, 0.42},
+    {128, 128, 128, 2, 2, 3.8, 0.54, 0.40},
+    {64, 64, 64, 4, 2, 1.8, 0.21, 0.16},
+};
+constexpr double kReduceFixed = 4.6, kReduceBytesPerUs = 10.3e6;      // the second kernel of a cut contraction
+constexpr size_t kMaxPartFloats = (size_t)64 << 20;                   // 256 MB of partial products at most
+
+static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+struct GemmProblem {
+  int64_t M, N, K;
+  int out_bytes;
+};
+
+// When the last workgroup ends: n0 of duration d0, then n1 of duration d1 <= d0, dealt to P places as they come free.
+static double makespan(int64_t n0, double d0, int64_t n1, double d1, int64_t P) {
+  const int64_t q = n0 / P, r = n0 % P;
+  if (n1 == 0) return (double)(q + (r > 0)) * d0;
+  if (r == 0) return (double)q * d0 + (double)cdiv(n1, P) * d1;
+  const int64_t fit = (P - r) * (int64_t)(d0 / d1);                   // shorter ones that run beside the longer ones' last round
+  if (n1 > fit) return (double)(q + 1) * d0 + (double)cdiv(n1 - fit, P) * d1;
+  const double beside = (double)q * d0 + (double)cdiv(n1, P - r) * d1, last = (double)(q + 1) * d0;
+  return beside > last ? beside : last;
+}
+
+// The cheapest tile shape, and the cheapest numbers of ranges the contractions of the np (1 or 2) problems of one grid are cut into, whose
+// partial products fit max_floats.  A pure function of the sizes; each thread keeps its latest answers.
+static GemmPlan plan_grid(int np, const GemmProblem (&pr)[2], size_t max_floats) {
+  struct Entry {
+    int64_t key[9];
+    GemmPlan plan;
+  };
+  static thread_local Entry cache[64];
+  const int64_t key[9] = {np, pr[0].M, pr[0].N, pr[0].K, pr[1].M, pr[1].N, pr[1].K, pr[0].out_bytes, (int64_t)max_floats};
+  uint64_t h = 0;
+  for (int64_t k : key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
+  Entry& slot = cache[h >> 58];
+  if (memcmp(slot.key, key, sizeof(key)) == 0) return slot.plan;      // an entry never written has np = 0
+
+  GemmPlan best{};
+  double best_t = 1e300;
+  for (const TileCost& c : kTiles) {
+    int64_t tiles[2] = {0, 0};
+    for (int i = 0; i < np; ++i) tiles[i] = cdiv(pr[i].M, c.tm) * cdiv(pr[i].N, c.tn);
+    for (int s0 = 1; s0 <= 32; s0 *= 2) {
+      for (int s1 = 1; s1 <= (np == 2 ? 32 : 1); s1 *= 2) {
+        const int want[2] = {s0, s1};
+        GemmPlan p{c.tile, c.nst, {1, 1}, {pr[0].K, pr[1].K}, 0};
+        double part_bytes = 0;
+        bool ok = true;
+        for (int i = 0; i < np; ++i) {
+          if (want[i] == 1) continue;
+          p.chunk[i] = cdiv(cdiv(pr[i].K, want[i]), 64) * 64;
+          p.splits[i] = (int)cdiv(pr[i].K, p.chunk[i]);
+          // ranges of at least 256, and no cut where the tiles alone fill the chip twice
+          ok = ok && p.splits[i] == want[i] && p.chunk[i] >= 256 && tiles[i] * want[i] < 4 * 256 * c.resident;
+          p.part_floats += (size_t)p.splits[i] * pr[i].M * pr[i].N;
+          part_bytes += (double)pr[i].M * pr[i].N * (8.0 * p.splits[i] + pr[i].out_bytes);
+        }
+        if (!ok || p.part_floats > max_floats) continue;
+        const int64_t n0 = tiles[0] * p.splits[0], n1 = tiles[1] * p.splits[1];
+        const int64_t share = cdiv(n0 + n1, 256) < c.resident ? cdiv(n0 + n1, 256) : c.resident;
+        const double step = c.lone > share * c.busy ? c.lone : share * c.busy;
+        const double d0 = c.fixed + step * cdiv(p.chunk[0], 64), d1 = c.fixed + step * cdiv(p.chunk[1], 64);
+        double t = np == 1 || d0 >= d1 ? makespan(n0, d0, n1, d1, 256 * c.resident) : makespan(n1, d1, n0, d0, 256 * c.resident);
+        if (part_bytes > 0) t += kReduceFixed + part_bytes / kReduceBytesPerUs;
+        if (t < best_t) {
+          best_t = t;
+          best = p;
+        }
+      }
     }
   }
-  // K-contiguous operands gain from 64-deep steps (whole cache lines per row); the weight-gradient form has none
-  const v2::GemmArgs g = v2::make_args(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr);
-  const bool k64 = K % v2::BK64 == 0 && mode != GEMM_TN;
-  switch (mode) {
-    case GEMM_NT:
-      if (k64) return f32 ? v2::launch_pipe<GEMM_NT, true, true>(g, st) : v2::launch_pipe<GEMM_NT, false, true>(g, st);
-      return f32 ? v2::launch_pipe<GEMM_NT, true, false>(g, st) : v2::launch_pipe<GEMM_NT, false, false>(g, st);
-    case GEMM_NN:
-      if (k64) return f32 ? v2::launch_pipe<GEMM_NN, true, true>(g, st) : v2::launch_pipe<GEMM_NN, false, true>(g, st);
-      return f32 ? v2::launch_pipe<GEMM_NN, true, false>(g, st) : v2::launch_pipe<GEMM_NN, false, false>(g, st);
-    default:
-      return f32 ? v2::launch_pipe<GEMM_TN, true, false>(g, st) : v2::launch_pipe<GEMM_TN, false, false>(g, st);
-  }
+  memcpy(slot.key, key, sizeof(key));
+  slot.plan = best;
+  return best;
+}
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, size_t max_floats) {
+  return plan_grid(1, {{M, N, K, 2}, {0, 0, 0, 0}}, max_floats);
+}
+static GemmPlan plan_dual(int64_t M0, int64_t N0, int64_t K0, int64_t M1, int64_t N1, int64_t K1, size_t max_floats) {
+  return plan_grid(2, {{M0, N0, K0, 4}, {M1, N1, K1, 2}}, max_floats);
+}
+size_t gemm_nt_scratch_floats(int64_t M, int64_t N, int64_t K) { return plan_gemm(M, N, K, kMaxPartFloats).part_floats; }
+size_t gemm_linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K) { return plan_dual(N, K, T, T, K, N, kMaxPartFloats).part_floats; }
+
+static void apply_plan(v2::GemmArgs& g, const GemmPlan& p, int which, float* part) {
+  const int tm = p.tile == 192 ? 128 : p.tile, tn = p.tile == 192 ? 256 : p.tile;
+  g.tiles_m = (int)((g.M + tm - 1) / tm);
+  g.tiles_n = (int)((g.N + tn - 1) / tn);
+  g.splits = p.splits[which];
+  g.k_chunk = p.chunk[which];
+  g.part = g.splits > 1 ? part : nullptr;
 }
 
-// C[M][N] (row stride ldc) = (accumulate ? C : 0) + part[0] + part[1] + ... + part[splits - 1], in that order; N % 4 == 0
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(float* __restrict__ C, int64_t ldc, const float* __restrict__ part, int splits,
-                                                            int64_t M, int64_t N, int accumulate) {
-  const int64_t n4 = N / 4, total = M * n4;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t r = i / n4, c4 = i - r * n4;
-    float* cp = C + r * ldc + c4 * 4;
-    f32x4_t v = accumulate ? *reinterpret_cast<const f32x4_t*>(cp) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const float* pp = part + r * N + c4 * 4;
-    for (int sidx = 0; sidx < splits; ++sidx) v += __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(pp + (int64_t)sidx * M * N));
-    *reinterpret_cast<f32x4_t*>(cp) = v;
-  }
+template <int MODE, bool C_F32, int EPI = v2::kEpiNone>
+static int launch_planned(const v2::GemmArgs& g, const GemmPlan& p, hipStream_t st) {
+  if (p.tile == 256) return v2::launch_pipe<MODE, C_F32, EPI>(g, st);
+  if (p.tile == 192) return v2::launch_small<MODE, C_F32, 2, 4, 3, EPI>(g, st);
+  if (p.tile == 128) return p.nst == 2 ? v2::launch_small<MODE, C_F32, 2, 2, 2, EPI>(g, st) : v2::launch_small<MODE, C_F32, 2, 2, 4, EPI>(g, st);
+  return v2::launch_small<MODE, C_F32, 1, 1, 4, EPI>(g, st);
 }
 
-// Into how many ranges the weight gradient of the linear y[T, N] = x[T, K] W^T is cut (1 = not at all), and the rows per
+int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
+                     void* C, int64_t ldc, int c_dtype, int accumulate, const void* R, int64_t ldr, const GemmScratch& scr, hipStream_t st) {
+  const bool f32 = c_dtype == DT_F32;
+  v2::GemmArgs g = v2::make_args(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr);
+  // the layer's single products are NT with bf16 results; the other five combinations (kernel-level entry point) keep the large tile
+  if (mode == GEMM_NT && f32) return v2::launch_pipe<GEMM_NT, true>(g, st);
+  if (mode == GEMM_NN) return f32 ? v2::launch_pipe<GEMM_NN, true>(g, st) : v2::launch_pipe<GEMM_NN, false>(g, st);
+  if (mode == GEMM_TN) return f32 ? v2::launch_pipe<GEMM_TN, true>(g, st) : v2::launch_pipe<GEMM_TN, false>(g, st);
+  const GemmPlan p = plan_gemm(M, N, K, N % 8 == 0 && ldc % 8 == 0 ? scr.floats : 0);
+  apply_plan(g, p, 0, scr.part);
+  const int rc = launch_planned<GEMM_NT, false>(g, p, st);
+  if (rc || g.splits <= 1) return rc;
+  hipLaunchKernelGGL(v2::splitk_reduce_bf16_kernel<false>, dim3((unsigned)v2::reduce_blocks(g, 8)), dim3(256), 0, st, g);
+  return (int)hipGetLastError();
+}
+
+// What taw_op_linear_bwd_scratch_floats offers the plan above at the kernel level: the ranges (1 = none) a weight gradient alone
+// would be cut into for the linear y[T, N] = x[T, K] W^T, and the rows per
 // range.  Its tiles contract over all T tokens: with few of them (narrow layers) a tile runs long after everything else
 // in the grid is done, most compute units idle.  The ranges are sized so that one takes at most about half of what a
 // compute unit's fair share of the whole grid (both GEMMs) takes; never shorter than 512 rows, never more than 32 ranges.
@@ -1045,36 +1273,37 @@ int gemm_dual_splits(int64_t T, int64_t N, int64_t K, int64_t* k_chunk) {
   return (int)sp;
 }
 
-bool gemm_mfma_dual_supported(int64_t K_tn, int64_t K_nn) { return K_tn >= v2::BK2 && K_tn % v2::BK2 == 0 && K_nn >= v2::BK2 && K_nn % v2::BK2 == 0; }
-
 int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, int64_t lda0, const void* B0, int64_t ldb0, float* C0,
                           int64_t ldc0, int accumulate0, int64_t M1, int64_t N1, int64_t K1, const void* A1, int64_t lda1,
-                          const void* B1, int64_t ldb1, void* C1, int64_t ldc1, float* part, int splits, int64_t k_chunk, hipStream_t st) {
+                          const void* B1, int64_t ldb1, void* C1, int64_t ldc1, const GemmScratch& scr, hipStream_t st) {
   v2::GemmArgs g0 = v2::make_args(M0, N0, K0, A0, lda0, B0, ldb0, C0, ldc0, accumulate0, nullptr, 0);
-  const v2::GemmArgs g1 = v2::make_args(M1, N1, K1, A1, lda1, B1, ldb1, C1, ldc1, 0, nullptr, 0);
-  if (part && splits > 1) {
-    g0.splits = splits;
-    g0.k_chunk = k_chunk;
-    g0.part = part;
-  }
-  const int rc = K1 % v2::BK64 == 0 ? v2::launch_dual<GEMM_TN, true, false, GEMM_NN, false, true>(g0, g1, st)
-                                    : v2::launch_dual<GEMM_TN, true, false, GEMM_NN, false, false>(g0, g1, st);
-  if (rc || g0.splits == 1) return rc;
-  const int64_t total = M0 * (N0 / 4);
-  const unsigned blocks = (unsigned)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, st, C0, ldc0, part, g0.splits, M0, N0, accumulate0);
+  v2::GemmArgs g1 = v2::make_args(M1, N1, K1, A1, lda1, B1, ldb1, C1, ldc1, 0, nullptr, 0);
+  const GemmPlan p = plan_dual(M0, N0, K0, M1, N1, K1, scr.floats);
+  apply_plan(g0, p, 0, scr.part);
+  apply_plan(g1, p, 1, scr.part + (p.splits[0] > 1 ? (size_t)p.splits[0] * M0 * N0 : 0));
+  int rc;
+  if (p.tile == 256) rc = v2::launch_dual(g0, g1, st);
+  else if (p.tile == 192) rc = v2::launch_small_dual<2, 4, 3>(g0, g1, st);
+  else if (p.tile == 128) rc = p.nst == 2 ? v2::launch_small_dual<2, 2, 2>(g0, g1, st) : v2::launch_small_dual<2, 2, 4>(g0, g1, st);
+  else rc = v2::launch_small_dual<1, 1, 4>(g0, g1, st);
+  const int n0 = v2::reduce_blocks(g0, 4), n1 = v2::reduce_blocks(g1, 8);
+  if (rc || n0 + n1 == 0) return rc;
+  hipLaunchKernelGGL(v2::splitk_reduce_dual_kernel, dim3((unsigned)(n0 + n1)), dim3(256), 0, st, g0, g1, n0);
   return (int)hipGetLastError();
 }
 
-bool gemm_mfma_rope_supported(int64_t M, int64_t N, int64_t K, int64_t rot_cols, int S) {
-  return M % BM == 0 && N % BN == 0 && K % v2::BK64 == 0 && rot_cols % BN == 0 && rot_cols % 128 == 0 && S >= 32;
-}
+bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols) { return N % 8 == 0 && rot_cols % 128 == 0; }
 
 int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
-                             const float* rope_table, int S, int64_t rot_cols, hipStream_t st) {
+                             const float* rope_table, int S, int64_t rot_cols, const GemmScratch& scr, hipStream_t st) {
   v2::GemmArgs g = v2::make_args(M, N, K, A, lda, B, ldb, C, ldc, 0, nullptr, 0);
   g.epi = v2::EpiArgs{rope_table, S, rot_cols};
-  return v2::launch_pipe<GEMM_NT, false, true, v2::kEpiRope>(g, st);
+  const GemmPlan p = plan_gemm(M, N, K, scr.floats);
+  apply_plan(g, p, 0, scr.part);
+  const int rc = launch_planned<GEMM_NT, false, v2::kEpiRope>(g, p, st);
+  if (rc || g.splits <= 1) return rc;
+  hipLaunchKernelGGL(v2::splitk_reduce_bf16_kernel<true>, dim3((unsigned)v2::reduce_blocks(g, 8)), dim3(256), 0, st, g);
+  return (int)hipGetLastError();
 }
 
 }  // namespace taw

@@ -116,8 +116,8 @@ struct Carve {
 struct Ctx {       // saved by the forward for the backward
   void *xn, *qkv, *o, *h, *hn, *gu, *a; float *lse, *r1, *r2; size_t bytes;
 };
-struct Work {      // scratch of the backward (the forward needs none of it)
-  void *da, *dgu, *dhn, *dh, *dO, *dqkv, *dxn; float *D, *partials, *splitk; size_t bytes;
+struct Work {      // scratch of the backward (the forward needs only scr)
+  void *da, *dgu, *dhn, *dh, *dO, *dqkv, *dxn; float *D, *partials; GemmScratch scr; size_t bytes;
 };
 
 // fp32 elements of partial weight gradients the backward of the linear y[T,N] = x[T,K] W^T needs (0: its weight gradient is not cut)
@@ -150,11 +150,16 @@ static Work carve_work(const taw_layer_desc* d, void* base) {
   w.dO = c.take(T * H * e); w.dqkv = c.take(T * 3 * H * e); w.dxn = c.take(T * H * e);
   w.D = (float*)c.take(attn_bwd_mfma_scratch_floats(d->B, d->S, d->n_heads, attn_mfma_supported(d->dtype, d->S, d->n_heads, d->head_dim) ? attn_bwd_form_of(d) : ATTN_BWD_SPLIT) * 4);   // covers the generic kernel's B*nh*S too
   w.partials = (float*)c.take((size_t)rmsnorm_bwd_partial_rows() * H * 4);
-  size_t sk = linear_bwd_scratch_floats((int64_t)T, (int64_t)H, (int64_t)I);                  // down
-  sk = std::max(sk, linear_bwd_scratch_floats((int64_t)T, (int64_t)(2 * I), (int64_t)H));     // gate, up
-  sk = std::max(sk, linear_bwd_scratch_floats((int64_t)T, (int64_t)H, (int64_t)H));           // output projection
-  sk = std::max(sk, linear_bwd_scratch_floats((int64_t)T, (int64_t)(3 * H), (int64_t)H));     // q, k, v
-  w.splitk = (float*)c.take(sk * 4);
+  size_t sk = 0;
+  if (d->dtype == TAW_BF16 && H % 8 == 0 && I % 8 == 0) {
+    const int64_t t = (int64_t)T, h = (int64_t)H, i = (int64_t)I;
+    for (size_t n : {gemm_nt_scratch_floats(t, 3 * h, h), gemm_nt_scratch_floats(t, h, h), gemm_nt_scratch_floats(t, 2 * i, h), gemm_nt_scratch_floats(t, h, i),
+                     gemm_linear_bwd_scratch_floats(t, h, i), gemm_linear_bwd_scratch_floats(t, 2 * i, h), gemm_linear_bwd_scratch_floats(t, h, h),
+                     gemm_linear_bwd_scratch_floats(t, 3 * h, h)})
+      sk = std::max(sk, n);
+  }
+  w.scr.floats = sk;
+  w.scr.part = (float*)c.take(w.scr.floats * 4);
   w.bytes = c.off;
   return w;
 }
@@ -177,27 +182,24 @@ extern "C" size_t taw_layer_workspace_bytes(const taw_layer_desc* desc) {
 
 // ------------------------------------------------------------------------------ op dispatch helpers
 static int gemm(const Plan& p, int dtype, int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
-                int64_t ldb, void* C, int64_t ldc, int c_dtype, int accumulate, const void* R, int64_t ldr, hipStream_t st) {
+                int64_t ldb, void* C, int64_t ldc, int c_dtype, int accumulate, const void* R, int64_t ldr, const GemmScratch& scr, hipStream_t st) {
   if (p.mfma_gemm && gemm_mfma_supported(dtype, mode, M, N, K, lda, ldb, ldc, c_dtype, ldr))
-    return launch_gemm_mfma(mode, M, N, K, A, lda, B, ldb, C, ldc, c_dtype, accumulate, R, ldr, st);
+    return launch_gemm_mfma(mode, M, N, K, A, lda, B, ldb, C, ldc, c_dtype, accumulate, R, ldr, scr, st);
   return launch_gemm_generic(dtype, mode, M, N, K, A, lda, B, ldb, C, ldc, c_dtype, accumulate, R, ldr, st);
 }
 
 // Backward of a linear y[T,N] = x[T,K] W[N,K]^T given dy: dx[T,K] = dy W (NN) and G[N,K] (+)= dy^T x (TN).
-// The two are independent; on the MFMA path they share one grid, and where the weight gradient has too few tiles to
-// fill its share of the chip it is cut along T into partial products in `part` (linear_bwd_scratch_floats elements;
-// nullptr: never cut), summed in a fixed order by a second kernel: the result does not depend on scheduling.
+// The two are independent; on the MFMA path they share one grid, and where one of them has too few tiles to fill its share of
+// the chip its contraction is cut into ranges whose partial products go to the scratch and are summed in a fixed order by a
+// second kernel: the result does not depend on scheduling.
 static int linear_bwd(const Plan& p, int dtype, int64_t T, int64_t N, int64_t K, const void* dy, const void* W, const void* x,
-                      void* dx, float* G, int accumulate, float* part, hipStream_t st) {
+                      void* dx, float* G, int accumulate, const GemmScratch& scr, hipStream_t st) {
   if (p.mfma_gemm && gemm_mfma_supported(dtype, GEMM_NN, T, K, N, N, K, K, dtype, 0) &&
-      gemm_mfma_supported(dtype, GEMM_TN, N, K, T, N, K, K, DT_F32, 0) && gemm_mfma_dual_supported(T, N)) {
-    int64_t chunk = T;
-    const int sp = part ? gemm_dual_splits(T, N, K, &chunk) : 1;
-    return launch_gemm_mfma_dual(N, K, T, dy, N, x, K, G, K, accumulate, T, K, N, dy, N, W, K, dx, K, part, sp, chunk, st);
-  }
-  int rc = gemm(p, dtype, GEMM_NN, T, K, N, dy, N, W, K, dx, K, dtype, 0, nullptr, 0, st);
+      gemm_mfma_supported(dtype, GEMM_TN, N, K, T, N, K, K, DT_F32, 0))
+    return launch_gemm_mfma_dual(N, K, T, dy, N, x, K, G, K, accumulate, T, K, N, dy, N, W, K, dx, K, scr, st);
+  int rc = gemm(p, dtype, GEMM_NN, T, K, N, dy, N, W, K, dx, K, dtype, 0, nullptr, 0, scr, st);
   if (rc) return rc;
-  return gemm(p, dtype, GEMM_TN, N, K, T, dy, N, x, K, G, K, DT_F32, accumulate, nullptr, 0, st);
+  return gemm(p, dtype, GEMM_TN, N, K, T, dy, N, x, K, G, K, DT_F32, accumulate, nullptr, 0, scr, st);
 }
 
 static const char* at(const void* base, size_t elem_off, int dtype) { return static_cast<const char*>(base) + elem_off * dt_size(dtype); }
@@ -216,32 +218,32 @@ extern "C" int taw_rope_table_init(const taw_layer_desc* desc, float* rope_table
 // The forward's kernel sequence into the intermediates `c`; y == nullptr stops after the SwiGLU
 // (all the backward needs when it rebuilds the intermediates).
 static int run_fwd(const taw_layer_desc* desc, const Plan& p, const taw_weight_layout& L, const void* W_chunk, const float* rope_table,
-                   const void* x, void* y, const Ctx& c, hipStream_t st) {
+                   const void* x, void* y, const Ctx& c, const GemmScratch& scr, hipStream_t st) {
   const int dt = desc->dtype;
   const int64_t T = (int64_t)desc->B * desc->S, H = desc->H, I = desc->I;
   // xn = rmsnorm(x; gamma_attn)
   TAW_LAUNCH(launch_rmsnorm_fwd(dt, T, (int)H, x, at(W_chunk, L.gamma_attn, dt), desc->rms_eps, c.xn, c.r1, st), "rmsnorm_fwd(attn)");
   // qkv = xn Wqkv^T, q and k (the first 2H columns) rotated: in the GEMM's epilogue where its tiles allow it
   if (p.mfma_gemm && dt == DT_BF16 && desc->head_dim == 128 && gemm_mfma_supported(dt, GEMM_NT, T, 3 * H, H, H, H, 3 * H, dt, 0) &&
-      gemm_mfma_rope_supported(T, 3 * H, H, 2 * H, desc->S)) {
-    TAW_LAUNCH(launch_gemm_mfma_nt_rope(T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, rope_table, desc->S, 2 * H, st),
+      gemm_mfma_rope_supported(3 * H, 2 * H)) {
+    TAW_LAUNCH(launch_gemm_mfma_nt_rope(T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, rope_table, desc->S, 2 * H, scr, st),
                "gemm qkv + rope");
   } else {
-    TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, dt, 0, nullptr, 0, st), "gemm qkv");
+    TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, dt, 0, nullptr, 0, scr, st), "gemm qkv");
     TAW_LAUNCH(launch_rope(dt, desc->B, desc->S, (int)(2 * H), desc->head_dim, c.qkv, 3 * H, rope_table, 0, st), "rope");
   }
   // o = causal softmax attention
   if (p.mfma_attn) TAW_LAUNCH(launch_attn_fwd_mfma(desc->B, desc->S, desc->n_heads, c.qkv, c.o, c.lse, st), "attention fwd (mfma)");
   else TAW_LAUNCH(launch_attn_fwd_generic(dt, desc->B, desc->S, desc->n_heads, desc->head_dim, c.qkv, c.o, c.lse, st), "attention fwd (generic)");
   // h = x + o Wo^T
-  TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, H, H, c.o, H, at(W_chunk, L.w_o, dt), H, c.h, H, dt, 0, x, H, st), "gemm o-proj");
+  TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, H, H, c.o, H, at(W_chunk, L.w_o, dt), H, c.h, H, dt, 0, x, H, scr, st), "gemm o-proj");
   // hn = rmsnorm(h; gamma_mlp)
   TAW_LAUNCH(launch_rmsnorm_fwd(dt, T, (int)H, c.h, at(W_chunk, L.gamma_mlp, dt), desc->rms_eps, c.hn, c.r2, st), "rmsnorm_fwd(mlp)");
   // gu = hn Wgu^T ; a = silu(g) u
-  TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 2 * I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, 2 * I, dt, 0, nullptr, 0, st), "gemm gate/up");
+  TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 2 * I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, 2 * I, dt, 0, nullptr, 0, scr, st), "gemm gate/up");
   TAW_LAUNCH(launch_swiglu_fwd(dt, T, (int)I, c.gu, c.a, st), "swiglu_fwd");
   // y = h + a Wd^T
-  if (y) TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, H, I, c.a, I, at(W_chunk, L.w_down, dt), I, y, H, dt, 0, c.h, H, st), "gemm down");
+  if (y) TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, H, I, c.a, I, at(W_chunk, L.w_down, dt), I, y, H, dt, 0, c.h, H, scr, st), "gemm down");
   return TAW_OK;
 }
 
@@ -263,7 +265,9 @@ extern "C" int taw_layer_fwd(const taw_layer_desc* desc, const void* W_chunk, co
   if (rc) return rc;
   taw_weight_layout L;
   taw_layer_weight_layout(desc, &L);
-  return run_fwd(desc, p, L, W_chunk, rope_table, x, y, carve_ctx(desc, recompute ? workspace : ctx), (hipStream_t)stream);
+  const Ctx c = carve_ctx(desc, recompute ? workspace : ctx);
+  const Work w = carve_work(desc, static_cast<char*>(workspace) + (recompute ? c.bytes : 0));
+  return run_fwd(desc, p, L, W_chunk, rope_table, x, y, c, w.scr, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------------------ backward
@@ -292,21 +296,22 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
   // the saved intermediates, or (TAW_RECOMPUTE) the front of the workspace, rebuilt here from x
   const Ctx c = carve_ctx(desc, recompute ? workspace : const_cast<void*>(ctx));
   const Work w = carve_work(desc, static_cast<char*>(workspace) + (recompute ? c.bytes : 0));
+  const GemmScratch& scr = w.scr;
   if (recompute) {
-    rc = run_fwd(desc, p, L, W_chunk, rope_table, x, nullptr, c, st);
+    rc = run_fwd(desc, p, L, W_chunk, rope_table, x, nullptr, c, scr, st);
     if (rc) return rc;
   }
 
   // y = h + a Wd^T :  da = dy Wd ;  G.Wd (+)= dy^T a
-  TAW_LAUNCH(linear_bwd(p, dt, T, H, I, dy, at(W_chunk, L.w_down, dt), c.a, w.da, G_shard + L.w_down, acc, w.splitk, st), "gemm da, G.w_down");
+  TAW_LAUNCH(linear_bwd(p, dt, T, H, I, dy, at(W_chunk, L.w_down, dt), c.a, w.da, G_shard + L.w_down, acc, scr, st), "gemm da, G.w_down");
   // a = silu(g) u
   TAW_LAUNCH(launch_swiglu_bwd(dt, T, (int)I, w.da, c.gu, w.dgu, st), "swiglu_bwd");
   // gu = hn Wgu^T :  dhn = dgu Wgu ;  G.Wgu (+)= dgu^T hn
-  TAW_LAUNCH(linear_bwd(p, dt, T, 2 * I, H, w.dgu, at(W_chunk, L.w_gate_up, dt), c.hn, w.dhn, G_shard + L.w_gate_up, acc, w.splitk, st), "gemm dhn, G.w_gate_up");
+  TAW_LAUNCH(linear_bwd(p, dt, T, 2 * I, H, w.dgu, at(W_chunk, L.w_gate_up, dt), c.hn, w.dhn, G_shard + L.w_gate_up, acc, scr, st), "gemm dhn, G.w_gate_up");
   // hn = rmsnorm(h) :  dh = dy + rmsnorm_bwd(dhn) ;  G.gamma_mlp
   TAW_LAUNCH(launch_rmsnorm_bwd(dt, T, (int)H, w.dhn, c.h, c.r2, at(W_chunk, L.gamma_mlp, dt), dy, w.dh, G_shard + L.gamma_mlp, acc, w.partials, st), "rmsnorm_bwd(mlp)");
   // h = x + o Wo^T :  do = dh Wo ;  G.Wo (+)= dh^T o
-  TAW_LAUNCH(linear_bwd(p, dt, T, H, H, w.dh, at(W_chunk, L.w_o, dt), c.o, w.dO, G_shard + L.w_o, acc, w.splitk, st), "gemm do, G.w_o");
+  TAW_LAUNCH(linear_bwd(p, dt, T, H, H, w.dh, at(W_chunk, L.w_o, dt), c.o, w.dO, G_shard + L.w_o, acc, scr, st), "gemm do, G.w_o");
   // attention backward
   // attention backward, then the rotary backward on dq, dk (the MFMA kernels apply it to their accumulators before storing)
   if (p.mfma_attn) {
@@ -318,7 +323,7 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
     TAW_LAUNCH(launch_rope(dt, desc->B, desc->S, (int)(2 * H), desc->head_dim, w.dqkv, 3 * H, rope_table, 1, st), "rope bwd");
   }
   // qkv = xn Wqkv^T :  dxn = dqkv Wqkv ;  G.Wqkv (+)= dqkv^T xn
-  TAW_LAUNCH(linear_bwd(p, dt, T, 3 * H, H, w.dqkv, at(W_chunk, L.w_qkv, dt), c.xn, w.dxn, G_shard + L.w_qkv, acc, w.splitk, st), "gemm dxn, G.w_qkv");
+  TAW_LAUNCH(linear_bwd(p, dt, T, 3 * H, H, w.dqkv, at(W_chunk, L.w_qkv, dt), c.xn, w.dxn, G_shard + L.w_qkv, acc, scr, st), "gemm dxn, G.w_qkv");
   // xn = rmsnorm(x) :  dx = dh + rmsnorm_bwd(dxn) ;  G.gamma_attn
   TAW_LAUNCH(launch_rmsnorm_bwd(dt, T, (int)H, w.dxn, x, c.r1, at(W_chunk, L.gamma_attn, dt), w.dh, dx, G_shard + L.gamma_attn, acc, w.partials, st), "rmsnorm_bwd(attn)");
   return TAW_OK;
@@ -405,7 +410,7 @@ extern "C" int taw_op_gemm(int32_t dtype, int32_t mode, int64_t M, int64_t N, in
   const bool can = gemm_mfma_supported(dtype, mode, M, N, K, lda, ldb, ldc, c_dtype, R ? ldr : 0);
   if (impl == TAW_IMPL_MFMA && !can) return fail(TAW_ERR_UNSUPPORTED, "MFMA GEMM needs bf16 and M, N, K, strides multiples of 8");
   if (impl != TAW_IMPL_GENERIC && can)
-    TAW_LAUNCH(launch_gemm_mfma(mode, M, N, K, A, lda, B, ldb, C, ldc, c_dtype, accumulate, R, ldr, st), "gemm (mfma)");
+    TAW_LAUNCH(launch_gemm_mfma(mode, M, N, K, A, lda, B, ldb, C, ldc, c_dtype, accumulate, R, ldr, GemmScratch{nullptr, 0}, st), "gemm (mfma)");
   else
     TAW_LAUNCH(launch_gemm_generic(dtype, mode, M, N, K, A, lda, B, ldb, C, ldc, c_dtype, accumulate, R, ldr, st), "gemm (generic)");
   return TAW_OK;
@@ -589,11 +594,11 @@ extern "C" int taw_op_qkv_rope(int32_t dtype, int32_t B, int32_t S, int32_t n_he
   const bool can = gemm_mfma_supported(dtype, GEMM_NT, T, 3 * H, H, H, H, 3 * H, dtype, 0);
   if (impl == TAW_IMPL_MFMA && !can) return fail(TAW_ERR_UNSUPPORTED, "MFMA GEMM needs bf16 and H a multiple of 8");
   if (impl != TAW_IMPL_GENERIC && can) {
-    if (head_dim == 128 && gemm_mfma_rope_supported(T, 3 * H, H, 2 * H, S)) {
-      TAW_LAUNCH(launch_gemm_mfma_nt_rope(T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, rope_table, S, 2 * H, st), "gemm qkv + rope");
+    if (head_dim == 128 && gemm_mfma_rope_supported(3 * H, 2 * H)) {
+      TAW_LAUNCH(launch_gemm_mfma_nt_rope(T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, rope_table, S, 2 * H, GemmScratch{nullptr, 0}, st), "gemm qkv + rope");
       return TAW_OK;
     }
-    TAW_LAUNCH(launch_gemm_mfma(GEMM_NT, T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, dtype, 0, nullptr, 0, st), "gemm qkv (mfma)");
+    TAW_LAUNCH(launch_gemm_mfma(GEMM_NT, T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, dtype, 0, nullptr, 0, GemmScratch{nullptr, 0}, st), "gemm qkv (mfma)");
   } else {
     TAW_LAUNCH(launch_gemm_generic(dtype, GEMM_NT, T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, dtype, 0, nullptr, 0, st), "gemm qkv (generic)");
   }
@@ -620,6 +625,6 @@ extern "C" int taw_op_linear_bwd(int32_t dtype, int64_t T, int64_t N, int64_t K,
   p.mfma_gemm = can && impl != TAW_IMPL_GENERIC;
   p.mfma_attn = false;
   if (scratch) TAW_REQUIRE_ALIGNED(scratch);
-  TAW_LAUNCH(linear_bwd(p, dtype, T, N, K, dy, W, x, dx, G, accumulate ? 1 : 0, scratch, st), "linear backward");
+  TAW_LAUNCH(linear_bwd(p, dtype, T, N, K, dy, W, x, dx, G, accumulate ? 1 : 0, GemmScratch{scratch, scratch ? linear_bwd_scratch_floats(T, N, K) : 0}, st), "linear backward");
   return TAW_OK;
 }

@@ -101,26 +101,31 @@ __host__ __device__ inline void gemm_tile_of_block(int block, int tiles_m, int t
 // ---- MFMA bf16 kernels (gemm_mfma.hip, attn_mfma.hip) -----------------------------------------
 bool gemm_mfma_supported(int dtype, int mode, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
                          int64_t ldc, int c_dtype, int64_t ldr);
+// Scratch a launch may put fp32 partial products into (a contraction cut into ranges, summed by a second kernel in a fixed order);
+// nullptr / 0: never cut.
+struct GemmScratch {
+  float* part;
+  size_t floats;
+};
 int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
                      int64_t ldb, void* C, int64_t ldc, int c_dtype, int accumulate, const void* R,
-                     int64_t ldr, hipStream_t st);
+                     int64_t ldr, const GemmScratch& scr, hipStream_t st);
 // A weight gradient C0[M0,N0] (fp32, TN form, optionally accumulated) and an input gradient C1[M1,N1] (bf16, NN form) in one
-// grid: the pair every linear of the backward has.  Needs both K % 32 == 0 on top of gemm_mfma_supported for each.
-bool gemm_mfma_dual_supported(int64_t K_tn, int64_t K_nn);
-// part / splits / k_chunk: the weight gradient cut into `splits` ranges of k_chunk contraction rows (gemm_dual_splits), their
-// partial products in part[splits][M0][N0] fp32, summed into C0 by a second kernel in a fixed order; splits <= 1 or part ==
-// nullptr: not cut
+// grid: the pair every linear of the backward has.
 int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, int64_t lda0, const void* B0, int64_t ldb0, float* C0,
                           int64_t ldc0, int accumulate0, int64_t M1, int64_t N1, int64_t K1, const void* A1, int64_t lda1,
-                          const void* B1, int64_t ldb1, void* C1, int64_t ldc1, float* part, int splits, int64_t k_chunk, hipStream_t st);
+                          const void* B1, int64_t ldb1, void* C1, int64_t ldc1, const GemmScratch& scr, hipStream_t st);
+// fp32 elements the two above use at most, given enough, for C[M,N] = A[M,K] B[N,K]^T (bf16) and for the backward of the linear
+// y[T,N] = x[T,K] W^T; a launch that gets fewer makes do with them
+size_t gemm_nt_scratch_floats(int64_t M, int64_t N, int64_t K);
+size_t gemm_linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K);
 // ranges (and rows per range) for the weight gradient of the linear y[T, N] = x[T, K] W^T; 1 = not cut
 int gemm_dual_splits(int64_t T, int64_t N, int64_t K, int64_t* k_chunk);
 // C[M,N] = A[M,K] B[N,K]^T (bf16) with the rotary embedding applied in the epilogue to the columns below rot_cols (heads of
-// 128, adjacent pairs, row r at position r % S; table [S, 64, 2] fp32).  Needs M % 256 == 0, N % 256 == 0, K % 64 == 0,
-// rot_cols % 256 == 0, S >= 32.
-bool gemm_mfma_rope_supported(int64_t M, int64_t N, int64_t K, int64_t rot_cols, int S);
+// 128, adjacent pairs, row r at position r % S; table [S, 64, 2] fp32).  Needs N % 8 == 0, rot_cols % 128 == 0.
+bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols);
 int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
-                             const float* rope_table, int S, int64_t rot_cols, hipStream_t st);
+                             const float* rope_table, int S, int64_t rot_cols, const GemmScratch& scr, hipStream_t st);
 // bf16, head_dim 128, and S * 3 * n_heads * head_dim * 2 bytes below 4 GiB (32-bit row offsets inside one batch element)
 bool attn_mfma_supported(int dtype, int S, int nh, int d);
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st);

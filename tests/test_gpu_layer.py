@@ -267,3 +267,10 @@ def test_recompute_mode_gives_the_same_results(taw, cfg):
     dxr, _ = O.layer_bwd(w64, cache, I.to_f64(dy, cfg.dtype))
     assert U.tensor_scale_err(U.from_dev(outs[1][0]), yr) < U.TOL[cfg.dtype]
     assert U.tensor_scale_err(U.from_dev(outs[1][1]), dxr) < U.TOL[cfg.dtype]
+
+
+@pytest.mark.parametrize("B,S,nh,I_", [(1, 50, 8, 2816), (3, 111, 8, 2816), (1, 1, 4, 1000)])
+def test_bf16_layer_of_few_tokens(taw, B, S, nh, I_):
+    """Few rows against wide weights: the contractions of the down projection and of the input gradients are cut into ranges (up to 8
+    of at least 256), the last one ragged, and summed by the second kernel, with the residual and the rotation where they belong."""
+    U.check_layer(taw, I.LayerConfig("few-tokens", I.BF16, B, S, nh * 128, nh, 128, I_, sigma_w=0.05), seed=B + S, gamma_jitter=0.1)

@@ -349,3 +349,33 @@ def test_optimizer_step(taw, dtype, n):
     assert U.tensor_scale_err(U.from_dev(chunk), w64) < (4e-3 if dtype == I.BF16 else 1e-6)
     if dtype == I.BF16:   # the chunk is exactly the master weights rounded to bf16
         assert np.array_equal(I.to_storage(master.cpu().numpy(), dtype), chunk.view(torch.int16).cpu().numpy().view(np.uint16))
+
+
+# sizes at which the launcher takes its smaller tiles (64 x 64 at the first three, 128 x 128 with two and with four stages, 128 x 256 and
+# 256 x 256 at the others), each with remainders in rows, columns and contraction: less than one step, a whole one, one more
+@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (65, 72, 8), (333, 264, 136), (2100, 2056, 264), (1501, 1032, 1032), (1000, 4104, 2056), (2050, 2056, 2056)],
+                         ids=lambda v: str(v))
+def test_linear_tile_shapes(taw, T, N, K):
+    """y = x W^T (+ residual) and its backward at every tile shape against fp64 products of the same bf16 operands.  bf16 results: one
+    rounding, 2^-9 of the element, so below 2^-8 of the tensor's scale; fp32 ones: accumulation order only, as in
+    test_gemm_mfma_fp32_output_is_accurate.  The weight gradient starts from values it has to keep or to forget."""
+    import torch
+    x, W, dy = (I.device_normal(s, seed=i, std=d) for i, (s, d) in enumerate((((T, K), 1.0), ((N, K), 0.02), ((T, N), 1.0))))
+    R = I.device_normal((T, N), seed=9, std=1.0)
+    y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    taw.taw_op_gemm(I.BF16, 0, T, N, K, x, K, W, K, y, N, I.BF16, 0, R, N, taw.TAW_IMPL_MFMA)
+    x64, W64, dy64 = x.double(), W.double(), dy.double()
+    refs = {"y": (y, x64 @ W64.t() + R.double(), 2.0 ** -8)}
+    n_scr = taw.taw_op_linear_bwd_scratch_floats(T, N, K)
+    scratch = torch.full((n_scr,), float("nan"), dtype=torch.float32, device="cuda") if n_scr else None
+    G0 = I.device_normal((N, K), seed=11, std=1.0, dtype=torch.float32)
+    for acc in (0, 1):
+        dx = torch.full((T, K), float("nan"), dtype=torch.bfloat16, device="cuda")
+        G = G0.clone()
+        taw.taw_op_linear_bwd(I.BF16, T, N, K, dy, W, x, dx, G, acc, taw.TAW_IMPL_MFMA, scratch=scratch)
+        refs[f"dx{acc}"] = (dx, dy64 @ W64, 2.0 ** -8)
+        refs[f"G{acc}"] = (G, dy64.t() @ x64 + acc * G0.double(), 2e-6)
+    torch.cuda.synchronize()
+    for k, (got, ref, tol) in refs.items():
+        err = float((got.double() - ref).abs().max() / ref.abs().max())
+        assert err < tol, (k, err)
