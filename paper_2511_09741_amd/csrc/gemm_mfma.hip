@@ -217,17 +217,20 @@ __device__ __forceinline__ void stage_rows(const f32x16_t& blk, float* stg_blk, 
 // Columns below rot_cols are heads of 128 whose adjacent pairs (2i, 2i+1) are rotated by the angle of
 // (row % S, i); table [S][64][2] fp32 of (cos, sin).  A lane holds 8 consecutive columns of a row here,
 // i.e. 4 whole pairs, in fp32: the fused qkv projection then needs no rotary pass of its own, and q, k
-// are rounded to bf16 once.  rot_cols is a multiple of 128.
+// are rounded to bf16 once.  rot_cols is a multiple of 128.  round_first: rounded to bf16 before the rotation too, as a
+// separate rotary pass over the stored projection does; kept where such a pass stood, since the scores of a wide layer (large q, k)
+// carry that rounding into y and the gradients at the 1 % level and a layer's results should not depend on how it is launched.
 constexpr int kEpiNone = 0, kEpiRope = 1;
 struct EpiArgs {
   const float* table;
   int S;
   int64_t rot_cols;
+  int round_first;
 };
 template <bool C_F32, int EPI = kEpiNone>
 __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                                 int wm, int wn, void* __restrict__ Cv, int64_t ldc, int accumulate,
-                                                const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0}) {
+                                                const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}) {
   constexpr int SLD = 132;
   constexpr int ES = C_F32 ? 4 : 2;                       // bytes per element of C (and R)
   float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
@@ -270,7 +273,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
             const float cc[4] = {cs0[0], cs0[2], cs1[0], cs1[2]}, sn[4] = {cs0[1], cs0[3], cs1[1], cs1[3]};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const float a = v[2 * e], b2 = v[2 * e + 1];
+              const float a = ea.round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = ea.round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1];
               v[2 * e] = a * cc[e] - b2 * sn[e];
               v[2 * e + 1] = a * sn[e] + b2 * cc[e];
             }
@@ -297,18 +300,24 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
   }
 }
 
-// the rotation of 4 or 8 consecutive columns col .. of row `row`, in place
-template <int V>
-__device__ __forceinline__ void rotate_chunk(float (&v)[V], int64_t row, int64_t col, const EpiArgs& ea) {
-  if (col >= ea.rot_cols) return;
-  const float* tb = ea.table + ((row % ea.S) * 64 + ((col & 127) >> 1)) * 2;
-#pragma unroll
-  for (int e = 0; e < V / 2; ++e) {
-    const float a = v[2 * e], b2 = v[2 * e + 1], c = tb[2 * e], sn = tb[2 * e + 1];
-    v[2 * e] = a * c - b2 * sn;
-    v[2 * e + 1] = a * sn + b2 * c;
+// the rotation of 8 consecutive columns col .. col + 7 of row `row`: the table's 4 pairs, and their use
+struct RotPairs {
+  f32x4_t cs[2];
+  __device__ __forceinline__ void load(int64_t row, int64_t col, const EpiArgs& ea) {
+    const unsigned pos = (unsigned)row % (unsigned)ea.S;      // token counts fit 32 bits
+    const float* tb = ea.table + ((int64_t)pos * 64 + ((col & 127) >> 1)) * 2;
+    cs[0] = *reinterpret_cast<const f32x4_t*>(tb);
+    cs[1] = *reinterpret_cast<const f32x4_t*>(tb + 4);
   }
-}
+  __device__ __forceinline__ void rotate(float (&v)[8], int round_first) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1], c = cs[e >> 1][2 * (e & 1)], sn = cs[e >> 1][2 * (e & 1) + 1];
+      v[2 * e] = a * c - b2 * sn;
+      v[2 * e + 1] = a * sn + b2 * c;
+    }
+  }
+};
 
 // ---- epilogue of a wavefront's (32 TM) x (32 TN) block at (mw, nw), any part of it possibly outside C: 32-row slices -> fp32
 // staging rows in LDS (one region per wavefront, in the ring, which every wavefront has finished reading) -> 16-byte accesses that
@@ -336,6 +345,7 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
 #pragma unroll 1
       for (int it = 0; it < CPR / 2; it += U) {
         Vec<T, V> r[U], c[U];
+        RotPairs rot[U];
         int64_t row[U], col[U];
         bool in[U];
 #pragma unroll
@@ -346,6 +356,7 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
           in[u] = row[u] < M && col[u] < N;
           if (in[u] && R) r[u].load(R + row[u] * ldr + col[u]);
           if (in[u] && accumulate) c[u].load(C + row[u] * ldc + col[u]);
+          if (EPI == kEpiRope && in[u] && col[u] < ea.rot_cols) rot[u].load(row[u], col[u], ea);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -354,8 +365,13 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
           const float* sp = stg + idx / CPR * SLD + idx % CPR * V;
           float v[V];
 #pragma unroll
-          for (int e = 0; e < V; ++e) v[e] = sp[e];
-          if constexpr (EPI == kEpiRope) rotate_chunk(v, row[u], col[u], ea);
+          for (int e = 0; e < V; e += 4) {
+            const f32x4_t q = *reinterpret_cast<const f32x4_t*>(sp + e);
+            v[e] = q[0]; v[e + 1] = q[1]; v[e + 2] = q[2]; v[e + 3] = q[3];
+          }
+          if constexpr (EPI == kEpiRope) {
+            if (col[u] < ea.rot_cols) rot[u].rotate(v, ea.round_first);
+          }
           Vec<T, V> o;
 #pragma unroll
           for (int e = 0; e < V; ++e) {
@@ -998,7 +1014,7 @@ inline GemmArgs make_args(int64_t M, int64_t N, int64_t K, const void* A, int64_
   g.R = R; g.ldr = ldr;
   g.tiles_m = (int)((M + BM - 1) / BM);
   g.tiles_n = (int)((N + BN - 1) / BN);
-  g.epi = EpiArgs{nullptr, 1, 0};
+  g.epi = EpiArgs{nullptr, 1, 0, 0};
   g.splits = 1;
   g.k_chunk = K;
   g.part = nullptr;
@@ -1064,7 +1080,13 @@ __device__ __forceinline__ void reduce_parts(const GemmArgs& g, int64_t first, i
         v[e] += q[0]; v[e + 1] += q[1]; v[e + 2] += q[2]; v[e + 3] += q[3];
       }
     }
-    if constexpr (ROPE) rotate_chunk(v, r, c, g.epi);
+    if constexpr (ROPE) {
+      if (c < g.epi.rot_cols) {
+        RotPairs rot;
+        rot.load(r, c, g.epi);
+        rot.rotate(v, g.epi.round_first);
+      }
+    }
     T* cp = static_cast<T*>(g.C) + r * g.ldc + c;
     Vec<T, V> x;
     if (g.R) {
@@ -1297,7 +1319,7 @@ bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols) { return N % 8 == 0 &
 int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
                              const float* rope_table, int S, int64_t rot_cols, const GemmScratch& scr, hipStream_t st) {
   v2::GemmArgs g = v2::make_args(M, N, K, A, lda, B, ldb, C, ldc, 0, nullptr, 0);
-  g.epi = v2::EpiArgs{rope_table, S, rot_cols};
+  g.epi = v2::EpiArgs{rope_table, S, rot_cols, !(M % BM == 0 && N % BN == 0 && S >= 32)};
   const GemmPlan p = plan_gemm(M, N, K, scr.floats);
   apply_plan(g, p, 0, scr.part);
   const int rc = launch_planned<GEMM_NT, false, v2::kEpiRope>(g, p, st);
