@@ -163,23 +163,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(REG ? 
     prow[c] = ((lds_acc[c] + lds_acc[(size_t)H + c]) + lds_acc[2 * (size_t)H + c]) + lds_acc[3 * (size_t)H + c];
 }
 
-// out[c] (=|+=) sum_p partials[p][c].  A workgroup owns 64 columns: thread (q = tid & 15, g = tid >> 4)
-// sums rows g, g + 16, ... of columns 4q .. 4q + 3 (16-byte loads, a 256-byte row segment per 16
-// threads), then the 16 row groups are added in a fixed order through LDS: reproducible, no atomics.
+// out[c] (=|+=) sum_p partials[p][c].  A workgroup owns 16 columns: thread (q = tid & 3, g = tid >> 2)
+// sums rows g, g + 64, ... of columns 4q .. 4q + 3 (16-byte loads, a 64-byte row segment per 4
+// threads), then the 64 row groups are added in a fixed order through LDS: reproducible, no atomics.
+// Bound by the latency of its dependent loads: 64 row groups leave 8 of 512 rows to a thread and all of them in
+// flight (with 16 groups, and a quarter of the workgroups: 12 us at 512 rows of 1024).
 __global__ void __launch_bounds__(256) colsum_kernel(const float* __restrict__ partials, int np, int H,
                                                      float* __restrict__ out, int accumulate) {
-  __shared__ float red[16][64];
-  const int q = threadIdx.x & 15, g = threadIdx.x >> 4;
-  const int c0 = blockIdx.x * 64 + 4 * q;
+  __shared__ float red[64][17], red2[16][17];
+  const int q = threadIdx.x & 3, g = threadIdx.x >> 2;
+  const int c0 = blockIdx.x * 16 + 4 * q;
   float s[4] = {0.f, 0.f, 0.f, 0.f};
   if (c0 + 3 < H && (H & 3) == 0) {
-    for (int p = g; p < np; p += 16) {
+#pragma unroll 8
+    for (int p = g; p < np; p += 64) {
       const f32x4_t v = *reinterpret_cast<const f32x4_t*>(partials + (int64_t)p * H + c0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) s[j] += v[j];
     }
   } else {
-    for (int p = g; p < np; p += 16)
+    for (int p = g; p < np; p += 64)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         if (c0 + j < H) s[j] += partials[(int64_t)p * H + c0 + j];
@@ -187,14 +190,18 @@ __global__ void __launch_bounds__(256) colsum_kernel(const float* __restrict__ p
 #pragma unroll
   for (int j = 0; j < 4; ++j) red[g][4 * q + j] = s[j];
   __syncthreads();
-  if (threadIdx.x < 64) {
-    const int c = blockIdx.x * 64 + threadIdx.x;
-    if (c < H) {
-      float t = 0.f;
+  const int c = threadIdx.x & 15, part = threadIdx.x >> 4;
+  float t = 0.f;
 #pragma unroll
-      for (int gg = 0; gg < 16; ++gg) t += red[gg][threadIdx.x];
-      out[c] = accumulate ? out[c] + t : t;
-    }
+  for (int k = 0; k < 4; ++k) t += red[4 * part + k][c];
+  red2[part][c] = t;
+  __syncthreads();
+  const int col = blockIdx.x * 16 + threadIdx.x;
+  if (threadIdx.x < 16 && col < H) {
+    t = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t += red2[k][threadIdx.x];
+    out[col] = accumulate ? out[col] + t : t;
   }
 }
 
@@ -520,7 +527,7 @@ static int rmsnorm_bwd_dispatch(int64_t T_, int H, const T* dout, const T* z, co
 #undef TAW_RN_BWD
   int e = last_err();
   if (e) return e;
-  hipLaunchKernelGGL(colsum_kernel, dim3((H + 63) / 64), dim3(256), 0, st, partials, grid, H, dgamma, accumulate);
+  hipLaunchKernelGGL(colsum_kernel, dim3((H + 15) / 16), dim3(256), 0, st, partials, grid, H, dgamma, accumulate);
   return last_err();
 }
 
