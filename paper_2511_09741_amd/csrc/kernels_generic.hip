@@ -1,80 +1,412 @@
 // Shape-generic kernels: fp32 arithmetic on fp32 or bf16 storage, any dimensions.  They carry the
-// fp32 configuration (head_dim 16, widths that fit no MFMA tile) and every bf16 shape the MFMA
-// kernels do not take.  Simple LDS-tiled GEMM and one-wavefront-per-row attention.
+// fp32 configuration (head_dim 16, widths that fit no bf16 MFMA tile) and every bf16 shape the MFMA
+// kernels do not take.  The layers they serve are small: what bounds them is the latency of a launch
+// and of the loads behind it, so a launch does as much as it can and has all of its loads in flight early.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "taw_internal.h"
 
 namespace taw {
 
 // =============================================================================== GEMM
-// C[m,n] (=|+=) sum_k A(m,k) B(k,n) (+ R[m,n]);  A(m,k) = A[m*a_rs + k*a_cs], B(k,n) = B[k*b_rs + n*b_cs].
-// 32x32 output tile per 256-thread workgroup, 2x2 outputs per thread, k ascending in steps of 16.
-template <typename TI, typename TC>
-__global__ void __launch_bounds__(256) gemm_generic_kernel(int64_t M, int64_t N, int64_t K, const TI* __restrict__ A,
-                                                           int64_t a_rs, int64_t a_cs, const TI* __restrict__ B,
-                                                           int64_t b_rs, int64_t b_cs, TC* __restrict__ C, int64_t ldc,
-                                                           int accumulate, const TC* __restrict__ R, int64_t ldr) {
-  __shared__ float As[16][33];  // [k][m]
-  __shared__ float Bs[16][33];  // [k][n]
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t m0 = (int64_t)blockIdx.y * 32, n0 = (int64_t)blockIdx.x * 32;
-  float acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
-  for (int64_t k0 = 0; k0 < K; k0 += 16) {
-    for (int e = threadIdx.x; e < 512; e += 256) {
-      const int kk = e & 15, mm = e >> 4;
-      const int64_t gm = m0 + mm, gn = n0 + mm, gk = k0 + kk;
-      As[kk][mm] = (gm < M && gk < K) ? (float)A[gm * a_rs + gk * a_cs] : 0.f;
-      Bs[kk][mm] = (gn < N && gk < K) ? (float)B[gk * b_rs + gn * b_cs] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const float a0 = As[kk][ty], a1 = As[kk][ty + 16];
-      const float b0 = Bs[kk][tx], b1 = Bs[kk][tx + 16];
-      acc[0][0] += a0 * b0; acc[0][1] += a0 * b1;
-      acc[1][0] += a1 * b0; acc[1][1] += a1 * b1;
-    }
-    __syncthreads();
+// C[m,n] (=|+=) sum_k A(m,k) B(k,n) (+ R[m,n]) on the fp32 matrix instruction (16x16x4, IEEE fp32 products and sums), operands
+// straight from memory into registers: of 16 consecutive k, lane group g = lane >> 4 loads k = 4g .. 4g + 3 (one 16-byte
+// load where the operand is contiguous along k) and matrix instruction i multiplies the four k = 4g + i, the same for both operands.
+//   SPLIT: a workgroup owns 16 x 16 outputs, its four wavefronts a quarter of K each, summed through LDS in wavefront order: every
+//     load of a short contraction is in flight at once, and a 128 x 64 result has 32 workgroups.
+//   otherwise: a workgroup owns 64 x 64, each wavefront 32 x 32 over all of K: more products per load, for results that fill the chip.
+// (32 x 32 tiles staged through LDS 16 k at a time, one exposed load latency per 16 k, took 6 - 30 us for the products of a
+// 64-wide layer with 128 tokens; these take 2 - 5.)
+namespace gen {
+
+struct Args {
+  int64_t M, N, K;
+  const void* A;
+  int64_t lda;
+  const void* B;
+  int64_t ldb;
+  void* C;
+  int64_t ldc;
+  int accumulate;
+  const void* R;
+  int64_t ldr;
+  int tiles_n, blocks;        // tiles along n, workgroups in all
+  const float* table;         // kRope: [S][d/2][2] (cos, sin); columns below rot_cols are rotated, row r at position r % S
+  int S, d;
+  int64_t rot_cols;
+  const void* gu;             // kSwigluBwd: [M][2N] gate | up
+  void* C2;                   // kSwigluFwd: silu(gate) up, [M][N]; C is [M][2N] gate | up and B has 2N rows
+};
+enum { kPlain = 0, kRope = 1, kSwigluFwd = 2, kSwigluBwd = 3 };
+
+template <typename T> __device__ __forceinline__ f32x4_t load4(const T* p) {
+  if constexpr (sizeof(T) == 4) {
+    return *reinterpret_cast<const f32x4_t*>(p);
+  } else {
+    const bf16x4_t v = *reinterpret_cast<const bf16x4_t*>(p);
+    return f32x4_t{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
   }
+}
+
+// the four values k .. k + 3 of one row (KC) or column of an operand; those at or beyond K are 0 and not read
+template <typename T, bool KC, bool VEC>
+__device__ __forceinline__ f32x4_t operand4(const T* mat, int64_t ld, int64_t idx, int64_t k, int64_t K) {
+  if (KC && VEC && k + 4 <= K) return load4(mat + idx * ld + k);
+  f32x4_t v;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i) v[i] = k + i < K ? (float)(KC ? mat[idx * ld + k + i] : mat[(k + i) * ld + idx]) : 0.f;
+  return v;
+}
+
+// one output (and, kSwigluFwd, its partner of the up half) leaves; lanes l, l ^ 1 hold columns 2j, 2j + 1 of one row
+template <typename TC, int EPI>
+__device__ __forceinline__ void finish(const Args& g, int64_t row, int64_t col, float v, float v2) {
+  if constexpr (EPI == kRope) {
+    const float w = __shfl_xor(v, 1, 64);
+    if (col < g.rot_cols && row < g.M) {
+      const float* tb = g.table + ((row % g.S) * (g.d / 2) + (col % g.d) / 2) * 2;
+      v = col & 1 ? w * tb[1] + v * tb[0] : v * tb[0] - w * tb[1];
+    }
+  }
+  if (row >= g.M || col >= g.N) return;
+  TC* C = static_cast<TC*>(g.C);
+  if constexpr (EPI == kSwigluFwd) {
+    TC* c = C + row * g.ldc + col;
+    c[0] = (TC)v;
+    c[g.N] = (TC)v2;
+    v = (float)(TC)v;          // the backward sees the stored gate and up: so does this product
+    v2 = (float)(TC)v2;
+    static_cast<TC*>(g.C2)[row * g.N + col] = (TC)(v / (1.0f + __expf(-v)) * v2);
+    return;
+  }
+  if constexpr (EPI == kSwigluBwd) {
+    v = (float)(TC)v;          // the gradient of a, in its storage type
+    const TC* gu = static_cast<const TC*>(g.gu) + row * 2 * g.N + col;
+    const float gg = (float)gu[0], uu = (float)gu[g.N], sig = 1.0f / (1.0f + __expf(-gg));
+    TC* c = C + row * g.ldc + col;
+    c[0] = (TC)(v * uu * sig * (1.0f + gg * (1.0f - sig)));
+    c[g.N] = (TC)(v * gg * sig);
+    return;
+  }
+  if (g.R) v += (float)static_cast<const TC*>(g.R)[row * g.ldr + col];
+  TC* c = C + row * g.ldc + col;
+  if (g.accumulate) v += (float)*c;
+  *c = (TC)v;
+}
+
+template <typename TI, typename TC, int MODE, bool VEC, bool SPLIT, int EPI>
+__device__ __forceinline__ void body(const Args& g, int block, float* red) {
+  constexpr bool A_KC = MODE != GEMM_TN, B_KC = MODE == GEMM_NT;
+  constexpr int R = SPLIT ? 1 : 2, NB = EPI == kSwigluFwd ? 2 : 1;        // R x R matrix tiles per wavefront; NB: B panels
+  constexpr int U = SPLIT ? 4 : 2;                                        // groups of 16 k whose loads are in flight together
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g4 = 4 * (lane >> 4);
+  const int tm = block / g.tiles_n, tn = block - tm * g.tiles_n;
+  const int64_t m0 = (int64_t)tm * (SPLIT ? 16 : 64) + (SPLIT ? 0 : 32 * (wave >> 1));
+  const int64_t n0 = (int64_t)tn * (SPLIT ? 16 : 64) + (SPLIT ? 0 : 32 * (wave & 1));
+  int64_t k0 = 0, k1 = g.K;
+  if (SPLIT) {
+    const int64_t part = (g.K + 63) / 64 * 16;
+    k0 = wave * part;
+    k1 = k0 + part < g.K ? k0 + part : g.K;
+  }
+  const TI* A = static_cast<const TI*>(g.A);
+  const TI* B = static_cast<const TI*>(g.B);
+  int64_t ar[R], bc[R];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t gm = m0 + ty + 16 * i, gn = n0 + tx + 16 * j;
-      if (gm < M && gn < N) {
-        float v = acc[i][j];
-        if (R) v += (float)R[gm * ldr + gn];
-        if (accumulate) v += (float)C[gm * ldc + gn];
-        C[gm * ldc + gn] = (TC)v;
+  for (int i = 0; i < R; ++i) {          // rows and columns outside the result read its last one
+    ar[i] = m0 + 16 * i + l16 < g.M ? m0 + 16 * i + l16 : g.M - 1;
+    bc[i] = n0 + 16 * i + l16 < g.N ? n0 + 16 * i + l16 : g.N - 1;
+  }
+  f32x4_t acc[NB][R][R];
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[q][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int64_t k = k0; k < k1; k += 16 * U) {
+    f32x4_t a[U][R], b[U][NB][R];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t kk = k + 16 * u + g4;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        a[u][i] = operand4<TI, A_KC, VEC>(A, g.lda, ar[i], kk, k1);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) b[u][q][i] = operand4<TI, B_KC, VEC>(B, g.ldb, bc[i] + q * g.N, kk, k1);
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+          for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < R; ++j) acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][q][j][e], acc[q][i][j], 0, 0, 0);
+  }
+  // accumulator register r of lane l: row 4 (l >> 4) + r, column l & 15
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[((q * 4 + wave) * 16 + g4 + r) * 16 + l16] = acc[q][0][0][r];
+    __syncthreads();
+    float v[2] = {0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[q] += red[(q * 4 + w) * 256 + threadIdx.x];
+    finish<TC, EPI>(g, m0 + (threadIdx.x >> 4), n0 + l16, v[0], v[1]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) finish<TC, EPI>(g, m0 + 16 * i + g4 + r, n0 + 16 * j + l16, acc[0][i][j][r], acc[NB - 1][i][j][r]);
+  }
 }
+
+template <typename TI, typename TC, int MODE, bool VEC, bool SPLIT, int EPI>
+__global__ void __launch_bounds__(256) gemm_kernel(Args g) {
+  __shared__ float red[SPLIT ? (EPI == kSwigluFwd ? 2 : 1) * 1024 : 1];
+  body<TI, TC, MODE, VEC, SPLIT, EPI>(g, (int)blockIdx.x, red);
+}
+// weight gradient (TN, fp32) and input gradient (NN) of a linear in one grid
+template <typename T, bool VEC, int EPI>
+__global__ void __launch_bounds__(256) gemm_dual_kernel(Args g0, Args g1) {
+  __shared__ float red[1024];
+  if ((int)blockIdx.x < g0.blocks) body<T, float, GEMM_TN, VEC, true, kPlain>(g0, (int)blockIdx.x, red);
+  else body<T, T, GEMM_NN, VEC, true, EPI>(g1, (int)blockIdx.x - g0.blocks, red);
+}
+
+constexpr int64_t kSplitTiles = 4096;      // results of more 16 x 16 tiles than these fill the chip with 64 x 64 ones
+
+inline bool take_split(const Args& g) { return ((g.M + 15) / 16) * ((g.N + 15) / 16) <= kSplitTiles; }
+inline void tile_up(Args& g, bool split) {
+  const int t = split ? 16 : 64;
+  g.tiles_n = (int)((g.N + t - 1) / t);
+  g.blocks = (int)((g.M + t - 1) / t) * g.tiles_n;
+}
+// 16-byte loads along k: only operands that are contiguous along k use them
+inline bool vec_ok(int mode, const Args& g) { return mode == GEMM_TN || (g.lda % 4 == 0 && (mode == GEMM_NN || g.ldb % 4 == 0)); }
+
+inline Args make(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, int accumulate,
+                 const void* R, int64_t ldr) {
+  return Args{M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, 0, 0, nullptr, 1, 2, 0, nullptr, nullptr};
+}
+
+template <typename TI, typename TC, int MODE, int EPI>
+int launch(Args g, hipStream_t st) {
+  const bool vec = vec_ok(MODE, g), split = take_split(g);
+  tile_up(g, split);
+#define TAW_GEN(VEC, SPLIT) hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, VEC, SPLIT, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g)
+  if (split) { if (vec) TAW_GEN(true, true); else TAW_GEN(false, true); }
+  else { if (vec) TAW_GEN(true, false); else TAW_GEN(false, false); }
+#undef TAW_GEN
+  return (int)hipGetLastError();
+}
+template <typename TI, typename TC>
+int launch_mode(int mode, const Args& g, hipStream_t st) {
+  if (mode == GEMM_NT) return launch<TI, TC, GEMM_NT, kPlain>(g, st);
+  if (mode == GEMM_NN) return launch<TI, TC, GEMM_NN, kPlain>(g, st);
+  return launch<TI, TC, GEMM_TN, kPlain>(g, st);
+}
+
+}  // namespace gen
 
 int launch_gemm_generic(int dtype, int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
                         const void* B, int64_t ldb, void* C, int64_t ldc, int c_dtype, int accumulate,
                         const void* R, int64_t ldr, hipStream_t st) {
   if (M == 0 || N == 0) return 0;
-  int64_t a_rs, a_cs, b_rs, b_cs;
-  if (mode == GEMM_NT) { a_rs = lda; a_cs = 1; b_rs = 1; b_cs = ldb; }
-  else if (mode == GEMM_NN) { a_rs = lda; a_cs = 1; b_rs = ldb; b_cs = 1; }
-  else { a_rs = 1; a_cs = lda; b_rs = ldb; b_cs = 1; }
-  const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32));
-  if (dtype == DT_BF16) {
-    if (c_dtype == DT_BF16)
-      hipLaunchKernelGGL((gemm_generic_kernel<bf16_t, bf16_t>), grid, dim3(256), 0, st, M, N, K, (const bf16_t*)A, a_rs, a_cs,
-                         (const bf16_t*)B, b_rs, b_cs, (bf16_t*)C, ldc, accumulate, (const bf16_t*)R, ldr);
-    else
-      hipLaunchKernelGGL((gemm_generic_kernel<bf16_t, float>), grid, dim3(256), 0, st, M, N, K, (const bf16_t*)A, a_rs, a_cs,
-                         (const bf16_t*)B, b_rs, b_cs, (float*)C, ldc, accumulate, (const float*)R, ldr);
-  } else {
-    hipLaunchKernelGGL((gemm_generic_kernel<float, float>), grid, dim3(256), 0, st, M, N, K, (const float*)A, a_rs, a_cs,
-                       (const float*)B, b_rs, b_cs, (float*)C, ldc, accumulate, (const float*)R, ldr);
-  }
+  const gen::Args g = gen::make(M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr);
+  if (dtype == DT_F32) return gen::launch_mode<float, float>(mode, g, st);
+  return c_dtype == DT_BF16 ? gen::launch_mode<bf16_t, bf16_t>(mode, g, st) : gen::launch_mode<bf16_t, float>(mode, g, st);
+}
+
+int launch_gemm_generic_rope(int dtype, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
+                             int64_t ldc, const float* table, int S, int d, int64_t rot_cols, hipStream_t st) {
+  gen::Args g = gen::make(M, N, K, A, lda, B, ldb, C, ldc, 0, nullptr, 0);
+  g.table = table; g.S = S; g.d = d; g.rot_cols = rot_cols;
+  return dtype == DT_F32 ? gen::launch<float, float, GEMM_NT, gen::kRope>(g, st) : gen::launch<bf16_t, bf16_t, GEMM_NT, gen::kRope>(g, st);
+}
+
+int launch_gemm_generic_swiglu(int dtype, int64_t T, int64_t I, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* gu, void* a,
+                               hipStream_t st) {
+  gen::Args g = gen::make(T, I, K, A, lda, W, ldw, gu, 2 * I, 0, nullptr, 0);
+  g.C2 = a;
+  return dtype == DT_F32 ? gen::launch<float, float, GEMM_NT, gen::kSwigluFwd>(g, st) : gen::launch<bf16_t, bf16_t, GEMM_NT, gen::kSwigluFwd>(g, st);
+}
+
+bool gemm_generic_linear_bwd_supported(int64_t T, int64_t N, int64_t K) {
+  const int64_t t = (T + 15) / 16, n = (N + 15) / 16, k = (K + 15) / 16;
+  return t * k <= gen::kSplitTiles && n * k <= gen::kSplitTiles;
+}
+int launch_gemm_generic_linear_bwd(int dtype, int64_t T, int64_t N, int64_t K, const void* dy, const void* W, const void* x, void* dx, float* G,
+                                   int accumulate, const void* gu, hipStream_t st) {
+  gen::Args g0 = gen::make(N, K, T, dy, N, x, K, G, K, accumulate, nullptr, 0);
+  gen::Args g1 = gen::make(T, K, N, dy, N, W, K, dx, gu ? 2 * K : K, 0, nullptr, 0);
+  g1.gu = gu;
+  gen::tile_up(g0, true);
+  gen::tile_up(g1, true);
+  const bool vec = gen::vec_ok(GEMM_NN, g1);
+  const dim3 grid((unsigned)(g0.blocks + g1.blocks));
+#define TAW_GEN(T_, VEC, EPI) hipLaunchKernelGGL((gen::gemm_dual_kernel<T_, VEC, gen::EPI>), grid, dim3(256), 0, st, g0, g1)
+#define TAW_GEN_T(T_) do { if (gu) { if (vec) TAW_GEN(T_, true, kSwigluBwd); else TAW_GEN(T_, false, kSwigluBwd); } \
+                           else { if (vec) TAW_GEN(T_, true, kPlain); else TAW_GEN(T_, false, kPlain); } } while (0)
+  if (dtype == DT_F32) TAW_GEN_T(float); else TAW_GEN_T(bf16_t);
+#undef TAW_GEN_T
+#undef TAW_GEN
   return (int)hipGetLastError();
 }
 
-// =============================================================================== attention
+// =============================================================================== attention, narrow heads
+// head_dim <= 32: one wavefront per (batch, head, row), a lane per row of the other side (keys of a query, queries of a key), which
+// it keeps in registers: DP = head_dim rounded up to 8, 16 or 32 values, loaded in pairs or fours (head_dim is even), so a wavefront has 64 rows
+// in flight and no serial chain over the sequence.  Each lane sums over its own rows; the DP sums then meet by halves: at step b a
+// lane keeps the half its bit b names and receives the other lane's, until lane l holds element l % DP.
+// V: values per load, 4 where head_dim is a multiple of 4, else 2
+template <int V, typename T, int DP>
+__device__ __forceinline__ void load_row(float (&v)[DP], const T* p, int d) {
+  typedef T vec __attribute__((ext_vector_type(V)));
+#pragma unroll
+  for (int i = 0; i < DP; i += V) {
+    if (i < d) {
+      const vec x = *reinterpret_cast<const vec*>(p + i);
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[i + e] = (float)x[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[i + e] = 0.f;
+    }
+  }
+}
+template <int DP> __device__ __forceinline__ float dot_row(const float (&a)[DP], const float (&b)[DP]) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < DP; ++i) s += a[i] * b[i];
+  return s;
+}
+template <int DP> __device__ __forceinline__ float sum_lanes(float (&v)[DP], int lane) {
+#pragma unroll
+  for (int n = DP / 2; n > 0; n /= 2) {
+    const bool up = (lane & n) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const float mine = up ? v[n + i] : v[i], other = up ? v[i] : v[n + i];
+      v[i] = mine + __shfl_xor(other, n, 64);
+    }
+  }
+#pragma unroll
+  for (int n = DP; n < 64; n *= 2) v[0] += __shfl_xor(v[0], n, 64);
+  return v[0];
+}
+
+template <typename T, int DP, int V>
+__global__ void __launch_bounds__(256) attn_fwd_narrow_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int B, int S,
+                                                              int nh, int d) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t gid = (int64_t)blockIdx.x * 4 + wave;  // (b, h, t)
+  if (gid >= (int64_t)B * nh * S) return;
+  const int t = (int)(gid % S), h = (int)((gid / S) % nh), b = (int)(gid / ((int64_t)S * nh));
+  const int64_t H = (int64_t)nh * d, ld = 3 * H;
+  const T* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * d;
+  const float scale = 1.0f / sqrtf((float)d);
+  float q[DP], acc[DP], m = -INFINITY, z = 0.f;
+  load_row<V>(q, qbase + (int64_t)t * ld, d);
+#pragma unroll
+  for (int i = 0; i < DP; ++i) acc[i] = 0.f;
+  for (int u = lane; u <= t; u += 64) {
+    float k[DP], v[DP];
+    const T* row = qbase + (int64_t)u * ld;
+    load_row<V>(k, row + H, d);
+    load_row<V>(v, row + 2 * H, d);
+    const float s = dot_row(q, k) * scale, mn = fmaxf(m, s), keep = expf(m - mn), p = expf(s - mn);      // first key: m = -inf, keep = 0
+    m = mn;
+    z = z * keep + p;
+#pragma unroll
+    for (int i = 0; i < DP; ++i) acc[i] = acc[i] * keep + p * v[i];
+  }
+  const float mt = wave_max(m), keep = expf(m - mt);        // lanes without a key: exp(-inf) = 0
+  z = wave_sum(z * keep);
+#pragma unroll
+  for (int i = 0; i < DP; ++i) acc[i] *= keep;
+  const float r = sum_lanes(acc, lane) * (1.0f / z);
+  if (lane < d) o[((int64_t)b * S + t) * H + (int64_t)h * d + lane] = (T)r;
+  if (lane == 0) lse[((int64_t)b * nh + h) * S + t] = mt + logf(z);
+}
+
+// First half of the grid: dq of a query; second half: dk, dv of a key.  D[t] = dO[t] . o[t] is formed where it is needed.  The gradients of
+// rotated q and k are rotated back before they leave where a table is given.
+template <typename T, int DP, int V>
+__global__ void __launch_bounds__(256) attn_bwd_narrow_kernel(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dO,
+                                                              const float* __restrict__ lse, T* __restrict__ dqkv, int B, int S, int nh, int d,
+                                                              const float* __restrict__ rope, int half) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool keys = (int)blockIdx.x >= half;
+  const int64_t gid = (int64_t)((int)blockIdx.x - (keys ? half : 0)) * 4 + wave;
+  if (gid >= (int64_t)B * nh * S) return;
+  const int t = (int)(gid % S), h = (int)((gid / S) % nh), b = (int)(gid / ((int64_t)S * nh));
+  const int64_t H = (int64_t)nh * d, ld = 3 * H;
+  const T* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * d;
+  const int64_t ooff = (int64_t)b * S * H + (int64_t)h * d;
+  const float* L = lse + ((int64_t)b * nh + h) * S;
+  const float scale = 1.0f / sqrtf((float)d);
+  auto leave = [&](float v, int64_t part, bool rotate) {
+    if (rope && rotate) {
+      const float w = __shfl_xor(v, 1, 64);
+      if (lane < d) {
+        const float* tb = rope + ((int64_t)t * (d / 2) + lane / 2) * 2;
+        v = lane & 1 ? v * tb[0] - w * tb[1] : v * tb[0] + w * tb[1];
+      }
+    }
+    if (lane < d) dqkv[((int64_t)b * S + t) * ld + part * H + (int64_t)h * d + lane] = (T)v;
+  };
+  float x[DP], y[DP], acc[DP], acc2[DP];
+#pragma unroll
+  for (int i = 0; i < DP; ++i) { acc[i] = 0.f; acc2[i] = 0.f; }
+  if (!keys) {        // x = q[t], y = dO[t]
+    load_row<V>(x, qbase + (int64_t)t * ld, d);
+    load_row<V>(y, dO + ooff + (int64_t)t * H, d);
+    load_row<V>(acc2, o + ooff + (int64_t)t * H, d);
+    const float Dt = dot_row(y, acc2), Lt = L[t];
+    for (int u = lane; u <= t; u += 64) {
+      float k[DP], v[DP];
+      const T* row = qbase + (int64_t)u * ld;
+      load_row<V>(k, row + H, d);
+      load_row<V>(v, row + 2 * H, d);
+      const float ds = expf(dot_row(x, k) * scale - Lt) * (dot_row(y, v) - Dt);
+#pragma unroll
+      for (int i = 0; i < DP; ++i) acc[i] += ds * k[i];
+    }
+    leave(sum_lanes(acc, lane) * scale, 0, true);
+  } else {            // x = k[t], y = v[t]
+    load_row<V>(x, qbase + (int64_t)t * ld + H, d);
+    load_row<V>(y, qbase + (int64_t)t * ld + 2 * H, d);
+    for (int u = t + lane; u < S; u += 64) {
+      float q[DP], g[DP], ov[DP];
+      load_row<V>(q, qbase + (int64_t)u * ld, d);
+      load_row<V>(g, dO + ooff + (int64_t)u * H, d);
+      load_row<V>(ov, o + ooff + (int64_t)u * H, d);
+      const float p = expf(dot_row(q, x) * scale - L[u]), ds = p * (dot_row(g, y) - dot_row(g, ov));
+#pragma unroll
+      for (int i = 0; i < DP; ++i) {
+        acc[i] += ds * q[i];
+        acc2[i] += p * g[i];
+      }
+    }
+    leave(sum_lanes(acc, lane) * scale, 1, true);
+    leave(sum_lanes(acc2, lane), 2, false);
+  }
+}
+
+// =============================================================================== attention, any head
 // One wavefront per (batch, head, row).  Scores of the row live in LDS (S floats per wavefront).
+constexpr int kNarrowHead = 32;      // wider rows would not fit a lane's registers
 constexpr int kGenAttnMaxS = 4096;  // backward: 4 wavefronts x 2 arrays x 4096 x 4 B = 128 KiB of LDS
 bool attn_generic_supported(int S, int d) { return S >= 1 && S <= kGenAttnMaxS && d >= 2; }
 
@@ -223,7 +555,21 @@ static int attn_fwd_generic_t(int B, int S, int nh, int d, const T* qkv, T* o, f
   return (int)hipGetLastError();
 }
 
+template <typename T>
+static int attn_fwd_narrow_t(int B, int S, int nh, int d, const T* qkv, T* o, float* lse, hipStream_t st) {
+  const dim3 grid((unsigned)(((int64_t)B * nh * S + 3) / 4));
+#define TAW_NARROW(DP, V) hipLaunchKernelGGL((attn_fwd_narrow_kernel<T, DP, V>), grid, dim3(256), 0, st, qkv, o, lse, B, S, nh, d)
+  if (d % 4 == 0) { if (d <= 8) TAW_NARROW(8, 4); else if (d <= 16) TAW_NARROW(16, 4); else TAW_NARROW(32, 4); }
+  else { if (d <= 8) TAW_NARROW(8, 2); else if (d <= 16) TAW_NARROW(16, 2); else TAW_NARROW(32, 2); }
+#undef TAW_NARROW
+  return (int)hipGetLastError();
+}
+
 int launch_attn_fwd_generic(int dtype, int B, int S, int nh, int d, const void* qkv, void* o, float* lse, hipStream_t st) {
+  if (d <= kNarrowHead) {
+    if (dtype == DT_BF16) return attn_fwd_narrow_t<bf16_t>(B, S, nh, d, (const bf16_t*)qkv, (bf16_t*)o, lse, st);
+    return attn_fwd_narrow_t<float>(B, S, nh, d, (const float*)qkv, (float*)o, lse, st);
+  }
   if (dtype == DT_BF16) return attn_fwd_generic_t<bf16_t>(B, S, nh, d, (const bf16_t*)qkv, (bf16_t*)o, lse, st);
   return attn_fwd_generic_t<float>(B, S, nh, d, (const float*)qkv, (float*)o, lse, st);
 }
@@ -245,10 +591,31 @@ static int attn_bwd_generic_t(int B, int S, int nh, int d, const T* qkv, const T
   return (int)hipGetLastError();
 }
 
-int launch_attn_bwd_generic(int dtype, int B, int S, int nh, int d, const void* qkv, const void* dO,
-                            const float* lse, const float* D, void* dqkv, hipStream_t st) {
-  if (dtype == DT_BF16) return attn_bwd_generic_t<bf16_t>(B, S, nh, d, (const bf16_t*)qkv, (const bf16_t*)dO, lse, D, (bf16_t*)dqkv, st);
-  return attn_bwd_generic_t<float>(B, S, nh, d, (const float*)qkv, (const float*)dO, lse, D, (float*)dqkv, st);
+template <typename T>
+static int attn_bwd_narrow_t(int B, int S, int nh, int d, const T* qkv, const T* o, const T* dO, const float* lse, T* dqkv, const float* rope, hipStream_t st) {
+  const int half = (int)(((int64_t)B * nh * S + 3) / 4);
+  const dim3 grid(2u * (unsigned)half);
+#define TAW_NARROW(DP, V) hipLaunchKernelGGL((attn_bwd_narrow_kernel<T, DP, V>), grid, dim3(256), 0, st, qkv, o, dO, lse, dqkv, B, S, nh, d, rope, half)
+  if (d % 4 == 0) { if (d <= 8) TAW_NARROW(8, 4); else if (d <= 16) TAW_NARROW(16, 4); else TAW_NARROW(32, 4); }
+  else { if (d <= 8) TAW_NARROW(8, 2); else if (d <= 16) TAW_NARROW(16, 2); else TAW_NARROW(32, 2); }
+#undef TAW_NARROW
+  return (int)hipGetLastError();
+}
+
+int launch_attn_bwd_generic(int dtype, int B, int S, int nh, int d, const void* qkv, const void* o, const void* dO,
+                            const float* lse, float* D, void* dqkv, const float* rope, hipStream_t st) {
+  if (d <= kNarrowHead) {
+    if (dtype == DT_BF16)
+      return attn_bwd_narrow_t<bf16_t>(B, S, nh, d, (const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)dO, lse, (bf16_t*)dqkv, rope, st);
+    return attn_bwd_narrow_t<float>(B, S, nh, d, (const float*)qkv, (const float*)o, (const float*)dO, lse, (float*)dqkv, rope, st);
+  }
+  const int64_t H = (int64_t)nh * d;
+  int rc = launch_attn_rowdot(dtype, B, S, nh, d, o, H, dO, H, D, st);
+  if (rc) return rc;
+  rc = dtype == DT_BF16 ? attn_bwd_generic_t<bf16_t>(B, S, nh, d, (const bf16_t*)qkv, (const bf16_t*)dO, lse, D, (bf16_t*)dqkv, st)
+                        : attn_bwd_generic_t<float>(B, S, nh, d, (const float*)qkv, (const float*)dO, lse, D, (float*)dqkv, st);
+  if (rc || !rope) return rc;
+  return launch_rope(dtype, B, S, (int)(2 * H), d, dqkv, 3 * H, rope, 1, st);
 }
 
 }  // namespace taw

@@ -193,10 +193,11 @@ static int gemm(const Plan& p, int dtype, int mode, int64_t M, int64_t N, int64_
 // the chip its contraction is cut into ranges whose partial products go to the scratch and are summed in a fixed order by a
 // second kernel: the result does not depend on scheduling.
 static int linear_bwd(const Plan& p, int dtype, int64_t T, int64_t N, int64_t K, const void* dy, const void* W, const void* x,
-                      void* dx, float* G, int accumulate, const GemmScratch& scr, hipStream_t st) {
+                      void* dx, float* G, int accumulate, const GemmScratch& scr, hipStream_t st, const void* gu = nullptr) {
   if (p.mfma_gemm && gemm_mfma_supported(dtype, GEMM_NN, T, K, N, N, K, K, dtype, 0) &&
       gemm_mfma_supported(dtype, GEMM_TN, N, K, T, N, K, K, DT_F32, 0))
     return launch_gemm_mfma_dual(N, K, T, dy, N, x, K, G, K, accumulate, T, K, N, dy, N, W, K, dx, K, scr, st);
+  if (!p.mfma_gemm && gemm_generic_linear_bwd_supported(T, N, K)) return launch_gemm_generic_linear_bwd(dtype, T, N, K, dy, W, x, dx, G, accumulate, gu, st);
   int rc = gemm(p, dtype, GEMM_NN, T, K, N, dy, N, W, K, dx, K, dtype, 0, nullptr, 0, scr, st);
   if (rc) return rc;
   return gemm(p, dtype, GEMM_TN, N, K, T, dy, N, x, K, G, K, DT_F32, accumulate, nullptr, 0, scr, st);
@@ -228,6 +229,9 @@ static int run_fwd(const taw_layer_desc* desc, const Plan& p, const taw_weight_l
       gemm_mfma_rope_supported(3 * H, 2 * H)) {
     TAW_LAUNCH(launch_gemm_mfma_nt_rope(T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, rope_table, desc->S, 2 * H, scr, st),
                "gemm qkv + rope");
+  } else if (!p.mfma_gemm) {
+    TAW_LAUNCH(launch_gemm_generic_rope(dt, T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, rope_table, desc->S, desc->head_dim, 2 * H, st),
+               "gemm qkv + rope (generic)");
   } else {
     TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, dt, 0, nullptr, 0, scr, st), "gemm qkv");
     TAW_LAUNCH(launch_rope(dt, desc->B, desc->S, (int)(2 * H), desc->head_dim, c.qkv, 3 * H, rope_table, 0, st), "rope");
@@ -240,8 +244,12 @@ static int run_fwd(const taw_layer_desc* desc, const Plan& p, const taw_weight_l
   // hn = rmsnorm(h; gamma_mlp)
   TAW_LAUNCH(launch_rmsnorm_fwd(dt, T, (int)H, c.h, at(W_chunk, L.gamma_mlp, dt), desc->rms_eps, c.hn, c.r2, st), "rmsnorm_fwd(mlp)");
   // gu = hn Wgu^T ; a = silu(g) u
-  TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 2 * I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, 2 * I, dt, 0, nullptr, 0, scr, st), "gemm gate/up");
-  TAW_LAUNCH(launch_swiglu_fwd(dt, T, (int)I, c.gu, c.a, st), "swiglu_fwd");
+  if (!p.mfma_gemm) {
+    TAW_LAUNCH(launch_gemm_generic_swiglu(dt, T, I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, c.a, st), "gemm gate/up + swiglu (generic)");
+  } else {
+    TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 2 * I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, 2 * I, dt, 0, nullptr, 0, scr, st), "gemm gate/up");
+    TAW_LAUNCH(launch_swiglu_fwd(dt, T, (int)I, c.gu, c.a, st), "swiglu_fwd");
+  }
   // y = h + a Wd^T
   if (y) TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, H, I, c.a, I, at(W_chunk, L.w_down, dt), I, y, H, dt, 0, c.h, H, scr, st), "gemm down");
   return TAW_OK;
@@ -303,9 +311,13 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
   }
 
   // y = h + a Wd^T :  da = dy Wd ;  G.Wd (+)= dy^T a
-  TAW_LAUNCH(linear_bwd(p, dt, T, H, I, dy, at(W_chunk, L.w_down, dt), c.a, w.da, G_shard + L.w_down, acc, scr, st), "gemm da, G.w_down");
-  // a = silu(g) u
-  TAW_LAUNCH(launch_swiglu_bwd(dt, T, (int)I, w.da, c.gu, w.dgu, st), "swiglu_bwd");
+  // a = silu(g) u :  dgu
+  if (!p.mfma_gemm && gemm_generic_linear_bwd_supported(T, H, I)) {
+    TAW_LAUNCH(linear_bwd(p, dt, T, H, I, dy, at(W_chunk, L.w_down, dt), c.a, w.dgu, G_shard + L.w_down, acc, scr, st, c.gu), "gemm dgu, G.w_down (generic)");
+  } else {
+    TAW_LAUNCH(linear_bwd(p, dt, T, H, I, dy, at(W_chunk, L.w_down, dt), c.a, w.da, G_shard + L.w_down, acc, scr, st), "gemm da, G.w_down");
+    TAW_LAUNCH(launch_swiglu_bwd(dt, T, (int)I, w.da, c.gu, w.dgu, st), "swiglu_bwd");
+  }
   // gu = hn Wgu^T :  dhn = dgu Wgu ;  G.Wgu (+)= dgu^T hn
   TAW_LAUNCH(linear_bwd(p, dt, T, 2 * I, H, w.dgu, at(W_chunk, L.w_gate_up, dt), c.hn, w.dhn, G_shard + L.w_gate_up, acc, scr, st), "gemm dhn, G.w_gate_up");
   // hn = rmsnorm(h) :  dh = dy + rmsnorm_bwd(dhn) ;  G.gamma_mlp
@@ -318,9 +330,8 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
     TAW_LAUNCH(launch_attn_bwd_mfma(desc->B, desc->S, desc->n_heads, c.qkv, c.o, w.dO, c.lse, w.D, w.dqkv, rope_table,
                                     attn_bwd_form_of(desc), st), "attention bwd (mfma)");
   } else {
-    TAW_LAUNCH(launch_attn_rowdot(dt, desc->B, desc->S, desc->n_heads, desc->head_dim, c.o, H, w.dO, H, w.D, st), "attention row dot");
-    TAW_LAUNCH(launch_attn_bwd_generic(dt, desc->B, desc->S, desc->n_heads, desc->head_dim, c.qkv, w.dO, c.lse, w.D, w.dqkv, st), "attention bwd (generic)");
-    TAW_LAUNCH(launch_rope(dt, desc->B, desc->S, (int)(2 * H), desc->head_dim, w.dqkv, 3 * H, rope_table, 1, st), "rope bwd");
+    TAW_LAUNCH(launch_attn_bwd_generic(dt, desc->B, desc->S, desc->n_heads, desc->head_dim, c.qkv, c.o, w.dO, c.lse, w.D, w.dqkv, rope_table, st),
+               "attention bwd (generic)");
   }
   // qkv = xn Wqkv^T :  dxn = dqkv Wqkv ;  G.Wqkv (+)= dqkv^T xn
   TAW_LAUNCH(linear_bwd(p, dt, T, 3 * H, H, w.dqkv, at(W_chunk, L.w_qkv, dt), c.xn, w.dxn, G_shard + L.w_qkv, acc, scr, st), "gemm dxn, G.w_qkv");
@@ -569,14 +580,11 @@ extern "C" int taw_op_attn_bwd(int32_t dtype, int32_t B, int32_t S, int32_t n_he
   TAW_REQUIRE_ALIGNED(qkv); TAW_REQUIRE_ALIGNED(o); TAW_REQUIRE_ALIGNED(dO); TAW_REQUIRE_ALIGNED(lse); TAW_REQUIRE_ALIGNED(dqkv);
   TAW_REQUIRE_ALIGNED(scratch); TAW_REQUIRE_ALIGNED(rope_table);
   const hipStream_t st = (hipStream_t)stream;
-  const int64_t H = (int64_t)n_heads * head_dim;
   if (mf) {
     const int form = impl == TAW_IMPL_MFMA_FUSED ? ATTN_BWD_FUSED : impl == TAW_IMPL_MFMA_ATOMIC ? ATTN_BWD_FUSED_ATOMIC : impl == TAW_IMPL_MFMA ? ATTN_BWD_SPLIT : ATTN_BWD_STORED;
     TAW_LAUNCH(launch_attn_bwd_mfma(B, S, n_heads, qkv, o, dO, lse, scratch, dqkv, rope_table, form, st), "attention bwd (mfma)");
   } else {
-    TAW_LAUNCH(launch_attn_rowdot(dtype, B, S, n_heads, head_dim, o, H, dO, H, scratch, st), "attention row dot");
-    TAW_LAUNCH(launch_attn_bwd_generic(dtype, B, S, n_heads, head_dim, qkv, dO, lse, scratch, dqkv, st), "attention bwd (generic)");
-    if (rope_table) TAW_LAUNCH(launch_rope(dtype, B, S, (int)(2 * H), head_dim, dqkv, 3 * H, rope_table, 1, st), "rope bwd");
+    TAW_LAUNCH(launch_attn_bwd_generic(dtype, B, S, n_heads, head_dim, qkv, o, dO, lse, scratch, dqkv, rope_table, st), "attention bwd (generic)");
   }
   return TAW_OK;
 }

@@ -57,12 +57,24 @@ int launch_attn_rowdot(int dtype, int B, int S, int nh, int d, const void* o, in
 int launch_gemm_generic(int dtype, int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
                         const void* B, int64_t ldb, void* C, int64_t ldc, int c_dtype, int accumulate,
                         const void* R, int64_t ldr, hipStream_t st);
+// the same for the products of a layer that end in something else, which then needs no launch of its own:
+// C = A B^T with columns below rot_cols rotated (heads of d, row r at position r % S)
+int launch_gemm_generic_rope(int dtype, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C,
+                             int64_t ldc, const float* table, int S, int d, int64_t rot_cols, hipStream_t st);
+// gu[T, 2I] = A W^T (W [2I, K] = gate | up) and a[T, I] = silu(gate) up
+int launch_gemm_generic_swiglu(int dtype, int64_t T, int64_t I, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* gu, void* a,
+                               hipStream_t st);
+// both products of a linear's backward in one grid: G (+)= dy^T x and dx = dy W, or, gu != nullptr, its image under the SwiGLU's backward, [T, 2K]
+bool gemm_generic_linear_bwd_supported(int64_t T, int64_t N, int64_t K);
+int launch_gemm_generic_linear_bwd(int dtype, int64_t T, int64_t N, int64_t K, const void* dy, const void* W, const void* x, void* dx, float* G,
+                                   int accumulate, const void* gu, hipStream_t st);
 // qkv: [B*S, 3H] (q | k | v, head-major);  o: [B*S, H];  lse: [B, nh, S] natural-log-sum-exp of the scaled scores
 bool attn_generic_supported(int S, int d);
 int launch_attn_fwd_generic(int dtype, int B, int S, int nh, int d, const void* qkv, void* o, float* lse,
                             hipStream_t st);
-int launch_attn_bwd_generic(int dtype, int B, int S, int nh, int d, const void* qkv, const void* dO,
-                            const float* lse, const float* D, void* dqkv, hipStream_t st);
+// D: scratch, B * nh * S floats (heads wider than 32); rope != nullptr: q and k were rotated, dq and dk come out unrotated
+int launch_attn_bwd_generic(int dtype, int B, int S, int nh, int d, const void* qkv, const void* o, const void* dO,
+                            const float* lse, float* D, void* dqkv, const float* rope, hipStream_t st);
 
 // ---- order in which a GEMM grid walks its 256 x 256 output tiles ------------------------------
 // Workgroup ids are dealt round-robin to the 8 XCDs (32 compute units and one 4 MiB L2 each), and each XCD

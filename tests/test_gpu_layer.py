@@ -274,3 +274,10 @@ def test_bf16_layer_of_few_tokens(taw, B, S, nh, I_):
     """Few rows against wide weights: the contractions of the down projection and of the input gradients are cut into ranges (up to 8
     of at least 256), the last one ragged, and summed by the second kernel, with the residual and the rotation where they belong."""
     U.check_layer(taw, I.LayerConfig("few-tokens", I.BF16, B, S, nh * 128, nh, 128, I_, sigma_w=0.05), seed=B + S, gamma_jitter=0.1)
+
+
+@pytest.mark.parametrize("B,S,nh,d,I_", [(2, 67, 3, 10, 77), (1, 130, 2, 24, 100), (1, 64, 1, 32, 33), (1, 65, 5, 8, 90), (1, 40, 2, 2, 8), (1, 50, 2, 36, 50)])
+def test_fp32_layer_head_dims(taw, B, S, nh, d, I_):
+    """Narrow heads (up to 32: rows in registers, loaded in pairs or fours) and one just beyond, on products with odd widths, one key more and
+    one less than a wavefront, rotation, SwiGLU and both of its backward's halves inside the products."""
+    U.check_layer(taw, I.LayerConfig("narrow", I.F32, B, S, nh * d, nh, d, I_, sigma_w=0.2), seed=d, gamma_jitter=0.1)

@@ -379,3 +379,11 @@ def test_linear_tile_shapes(taw, T, N, K):
     for k, (got, ref, tol) in refs.items():
         err = float((got.double() - ref).abs().max() / ref.abs().max())
         assert err < tol, (k, err)
+
+
+@pytest.mark.parametrize("dtype", [I.F32, I.BF16])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_gemm_generic_large_tiles(taw, dtype, mode):
+    """More than 4096 tiles of 16 x 16: the generic product takes 64 x 64 ones, ragged at every edge and in K."""
+    _gemm_case(taw, dtype, mode, 1030, 1051, 70, taw.TAW_IMPL_GENERIC, residual=True)
+    _gemm_case(taw, dtype, mode, 1030, 1052, 33, taw.TAW_IMPL_GENERIC, c_f32=True, accumulate=True)
