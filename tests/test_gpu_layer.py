@@ -281,3 +281,23 @@ def test_fp32_layer_head_dims(taw, B, S, nh, d, I_):
     """Narrow heads (up to 32: rows in registers, loaded in pairs or fours) and one just beyond, on products with odd widths, one key more and
     one less than a wavefront, rotation, SwiGLU and both of its backward's halves inside the products."""
     U.check_layer(taw, I.LayerConfig("narrow", I.F32, B, S, nh * d, nh, d, I_, sigma_w=0.2), seed=d, gamma_jitter=0.1)
+
+
+@pytest.mark.parametrize("B,S", [(52, 100), (160, 33), (41, 128)])
+def test_short_sequences_across_large_tiles(taw, B, S):
+    """Many short sequences in one call: 256 x 256 tiles whose 32-row slices start anywhere in a sequence and cross into the next (the rotation's
+    positions wrap inside a tile), against one sequence at a time on the small tiles.  The two differ in the order of fp32 sums only, so by a bf16
+    rounding here and there: h's and y's, 2^-8 of an element each, and through attention and MLP at most about as much again."""
+    import torch
+    mk = lambda b: I.LayerConfig("short", I.BF16, b, S, 1024, 8, 128, 136, sigma_w=0.05)
+    w = I.make_weights(mk(B), 1)
+    x, _ = I.make_activations(mk(B), 1)
+    xd = U.to_dev(x, I.BF16)
+    many, one = U.DeviceLayer(taw, mk(B)), U.DeviceLayer(taw, mk(1))
+    many.set_weights(w)
+    one.set_weights(w)
+    y = many.fwd(xd).double().reshape(B, S, -1)
+    for b in sorted({0, 1, 2, 256 // S, 512 // S, B // 2, B - 1}):
+        ref = one.fwd(xd.reshape(B, S, -1)[b:b + 1].contiguous()).double().reshape(S, -1)
+        err = float((y[b] - ref).abs().max() / ref.abs().max())
+        assert err < 2.0 ** -6, (b, err)
