@@ -186,14 +186,15 @@ __device__ __forceinline__ void stage_barrier() {
 constexpr int kWaves8 = 8, kThreads8 = 512;
 constexpr int kTileBytes = 64 * D * 2;      // a [64][128] bf16 tile: 16 KiB
 
-// This wavefront's share (2 of the 16 one-KiB pieces) of a [64][128] tile load: rows row0 .. row0+63
+// This wavefront's share (16 / NW of the 16 one-KiB pieces, NW wavefronts in the workgroup) of a [64][128] tile load: rows row0 .. row0+63
 // of a row-major matrix (row stride ld_bytes, rows clamped to limit-1) into the swizzled LDS tile at
 // lds_tile.  Piece j holds rows 4j..4j+3; lane l writes slot l&15 of row 4j + (l>>4), and slot s of
 // row r holds chunk s ^ swizzle(r): the lane fetches the chunk that belongs where it writes.
+template <int NW = kWaves8>
 __device__ __forceinline__ void tile_dma(uint64_t base, unsigned ld_bytes, int row0, int limit, unsigned lds_tile, int lane, int wave) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int j = wave + 8 * i;
+  for (int i = 0; i < 16 / NW; ++i) {
+    const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
     const int c = swz(r, lane & 15);
     int rg = row0 + r;
@@ -248,8 +249,8 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 }
 
 // =============================================================================== forward
-// Workgroup: 8 wavefronts (two per SIMD, so one's softmax arithmetic overlaps the other's MFMAs),
-// one (batch, head, 256 query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
+// Workgroup: NW = 8 wavefronts (two per SIMD, so one's softmax arithmetic overlaps the other's MFMAs) or, where there are
+// few tiles (few_tiles), 4; one (batch, head, 32 NW query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
 // through a 4-stage LDS ring of 64-key tiles filled by direct global->LDS loads issued three
 // tiles ahead; one workgroup barrier per tile.
 //
@@ -260,9 +261,10 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // result independent of which maximum was used.
 constexpr float kMaxSlack = 8.0f;
 
-__global__ void __launch_bounds__(kThreads8, 1)
+template <int NW>
+__global__ void __launch_bounds__(NW * 64, 2)
 attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int B, int S, int nh, float scale) {
-  constexpr int BQ = 256, WQ = 32, BKV = 64, NS = 4;
+  constexpr int WQ = 32, BQ = NW * WQ, BKV = 64, NS = 4;
   constexpr int kStage = 2 * kTileBytes;   // K tile | V tile
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
@@ -274,7 +276,7 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   la.init(lane);
   const int nqt = (S + BQ - 1) / BQ;
   int bh, rank;
-  pair_tile_of_block((int)blockIdx.x, B * nh, nqt, bh, rank);
+  pair_tile_of_block<NW == kWaves8>((int)blockIdx.x, B * nh, nqt, bh, rank);
   const int qt = nqt - 1 - rank;                       // longest rows first
   const int b = bh / nh, h = bh % nh;
   const int64_t H = (int64_t)nh * D, ld = 3 * H;
@@ -288,8 +290,8 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   const int nkv = (kv_end + BKV - 1) / BKV;
   auto issue = [&](int t) {
     const unsigned st = lds0 + (t & (NS - 1)) * kStage;
-    tile_dma(kbase, ldb, t * BKV, S, st, lane, wave);
-    tile_dma(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
+    tile_dma<NW>(kbase, ldb, t * BKV, S, st, lane, wave);
+    tile_dma<NW>(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
   };
   for (int t = 0; t < NS - 2 && t < nkv; ++t) issue(t);
 
@@ -314,7 +316,7 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   // every barrier: wavefronts 0..3 do S = K Q^T, softmax, O += V^T P within the tile's period; the
   // late ones 4..7 start a period with the O += V^T P of the previous tile (its P waits in registers,
   // its V stays in the ring one period longer, which is why tiles are issued two ahead, not three).
-  const bool late = wave >= kWaves8 / 2;
+  const bool late = NW == kWaves8 && wave >= NW / 2;       // 4 wavefronts have a SIMD each
   bf16x8_t pf[2][2];
   bool pend = false;
   unsigned pend_tr = 0;
@@ -348,7 +350,7 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   for (int j = 0; j < nkv; ++j) {
     // tile j has landed (each wavefront waits for its own pieces, the barrier collects them); the
     // barrier also says every wavefront is done with tile j-2, whose stage tile j+2 goes into
-    if (j + 1 < nkv) wait_vmcnt<4>(); else wait_vmcnt<0>();
+    if (j + 1 < nkv) wait_vmcnt<2 * (16 / NW)>(); else wait_vmcnt<0>();
     stage_barrier();
     if (j + NS - 2 < nkv) issue(j + NS - 2);
     if (pend) {                                        // late wavefronts: the previous tile's O += V^T P
@@ -558,17 +560,16 @@ __global__ void __launch_bounds__(256) attn_bwd_prep_kernel(const bf16_t* __rest
 }
 
 // =============================================================================== backward: dK, dV
-// Workgroup: 8 wavefronts, one (batch, head, 256 keys); wavefront w owns keys 32w..32w+31.  Their V rows stay in
-// registers as B operands; their K rows are read from a copy of the key tile in LDS (64 KiB), which leaves the
+// Workgroup: NW = 8 wavefronts (4 where few_tiles says so), one (batch, head, 32 NW keys); wavefront w owns keys 32w..32w+31.
+// Their V rows stay in registers as B operands; their K rows are read from a copy of the key tile in LDS (8 NW KiB), which leaves the
 // registers for both score accumulators at once and for reading fragments ahead of the MFMAs.  Query rows stream
 // through a 2-stage LDS ring in blocks of 64 (Q and dO tiles plus the rows' lse and D), from the diagonal to the end
 // of the sequence, filled by direct global->LDS loads one block ahead (a block takes several microseconds to process,
 // more than a load takes to land).
 //   S = Q K^T and dP = dO V^T as two alternating accumulation chains;  P = exp(S/sqrt(d) - lse);  dS = P (dP - D)
 //   dV^T += dO^T P;   dK^T += Q^T dS  (scaled by 1/sqrt(d) at the end)
-constexpr int kKvOffRing = 65536;                                        // key tile [256][128] bf16 in front of the ring
 constexpr int kKvStage = 2 * kTileBytes + 2 * 64 * 4;                    // Q tile | dO tile | lse[64] | D[64]
-constexpr size_t kKvLds = kKvOffRing + 2 * kKvStage;
+template <int NW> constexpr size_t kKvLds = NW * 8192 + 2 * kKvStage;     // key tile [32 NW][128] bf16 in front of the ring
 //
 // STORE_DS: every dS block this kernel forms is also written to memory (bf16, exactly what the dK product multiplies by) for
 // a dQ kernel that then needs one matrix product instead of three (attn_bwd_dq_stored_kernel).  Layout of `ds`, per (batch,
@@ -588,12 +589,12 @@ constexpr size_t kKvLds = kKvOffRing + 2 * kKvStage;
 // over and over to the same few KiB: it is the issue of the store instructions that costs, not the traffic.
 // (ds_block_offset, ds_unit_offset, ds_slot, ds_row_of_slot: taw_internal.h, where host code can check them)
 
-template <bool STORE_DS>
-__global__ void __launch_bounds__(kThreads8, 1)
+template <bool STORE_DS, int NW>
+__global__ void __launch_bounds__(NW * 64, 2)
 attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
                     const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
                     const float* __restrict__ rope, unsigned char* __restrict__ ds, int64_t ds_pair_bytes) {
-  constexpr int BKVW = 256, BQ = 64, NS = 2;
+  constexpr int BKVW = NW * 32, BQ = 64, NS = 2, kKvOffRing = NW * 8192;
   constexpr int kStage = kKvStage;
   constexpr int kA = 1;                                // fragment reads run this many MFMA steps ahead of their use (deeper costs registers this kernel does not have)
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
@@ -622,7 +623,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   // key tile -> LDS (8 pieces of 4 rows per wavefront)
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int j = wave + 8 * i;
+    const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
     const int cc = swz(r, lane & 15);
     int rg = kv0 + r;
@@ -632,8 +633,8 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   auto issue = [&](int t) {
     const unsigned st = lds0 + kKvOffRing + (t & (NS - 1)) * kStage;
     const int row0 = (jb + t) * BQ;
-    tile_dma(qb64, ldb, row0, S, st, lane, wave);
-    tile_dma(do64, ldob, row0, S, st + kTileBytes, lane, wave);
+    tile_dma<NW>(qb64, ldb, row0, S, st, lane, wave);
+    tile_dma<NW>(do64, ldob, row0, S, st + kTileBytes, lane, wave);
     if (wave < 2)
       lds_dma4(wave == 0 ? l64 : d64, (unsigned)(row0 + lane) * 4u, st + 2 * kTileBytes + wave * (BQ * 4));
   };
@@ -911,22 +912,24 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
 // =============================================================================== backward: dQ from stored dS
 // dQ^T[d][q] += K^T[d][kv] dS^T[kv][q] with dS read back from what attn_bwd_dkv_kernel<true> wrote: one product per (query
 // block, key block) pair instead of three, paid for with S^2 bytes per (batch, head) written once and read once.  Same
-// workgroup shape as the kernel above (256 query rows, wavefront w owns the 32-row group w), keys in tiles of 64 through a
+// workgroup shape as the kernel above (256 query rows, wavefront w owns the 32-row group w; 128 and 4 wavefronts where
+// few_tiles says so), keys in tiles of 64 through a
 // 3-stage ring filled by direct global->LDS loads two tiles ahead: the K tile [64][128], shared, and per wavefront the two
 // dS units (32 keys each) of its own row group, 4 KiB copied as they lie in memory (consecutive tiles are consecutive
 // there: eight sequential streams per workgroup).  Both operands are transposing reads: K^T as in the kernel above, dS^T
 // from the wavefront's units at the slots ds_slot() gave them.  The 32 rows of a group come in the order the dK/dV kernel's
 // accumulators had them (ds_row_of_slot); only the epilogue needs to know.  With 16 MFMAs per wavefront and 48 KiB per
 // tile the kernel is bound by the rate the dS matrix streams in from memory.
-constexpr int kDqsStage = kTileBytes + 8 * 4096;       // K tile | 8 wavefronts x (2 units of 2 KiB)
+template <int NW> constexpr int kDqsStage = kTileBytes + NW * 4096;        // K tile | NW wavefronts x (2 units of 2 KiB)
 constexpr int kDqsStages = 3;
-constexpr size_t kDqsLds = (size_t)kDqsStages * kDqsStage;       // 144 KiB
-static_assert(kDqsLds <= 160 * 1024, "LDS budget");
-__global__ void __launch_bounds__(kThreads8, 1)
+template <int NW> constexpr size_t kDqsLds = (size_t)kDqsStages * kDqsStage<NW>;       // 144 KiB with 8 wavefronts
+static_assert(kDqsLds<kWaves8> <= 160 * 1024, "LDS budget");
+template <int NW>
+__global__ void __launch_bounds__(NW * 64, 2)
 attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* __restrict__ ds, int64_t ds_pair_bytes,
                           bf16_t* __restrict__ dqkv, int B, int S, int nh, float scale, const float* __restrict__ rope) {
-  constexpr int BQ = 256, WQ = 32, BKV = 64, NS = kDqsStages;
-  constexpr int kStage = kDqsStage;
+  constexpr int WQ = 32, BQ = NW * WQ, BKV = 64, NS = kDqsStages, kDmaPerTile = 16 / NW + 4;
+  constexpr int kStage = kDqsStage<NW>;
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
@@ -943,16 +946,16 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
   const int64_t H = (int64_t)nh * D, ld = 3 * H;
   const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * D;
   const uint64_t kbase = (uint64_t)(qbase + H);
-  // this wavefront's units of block qt, key group 0 first: 2 KiB per key group, 8 (qt + 1) of them
-  const uint64_t dsbase = (uint64_t)(ds + (int64_t)bh * ds_pair_bytes + ds_unit_offset(qt, wave, 0));
+  // this wavefront's units of its block of 256 rows (ib), key group 0 first: 2 KiB per key group, 8 (ib + 1) of them
+  const uint64_t dsbase = (uint64_t)(ds + (int64_t)bh * ds_pair_bytes + ds_unit_offset(qt * BQ >> 8, (qt * BQ >> 5 & 7) + wave, 0));
   const unsigned ldb = (unsigned)(ld * 2);
   const int q0 = qt * BQ, q0w = q0 + wave * WQ;
 
   const int kv_end = (q0 + BQ < S) ? q0 + BQ : S;
-  const int nkv = (kv_end + BKV - 1) / BKV;               // key groups 0 .. 2 nkv - 1 <= 8 (qt + 1) - 1: every unit read exists
+  const int nkv = (kv_end + BKV - 1) / BKV;               // key groups 0 .. 2 nkv - 1 <= 8 (ib + 1) - 1: every unit read exists
   auto issue = [&](int t, int stage) {
     const unsigned st = lds0 + stage * kStage;
-    tile_dma(kbase, ldb, t * BKV, S, st, lane, wave);
+    tile_dma<NW>(kbase, ldb, t * BKV, S, st, lane, wave);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       lds_dma16_nt(dsbase, (unsigned)(t * 4096 + i * 1024 + lane * 16), st + kTileBytes + wave * 4096 + i * 1024);      // (6.0 instead of 6.8 ms at S = 32768)
@@ -976,8 +979,8 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
 
   int stage = 0, stage_in = NS - 1;                     // stage of tile j; stage the next issue goes into
   for (int j = 0; j < nkv; ++j) {
-    // 6 loads per tile and wavefront; tiles j and j + 1 are in flight here (issued two ahead)
-    if (j + 1 < nkv) wait_vmcnt<6>(); else wait_vmcnt<0>();
+    // kDmaPerTile loads per tile and wavefront; tiles j and j + 1 are in flight here (issued two ahead)
+    if (j + 1 < nkv) wait_vmcnt<kDmaPerTile>(); else wait_vmcnt<0>();
     stage_barrier();                                    // the K tile j is visible; everybody is done with tile j - 1, whose stage tile j + 2 takes
     if (j + NS - 1 < nkv) issue(j + NS - 1, stage_in);
     const unsigned so = lds0 + stage * kStage;
@@ -1403,14 +1406,49 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(f32x4_t* __restrict__ p, 
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (size_t)gridDim.x * 256) p[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
+// Whether the forward and the pair of backward kernels with stored dS run as 128-row workgroups of 4 wavefronts (one per SIMD)
+// instead of 256-row workgroups of 8.  Bound, where every workgroup has a compute unit to itself, by the serial chain of
+// the longest one over its 64-row blocks: with two wavefronts per SIMD a block takes their matrix instructions twice over
+// (forward 1.6 us, alone 1.2), and with 256 compute units the halves have somewhere to go.  Both measured, us
+// forward / backward, 8 wavefronts -> 4 (n8 = 256-row tiles of all (batch, head) pairs):
+//   n8 = 8    2 x 333 tokens, 2 heads     12.6 / 31.1 -> 10.6 / 25.2
+//   n8 = 144  3 x 1501 tokens, 8 heads    41.5 / 103  -> 33.7 / 83
+//   n8 = 256  2048 tokens, 32 heads       56.4 / 151  -> 48.7 / 128;   32768 tokens, 2 heads   757 / 1987 -> 630 / 1752
+//   n8 = 384  2048 tokens, 48 heads       60.3 / 177  -> 76.7 / 202: two wavefronts overlap better once the chip is full
+// With more than 256 of the halves the gain is the finer causal triangle, which one or two tiles per pair don't have:
+//   n8 = 256  8 x 200 tokens, 32 heads    15.2 / 38.7 -> 17.8 / 44.3;  2 x 512 tokens, 64 heads  23.0 / 56.1 -> 22.8 / 57.7
+bool few_tiles(int B, int S, int nh) {
+  const int64_t pairs = (int64_t)B * nh, n8 = ((int64_t)S + 255) / 256 * pairs, n4 = ((int64_t)S + 127) / 128 * pairs;
+  return n4 <= 256 || (n8 <= 256 && S > 512);
+}
+
+
+template <int NW>
 int launch_fwd(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st) {
-  constexpr int BQ = 256;
-  constexpr size_t lds = 4 * 2 * kTileBytes;      // the ring; the output staging (8 x 32 x 136 bf16) fits inside
-  static_assert(lds >= 8 * 32 * 136 * sizeof(bf16_t), "staging area");
-  TAW_SET_LDS_LIMIT_ONCE(attn_fwd_kernel, lds);
-  const int nqt = (S + BQ - 1) / BQ;
+  constexpr size_t lds = 4 * 2 * kTileBytes;      // the ring; the output staging (NW x 32 x 136 bf16) fits inside
+  static_assert(lds >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE(attn_fwd_kernel<NW>, lds);
+  const int nqt = (S + 32 * NW - 1) / (32 * NW);
   const float scale = 1.0f / sqrtf((float)D);
-  hipLaunchKernelGGL(attn_fwd_kernel, dim3((unsigned)(nqt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (bf16_t*)o, lse, B, S, nh, scale);
+  hipLaunchKernelGGL(attn_fwd_kernel<NW>, dim3((unsigned)(nqt * B * nh)), dim3(NW * 64), lds, st, (const bf16_t*)qkv, (bf16_t*)o, lse, B, S, nh, scale);
+  return (int)hipGetLastError();
+}
+
+template <int NW>
+int launch_bwd_stored(int B, int S, int Sp, int nh, const void* qkv, const void* dO, const float* lse2, const float* Dv, void* dqkv,
+                      unsigned char* ds, int64_t pair_bytes, const float* rope_table, hipStream_t st) {
+  const float scale = 1.0f / sqrtf((float)D);
+  const int nt = (S + 32 * NW - 1) / (32 * NW);
+  static_assert(kKvLds<NW> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<true, NW>), kKvLds<NW>);
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<true, NW>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), kKvLds<NW>, st, (const bf16_t*)qkv, (const bf16_t*)dO,
+                     lse2, Dv, (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, ds, pair_bytes);
+  const int rc = (int)hipGetLastError();
+  if (rc) return rc;
+  static_assert(kDqsLds<NW> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dq_stored_kernel<NW>, kDqsLds<NW>);
+  hipLaunchKernelGGL(attn_bwd_dq_stored_kernel<NW>, dim3((unsigned)(nt * B * nh)), dim3(NW * 64), kDqsLds<NW>, st, (const bf16_t*)qkv, ds, pair_bytes,
+                     (bf16_t*)dqkv, B, S, nh, scale, rope_table);
   return (int)hipGetLastError();
 }
 
@@ -1421,7 +1459,7 @@ bool attn_mfma_supported(int dtype, int S, int nh, int d) {
 }
 
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st) {
-  return launch_fwd(B, S, nh, qkv, o, lse, st);
+  return few_tiles(B, S, nh) ? launch_fwd<4>(B, S, nh, qkv, o, lse, st) : launch_fwd<kWaves8>(B, S, nh, qkv, o, lse, st);
 }
 
 // Workers per (batch, head) for the slot form: as many as fill the 256 compute units in whole rounds, preferring few (every
@@ -1501,25 +1539,15 @@ int launch_attn_bwd_mfma(int B, int S, int nh, const void* qkv, const void* o, c
     // the stored dS follows the row statistics (a multiple of 512 bytes in front of it)
     unsigned char* ds = reinterpret_cast<unsigned char*>(slots);
     const int64_t pair_bytes = attn_bwd_ds_pair_bytes(S);
-    constexpr size_t lds = kKvLds;
-    TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dkv_kernel<true>, lds);
-    const int nkt = (S + 255) / 256;
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<true>, dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2,
-                       Dv, (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, ds, pair_bytes);
-    int rc = (int)hipGetLastError();
-    if (rc) return rc;
-    static_assert(kDqsLds >= 8 * 32 * 136 * sizeof(bf16_t), "staging area");
-    TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dq_stored_kernel, kDqsLds);
-    hipLaunchKernelGGL(attn_bwd_dq_stored_kernel, dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), kDqsLds, st, (const bf16_t*)qkv, ds, pair_bytes,
-                       (bf16_t*)dqkv, B, S, nh, scale, rope_table);
-    return (int)hipGetLastError();
+    return few_tiles(B, S, nh) ? launch_bwd_stored<4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st)
+                               : launch_bwd_stored<kWaves8>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
   }
   {
-    constexpr size_t lds = kKvLds;
+    constexpr size_t lds = kKvLds<kWaves8>;
     static_assert(lds >= 8 * 32 * 136 * sizeof(bf16_t), "staging area");
-    TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dkv_kernel<false>, lds);
+    TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<false, kWaves8>), lds);
     const int nkt = (S + 255) / 256;
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<false>, dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<false, kWaves8>), dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
                        (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, nullptr, (int64_t)0);
     int rc = (int)hipGetLastError();
     if (rc) return rc;

@@ -387,3 +387,29 @@ def test_gemm_generic_large_tiles(taw, dtype, mode):
     """More than 4096 tiles of 16 x 16: the generic product takes 64 x 64 ones, ragged at every edge and in K."""
     _gemm_case(taw, dtype, mode, 1030, 1051, 70, taw.TAW_IMPL_GENERIC, residual=True)
     _gemm_case(taw, dtype, mode, 1030, 1052, 33, taw.TAW_IMPL_GENERIC, c_f32=True, accumulate=True)
+
+
+@pytest.mark.parametrize("S", [1, 64, 65, 128, 129, 257, 333, 385, 640])
+def test_attn_mfma_few_and_many_tiles_agree(taw, S):
+    """Few tiles run on 128-row workgroups of 4 wavefronts, many on 256-row workgroups of 8.  A wavefront does the same arithmetic in the same
+    order in both, so a batch of many sequences has to equal its sequences one by one, bit for bit."""
+    import torch
+    nh, B = 4, -(-600 // (4 * ((S + 255) // 256)))
+    H = nh * 128
+    g = torch.Generator(device="cuda").manual_seed(S)
+    draw = lambda *shape: torch.empty(shape, device="cuda").normal_(generator=g).bfloat16()
+    qkv, dO = draw(B, S, 3 * H), draw(B, S, H)
+
+    def both(qkv, dO):
+        b = qkv.shape[0]
+        o, dqkv = torch.empty_like(dO), torch.empty_like(qkv)
+        lse = torch.empty(b * nh * S, dtype=torch.float32, device="cuda")
+        taw.taw_op_attn_fwd(I.BF16, b, S, nh, 128, qkv, o, lse, taw.TAW_IMPL_MFMA)
+        scratch = torch.full((taw.taw_op_attn_bwd_scratch_floats(b, S, nh),), float("nan"), dtype=torch.float32, device="cuda")
+        taw.taw_op_attn_bwd(I.BF16, b, S, nh, 128, qkv, o, dO, lse, dqkv, scratch, None, taw.TAW_IMPL_MFMA_STORED)
+        return o, lse.view(b, -1), dqkv
+
+    many = both(qkv, dO)
+    for i in (0, B // 2, B - 1):
+        for a, b in zip(both(qkv[i:i + 1].contiguous(), dO[i:i + 1].contiguous()), many):
+            assert torch.equal(a[0], b[i])
