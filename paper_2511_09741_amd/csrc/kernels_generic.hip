@@ -325,7 +325,9 @@ __global__ void __launch_bounds__(256) attn_fwd_narrow_kernel(const T* __restric
     const T* row = qbase + (int64_t)u * ld;
     load_row<V>(k, row + H, d);
     load_row<V>(v, row + 2 * H, d);
-    const float s = dot_row(q, k) * scale, mn = fmaxf(m, s), keep = expf(m - mn), p = expf(s - mn);      // first key: m = -inf, keep = 0
+    // a key whose score overflowed to -inf has weight 0, also where the lane has seen no other yet (expf(-inf + inf) is NaN)
+    const float s = dot_row(q, k) * scale, mn = fmaxf(m, s);
+    const float keep = m == -INFINITY ? 0.f : expf(m - mn), p = s == -INFINITY ? 0.f : expf(s - mn);
     m = mn;
     z = z * keep + p;
 #pragma unroll

@@ -202,6 +202,38 @@ def test_attention_generic(taw, dtype, B, S, nh, d):
     _attn_case(taw, dtype, B, S, nh, d, taw.TAW_IMPL_GENERIC, seed=S)
 
 
+@pytest.mark.parametrize("d", [6, 8, 16, 32, 36])
+def test_attention_generic_scores_that_overflow(taw, d):
+    """Finite q and k whose scores overflow fp32 to -inf: such a key has weight 0, first in its lane or not, as long as the row has one
+    finite score.  Keys 0 - 3, 64 and 70 are anti-parallel to every later query at 1e20 each; the rest of the row is ordinary."""
+    import torch
+    S, nh = 140, 2
+    H = nh * d
+    rng = np.random.default_rng(d)
+    qkv, _ = draw(rng, (S, 3 * H), I.F32)
+    far = [0, 1, 2, 3, 64, 70]
+    q, k = qkv[:, :H].reshape(S, nh, d), qkv[:, H:2 * H].reshape(S, nh, d)
+    q[:, :, 0] = 1e20
+    k[:, :, 0] = 0.0
+    k[far, :, 0] = -1e20
+    q[far, :, 0] = 0.0                                  # their own scores stay finite
+    o = U.empty_dev((S, H), I.F32)
+    lse = torch.empty(nh * S, dtype=torch.float32, device="cuda")
+    taw.taw_op_attn_fwd(I.F32, 1, S, nh, d, U.to_dev(qkv, I.F32), o, lse, taw.TAW_IMPL_GENERIC)
+    got_o, got_lse = U.from_dev(o).reshape(S, nh, d), U.from_dev(lse).reshape(nh, S)
+    v = qkv[:, 2 * H:].reshape(S, nh, d).astype(np.float64)
+    for h in range(nh):
+        for t in range(S):
+            s = q[t, h].astype(np.float64) @ k[:t + 1, h].astype(np.float64).T / np.sqrt(d)
+            s[s < -np.finfo(np.float32).max] = -np.inf
+            if not np.isfinite(s).any():
+                continue                                # no key left: 0 / 0
+            m = s.max()
+            p = np.exp(s - m)
+            assert abs(got_lse[h, t] - (m + np.log(p.sum()))) < 1e-4, (h, t)
+            assert np.max(np.abs(got_o[t, h] - p @ v[:t + 1, h] / p.sum())) < 1e-4, (h, t)
+
+
 @pytest.mark.parametrize("src_dtype", [I.F32, I.BF16])
 @pytest.mark.parametrize("n", [0, 1, 3, 4, 1027, 13490, 1 << 20])      # 13490: whole workgroups, a partly filled one and a scalar tail
 def test_grad_accum(taw, src_dtype, n):
