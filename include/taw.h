@@ -96,7 +96,10 @@ int taw_layer_weight_layout(const taw_layer_desc* desc, taw_weight_layout* out);
 
 /* Bytes of the activation cache that taw_layer_fwd writes and taw_layer_bwd reads (the cached
  * A_j of the forward phase), and of the scratch workspace either call needs.  Both return 0 for
- * an invalid descriptor.  The workspace holds nothing between calls and may be shared by layers. */
+ * an invalid descriptor.  The workspace holds nothing between calls and may be shared by layers.
+ * taw_layer_fwd touches it only with TAW_RECOMPUTE: without that flag, forwards and one backward may
+ * share a workspace and overlap in time on different streams.  (With few tokens the cache also has room for
+ * partial products of the forward's GEMMs, so that this holds there too.) */
 size_t taw_layer_ctx_bytes(const taw_layer_desc* desc);
 size_t taw_layer_workspace_bytes(const taw_layer_desc* desc);
 

@@ -113,10 +113,10 @@ struct Carve {
   void* take(size_t bytes) { void* p = base ? base + off : nullptr; off += round_up(bytes, 256); return p; }
 };
 
-struct Ctx {       // saved by the forward for the backward
-  void *xn, *qkv, *o, *h, *hn, *gu, *a; float *lse, *r1, *r2; size_t bytes;
+struct Ctx {       // saved by the forward for the backward; scr: partial products of the forward's own GEMMs, nothing the backward reads
+  void *xn, *qkv, *o, *h, *hn, *gu, *a; float *lse, *r1, *r2; GemmScratch scr; size_t bytes;
 };
-struct Work {      // scratch of the backward (the forward needs only scr)
+struct Work {      // scratch of the backward
   void *da, *dgu, *dhn, *dh, *dO, *dqkv, *dxn; float *D, *partials; GemmScratch scr; size_t bytes;
 };
 
@@ -133,12 +133,23 @@ static int attn_bwd_form_of(const taw_layer_desc* d) {
   return (d->flags & TAW_ATTN_BWD_FUSED) ? ATTN_BWD_FUSED : (d->flags & TAW_ATTN_BWD_RECOMPUTE) ? ATTN_BWD_SPLIT : ATTN_BWD_STORED;
 }
 
+// Whether every GEMM of the layer runs on the MFMA kernels is make_plan's question; these are the layers whose GEMMs may be cut at all.
+static bool gemms_may_be_cut(const taw_layer_desc* d) { return d->dtype == TAW_BF16 && d->H % 8 == 0 && d->I % 8 == 0; }
+
+// The forward's partial products live in the cache, not in the workspace: layers share the workspace, and a forward may run on one
+// stream while another layer's backward uses it on a second one.
 static Ctx carve_ctx(const taw_layer_desc* d, void* base) {
   const size_t e = dt_size(d->dtype), T = (size_t)d->B * d->S, H = d->H, I = d->I;
   Carve c(base); Ctx x;
   x.xn = c.take(T * H * e); x.qkv = c.take(T * 3 * H * e); x.o = c.take(T * H * e); x.h = c.take(T * H * e);
   x.hn = c.take(T * H * e); x.gu = c.take(T * 2 * I * e); x.a = c.take(T * I * e);
   x.lse = (float*)c.take((size_t)d->B * d->n_heads * d->S * 4); x.r1 = (float*)c.take(T * 4); x.r2 = (float*)c.take(T * 4);
+  x.scr.floats = 0;
+  if (gemms_may_be_cut(d)) {
+    const int64_t t = (int64_t)T, h = (int64_t)H, i = (int64_t)I;
+    x.scr.floats = std::max({gemm_nt_scratch_floats(t, 3 * h, h), gemm_nt_scratch_floats(t, h, h), gemm_nt_scratch_floats(t, 2 * i, h), gemm_nt_scratch_floats(t, h, i)});
+  }
+  x.scr.part = (float*)c.take(x.scr.floats * 4);
   x.bytes = c.off;
   return x;
 }
@@ -150,15 +161,12 @@ static Work carve_work(const taw_layer_desc* d, void* base) {
   w.dO = c.take(T * H * e); w.dqkv = c.take(T * 3 * H * e); w.dxn = c.take(T * H * e);
   w.D = (float*)c.take(attn_bwd_mfma_scratch_floats(d->B, d->S, d->n_heads, attn_mfma_supported(d->dtype, d->S, d->n_heads, d->head_dim) ? attn_bwd_form_of(d) : ATTN_BWD_SPLIT) * 4);   // covers the generic kernel's B*nh*S too
   w.partials = (float*)c.take((size_t)rmsnorm_bwd_partial_rows() * H * 4);
-  size_t sk = 0;
-  if (d->dtype == TAW_BF16 && H % 8 == 0 && I % 8 == 0) {
+  w.scr.floats = 0;
+  if (gemms_may_be_cut(d)) {
     const int64_t t = (int64_t)T, h = (int64_t)H, i = (int64_t)I;
-    for (size_t n : {gemm_nt_scratch_floats(t, 3 * h, h), gemm_nt_scratch_floats(t, h, h), gemm_nt_scratch_floats(t, 2 * i, h), gemm_nt_scratch_floats(t, h, i),
-                     gemm_linear_bwd_scratch_floats(t, h, i), gemm_linear_bwd_scratch_floats(t, 2 * i, h), gemm_linear_bwd_scratch_floats(t, h, h),
-                     gemm_linear_bwd_scratch_floats(t, 3 * h, h)})
-      sk = std::max(sk, n);
+    w.scr.floats = std::max({gemm_linear_bwd_scratch_floats(t, h, i), gemm_linear_bwd_scratch_floats(t, 2 * i, h), gemm_linear_bwd_scratch_floats(t, h, h),
+                             gemm_linear_bwd_scratch_floats(t, 3 * h, h)});
   }
-  w.scr.floats = sk;
   w.scr.part = (float*)c.take(w.scr.floats * 4);
   w.bytes = c.off;
   return w;
@@ -219,7 +227,8 @@ extern "C" int taw_rope_table_init(const taw_layer_desc* desc, float* rope_table
 // The forward's kernel sequence into the intermediates `c`; y == nullptr stops after the SwiGLU
 // (all the backward needs when it rebuilds the intermediates).
 static int run_fwd(const taw_layer_desc* desc, const Plan& p, const taw_weight_layout& L, const void* W_chunk, const float* rope_table,
-                   const void* x, void* y, const Ctx& c, const GemmScratch& scr, hipStream_t st) {
+                   const void* x, void* y, const Ctx& c, hipStream_t st) {
+  const GemmScratch& scr = c.scr;
   const int dt = desc->dtype;
   const int64_t T = (int64_t)desc->B * desc->S, H = desc->H, I = desc->I;
   // xn = rmsnorm(x; gamma_attn)
@@ -273,9 +282,7 @@ extern "C" int taw_layer_fwd(const taw_layer_desc* desc, const void* W_chunk, co
   if (rc) return rc;
   taw_weight_layout L;
   taw_layer_weight_layout(desc, &L);
-  const Ctx c = carve_ctx(desc, recompute ? workspace : ctx);
-  const Work w = carve_work(desc, static_cast<char*>(workspace) + (recompute ? c.bytes : 0));
-  return run_fwd(desc, p, L, W_chunk, rope_table, x, y, c, w.scr, (hipStream_t)stream);
+  return run_fwd(desc, p, L, W_chunk, rope_table, x, y, carve_ctx(desc, recompute ? workspace : ctx), (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------------------ backward
@@ -306,7 +313,7 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
   const Work w = carve_work(desc, static_cast<char*>(workspace) + (recompute ? c.bytes : 0));
   const GemmScratch& scr = w.scr;
   if (recompute) {
-    rc = run_fwd(desc, p, L, W_chunk, rope_table, x, nullptr, c, scr, st);
+    rc = run_fwd(desc, p, L, W_chunk, rope_table, x, nullptr, c, st);
     if (rc) return rc;
   }
 

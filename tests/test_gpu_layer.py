@@ -276,6 +276,24 @@ def test_bf16_layer_of_few_tokens(taw, B, S, nh, I_):
     U.check_layer(taw, I.LayerConfig("few-tokens", I.BF16, B, S, nh * 128, nh, 128, I_, sigma_w=0.05), seed=B + S, gamma_jitter=0.1)
 
 
+@pytest.mark.parametrize("cfg", [I.CONFIGS["C1"], I.LayerConfig("few", I.BF16, 2, 8, 2560, 20, 128, 6912), I.LayerConfig("some", I.BF16, 1, 1024, 1024, 8, 128, 2816)],
+                         ids=["fp32", "16-tokens", "1024-tokens"])
+def test_forward_leaves_the_shared_workspace_alone(taw, cfg):
+    """Without TAW_RECOMPUTE the forward writes its cache and y, nothing else: a backward of another layer may be using the workspace on
+    another stream.  With few tokens its contractions are cut, and the partial products have to fit the cache, not overrun it."""
+    import torch
+    L = U.DeviceLayer(taw, cfg)
+    L.set_weights(I.make_weights(cfg, 0))
+    x, _ = I.make_activations(cfg, 0)
+    n = L.ctx.numel()
+    L.ctx = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    L.ws.fill_(0x5A)
+    L.fwd(U.to_dev(x, cfg.dtype))
+    torch.cuda.synchronize()
+    assert bool((L.ws == 0x5A).all())
+    assert bool((L.ctx[n:] == 0x5A).all())
+
+
 @pytest.mark.parametrize("B,S,nh,d,I_", [(2, 67, 3, 10, 77), (1, 130, 2, 24, 100), (1, 64, 1, 32, 33), (1, 65, 5, 8, 90), (1, 40, 2, 2, 8), (1, 50, 2, 36, 50)])
 def test_fp32_layer_head_dims(taw, B, S, nh, d, I_):
     """Narrow heads (up to 32: rows in registers, loaded in pairs or fours) and one just beyond, on products with odd widths, one key more and
