@@ -80,6 +80,17 @@ int taw_diag_issue_rate(int32_t mode, int32_t kind, int32_t nvalu, double* cycle
  * the tests check that the map is a bijection for ragged grids and count the operand panels such a block shares. */
 int taw_diag_gemm_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t* tile_rows, int32_t* tile_cols);
 
+/* What the MFMA GEMM launchers choose for a problem, on the host: the tile shape, and into how many ranges of the
+ * contraction the products are cut (1 = not cut), given the scratch they ask for.
+ *   backward == 0   C[M,N] = A[M,K] B[N,K]^T with bf16 results (row strides ldc of C and ldr of the residual, 0 = N): `splits`
+ *   backward != 0   the backward of the linear y[M,N] = x[M,K] W[N,K]^T: `splits` of the weight gradient, `splits_dx` of dx
+ * scratch_floats: fp32 elements of partial products. */
+typedef struct {
+  int32_t tile_m, tile_n, stages, splits, splits_dx;
+  int64_t scratch_floats;
+} taw_diag_gemm_plan_info;
+int taw_diag_gemm_plan(int32_t backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr, taw_diag_gemm_plan_info* out);
+
 #ifdef __cplusplus
 }
 #endif

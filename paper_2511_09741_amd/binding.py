@@ -44,6 +44,11 @@ class taw_diag_rate(C.Structure):
     _fields_ = [("tflops", C.c_double), ("clock_ghz", C.c_double), ("mfma_busy", C.c_double), ("ms", C.c_double)]
 
 
+class taw_diag_gemm_plan_info(C.Structure):
+    _fields_ = [("tile_m", C.c_int32), ("tile_n", C.c_int32), ("stages", C.c_int32), ("splits", C.c_int32), ("splits_dx", C.c_int32),
+                ("scratch_floats", C.c_int64)]
+
+
 class taw_sched_desc(C.Structure):
     _fields_ = [("P", C.c_int32), ("D", C.c_int32), ("L", C.c_int32), ("N", C.c_int32)]
 
@@ -77,6 +82,7 @@ _SIGS = {
     "taw_diag_lds_read_rate": (C.c_int, [_i32, _i32, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     "taw_diag_dq_update_rate": (C.c_int, [_vp, _i32, _i32, _i32, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     "taw_diag_gemm_tile_order": (C.c_int, [_i32, _i32, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
+    "taw_diag_gemm_plan": (C.c_int, [_i32, _i64, _i64, _i64, _i64, _i64, C.POINTER(taw_diag_gemm_plan_info)]),
     "taw_diag_issue_rate": (C.c_int, [_i32, _i32, _i32, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     "taw_diag_attn_ds_layout": (C.c_int, [_i32, C.POINTER(C.c_int64), C.POINTER(C.c_int64), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "taw_diag_store_cost_bytes": (C.c_size_t, []),
@@ -338,6 +344,13 @@ def taw_diag_gemm_tile_order(tiles_m, tiles_n):
     rows, cols = (C.c_int32 * n)(), (C.c_int32 * n)()
     _check(load().taw_diag_gemm_tile_order(tiles_m, tiles_n, rows, cols))
     return list(rows), list(cols)
+
+
+def taw_diag_gemm_plan(backward, M, N, K, ldc=0, ldr=0) -> dict:
+    """What the MFMA GEMM launchers choose for C[M,N] = A[M,K] B[N,K]^T, or for the backward of the linear y[M,N] = x[M,K] W^T.  Host only."""
+    out = taw_diag_gemm_plan_info()
+    _check(load().taw_diag_gemm_plan(int(backward), M, N, K, ldc, ldr, C.byref(out)))
+    return {k: int(getattr(out, k)) for k, _ in out._fields_}
 
 
 def taw_diag_attn_ds_layout(S) -> dict:

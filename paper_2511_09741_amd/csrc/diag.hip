@@ -411,6 +411,14 @@ extern "C" int taw_diag_gemm_tile_order(int32_t tiles_m, int32_t tiles_n, int32_
   return TAW_OK;
 }
 
+extern "C" int taw_diag_gemm_plan(int32_t backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr, taw_diag_gemm_plan_info* out) {
+  if (M < 1 || N < 1 || K < 1) return TAW_ERR_SHAPE;
+  if (!out) return TAW_ERR_NULL;
+  const taw::GemmPlanInfo p = taw::gemm_plan_info(backward != 0, M, N, K, ldc ? ldc : N, ldr ? ldr : N);
+  *out = taw_diag_gemm_plan_info{p.tile_m, p.tile_n, p.stages, p.splits[0], backward ? p.splits[1] : 1, (int64_t)p.part_floats};
+  return TAW_OK;
+}
+
 extern "C" int taw_diag_attn_ds_layout(int32_t S, int64_t* pair_bytes, int64_t* unit_offsets, int32_t* slots, int32_t* rows) {
   if (S < 1 || S > (1 << 20)) return TAW_ERR_SHAPE;
   if (!pair_bytes || !unit_offsets || !slots || !rows) return TAW_ERR_NULL;

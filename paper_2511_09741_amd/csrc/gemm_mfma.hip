@@ -1298,6 +1298,12 @@ static int launch_planned(const v2::GemmArgs& g, const GemmPlan& p, hipStream_t 
   return v2::launch_small<MODE, C_F32, 1, 1, 4, EPI>(g, st);
 }
 
+// The scratch a forward product C[M,N] may use for partial products: the reduction moves 8 columns at a time.
+static size_t nt_scratch_limit(int64_t N, int64_t ldc, int64_t ldr, size_t floats) {
+  (void)ldr;
+  return N % 8 == 0 && ldc % 8 == 0 ? floats : 0;
+}
+
 int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                      void* C, int64_t ldc, int c_dtype, int accumulate, const void* R, int64_t ldr, const GemmScratch& scr, hipStream_t st) {
   const bool f32 = c_dtype == DT_F32;
@@ -1306,7 +1312,7 @@ int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, i
   if (mode == GEMM_NT && f32) return v2::launch_pipe<GEMM_NT, true>(g, st);
   if (mode == GEMM_NN) return f32 ? v2::launch_pipe<GEMM_NN, true>(g, st) : v2::launch_pipe<GEMM_NN, false>(g, st);
   if (mode == GEMM_TN) return f32 ? v2::launch_pipe<GEMM_TN, true>(g, st) : v2::launch_pipe<GEMM_TN, false>(g, st);
-  const GemmPlan p = plan_gemm(M, N, K, N % 8 == 0 && ldc % 8 == 0 ? scr.floats : 0);
+  const GemmPlan p = plan_gemm(M, N, K, nt_scratch_limit(N, ldc, R ? ldr : 0, scr.floats));
   apply_plan(g, p, 0, scr.part);
   const int rc = launch_planned<GEMM_NT, false>(g, p, st);
   if (rc || g.splits <= 1) return rc;
@@ -1349,6 +1355,11 @@ int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, in
   if (rc || n0 + n1 == 0) return rc;
   hipLaunchKernelGGL(v2::splitk_reduce_dual_kernel, dim3((unsigned)(n0 + n1)), dim3(256), 0, st, g0, g1, n0);
   return (int)hipGetLastError();
+}
+
+GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr) {
+  const GemmPlan p = backward ? plan_dual(N, K, M, M, K, N, kMaxPartFloats) : plan_gemm(M, N, K, nt_scratch_limit(N, ldc, ldr, kMaxPartFloats));
+  return GemmPlanInfo{p.tile == 192 ? 128 : p.tile, p.tile == 192 ? 256 : p.tile, p.nst, {p.splits[0], p.splits[1]}, p.part_floats};
 }
 
 bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols) { return N % 8 == 0 && rot_cols % 128 == 0; }

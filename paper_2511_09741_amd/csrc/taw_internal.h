@@ -131,6 +131,12 @@ int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, in
 // y[T,N] = x[T,K] W^T; a launch that gets fewer makes do with them
 size_t gemm_nt_scratch_floats(int64_t M, int64_t N, int64_t K);
 size_t gemm_linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K);
+// what the two above launch when they get that scratch (backward: for the linear y[M,N] = x[M,K] W^T, splits of the weight gradient first)
+struct GemmPlanInfo {
+  int tile_m, tile_n, stages, splits[2];
+  size_t part_floats;
+};
+GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr);
 // ranges (and rows per range) for the weight gradient of the linear y[T, N] = x[T, K] W^T; 1 = not cut
 int gemm_dual_splits(int64_t T, int64_t N, int64_t K, int64_t* k_chunk);
 // C[M,N] = A[M,K] B[N,K]^T (bf16) with the rotary embedding applied in the epilogue to the columns below rot_cols (heads of

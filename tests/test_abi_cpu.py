@@ -31,7 +31,7 @@ def declared_functions():
 
 def test_every_declared_symbol_is_exported(lib):
     names = declared_functions()
-    assert len(names) == 38
+    assert len(names) == 39
     for n in names:
         assert hasattr(lib, n), f"{n} declared in include/ but not exported"
     assert set(names) == set(taw.EXPORTS)
@@ -261,6 +261,24 @@ def test_gemm_tile_order_is_a_bijection_that_keeps_concurrent_tiles_together(lib
                 assert len({rows[b] for b in mine}) == 8 and len({cols[b] for b in mine}) == 4
     with pytest.raises(taw.TawError) as e:
         taw.taw_diag_gemm_tile_order(0, 4)
+    assert e.value.status == taw.TAW_ERR_SHAPE
+
+
+@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (18, 7680, 2560), (50, 1024, 2816), (333, 264, 136), (1024, 4096, 11008), (4503, 1024, 2816),
+                                   (65536, 1024, 1024), (65536, 22016, 8192)])
+def test_gemm_plans(lib, T, N, K):
+    """A plan is one of the five tile shapes; ranges of a cut contraction have at least 256 rows and their partial products are what the
+    scratch is for; results with rows that the reduction cannot move 8 columns at a time are not cut."""
+    f, b = taw.taw_diag_gemm_plan(0, T, N, K), taw.taw_diag_gemm_plan(1, T, N, K)
+    for p in (f, b):
+        assert (p["tile_m"], p["tile_n"], p["stages"]) in {(64, 64, 4), (128, 128, 2), (128, 128, 4), (128, 256, 3), (256, 256, 2)}
+    for n, depth in ((f["splits"], K), (b["splits"], T), (b["splits_dx"], N)):
+        assert 1 <= n <= 32 and (n == 1 or depth / n > 255)
+    assert f["scratch_floats"] == (f["splits"] * T * N if f["splits"] > 1 else 0)
+    assert b["scratch_floats"] == (b["splits"] * N * K if b["splits"] > 1 else 0) + (b["splits_dx"] * T * K if b["splits_dx"] > 1 else 0)
+    assert taw.taw_diag_gemm_plan(0, T, N, K, ldc=N + 4)["splits"] == 1
+    with pytest.raises(taw.TawError) as e:
+        taw.taw_diag_gemm_plan(0, T, 0, K)
     assert e.value.status == taw.TAW_ERR_SHAPE
 
 

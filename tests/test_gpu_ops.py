@@ -383,14 +383,22 @@ def test_optimizer_step(taw, dtype, n):
         assert np.array_equal(I.to_storage(master.cpu().numpy(), dtype), chunk.view(torch.int16).cpu().numpy().view(np.uint16))
 
 
-# sizes at which the launcher takes its smaller tiles (64 x 64 at the first three, 128 x 128 with two and with four stages, 128 x 256 and
-# 256 x 256 at the others), each with remainders in rows, columns and contraction: less than one step, a whole one, one more
-@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (65, 72, 8), (333, 264, 136), (2100, 2056, 264), (1501, 1032, 1032), (1000, 4104, 2056), (2050, 2056, 2056)],
-                         ids=lambda v: str(v))
-def test_linear_tile_shapes(taw, T, N, K):
+# every tile shape (rows, columns, stages of its ring) of the product and of its backward, each with remainders in rows, columns and contraction:
+# less than one step, a whole one, one more
+S64, S128D, S128, S192, S256 = (64, 64, 4), (128, 128, 2), (128, 128, 4), (128, 256, 3), (256, 256, 2)
+
+
+@pytest.mark.parametrize("T,N,K,fwd,bwd", [(1, 8, 8, S64, S64), (65, 72, 8, S64, S64), (333, 264, 136, S64, S64), (2100, 2056, 264, S128D, S64),
+                                           (1501, 1032, 1032, S64, S128), (1000, 4104, 2056, S192, S192), (2050, 2056, 2056, S192, S256),
+                                           (333, 6152, 136, S128, S64), (1300, 6152, 72, S256, S64), (777, 520, 3080, S64, S128D)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_linear_tile_shapes(taw, T, N, K, fwd, bwd):
     """y = x W^T (+ residual) and its backward at every tile shape against fp64 products of the same bf16 operands.  bf16 results: one
     rounding, 2^-9 of the element, so below 2^-8 of the tensor's scale; fp32 ones: accumulation order only, as in
     test_gemm_mfma_fp32_output_is_accurate.  The weight gradient starts from values it has to keep or to forget."""
+    for backward, want in ((0, fwd), (1, bwd)):
+        p = taw.taw_diag_gemm_plan(backward, T, N, K)
+        assert (p["tile_m"], p["tile_n"], p["stages"]) == want, (backward, p)
     import torch
     x, W, dy = (I.device_normal(s, seed=i, std=d) for i, (s, d) in enumerate((((T, K), 1.0), ((N, K), 0.02), ((T, N), 1.0))))
     R = I.device_normal((T, N), seed=9, std=1.0)
