@@ -1097,8 +1097,8 @@ int launch_small_dual(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
-// C = (accumulate ? C : 0) + R + part[0] + part[1] + ... + part[splits - 1], the partial products in that order, with the rotation of the
-// fused epilogue where the GEMM asks for it; two GEMMs' worth in one grid, 8 columns per thread, blocks of the first first
+// C = rotated(part[0] + part[1] + ... + part[splits - 1]) + R + (accumulate ? C : 0), added in that order, the rotation where the GEMM asks for
+// it; two GEMMs' worth in one grid, 8 columns per thread (4 of fp32), blocks of the first first
 template <bool C_F32, bool ROPE>
 __device__ __forceinline__ void reduce_parts(const GemmArgs& g, int64_t first, int64_t stride) {
   constexpr int V = C_F32 ? 4 : 8;
@@ -1298,11 +1298,9 @@ static int launch_planned(const v2::GemmArgs& g, const GemmPlan& p, hipStream_t 
   return v2::launch_small<MODE, C_F32, 1, 1, 4, EPI>(g, st);
 }
 
-// The scratch a forward product C[M,N] may use for partial products: the reduction moves 8 columns at a time.
-static size_t nt_scratch_limit(int64_t N, int64_t ldc, int64_t ldr, size_t floats) {
-  (void)ldr;
-  return N % 8 == 0 && ldc % 8 == 0 ? floats : 0;
-}
+// The scratch a forward product C[M,N] may use for partial products: the reduction moves 8 columns of C and of the residual at a time
+// (ldr = 0: there is none).
+static size_t nt_scratch_limit(int64_t N, int64_t ldc, int64_t ldr, size_t floats) { return N % 8 == 0 && ldc % 8 == 0 && ldr % 8 == 0 ? floats : 0; }
 
 int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                      void* C, int64_t ldc, int c_dtype, int accumulate, const void* R, int64_t ldr, const GemmScratch& scr, hipStream_t st) {

@@ -277,6 +277,7 @@ def test_gemm_plans(lib, T, N, K):
     assert f["scratch_floats"] == (f["splits"] * T * N if f["splits"] > 1 else 0)
     assert b["scratch_floats"] == (b["splits"] * N * K if b["splits"] > 1 else 0) + (b["splits_dx"] * T * K if b["splits_dx"] > 1 else 0)
     assert taw.taw_diag_gemm_plan(0, T, N, K, ldc=N + 4)["splits"] == 1
+    assert taw.taw_diag_gemm_plan(0, T, N, K, ldr=N + 4)["splits"] == 1
     with pytest.raises(taw.TawError) as e:
         taw.taw_diag_gemm_plan(0, T, 0, K)
     assert e.value.status == taw.TAW_ERR_SHAPE
