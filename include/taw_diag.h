@@ -84,10 +84,11 @@ int taw_diag_gemm_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t* tile_row
  * contraction the products are cut (1 = not cut), given the scratch they ask for.
  *   backward == 0   C[M,N] = A[M,K] B[N,K]^T with bf16 results (row strides ldc of C and ldr of the residual, 0 = N): `splits`
  *   backward != 0   the backward of the linear y[M,N] = x[M,K] W[N,K]^T: `splits` of the weight gradient, `splits_dx` of dx
- * scratch_floats: fp32 elements of partial products. */
+ * scratch_floats: fp32 elements of partial products.
+ * planned: how many plans the calling thread has worked out so far; it remembers its latest ones. */
 typedef struct {
   int32_t tile_m, tile_n, stages, splits, splits_dx;
-  int64_t scratch_floats;
+  int64_t scratch_floats, planned;
 } taw_diag_gemm_plan_info;
 int taw_diag_gemm_plan(int32_t backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr, taw_diag_gemm_plan_info* out);
 

@@ -46,7 +46,7 @@ class taw_diag_rate(C.Structure):
 
 class taw_diag_gemm_plan_info(C.Structure):
     _fields_ = [("tile_m", C.c_int32), ("tile_n", C.c_int32), ("stages", C.c_int32), ("splits", C.c_int32), ("splits_dx", C.c_int32),
-                ("scratch_floats", C.c_int64)]
+                ("scratch_floats", C.c_int64), ("planned", C.c_int64)]
 
 
 class taw_sched_desc(C.Structure):

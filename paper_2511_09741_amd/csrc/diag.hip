@@ -415,7 +415,7 @@ extern "C" int taw_diag_gemm_plan(int32_t backward, int64_t M, int64_t N, int64_
   if (M < 1 || N < 1 || K < 1) return TAW_ERR_SHAPE;
   if (!out) return TAW_ERR_NULL;
   const taw::GemmPlanInfo p = taw::gemm_plan_info(backward != 0, M, N, K, ldc ? ldc : N, ldr ? ldr : N);
-  *out = taw_diag_gemm_plan_info{p.tile_m, p.tile_n, p.stages, p.splits[0], backward ? p.splits[1] : 1, (int64_t)p.part_floats};
+  *out = taw_diag_gemm_plan_info{p.tile_m, p.tile_n, p.stages, p.splits[0], backward ? p.splits[1] : 1, (int64_t)p.part_floats, p.planned};
   return TAW_OK;
 }
 

@@ -1221,19 +1221,8 @@ static double makespan(int64_t n0, double d0, int64_t n1, double d1, int64_t P) 
 }
 
 // The cheapest tile shape, and the cheapest numbers of ranges the contractions of the np (1 or 2) problems of one grid are cut into, whose
-// partial products fit max_floats.  A pure function of the sizes; each thread keeps its latest answers.
-static GemmPlan plan_grid(int np, const GemmProblem (&pr)[2], size_t max_floats) {
-  struct Entry {
-    int64_t key[9];
-    GemmPlan plan;
-  };
-  static thread_local Entry cache[64];
-  const int64_t key[9] = {np, pr[0].M, pr[0].N, pr[0].K, pr[1].M, pr[1].N, pr[1].K, pr[0].out_bytes, (int64_t)max_floats};
-  uint64_t h = 0;
-  for (int64_t k : key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
-  Entry& slot = cache[h >> 58];
-  if (memcmp(slot.key, key, sizeof(key)) == 0) return slot.plan;      // an entry never written has np = 0
-
+// partial products fit max_floats.  A pure function of the sizes; takes 2 - 3 us.
+static GemmPlan work_out_plan(int np, const GemmProblem (&pr)[2], size_t max_floats) {
   GemmPlan best{};
   double best_t = 1e300;
   for (const TileCost& c : kTiles) {
@@ -1268,9 +1257,43 @@ static GemmPlan plan_grid(int np, const GemmProblem (&pr)[2], size_t max_floats)
       }
     }
   }
-  memcpy(slot.key, key, sizeof(key));
-  slot.plan = best;
   return best;
+}
+
+// Each thread's latest plans, in rows of 16 by the key's hash, the places of a row taken in turn: the eight products of a layer shape
+// cannot push each other out, and a few dozen shapes fit.  (64 places, one to a hash: the products of one small layer, each under two
+// limits, did, and a step of 110 us worked out 10 plans again, 2.4 us each.)
+struct PlanMemory {
+  static constexpr int kRows = 32, kWays = 16;
+  struct Entry {
+    int64_t key[9];      // np = 0: never written
+    GemmPlan plan;
+  } entry[kRows][kWays];
+  unsigned next[kRows];
+  int64_t planned;
+};
+static thread_local PlanMemory g_plans;
+
+static GemmPlan remembered_plan(int np, const GemmProblem (&pr)[2], size_t max_floats) {
+  PlanMemory& mem = g_plans;
+  const int64_t key[9] = {np, pr[0].M, pr[0].N, pr[0].K, pr[1].M, pr[1].N, pr[1].K, pr[0].out_bytes, (int64_t)max_floats};
+  uint64_t h = 0;
+  for (int64_t k : key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
+  const int row = (int)(h >> 59);
+  for (const PlanMemory::Entry& e : mem.entry[row])
+    if (memcmp(e.key, key, sizeof(key)) == 0) return e.plan;
+  PlanMemory::Entry& e = mem.entry[row][mem.next[row]++ % PlanMemory::kWays];
+  memcpy(e.key, key, sizeof(key));
+  e.plan = work_out_plan(np, pr, max_floats);
+  ++mem.planned;
+  return e.plan;
+}
+
+// The plan without a limit wherever its partial products fit (it is then also the cheapest within the limit): sizing the scratch and
+// launching ask for the same one.
+static GemmPlan plan_grid(int np, const GemmProblem (&pr)[2], size_t max_floats) {
+  const GemmPlan p = remembered_plan(np, pr, kMaxPartFloats);
+  return p.part_floats <= max_floats ? p : remembered_plan(np, pr, max_floats);
 }
 static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, size_t max_floats) {
   return plan_grid(1, {{M, N, K, 2}, {0, 0, 0, 0}}, max_floats);
@@ -1357,7 +1380,7 @@ int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, in
 
 GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr) {
   const GemmPlan p = backward ? plan_dual(N, K, M, M, K, N, kMaxPartFloats) : plan_gemm(M, N, K, nt_scratch_limit(N, ldc, ldr, kMaxPartFloats));
-  return GemmPlanInfo{p.tile == 192 ? 128 : p.tile, p.tile == 192 ? 256 : p.tile, p.nst, {p.splits[0], p.splits[1]}, p.part_floats};
+  return GemmPlanInfo{p.tile == 192 ? 128 : p.tile, p.tile == 192 ? 256 : p.tile, p.nst, {p.splits[0], p.splits[1]}, p.part_floats, g_plans.planned};
 }
 
 bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols) { return N % 8 == 0 && rot_cols % 128 == 0; }

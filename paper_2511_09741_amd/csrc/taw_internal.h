@@ -135,6 +135,7 @@ size_t gemm_linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K);
 struct GemmPlanInfo {
   int tile_m, tile_n, stages, splits[2];
   size_t part_floats;
+  int64_t planned;      // plans the calling thread has worked out so far (the others it remembered)
 };
 GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr);
 // ranges (and rows per range) for the weight gradient of the linear y[T, N] = x[T, K] W^T; 1 = not cut

@@ -283,6 +283,37 @@ def test_gemm_plans(lib, T, N, K):
     assert e.value.status == taw.TAW_ERR_SHAPE
 
 
+def test_gemm_plans_are_worked_out_once(lib):
+    """A program calls its few layer shapes over and over: after a first call per shape everything about their products is remembered, the
+    scratch sizes and the launches' plans, for one shape (which must not push out its own) and for twenty in turn."""
+    import threading
+    planned = lambda: taw.taw_diag_gemm_plan(0, 8, 8, 8)["planned"]
+
+    def layer(T, H, I_):
+        d = taw.make_desc(taw.TAW_BF16, 1, T, H, H // 128, 128, I_)
+        taw.taw_layer_ctx_bytes(d), taw.taw_layer_workspace_bytes(d)
+        for N, K in ((3 * H, H), (H, H), (2 * I_, H), (H, I_)):
+            taw.taw_diag_gemm_plan(0, T, N, K), taw.taw_diag_gemm_plan(1, T, N, K)
+
+    shapes = [(T, H, I_) for T in (50, 666, 4503, 16384) for H, I_ in ((128, 512), (256, 392), (1024, 2816), (2048, 5632), (4096, 11008))]
+    counts = {}
+
+    def run():                                            # a thread of its own: what it remembers starts empty
+        planned()
+        for group in [[s] for s in shapes] + [shapes]:
+            for s in group:
+                layer(*s)
+            before = planned()
+            for s in group:
+                layer(*s)
+            counts[tuple(group)] = planned() - before
+
+    t = threading.Thread(target=run)
+    t.start()
+    t.join()
+    assert counts and not any(counts.values()), {k: n for k, n in counts.items() if n}
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(taw, "_lib", None)
     monkeypatch.setattr(taw, "LIB_PATH", str(tmp_path / "nope.so"))
