@@ -1341,24 +1341,6 @@ int launch_gemm_mfma(int mode, int64_t M, int64_t N, int64_t K, const void* A, i
   return (int)hipGetLastError();
 }
 
-// What taw_op_linear_bwd_scratch_floats offers the plan above at the kernel level: the ranges (1 = none) a weight gradient alone
-// would be cut into for the linear y[T, N] = x[T, K] W^T, and the rows per
-// range.  Its tiles contract over all T tokens: with few of them (narrow layers) a tile runs long after everything else
-// in the grid is done, most compute units idle.  The ranges are sized so that one takes at most about half of what a
-// compute unit's fair share of the whole grid (both GEMMs) takes; never shorter than 512 rows, never more than 32 ranges.
-int gemm_dual_splits(int64_t T, int64_t N, int64_t K, int64_t* k_chunk) {
-  const int64_t tn_tiles = ((N + BM - 1) / BM) * ((K + BN - 1) / BN), nn_tiles = ((T + BM - 1) / BM) * ((K + BN - 1) / BN);
-  const double fair = ((double)tn_tiles * (double)T + (double)nn_tiles * (double)N) / 256.0;     // contraction rows per compute unit
-  int64_t sp = fair > 0 ? (int64_t)(2.0 * (double)T / fair + 0.999) : 1;
-  if (sp > 32) sp = 32;
-  if (sp > T / 512) sp = T / 512;
-  if (sp < 2) { *k_chunk = T; return 1; }
-  int64_t chunk = ((T + sp - 1) / sp + 63) / 64 * 64;
-  sp = (T + chunk - 1) / chunk;
-  *k_chunk = chunk;
-  return (int)sp;
-}
-
 int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, int64_t lda0, const void* B0, int64_t ldb0, float* C0,
                           int64_t ldc0, int accumulate0, int64_t M1, int64_t N1, int64_t K1, const void* A1, int64_t lda1,
                           const void* B1, int64_t ldb1, void* C1, int64_t ldc1, const GemmScratch& scr, hipStream_t st) {

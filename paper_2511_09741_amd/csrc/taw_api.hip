@@ -120,14 +120,6 @@ struct Work {      // scratch of the backward
   void *da, *dgu, *dhn, *dh, *dO, *dqkv, *dxn; float *D, *partials; GemmScratch scr; size_t bytes;
 };
 
-// fp32 elements of partial weight gradients the backward of the linear y[T,N] = x[T,K] W^T needs (0: its weight gradient is not cut)
-static size_t linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K) {
-  if (T <= 0 || N <= 0 || K <= 0) return 0;
-  int64_t chunk;
-  const int sp = gemm_dual_splits(T, N, K, &chunk);
-  return sp > 1 ? (size_t)sp * (size_t)N * (size_t)K : 0;
-}
-
 // which form of the MFMA attention backward the layer runs
 static int attn_bwd_form_of(const taw_layer_desc* d) {
   return (d->flags & TAW_ATTN_BWD_FUSED) ? ATTN_BWD_FUSED : (d->flags & TAW_ATTN_BWD_RECOMPUTE) ? ATTN_BWD_SPLIT : ATTN_BWD_STORED;
@@ -621,7 +613,10 @@ extern "C" int taw_op_qkv_rope(int32_t dtype, int32_t B, int32_t S, int32_t n_he
   return TAW_OK;
 }
 
-extern "C" size_t taw_op_linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K) { return linear_bwd_scratch_floats(T, N, K); }
+// the layer's own scratch for this product: the same plan, so the same cuts
+extern "C" size_t taw_op_linear_bwd_scratch_floats(int64_t T, int64_t N, int64_t K) {
+  return T > 0 && N > 0 && K > 0 && N % 8 == 0 && K % 8 == 0 ? gemm_linear_bwd_scratch_floats(T, N, K) : 0;
+}
 
 extern "C" int taw_op_linear_bwd(int32_t dtype, int64_t T, int64_t N, int64_t K, const void* dy, const void* W, const void* x, void* dx,
                                  float* G, int32_t accumulate, float* scratch, int32_t impl, void* stream) {
@@ -640,6 +635,6 @@ extern "C" int taw_op_linear_bwd(int32_t dtype, int64_t T, int64_t N, int64_t K,
   p.mfma_gemm = can && impl != TAW_IMPL_GENERIC;
   p.mfma_attn = false;
   if (scratch) TAW_REQUIRE_ALIGNED(scratch);
-  TAW_LAUNCH(linear_bwd(p, dtype, T, N, K, dy, W, x, dx, G, accumulate ? 1 : 0, GemmScratch{scratch, scratch ? linear_bwd_scratch_floats(T, N, K) : 0}, st), "linear backward");
+  TAW_LAUNCH(linear_bwd(p, dtype, T, N, K, dy, W, x, dx, G, accumulate ? 1 : 0, GemmScratch{scratch, scratch ? taw_op_linear_bwd_scratch_floats(T, N, K) : 0}, st), "linear backward");
   return TAW_OK;
 }

@@ -138,8 +138,6 @@ struct GemmPlanInfo {
   int64_t planned;      // plans the calling thread has worked out so far (the others it remembered)
 };
 GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr);
-// ranges (and rows per range) for the weight gradient of the linear y[T, N] = x[T, K] W^T; 1 = not cut
-int gemm_dual_splits(int64_t T, int64_t N, int64_t K, int64_t* k_chunk);
 // C[M,N] = A[M,K] B[N,K]^T (bf16) with the rotary embedding applied in the epilogue to the columns below rot_cols (heads of
 // 128, adjacent pairs, row r at position r % S; table [S, 64, 2] fp32).  Needs N % 8 == 0, rot_cols % 128 == 0.
 bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols);

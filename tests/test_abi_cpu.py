@@ -321,20 +321,19 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         taw.load()
 
 
-def test_linear_bwd_scratch_rule(lib):
-    """The weight gradient is cut only where it has too few tiles for its share of the chip: never at the 4096- and
-    5120-wide layers, at most 32 ranges of at least 512 tokens elsewhere, nothing for empty or tiny problems."""
+def test_linear_bwd_scratch_is_the_layers(lib):
+    """The kernel-level backward of a linear asks for the scratch of the plan that the layer runs for the same product, so it gets the same
+    tiles and cuts; nothing for empty problems and for widths the matrix kernels do not take."""
     f = taw.taw_op_linear_bwd_scratch_floats
-    for T in (8192, 32768, 65536):
-        for H, Iw in ((4096, 11008), (5120, 13824)):
+    cut = 0
+    for T in (1, 50, 768, 1024, 4503, 65536):
+        for H, Iw in ((128, 392), (1024, 2816), (2048, 5632), (4096, 11008), (8192, 22016)):
             for N, K in ((H, Iw), (2 * Iw, H), (H, H), (3 * H, H)):
-                assert f(T, N, K) == 0
-    for T, N, K in ((65536, 1024, 1024), (65536, 1024, 2816), (65536, 3072, 1024), (65536, 2048, 2048), (2080, 256, 256), (1 << 20, 8, 8)):
-        n = f(T, N, K)
-        assert n > 0 and n % (N * K) == 0
-        splits = n // (N * K)
-        assert 2 <= splits <= 32 and T // splits >= 512 - 64
-    for T, N, K in ((0, 8, 8), (8, 0, 8), (-1, 8, 8), (256, 256, 256), (1023, 8, 8)):
+                n = f(T, N, K)
+                assert n == taw.taw_diag_gemm_plan(1, T, N, K)["scratch_floats"]
+                cut += n > 0
+    assert cut > 20
+    for T, N, K in ((0, 8, 8), (8, 0, 8), (-1, 8, 8), (8, 8, 0), (65536, 1020, 1024), (65536, 1024, 1020), (256, 256, 256)):
         assert f(T, N, K) == 0
 
 

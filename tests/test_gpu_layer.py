@@ -100,16 +100,23 @@ def test_bf16_layer_on_mfma_kernels(taw, B, S, nh, I_, sigma):
     U.check_layer(taw, cfg, seed=B + S, gamma_jitter=0.1)
 
 
+def _cuts(taw, T, H, I_):
+    """ranges each product's contraction is cut into: the forward products, and the input gradients ("d...") and weight gradients ("G...")"""
+    out = {}
+    for k, N, K in (("qkv", 3 * H, H), ("o", H, H), ("gate_up", 2 * I_, H), ("down", H, I_)):
+        f, b = taw.taw_diag_gemm_plan(0, T, N, K), taw.taw_diag_gemm_plan(1, T, N, K)
+        out.update({k: f["splits"], "d" + k: b["splits_dx"], "G" + k: b["splits"]})
+    return {k: n for k, n in out.items() if n > 1}
+
+
 @pytest.mark.parametrize("H,nh,B,S", [(1024, 8, 4, 512), (2048, 16, 2, 384)])
 def test_bf16_layer_at_the_widths_of_the_papers_throughput_table(taw, H, nh, B, S):
     """The narrower models of the paper's throughput table (Experiments, Throughput and Memory Usage: H = 1024 and 2048,
     heads of 128, I = 8H/3 rounded up to 256, micro-batches of several sequences): whole layer against the oracle, every
-    element, at a reduced sequence length.  The first case has 2048 tokens: all four of its weight gradients are computed in
-    3 - 4 ranges of tokens and summed by the second kernel, as at the table's own sizes."""
+    element, at a reduced sequence length.  Some of their products are cut into ranges summed by the second kernel: weight
+    gradients along the tokens, input gradients and the 2048-wide down projection along the widths."""
     cfg = I.LayerConfig(f"table-{H}", I.BF16, B, S, H, nh, 128, (8 * H // 3 + 255) // 256 * 256)
-    T = B * S
-    cut = [taw.taw_op_linear_bwd_scratch_floats(T, N, K) > 0 for N, K in ((H, cfg.I), (2 * cfg.I, H), (H, H), (3 * H, H))]
-    assert all(cut) == (H == 1024)
+    assert _cuts(taw, B * S, H, cfg.I) == ({"Gdown": 2, "Go": 2, "dqkv": 2, "dgate_up": 4} if H == 1024 else {"down": 2, "dqkv": 2, "dgate_up": 2})
     U.check_layer(taw, cfg, seed=H + S)
 
 
@@ -267,15 +274,6 @@ def test_recompute_mode_gives_the_same_results(taw, cfg):
     dxr, _ = O.layer_bwd(w64, cache, I.to_f64(dy, cfg.dtype))
     assert U.tensor_scale_err(U.from_dev(outs[1][0]), yr) < U.TOL[cfg.dtype]
     assert U.tensor_scale_err(U.from_dev(outs[1][1]), dxr) < U.TOL[cfg.dtype]
-
-
-def _cuts(taw, T, H, I_):
-    """ranges each product's contraction is cut into: the forward products, and the input gradients ("d...") and weight gradients ("G...")"""
-    out = {}
-    for k, N, K in (("qkv", 3 * H, H), ("o", H, H), ("gate_up", 2 * I_, H), ("down", H, I_)):
-        f, b = taw.taw_diag_gemm_plan(0, T, N, K), taw.taw_diag_gemm_plan(1, T, N, K)
-        out.update({k: f["splits"], "d" + k: b["splits_dx"], "G" + k: b["splits"]})
-    return {k: n for k, n in out.items() if n > 1}
 
 
 @pytest.mark.parametrize("B,S,nh,I_,cuts", [(1, 50, 8, 2816, {"down": 8, "dqkv": 4, "dgate_up": 4}), (3, 111, 8, 2816, {"dqkv": 8, "dgate_up": 2}),

@@ -421,6 +421,36 @@ def test_linear_tile_shapes(taw, T, N, K, fwd, bwd):
         assert err < tol, (k, err)
 
 
+# cut contractions of a linear's backward on every tile shape: the input gradient's (ranges of N), the weight gradient's (of T), both
+@pytest.mark.parametrize("T,N,K,tile,cut_dx,cut_g", [(16, 2056, 72, S64, 4, 1), (520, 4104, 520, S128D, 8, 1), (777, 4104, 264, S128, 4, 1),
+                                                     (1030, 5640, 520, S192, 4, 1), (1030, 2056, 2824, S256, 2, 1), (2050, 72, 72, S64, 1, 4),
+                                                     (4100, 520, 520, S128D, 1, 8), (4100, 1032, 264, S128, 1, 4), (4100, 520, 2056, S192, 1, 2),
+                                                     (2050, 1032, 2824, S256, 1, 2), (600, 2056, 8, S64, 4, 2)], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_linear_backward_cut_contractions(taw, T, N, K, tile, cut_dx, cut_g):
+    """Both gradients against fp64 products of the same bf16 operands (bounds as in test_linear_tile_shapes), over scratch with stale contents, with
+    the last range ragged; and against the call without scratch, which cuts nothing: fp32 sums in another order, so G by a few 2^-24 of
+    what was summed and dx by a bf16 rounding here and there."""
+    import torch
+    p = taw.taw_diag_gemm_plan(1, T, N, K)
+    assert ((p["tile_m"], p["tile_n"], p["stages"]), p["splits_dx"], p["splits"]) == (tile, cut_dx, cut_g)
+    x, W, dy = (I.device_normal(s, seed=i, std=d) for i, (s, d) in enumerate((((T, K), 1.0), ((N, K), 0.02), ((T, N), 1.0))))
+    G0 = I.device_normal((N, K), seed=11, std=1.0, dtype=torch.float32)
+    n_scr = taw.taw_op_linear_bwd_scratch_floats(T, N, K)
+    assert n_scr == p["scratch_floats"] > 0
+    scratch = torch.full((n_scr + 1024,), float("nan"), dtype=torch.float32, device="cuda")
+    got = {}
+    for scr in (scratch, None):
+        dx, G = torch.full((T, K), float("nan"), dtype=torch.bfloat16, device="cuda"), G0.clone()
+        taw.taw_op_linear_bwd(I.BF16, T, N, K, dy, W, x, dx, G, 1, taw.TAW_IMPL_MFMA, scratch=scr)
+        got[scr is None] = dx.double(), G.double()
+    torch.cuda.synchronize()
+    assert bool(scratch[n_scr:].isnan().all()) and not bool(scratch[:n_scr].isnan().any())
+    refs = dy.double() @ W.double(), dy.double().t() @ x.double() + G0.double()
+    for a, b, ref, tol in zip(got[False], got[True], refs, (2.0 ** -8, 2e-6)):
+        scale = float(ref.abs().max())
+        assert float((a - ref).abs().max()) < tol * scale and float((a - b).abs().max()) < tol * scale
+
+
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16])
 @pytest.mark.parametrize("mode", [0, 1, 2])
 def test_gemm_generic_large_tiles(taw, dtype, mode):
