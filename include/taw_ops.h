@@ -100,8 +100,10 @@ int taw_op_attn_bwd(int32_t dtype, int32_t B, int32_t S, int32_t n_heads, int32_
 
 /* The fused qkv projection with the rotary embedding, as taw_layer_fwd runs it:
  *   qkv [B*S, 3H] = xn [B*S, H] w_qkv[3H, H]^T, then q and k (columns 0 .. 2H-1) rotated by position.
- * On the MFMA path the rotation happens in the GEMM's epilogue when B*S and H allow it (otherwise,
- * and on the generic path, a rotary pass follows the GEMM: same result up to one more rounding). */
+ * The rotation happens inside the product, on its fp32 sums; MFMA products with heads other than 128 are followed by a
+ * rotary pass, which rotates the stored (bf16) projection.  On the MFMA path with heads of 128 the sums are rounded to bf16 before the
+ * rotation, as that pass does, unless B*S is a multiple of 256, n_heads even and S >= 32 (one rounding of q and k less).
+ * The layer gives the same bits, up to the order of fp32 sums where it cuts the contraction (few tokens, H >= 2560). */
 int taw_op_qkv_rope(int32_t dtype, int32_t B, int32_t S, int32_t n_heads, int32_t head_dim, const void* xn,
                     const void* w_qkv, void* qkv, const float* rope_table, int32_t impl, void* stream);
 

@@ -217,9 +217,8 @@ __device__ __forceinline__ void stage_rows(const f32x16_t& blk, float* stg_blk, 
 // Columns below rot_cols are heads of 128 whose adjacent pairs (2i, 2i+1) are rotated by the angle of
 // (row % S, i); table [S][64][2] fp32 of (cos, sin).  A lane holds 8 consecutive columns of a row here,
 // i.e. 4 whole pairs, in fp32: the fused qkv projection then needs no rotary pass of its own, and q, k
-// are rounded to bf16 once.  rot_cols is a multiple of 128.  round_first: rounded to bf16 before the rotation too, as a
-// separate rotary pass over the stored projection does; kept where such a pass stood, since the scores of a wide layer (large q, k)
-// carry that rounding into y and the gradients at the 1 % level and a layer's results should not depend on how it is launched.
+// are rounded to bf16 once.  rot_cols is a multiple of 128. round_first: rounded to bf16 before the rotation too, as the
+// separate rotary pass did that rotated q and k of these sizes before (launch_gemm_mfma_nt_rope).
 constexpr int kEpiNone = 0, kEpiRope = 1;
 struct EpiArgs {
   const float* table;
@@ -1370,6 +1369,9 @@ bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols) { return N % 8 == 0 &
 int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
                              const float* rope_table, int S, int64_t rot_cols, const GemmScratch& scr, hipStream_t st) {
   v2::GemmArgs g = v2::make_args(M, N, K, A, lda, B, ldb, C, ldc, 0, nullptr, 0);
+  // Sizes outside this condition were rotated by a pass of their own once, after a rounding to bf16, and keep that rounding: without it their
+  // error against fp64 is lower (dx, 1000 tokens at H = 8192: 1.39 % instead of 1.56 %; 666 at 4096: 0.71 instead of 0.75), but q and k reach
+  // dx through the scores, and it moves by more than bf16 results are held to (1.5 and 0.8 %).  With it everywhere the others would lose.
   g.epi = v2::EpiArgs{rope_table, S, rot_cols, !(M % BM == 0 && N % BN == 0 && S >= 32)};
   const GemmPlan p = plan_gemm(M, N, K, scr.floats);
   apply_plan(g, p, 0, scr.part);

@@ -225,7 +225,7 @@ static int run_fwd(const taw_layer_desc* desc, const Plan& p, const taw_weight_l
   const int64_t T = (int64_t)desc->B * desc->S, H = desc->H, I = desc->I;
   // xn = rmsnorm(x; gamma_attn)
   TAW_LAUNCH(launch_rmsnorm_fwd(dt, T, (int)H, x, at(W_chunk, L.gamma_attn, dt), desc->rms_eps, c.xn, c.r1, st), "rmsnorm_fwd(attn)");
-  // qkv = xn Wqkv^T, q and k (the first 2H columns) rotated: in the GEMM's epilogue where its tiles allow it
+  // qkv = xn Wqkv^T, q and k (the first 2H columns) rotated in the GEMM's epilogue; by a pass of its own for MFMA products with heads other than 128
   if (p.mfma_gemm && dt == DT_BF16 && desc->head_dim == 128 && gemm_mfma_supported(dt, GEMM_NT, T, 3 * H, H, H, H, 3 * H, dt, 0) &&
       gemm_mfma_rope_supported(3 * H, 2 * H)) {
     TAW_LAUNCH(launch_gemm_mfma_nt_rope(T, 3 * H, H, c.xn, H, at(W_chunk, L.w_qkv, dt), H, c.qkv, 3 * H, rope_table, desc->S, 2 * H, scr, st),
@@ -606,10 +606,10 @@ extern "C" int taw_op_qkv_rope(int32_t dtype, int32_t B, int32_t S, int32_t n_he
       return TAW_OK;
     }
     TAW_LAUNCH(launch_gemm_mfma(GEMM_NT, T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, dtype, 0, nullptr, 0, GemmScratch{nullptr, 0}, st), "gemm qkv (mfma)");
+    TAW_LAUNCH(launch_rope(dtype, B, S, (int)(2 * H), head_dim, qkv, 3 * H, rope_table, 0, st), "rope");
   } else {
-    TAW_LAUNCH(launch_gemm_generic(dtype, GEMM_NT, T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, dtype, 0, nullptr, 0, st), "gemm qkv (generic)");
+    TAW_LAUNCH(launch_gemm_generic_rope(dtype, T, 3 * H, H, xn, H, w_qkv, H, qkv, 3 * H, rope_table, S, head_dim, 2 * H, st), "gemm qkv + rope (generic)");
   }
-  TAW_LAUNCH(launch_rope(dtype, B, S, (int)(2 * H), head_dim, qkv, 3 * H, rope_table, 0, st), "rope");
   return TAW_OK;
 }
 
