@@ -28,7 +28,7 @@ def test_fp32_ragged_shapes(taw, B, S, H, nh, I_):
 
 
 def test_bf16_storage_on_generic_kernels(taw):
-    """bf16 storage with head_dim 16: no MFMA kernel takes it, the generic path must."""
+    """bf16 storage with head_dim 16: the generic attention between the MFMA products."""
     cfg = I.LayerConfig("bf16-generic", I.BF16, 2, 48, 64, 4, 16, 88)
     U.check_layer(taw, cfg, seed=5, sigma_w=0.2, gamma_jitter=0.2)
 
@@ -327,6 +327,15 @@ def test_fp32_layer_head_dims(taw, B, S, nh, d, I_):
     """Narrow heads (up to 32: rows in registers, loaded in pairs or fours) and one just beyond, on products with odd widths, one key more and
     one less than a wavefront, rotation, SwiGLU and both of its backward's halves inside the products."""
     U.check_layer(taw, I.LayerConfig("narrow", I.F32, B, S, nh * d, nh, d, I_, sigma_w=0.2), seed=d, gamma_jitter=0.1)
+
+
+@pytest.mark.parametrize("dtype,B,S,nh,d,I_", [(I.BF16, 2, 67, 3, 10, 77), (I.BF16, 1, 130, 3, 20, 100), (I.BF16, 1, 65, 5, 8, 91), (I.BF16, 1, 50, 3, 36, 50),
+                                               (I.F32, 1, 1100, 33, 32, 1001), (I.BF16, 1, 1100, 33, 30, 1001)], ids=str)
+def test_layer_on_generic_products(taw, dtype, B, S, nh, d, I_):
+    """bf16 layers with widths no MFMA product takes (H or I no multiple of 8): rotation, SwiGLU and its backward inside the generic products, on
+    16 x 16 tiles; and layers whose products have too many of those (4096) for one grid of the two gradients, with SwiGLU's backward on its own.
+    Weights of H^-1/2: scores of standard deviation 1, which the rounding of q and k to bf16 moves by about 2^-8 of themselves, 1 - 2 % at most."""
+    U.check_layer(taw, I.LayerConfig("generic", dtype, B, S, nh * d, nh, d, I_, sigma_w=(nh * d) ** -0.5), seed=d, gamma_jitter=0.1)
 
 
 @pytest.mark.parametrize("B,S", [(52, 100), (160, 33), (41, 128), (64, 48)])
