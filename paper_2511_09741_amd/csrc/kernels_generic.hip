@@ -342,15 +342,15 @@ __global__ void __launch_bounds__(256) attn_fwd_narrow_kernel(const T* __restric
   if (lane == 0) lse[((int64_t)b * nh + h) * S + t] = mt + logf(z);
 }
 
-// First half of the grid: dq of a query; second half: dk, dv of a key.  D[t] = dO[t] . o[t] is formed where it is needed.  The gradients of
+// blockIdx.y = 0: dq of a query; 1: dk, dv of a key (along y, since a launch takes fewer than 2^32 work-items along x).  D[t] = dO[t] . o[t] is formed where it is needed.  The gradients of
 // rotated q and k are rotated back before they leave where a table is given.
 template <typename T, int DP, int V>
 __global__ void __launch_bounds__(256) attn_bwd_narrow_kernel(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dO,
                                                               const float* __restrict__ lse, T* __restrict__ dqkv, int B, int S, int nh, int d,
-                                                              const float* __restrict__ rope, int half) {
+                                                              const float* __restrict__ rope) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool keys = (int)blockIdx.x >= half;
-  const int64_t gid = (int64_t)((int)blockIdx.x - (keys ? half : 0)) * 4 + wave;
+  const bool keys = blockIdx.y != 0;
+  const int64_t gid = (int64_t)blockIdx.x * 4 + wave;
   if (gid >= (int64_t)B * nh * S) return;
   const int t = (int)(gid % S), h = (int)((gid / S) % nh), b = (int)(gid / ((int64_t)S * nh));
   const int64_t H = (int64_t)nh * d, ld = 3 * H;
@@ -595,9 +595,8 @@ static int attn_bwd_generic_t(int B, int S, int nh, int d, const T* qkv, const T
 
 template <typename T>
 static int attn_bwd_narrow_t(int B, int S, int nh, int d, const T* qkv, const T* o, const T* dO, const float* lse, T* dqkv, const float* rope, hipStream_t st) {
-  const int half = (int)(((int64_t)B * nh * S + 3) / 4);
-  const dim3 grid(2u * (unsigned)half);
-#define TAW_NARROW(DP, V) hipLaunchKernelGGL((attn_bwd_narrow_kernel<T, DP, V>), grid, dim3(256), 0, st, qkv, o, dO, lse, dqkv, B, S, nh, d, rope, half)
+  const dim3 grid((unsigned)(((int64_t)B * nh * S + 3) / 4), 2);
+#define TAW_NARROW(DP, V) hipLaunchKernelGGL((attn_bwd_narrow_kernel<T, DP, V>), grid, dim3(256), 0, st, qkv, o, dO, lse, dqkv, B, S, nh, d, rope)
   if (d % 4 == 0) { if (d <= 8) TAW_NARROW(8, 4); else if (d <= 16) TAW_NARROW(16, 4); else TAW_NARROW(32, 4); }
   else { if (d <= 8) TAW_NARROW(8, 2); else if (d <= 16) TAW_NARROW(16, 2); else TAW_NARROW(32, 2); }
 #undef TAW_NARROW

@@ -234,6 +234,27 @@ def test_attention_generic_scores_that_overflow(taw, d):
             assert np.max(np.abs(got_o[t, h] - p @ v[:t + 1, h] / p.sum())) < 1e-4, (h, t)
 
 
+def test_attention_generic_of_very_many_rows(taw):
+    """2^25 rows (batch x heads x positions): one wavefront each is half of the 2^32 work-items a launch takes along x.  A batch of repeated pairs of
+    sequences equals the pair, bit for bit."""
+    import torch
+    B, S, nh, d = 16384, 64, 32, 2
+    H = nh * d
+    g = torch.Generator(device="cuda").manual_seed(0)
+    qkv, dO = (torch.empty(2, S, n, device="cuda").normal_(generator=g) for n in (3 * H, H))
+
+    def both(qkv, dO):
+        b = qkv.shape[0]
+        o, dqkv = torch.empty_like(dO), torch.empty_like(qkv)
+        lse, scratch = (torch.empty(b * nh * S, dtype=torch.float32, device="cuda") for _ in range(2))
+        taw.taw_op_attn_fwd(I.F32, b, S, nh, d, qkv, o, lse, taw.TAW_IMPL_GENERIC)
+        taw.taw_op_attn_bwd(I.F32, b, S, nh, d, qkv, o, dO, lse, dqkv, scratch, None, taw.TAW_IMPL_GENERIC)
+        return o, dqkv
+
+    for a, b in zip(both(qkv, dO), both(qkv.repeat(B // 2, 1, 1), dO.repeat(B // 2, 1, 1))):
+        assert torch.equal(a.expand(B // 2, *a.shape), b.view(B // 2, *a.shape))
+
+
 @pytest.mark.parametrize("src_dtype", [I.F32, I.BF16])
 @pytest.mark.parametrize("n", [0, 1, 3, 4, 1027, 13490, 1 << 20])      # 13490: whole workgroups, a partly filled one and a scalar tail
 def test_grad_accum(taw, src_dtype, n):
