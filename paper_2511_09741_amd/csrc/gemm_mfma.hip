@@ -4,15 +4,16 @@
 //   NN  C[M,N] = A[M,K] B[K,N]        B is N-contiguous                 (input gradients)
 //   TN  C[M,N] = A[K,M]^T B[K,N]      both operands contiguous along the output dim (weight gradients)
 //
-// One 256-thread workgroup (4 wavefronts, one per SIMD) owns a 256x256 output tile; each
-// wavefront owns 128x128 of it as 4x4 MFMA tiles (256 fp32 accumulators per lane).  K advances in
-// steps of 64 (NT and NN) or 32 (TN) through an LDS ring filled by direct global->LDS loads.  Any K:
-// the last step's loads are clamped into the matrix and its fragments beyond K zeroed in registers.
+// One 256-thread workgroup (4 wavefronts, one per SIMD) owns an output tile: 256x256, each wavefront
+// 128x128 of it as 4x4 MFMA tiles (256 fp32 accumulators per lane), or, where those would leave the
+// chip idle, 128x256, 128x128 or 64x64 (work_out_plan).  K advances in steps of 64 (the 256x256 TN
+// product: 32) through an LDS ring filled by direct global->LDS loads.  Any K: the last step's loads
+// are clamped into the matrix and what lies beyond K is zeroed in LDS once it has landed.
 //
 // LDS layouts.  A K-contiguous operand is stored [row][64] with its 16-byte chunks XOR-swizzled by
 // (row>>1)&7: every MFMA operand (8 consecutive k of one row) is one ds_read_b128 and 16
 // consecutive lanes touch 16 distinct bank groups.  An operand that is contiguous along the output
-// dimension is stored as it comes, [k][256], chunks swizzled by (k&3)<<2, and read with
+// dimension is stored as it comes, [k][columns], chunks swizzled by (k&3)<<2, and read with
 // ds_read_b64_tr_b16, which hands each lane 4 consecutive k of one column: the transposition the
 // MFMA operand layout needs happens in the LDS read, not in a separate pass over HBM.
 //
@@ -32,8 +33,8 @@ namespace {
 constexpr int BM = 256, BN = 256;
 constexpr int kThreads = 256;
 
-// =============================================================================== pipelined kernel
-// Same tile shape and operand layouts, different data movement: K advances in steps of 32 through
+// =============================================================================== 256 x 256 tiles, TN
+// K advances in steps of 32 through
 // a 4-stage ring of LDS tiles (4 x 32 KiB) filled by direct global->LDS loads
 // (global_load_lds_dwordx4: no staging registers, no LDS store instructions).  Each lane picks
 // the global chunk whose swizzled home is the LDS slot its lane number writes, so the swizzle
@@ -46,7 +47,7 @@ constexpr int kThreads = 256;
 // fragment read, 1 direct load}, each closed by a scheduling barrier: one wavefront per SIMD
 // issues in order, so the matrix pipe only stays busy if the LDS reads, the loads and their few
 // scalar instructions sit in the shadow of the MFMAs instead of in front of them.
-// A K that is no multiple of the step: the rows / chunks of the last tile beyond K are loaded from its last
+// A K that is no multiple of the step: the k rows of the last tile beyond K are loaded from its last
 // valid one (clamp_tail, before that tile's loads are issued) and zeroed in LDS once it has landed (zero_tail),
 // so no step is changed.  (A separate kernel staged through registers served these K before: 44 tiles of a
 // 4503-token weight gradient took 212 us in it.)
@@ -90,59 +91,36 @@ __device__ __forceinline__ void zero_lds(unsigned char* p, int from, int to, int
   for (int o = from + 16 * tid; o < to; o += 16 * kThreads) *reinterpret_cast<u32x4_t*>(p + o) = u32x4_t{0u, 0u, 0u, 0u};
 }
 
-// One operand of the tile: where its direct loads come from and where its MFMA fragments sit in LDS.
-//   KC tile [256 rows][32 k] (64-byte rows): load instruction j = 4 i + wave covers rows 16 j .. 16 j + 15;
-//      lane l writes slot (l & 3) of row 16 j + (l >> 2); slot s of row r holds chunk s ^ ((r >> 2) & 3).
-//   NC tile [32 k][256 cols] (512-byte rows): load instruction j covers k rows 2 j, 2 j + 1;
-//      lane l writes position (l & 31) of k row 2 j + (l >> 5); position p of row k holds chunk p ^ ((k & 3) << 2).
-// Rows (KC) / column chunks (NC) outside the matrix are clamped to the last valid one: they feed
-// output rows / columns that the epilogue does not store.
-template <bool KC>
+// One operand of the tile, contiguous along its 256 columns: where its direct loads come from and where its MFMA fragments sit in LDS.
+//   Tile [32 k][256 cols] (512-byte rows): load instruction j = 4 i + wave covers k rows 2 j, 2 j + 1;
+//   lane l writes position (l & 31) of k row 2 j + (l >> 5); position p of row k holds chunk p ^ ((k & 3) << 2).
+// Column chunks outside the matrix are clamped to the last valid one: they feed output rows / columns that the epilogue does not store.
 struct Operand {
   uint64_t base;          // tile origin at the current K position (bytes); wavefront-uniform
   uint64_t kstep;         // bytes per K step
   unsigned goff[4];       // per-lane byte offsets of the 4 loads of a step
-  // LDS byte offsets (inside an operand tile) of this lane's fragment reads.
-  //   KC: rd[ks] for MFMA k-step ks; fragment i is 2048 i bytes further (32 rows)
-  //   NC: rd[i] for fragment i; MFMA k-step ks adds 8192, the second transposing read of a fragment 2048
-  unsigned rd[KC ? 2 : 4];
+  unsigned rd[4];         // LDS byte offset (inside an operand tile) of fragment i; MFMA k-step ks adds 8192, the second transposing read 2048
 
   __device__ __forceinline__ void init(const bf16_t* mat, int64_t ld, int64_t origin, int64_t extent, int w0, int lane, int wave) {
-    if (KC) {
-      base = (uint64_t)(mat + origin * ld);
-      kstep = BK2 * 2;
+    base = (uint64_t)(mat + origin);
+    kstep = (uint64_t)ld * (BK2 * 2);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int64_t r = 16 * (4 * i + wave) + (lane >> 2);
-        if (origin + r >= extent) r = extent - 1 - origin;
-        const int c = (lane & 3) ^ ((lane >> 4) & 3);
-        goff[i] = (unsigned)(r * ld * 2 + c * 16);
-      }
-      const int r = w0 + (lane & 31);
+    for (int i = 0; i < 4; ++i) {
+      const int k = 2 * (4 * i + wave) + (lane >> 5);
+      int64_t col = ((lane & 31) ^ ((k & 3) << 2)) * 8;
+      if (origin + col >= extent) col = extent - 8 - origin;
+      goff[i] = (unsigned)((k * ld + col) * 2);
+    }
+    const int blk = lane >> 4, l16 = lane & 15;
+    const int k = 8 * (blk >> 1) + (l16 >> 2);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) rd[ks] = r * 64 + (((2 * ks + (lane >> 5)) ^ ((r >> 2) & 3)) << 4);
-    } else {
-      base = (uint64_t)(mat + origin);
-      kstep = (uint64_t)ld * (BK2 * 2);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = 2 * (4 * i + wave) + (lane >> 5);
-        int64_t col = ((lane & 31) ^ ((k & 3) << 2)) * 8;
-        if (origin + col >= extent) col = extent - 8 - origin;
-        goff[i] = (unsigned)((k * ld + col) * 2);
-      }
-      const int blk = lane >> 4, l16 = lane & 15;
-      const int k = 8 * (blk >> 1) + (l16 >> 2);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int n = w0 + 32 * i + 16 * (blk & 1) + 4 * (l16 & 3);
-        rd[i] = k * 512 + (((n >> 3) ^ ((k & 3) << 2)) << 4) + (n & 7) * 2;
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int n = w0 + 32 * i + 16 * (blk & 1) + 4 * (l16 & 3);
+      rd[i] = k * 512 + (((n >> 3) ^ ((k & 3) << 2)) << 4) + (n & 7) * 2;
     }
   }
-  // the next loads are those of the last K step, of which only `rem` rows / columns of k exist
+  // the next loads are those of the last K step, of which only `rem` rows of k exist
   __device__ __forceinline__ void clamp_tail(int rem, int64_t ld, int lane, int wave) {
-    static_assert(!KC, "the 32-deep loop runs the TN form only");
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int k = 2 * (4 * i + wave) + (lane >> 5);
@@ -154,17 +132,13 @@ struct Operand {
   // direct load number i (0..3) of the current K step into the operand tile at LDS address lds_op
   __device__ __forceinline__ void dma(int i, unsigned lds_op, int wave) const { lds_dma16(base, goff[i], lds_op + (4 * i + wave) * 1024); }
   __device__ __forceinline__ void advance() { base += kstep; }
-  // fragment i (32 rows / columns starting at w0 + 32 i) of MFMA k-step ks from the operand tile at op
+  // fragment i (32 columns starting at w0 + 32 i) of MFMA k-step ks from the operand tile at op
   __device__ __forceinline__ bf16x8_t frag(const lds_u8_t* op, int i, int ks) const {
-    if (KC) {
-      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(op + rd[ks] + 2048 * i);
-    } else {
-      union { s16x4_t h[2]; bf16x8_t v; } u;
+    union { s16x4_t h[2]; bf16x8_t v; } u;
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
-        u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + 8192 * ks + 2048 * r));
-      return u.v;
-    }
+    for (int r = 0; r < 2; ++r)
+      u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + 8192 * ks + 2048 * r));
+    return u.v;
   }
 };
 
@@ -467,8 +441,8 @@ struct GemmArgs {
   float* part;
 };
 
-template <int MODE, bool C_F32>
-__device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
+template <bool C_F32>
+__device__ __forceinline__ void gemm_tn_body(const GemmArgs& ga, int block) {
   const int64_t M = ga.M, N = ga.N, lda = ga.lda, ldb = ga.ldb, ldr = ga.ldr;
   int64_t K = ga.K, ldc = ga.ldc;
   const bf16_t* __restrict__ A = ga.A;
@@ -477,7 +451,7 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
   const void* __restrict__ Rv = ga.R;
   int accumulate = ga.accumulate;
   const int tiles_m = ga.tiles_m, tiles_n = ga.tiles_n;
-  if (MODE == GEMM_TN && C_F32 && ga.splits > 1) {      // workgroup-uniform: this workgroup's range of the contraction
+  if (C_F32 && ga.splits > 1) {      // workgroup-uniform: this workgroup's range of the contraction
     const int ntl = tiles_m * tiles_n, sp = block / ntl;
     block -= sp * ntl;
     const int64_t k0 = (int64_t)sp * ga.k_chunk;
@@ -488,8 +462,6 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
     ldc = N;
     accumulate = 0;
   }
-  constexpr bool A_KC = (MODE != GEMM_TN);
-  constexpr bool B_KC = (MODE == GEMM_NT);
   extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
   const lds_u8_t* lds = (const lds_u8_t*)lds2;
   const unsigned lds0 = (unsigned)(size_t)lds;
@@ -502,8 +474,7 @@ __device__ __forceinline__ void gemm_dlds_body(const GemmArgs& ga, int block) {
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  Operand<A_KC> oa;
-  Operand<B_KC> ob;
+  Operand oa, ob;
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
@@ -730,8 +701,7 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
     B += MODE == GEMM_NT ? k0 : k0 * ldb;
     K = K - k0 < ga.k_chunk ? K - k0 : ga.k_chunk;
   }
-  constexpr bool A_KC = (MODE != GEMM_TN);
-  constexpr bool B_KC = (MODE == GEMM_NT);
+  static_assert(MODE != GEMM_TN, "A is K-contiguous here");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
   const lds_u8_t* lds = (const lds_u8_t*)lds2;
   const unsigned lds0 = (unsigned)(size_t)lds;
@@ -744,8 +714,8 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  Operand64<A_KC, 256> oa;
-  Operand64<B_KC, 256> ob;
+  Operand64<true, 256> oa;
+  Operand64<MODE == GEMM_NT, 256> ob;
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
@@ -1017,7 +987,7 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
 template <int MODE, bool C_F32, int EPI = kEpiNone>
 __global__ void __launch_bounds__(kThreads, 1) gemm_pipe_kernel(GemmArgs g) {
   if constexpr (MODE != GEMM_TN) gemm_dlds64_body<MODE, C_F32, EPI>(g, (int)blockIdx.x);
-  else gemm_dlds_body<MODE, C_F32>(g, (int)blockIdx.x);
+  else gemm_tn_body<C_F32>(g, (int)blockIdx.x);
 }
 // The layer's backward has such pairs at every linear: the input gradient and the weight gradient
 // read the same incoming gradient and write different outputs.  Neither tile count is a multiple
@@ -1025,7 +995,7 @@ __global__ void __launch_bounds__(kThreads, 1) gemm_pipe_kernel(GemmArgs g) {
 // one grid leaves one.  n1 >= 0: the second's n1 workgroups go first (dual_order).
 __global__ void __launch_bounds__(kThreads, 1) gemm_dual_kernel(GemmArgs g0, GemmArgs g1, int n0, int n1) {
   const int b = (int)blockIdx.x, b0 = n1 < 0 ? b : b - n1;      // this workgroup's index within the first problem, if it is one of its
-  if (b0 >= 0 && b0 < n0) gemm_dlds_body<GEMM_TN, true>(g0, b0);
+  if (b0 >= 0 && b0 < n0) gemm_tn_body<true>(g0, b0);
   else gemm_dlds64_body<GEMM_NN, false>(g1, n1 < 0 ? b - n0 : b);
 }
 template <int MODE, bool C_F32, int TM, int TN, int NST, int EPI = kEpiNone>
