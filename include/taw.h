@@ -99,7 +99,8 @@ int taw_layer_weight_layout(const taw_layer_desc* desc, taw_weight_layout* out);
  * an invalid descriptor.  The workspace holds nothing between calls and may be shared by layers.
  * taw_layer_fwd touches it only with TAW_RECOMPUTE: without that flag, forwards and one backward may
  * share a workspace and overlap in time on different streams.  (With few tokens the cache also has room for
- * partial products of the forward's GEMMs, so that this holds there too.) */
+ * partial products of the forward's GEMMs, so that this holds there too: up to about as much again, never more
+ * than 256 MiB.) */
 size_t taw_layer_ctx_bytes(const taw_layer_desc* desc);
 size_t taw_layer_workspace_bytes(const taw_layer_desc* desc);
 

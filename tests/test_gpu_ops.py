@@ -297,8 +297,8 @@ def test_weight_stage_double_buffer(taw):
 
 
 # ----------------------------------------------------------------------------- MFMA kernels (bf16)
-# K % 64 == 0 runs the 64-deep pipelined kernel (1, 2, 3 and many K steps), K % 32 == 0 the 32-deep one,
-# any other K the register-staged kernel
+# 1, 2, 3 and many steps of K (64 deep; 32 in the TN form's large tile), the last one whole or not.  NT with bf16 results takes the tile its
+# plan names, everything else 256 x 256
 MFMA_GEMM_SHAPES = {
     0: [(256, 256, 64), (8, 8, 8), (300, 520, 136), (257, 263, 72), (1000, 264, 4104), (512, 768, 1024), (1, 3, 8),
         (300, 520, 96), (257, 263, 128), (264, 520, 192), (300, 264, 160), (1000, 264, 4096), (5, 3, 32)],
@@ -319,7 +319,7 @@ def test_gemm_mfma_shapes(taw, mode):
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
 def test_gemm_mfma_epilogues(taw, mode):
-    for shp in ((520, 264, 200) if mode != 2 else (520, 264, 203), (520, 264, 192), (520, 264, 160)):   # one per kernel
+    for shp in ((520, 264, 200) if mode != 2 else (520, 264, 203), (520, 264, 192), (520, 264, 160)):   # a last step of 8 (TN: 11), 64 and 32
         _gemm_case(taw, I.BF16, mode, *shp, taw.TAW_IMPL_MFMA, residual=True)
         _gemm_case(taw, I.BF16, mode, *shp, taw.TAW_IMPL_MFMA, c_f32=True)
         _gemm_case(taw, I.BF16, mode, *shp, taw.TAW_IMPL_MFMA, c_f32=True, accumulate=True)
