@@ -200,10 +200,15 @@ struct EpiArgs {
   int64_t rot_cols;
   int round_first;
 };
-template <bool C_F32, int EPI = kEpiNone>
+//
+// EDGE: the same for a block that reaches over the edge of C (rows and columns of C: `rows`, `cols` from the block's corner on, cols a multiple
+// of the 16-byte chunk): loads clamped into C, stores predicated, a unit's values all formed before its first store so that its reads stay
+// in flight together.  (As a loop of four chunks at a time this cost an edge tile 5 - 6 us, 10 with a residual.  4503 x 3072 x 1024, one round of
+// tiles: 32.6 -> 27.0 us, with a residual 42.3 -> 30.0, with rotation 41.6 -> 30.3; 255 x 256 x 64 in fp32 18.5 -> 11.3.)
+template <bool C_F32, int EPI = kEpiNone, bool EDGE = false>
 __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                                 int wm, int wn, void* __restrict__ Cv, int64_t ldc, int accumulate,
-                                                const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}) {
+                                                const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}, int rows = 128, int cols = 128) {
   constexpr int SLD = 132;
   constexpr int ES = C_F32 ? 4 : 2;                       // bytes per element of C (and R)
   float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
@@ -215,6 +220,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
   const unsigned coff0 = (unsigned)(rr0 * ldc) * ES + ch * 16, roff0 = (unsigned)(rr0 * ldr) * ES + ch * 16;
   const unsigned cstep = (unsigned)(RPP * ldc) * ES, rstep = (unsigned)(RPP * ldr) * ES;
   const float* srow = stg + rr0 * SLD + ch * (16 / ES);
+  const int chc = EDGE && ch * 16 >= cols * ES ? cols * ES / 16 - 1 : ch;       // EDGE: the chunk column this lane loads
   typedef typename std::conditional<C_F32, f32x4_t, bf16x8_t>::type chunk_t;
   // What the result is combined with is fetched one unit ahead: a 32-row slice, or half of one where fp32 rows would not fit the
   // registers.  (Fetched pass by pass, each store behind its own load, every pass waits for memory: the forward of the 1024-wide layer on 65536 tokens took 6 % longer, a 4096-wide step
@@ -231,36 +237,81 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
   auto fetch = [&](Extra& x, int u) {
     const int row = (u / UPS) * 32 + (u % UPS) * (32 / UPS);
     if constexpr (COMBINE) {
+      auto edge_off = [&](int it, int64_t ld) {
+        const int r = row + it * RPP + rr0;
+        return (unsigned)((r < rows ? r : rows - 1) * ld) * ES + chc * 16;
+      };
       if (rw) {
         const char* ri = rw + (int64_t)row * ldr * ES;
 #pragma unroll
-        for (int it = 0; it < UP; ++it) x.r[it] = *reinterpret_cast<const chunk_t*>(ri + roff0 + it * rstep);
+        for (int it = 0; it < UP; ++it) x.r[it] = *reinterpret_cast<const chunk_t*>(EDGE ? rw + edge_off(it, ldr) : ri + roff0 + it * rstep);
       }
       if (accumulate) {
         const char* ci = cw + (int64_t)row * ldc * ES;
 #pragma unroll
-        for (int it = 0; it < UP; ++it) x.c[it] = *reinterpret_cast<const chunk_t*>(ci + coff0 + it * cstep);
+        for (int it = 0; it < UP; ++it) x.c[it] = *reinterpret_cast<const chunk_t*>(EDGE ? cw + edge_off(it, ldc) : ci + coff0 + it * cstep);
       }
     } else if (rotate) {
 #pragma unroll
       for (int it = 0; it < UP; ++it) {
         int pos = pos0 + it * RPP;
-        pos = pos >= ea.S ? pos - ea.S : pos;      // 32 rows never span more than one sequence boundary (S >= 32)
+        if (EDGE && ea.S < 32) pos = (int)((unsigned)pos % (unsigned)ea.S);
+        else pos = pos >= ea.S ? pos - ea.S : pos;      // 32 rows never span more than one sequence boundary (S >= 32)
         x.cs[2 * it] = *reinterpret_cast<const f32x4_t*>(tab + (int64_t)pos * 128);
         x.cs[2 * it + 1] = *reinterpret_cast<const f32x4_t*>(tab + (int64_t)pos * 128 + 4);
       }
       pos0 += 32;
-      pos0 = pos0 >= ea.S ? pos0 - ea.S : pos0;
+      if (EDGE && ea.S < 32) pos0 = (int)((unsigned)pos0 % (unsigned)ea.S);
+      else pos0 = pos0 >= ea.S ? pos0 - ea.S : pos0;
+    }
+  };
+  // pass `it` of a slice: the staged chunk with everything added to it or done to it
+  auto value = [&](int it, const Extra& x, int p) -> chunk_t {
+    const float* sp = srow + it * RPP * SLD;
+    if constexpr (C_F32) {
+      f32x4_t v = *reinterpret_cast<const f32x4_t*>(sp);
+      if (rw) v += x.r[p];
+      if (accumulate) v += x.c[p];
+      return v;
+    } else {
+      const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(sp), v1 = *reinterpret_cast<const f32x4_t*>(sp + 4);
+      float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+      if constexpr (!COMBINE) {
+        if (rotate) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float c = x.cs[2 * p + (e >> 1)][2 * (e & 1)], sn = x.cs[2 * p + (e >> 1)][2 * (e & 1) + 1];
+            const float a = ea.round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = ea.round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1];
+            v[2 * e] = a * c - b2 * sn;
+            v[2 * e + 1] = a * sn + b2 * c;
+          }
+        }
+      } else {
+        if (rw) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] += (float)x.r[p][e];
+        }
+        if (accumulate) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] += (float)x.c[p][e];
+        }
+      }
+      bf16x8_t o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
+      return o;
     }
   };
   fetch(extra[0], 0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if (EDGE && 32 * i >= rows) break;
 #pragma unroll
     for (int j = 0; j < 4; ++j) stage_rows<SLD>(acc[i][j], stg + 32 * j, lane);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
     char* ci = cw + (int64_t)(32 * i) * ldc * ES;
+    chunk_t out[EDGE ? UP : 1];
 #pragma unroll
     for (int it = 0; it < NPASS; ++it) {
       const int u = i * UPS + it / UP, p = it % UP;
@@ -269,40 +320,17 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
         if (u + 1 < 4 * UPS) fetch(extra[(u + 1) & 1], u + 1);
         __builtin_amdgcn_sched_barrier(0);
       }
-      const Extra& x = extra[u & 1];
-      const float* sp = srow + it * RPP * SLD;
-      if constexpr (C_F32) {
-        f32x4_t v = *reinterpret_cast<const f32x4_t*>(sp);
-        if (rw) v += x.r[p];
-        if (accumulate) v += x.c[p];
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(ci + coff0 + it * cstep));
-      } else {
-        const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(sp), v1 = *reinterpret_cast<const f32x4_t*>(sp + 4);
-        float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-        if constexpr (!COMBINE) {
-          if (rotate) {
+      if constexpr (EDGE) {
+        out[p] = value(it, extra[u & 1], p);
+        if (p + 1 == UP) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float c = x.cs[2 * p + (e >> 1)][2 * (e & 1)], sn = x.cs[2 * p + (e >> 1)][2 * (e & 1) + 1];
-              const float a = ea.round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = ea.round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1];
-              v[2 * e] = a * c - b2 * sn;
-              v[2 * e + 1] = a * sn + b2 * c;
-            }
-          }
-        } else {
-          if (rw) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += (float)x.r[p][e];
-          }
-          if (accumulate) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += (float)x.c[p][e];
+          for (int q = 0; q < UP; ++q) {
+            const int pass = it + 1 - UP + q;
+            if (ch == chc && 32 * i + pass * RPP + rr0 < rows) *reinterpret_cast<chunk_t*>(ci + coff0 + pass * cstep) = out[q];
           }
         }
-        bf16x8_t o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
-        __builtin_nontemporal_store(o, reinterpret_cast<bf16x8_t*>(ci + coff0 + it * cstep));
+      } else {
+        __builtin_nontemporal_store(value(it, extra[u & 1], p), reinterpret_cast<chunk_t*>(ci + coff0 + it * cstep));
       }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -332,7 +360,7 @@ struct RotPairs {
 // ---- epilogue of a wavefront's (32 TM) x (32 TN) block at (mw, nw), any part of it possibly outside C: 32-row slices -> fp32
 // staging rows in LDS (one region per wavefront, in the ring, which every wavefront has finished reading) -> 16-byte accesses that
 // cover whole row segments of C, four at a time so that what they read (residual, accumulated C) is fetched together; element by
-// element where C's or R's rows are not 16-byte aligned.  Loops over the staged slice stay loops: unrolled, this path of the 256 x 256
+// element, several at a time, where C's or R's rows are not 16-byte aligned (4503 x 3067 x 1024 with a residual, one at a time: 118 us; eight: 57).  Loops over the staged slice stay loops: unrolled, this path of the 256 x 256
 // tile would be most of a kernel's code.
 template <bool C_F32, int TM, int TN, int EPI = kEpiNone>
 __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
@@ -340,6 +368,7 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
                                               const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
   typedef typename std::conditional<C_F32, float, bf16_t>::type T;
   constexpr int SLD = 32 * TN + 4, V = C_F32 ? 4 : 8, CPR = 32 * TN / V, U = CPR / 2 < 4 ? CPR / 2 : 4;      // CPR: chunks of V columns per row
+  constexpr int UE = TM * TN == 16 ? 8 : 1;      // single elements in flight per lane: the registers that a tile's main loop leaves
   float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
   T* C = static_cast<T*>(Cv);
   const T* R = static_cast<const T*>(Rv);
@@ -393,14 +422,46 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
         }
       }
     } else {
+      if constexpr (UE == 1) {
 #pragma unroll 1
-      for (int e = lane; e < 32 * 32 * TN; e += 64) {
-        const int64_t row = row0 + e / (32 * TN), col = nw + e % (32 * TN);
-        if (row < M && col < N) {
-          float x = stg[e / (32 * TN) * SLD + e % (32 * TN)];
-          if (R) x += (float)R[row * ldr + col];
-          if (accumulate) x += (float)C[row * ldc + col];
-          C[row * ldc + col] = (T)x;
+        for (int e = lane; e < 32 * 32 * TN; e += 64) {
+          const int64_t row = row0 + e / (32 * TN), col = nw + e % (32 * TN);
+          if (row < M && col < N) {
+            float x = stg[e / (32 * TN) * SLD + e % (32 * TN)];
+            if (R) x += (float)R[row * ldr + col];
+            if (accumulate) x += (float)C[row * ldc + col];
+            C[row * ldc + col] = (T)x;
+          }
+        }
+      } else {
+#pragma unroll 1
+        for (int e0 = lane; e0 < 32 * 32 * TN; e0 += 64 * UE) {
+          float x[UE];
+          T r[UE], c[UE];
+          int64_t row[UE], col[UE];
+#pragma unroll
+          for (int u = 0; u < UE; ++u) {
+            const int e = e0 + 64 * u;
+            row[u] = row0 + e / (32 * TN);
+            col[u] = nw + e % (32 * TN);
+            x[u] = stg[e / (32 * TN) * SLD + e % (32 * TN)];
+          }
+          // loads clamped into C, so that they need no branch and are in flight together
+          auto at = [&](const T* p, int u, int64_t ld) { return p[(row[u] < M ? row[u] : M - 1) * ld + (col[u] < N ? col[u] : N - 1)]; };
+          if (R) {
+#pragma unroll
+            for (int u = 0; u < UE; ++u) r[u] = at(R, u, ldr);
+          }
+          if (accumulate) {
+#pragma unroll
+            for (int u = 0; u < UE; ++u) c[u] = at(C, u, ldc);
+          }
+#pragma unroll
+          for (int u = 0; u < UE; ++u) {
+            if (R) x[u] += (float)r[u];
+            if (accumulate) x[u] += (float)c[u];
+            if (row[u] < M && col[u] < N) C[row[u] * ldc + col[u]] = (T)x[u];
+          }
         }
       }
     }
@@ -415,9 +476,18 @@ __device__ __forceinline__ void store_tile(const f32x16_t (&acc)[4][4], unsigned
                                            int wm, int wn, int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
                                            const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
   constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
-  const bool full = m0 + BM <= M && n0 + BN <= N && (ldc & V) == 0 && (!Rv || (ldr & V) == 0) && (EPI == kEpiNone || ea.S >= 32);    // workgroup-uniform
-  if (full) store_tile_full<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea);
-  else store_checked<C_F32, 4, 4, EPI>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, Cv, ldc, accumulate, Rv, ldr, ea);
+  const bool aligned = (ldc & V) == 0 && (!Rv || (ldr & V) == 0);      // workgroup-uniform, as everything here
+  const bool full = m0 + BM <= M && n0 + BN <= N && aligned && (EPI == kEpiNone || ea.S >= 32);
+  if (full) {
+    store_tile_full<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea);
+  } else if (EPI != kEpiNone || (aligned && (N & V) == 0)) {
+    const int64_t rows = M - m0 - wm, cols = N - n0 - wn;
+    if (rows > 0 && cols > 0)
+      store_tile_full<C_F32, EPI, true>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea, rows < 128 ? (int)rows : 128,
+                                        cols < 128 ? (int)cols : 128);
+  } else {
+    store_checked<C_F32, 4, 4>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, Cv, ldc, accumulate, Rv, ldr, ea);
+  }
 }
 
 // one GEMM as the pipelined kernels take it

@@ -337,10 +337,10 @@ def test_layer_on_generic_products(taw, dtype, B, S, nh, d, I_):
     U.check_layer(taw, I.LayerConfig("generic", dtype, B, S, nh * d, nh, d, I_, sigma_w=(nh * d) ** -0.5), seed=d, gamma_jitter=0.1)
 
 
-@pytest.mark.parametrize("B,S", [(52, 100), (160, 33), (41, 128), (64, 48)])
+@pytest.mark.parametrize("B,S", [(52, 100), (160, 33), (41, 128), (260, 20), (64, 48)])
 def test_short_sequences_across_large_tiles(taw, B, S):
     """Many short sequences in one call: 256 x 256 tiles whose 32-row slices start anywhere in a sequence and cross into the next (the rotation's
-    positions wrap inside a tile), against one sequence at a time on the small tiles.  The two differ in the order of fp32 sums only, so by a bf16
+    positions wrap inside a tile, at 20 tokens inside a slice more than once), against one sequence at a time on the small tiles.  The two differ in the order of fp32 sums only, so by a bf16
     rounding here and there: h's and y's, 2^-8 of an element each, and through attention and MLP at most about as much again.  In the last case the
     batch (a multiple of 256 tokens) rotates unrounded sums and one sequence rounds q and k first: scores (standard deviation 2.6) move by up to
     2^-8 of themselves, the attention's half of h by up to 4 %."""

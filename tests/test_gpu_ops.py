@@ -404,6 +404,26 @@ def test_optimizer_step(taw, dtype, n):
         assert np.array_equal(I.to_storage(master.cpu().numpy(), dtype), chunk.view(torch.int16).cpu().numpy().view(np.uint16))
 
 
+@pytest.mark.parametrize("mode,f32,M,N", [(0, 1, 300, 264), (0, 1, 257, 263), (0, 1, 129, 130), (1, 0, 300, 264), (1, 0, 385, 520), (1, 1, 513, 8), (2, 0, 264, 136),
+                                          (2, 1, 8, 392)])
+@pytest.mark.parametrize("pad", [0, 8, 3])
+def test_gemm_mfma_edges_of_large_tiles(taw, mode, f32, M, N, pad):
+    """256 x 256 tiles that reach over the edge of C by rows, by columns, by whole wavefronts' blocks; results and residuals inside larger matrices with
+    aligned and unaligned rows, nothing outside them touched.  Bounds as in test_linear_tile_shapes."""
+    import torch
+    K, dt = 136, torch.float32 if f32 else torch.bfloat16
+    A, B = (I.device_normal(s, seed=i, std=1.0) for i, s in enumerate(((K, M) if mode == 2 else (M, K), (N, K) if mode == 0 else (K, N))))
+    ref = (A.double().t() if mode == 2 else A.double()) @ (B.double().t() if mode == 0 else B.double())
+    for residual, acc in ((0, 0), (1, 0), (0, 1), (1, 1)):
+        C = torch.full((M + 2, N + pad), 7.0, dtype=dt, device="cuda")
+        R = I.device_normal((M, N + pad), seed=5, std=1.0, dtype=dt) if residual else None
+        taw.taw_op_gemm(I.BF16, mode, M, N, K, A, A.shape[1], B, B.shape[1], C, N + pad, I.F32 if f32 else I.BF16, acc, R, N + pad, taw.TAW_IMPL_MFMA)
+        want = ref + 7.0 * acc + (R[:, :N].double() if residual else 0.0)
+        err = float((C[:M, :N].double() - want).abs().max() / want.abs().max())
+        assert err < (2e-6 if f32 else 2.0 ** -8), (residual, acc, err)
+        assert bool((C[M:] == 7).all()) and bool((C[:, N:] == 7).all())
+
+
 # every tile shape (rows, columns, stages of its ring) of the product and of its backward, each with remainders in rows, columns and contraction:
 # less than one step, a whole one, one more
 S64, S128D, S128, S192, S256 = (64, 64, 4), (128, 128, 2), (128, 128, 4), (128, 256, 3), (256, 256, 2)
