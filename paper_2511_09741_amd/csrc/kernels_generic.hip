@@ -11,11 +11,13 @@ namespace taw {
 
 // =============================================================================== GEMM
 // C[m,n] (=|+=) sum_k A(m,k) B(k,n) (+ R[m,n]) on the fp32 matrix instruction (16x16x4, IEEE fp32 products and sums), operands
-// straight from memory into registers: of 16 consecutive k, lane group g = lane >> 4 loads k = 4g .. 4g + 3 (one 16-byte
-// load where the operand is contiguous along k) and matrix instruction i multiplies the four k = 4g + i, the same for both operands.
+// straight from memory into registers: of 16 consecutive k, lane group g = lane >> 4 loads k = 4g .. 4g + 3 (one load of four
+// values, at any alignment, where the operand is contiguous along k) and matrix instruction i multiplies the four k = 4g + i, the same for both operands.
 //   SPLIT: a workgroup owns 16 x 16 outputs, its four wavefronts a quarter of K each, summed through LDS in wavefront order: every
 //     load of a short contraction is in flight at once, and a 128 x 64 result has 32 workgroups.
-//   otherwise: a workgroup owns 64 x 64, each wavefront 32 x 32 over all of K: more products per load, for results that fill the chip.
+//   otherwise: a workgroup owns 64 x 64, each wavefront 32 x 32 over all of K: more products per load, for results that fill the chip; an
+//     operand contiguous along the result is loaded two columns at a time (1024 x 4096 x 1024 TN in bf16: 200 -> 133 us; one 2-byte load per value
+//     was slower there than the staged tiles below).
 // (32 x 32 tiles staged through LDS 16 k at a time, one exposed load latency per 16 k, took 6 - 30 us for the products of a
 // 64-wide layer with 128 tokens; these take 2 - 5.)
 namespace gen {
@@ -40,23 +42,41 @@ struct Args {
 };
 enum { kPlain = 0, kRope = 1, kSwigluFwd = 2, kSwigluBwd = 3 };
 
-template <typename T> __device__ __forceinline__ f32x4_t load4(const T* p) {
-  if constexpr (sizeof(T) == 4) {
-    return *reinterpret_cast<const f32x4_t*>(p);
-  } else {
-    const bf16x4_t v = *reinterpret_cast<const bf16x4_t*>(p);
-    return f32x4_t{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-  }
+// N consecutive values from an address aligned to one of them only: as wide a load as the device takes there
+template <typename T, int N> struct Run { T v[N]; };
+template <int N, typename T> __device__ __forceinline__ Run<T, N> load_run(const T* p) {
+  Run<T, N> r;
+  __builtin_memcpy(&r, p, sizeof(r));
+  return r;
 }
 
 // the four values k .. k + 3 of one row (KC) or column of an operand; those at or beyond K are 0 and not read
-template <typename T, bool KC, bool VEC>
+template <typename T, bool KC>
 __device__ __forceinline__ f32x4_t operand4(const T* mat, int64_t ld, int64_t idx, int64_t k, int64_t K) {
-  if (KC && VEC && k + 4 <= K) return load4(mat + idx * ld + k);
   f32x4_t v;
+  if (KC && k + 4 <= K) {
+    const Run<T, 4> r = load_run<4>(mat + idx * ld + k);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = k + i < K ? (float)(KC ? mat[idx * ld + k + i] : mat[(k + i) * ld + idx]) : 0.f;
+    for (int i = 0; i < 4; ++i) v[i] = (float)r.v[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = k + i < K ? (float)(KC ? mat[idx * ld + k + i] : mat[(k + i) * ld + idx]) : 0.f;
+  }
   return v;
+}
+// the same of the two columns idx, idx + 1 of an operand contiguous along them, of which the last two, `last` and last + 1, are read where idx
+// lies beyond them (idx = last + 1, the last column alone, then comes first)
+template <typename T>
+__device__ __forceinline__ void operand4x2(f32x4_t& v0, f32x4_t& v1, const T* mat, int64_t ld, int64_t idx, int64_t last, int64_t k, int64_t K) {
+  const bool beyond = idx > last;
+  const T* p = mat + (beyond ? last : idx);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    Run<T, 2> r{{(T)0.f, (T)0.f}};
+    if (k + i < K) r = load_run<2>(p + (k + i) * ld);
+    v0[i] = (float)(beyond ? r.v[1] : r.v[0]);
+    v1[i] = (float)r.v[1];
+  }
 }
 
 // one output (and, kSwigluFwd, its partner of the up half) leaves; lanes l, l ^ 1 hold columns 2j, 2j + 1 of one row
@@ -65,7 +85,8 @@ __device__ __forceinline__ void finish(const Args& g, int64_t row, int64_t col, 
   if constexpr (EPI == kRope) {
     const float w = __shfl_xor(v, 1, 64);
     if (col < g.rot_cols && row < g.M) {
-      const float* tb = g.table + ((row % g.S) * (g.d / 2) + (col % g.d) / 2) * 2;
+      // 32-bit remainders (token counts and widths fit): 64-bit ones, once per output of a 64 x 64 tile, were 33 KB of code
+      const float* tb = g.table + (int64_t)((unsigned)row % (unsigned)g.S) * g.d + ((unsigned)col % (unsigned)g.d) / 2 * 2;
       v = col & 1 ? w * tb[1] + v * tb[0] : v * tb[0] - w * tb[1];
     }
   }
@@ -95,7 +116,7 @@ __device__ __forceinline__ void finish(const Args& g, int64_t row, int64_t col, 
   *c = (TC)v;
 }
 
-template <typename TI, typename TC, int MODE, bool VEC, bool SPLIT, int EPI>
+template <typename TI, typename TC, int MODE, bool SPLIT, int EPI>
 __device__ __forceinline__ void body(const Args& g, int block, float* red) {
   constexpr bool A_KC = MODE != GEMM_TN, B_KC = MODE == GEMM_NT;
   constexpr int R = SPLIT ? 1 : 2, NB = EPI == kSwigluFwd ? 2 : 1;        // R x R matrix tiles per wavefront; NB: B panels
@@ -112,9 +133,13 @@ __device__ __forceinline__ void body(const Args& g, int block, float* red) {
   }
   const TI* A = static_cast<const TI*>(g.A);
   const TI* B = static_cast<const TI*>(g.B);
+  // Rows and columns of the result this lane loads the operands of: those outside it read its last one.  Of the 32 rows (columns) of a
+  // wavefront, matrix tile i has 16 i .. 16 i + 15 where they are loaded along k, and every second one where the operand is contiguous along
+  // them: then one load of two adjacent values serves both tiles.
+  constexpr bool A_PAIR = !SPLIT && !A_KC, B_PAIR = !SPLIT && !B_KC;
   int64_t ar[R], bc[R];
 #pragma unroll
-  for (int i = 0; i < R; ++i) {          // rows and columns outside the result read its last one
+  for (int i = 0; i < R; ++i) {
     ar[i] = m0 + 16 * i + l16 < g.M ? m0 + 16 * i + l16 : g.M - 1;
     bc[i] = n0 + 16 * i + l16 < g.N ? n0 + 16 * i + l16 : g.N - 1;
   }
@@ -130,11 +155,15 @@ __device__ __forceinline__ void body(const Args& g, int block, float* red) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t kk = k + 16 * u + g4;
+      if constexpr (A_PAIR) operand4x2<TI>(a[u][0], a[u][1], A, g.lda, m0 + 2 * l16, g.M - 2, kk, k1);
+      if constexpr (B_PAIR) operand4x2<TI>(b[u][0][0], b[u][0][1], B, g.ldb, n0 + 2 * l16, g.N - 2, kk, k1);
 #pragma unroll
       for (int i = 0; i < R; ++i) {
-        a[u][i] = operand4<TI, A_KC, VEC>(A, g.lda, ar[i], kk, k1);
+        if constexpr (!A_PAIR) a[u][i] = operand4<TI, A_KC>(A, g.lda, ar[i], kk, k1);
+        if constexpr (!B_PAIR) {
 #pragma unroll
-        for (int q = 0; q < NB; ++q) b[u][q][i] = operand4<TI, B_KC, VEC>(B, g.ldb, bc[i] + q * g.N, kk, k1);
+          for (int q = 0; q < NB; ++q) b[u][q][i] = operand4<TI, B_KC>(B, g.ldb, bc[i] + q * g.N, kk, k1);
+        }
       }
     }
 #pragma unroll
@@ -167,34 +196,39 @@ __device__ __forceinline__ void body(const Args& g, int block, float* red) {
 #pragma unroll
       for (int j = 0; j < R; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) finish<TC, EPI>(g, m0 + 16 * i + g4 + r, n0 + 16 * j + l16, acc[0][i][j][r], acc[NB - 1][i][j][r]);
+        for (int r = 0; r < 4; ++r)
+          finish<TC, EPI>(g, m0 + (A_PAIR ? 2 * (g4 + r) + i : 16 * i + g4 + r), n0 + (B_PAIR ? 2 * l16 + j : 16 * j + l16), acc[0][i][j][r],
+                          acc[NB - 1][i][j][r]);
   }
 }
 
-template <typename TI, typename TC, int MODE, bool VEC, bool SPLIT, int EPI>
+template <typename TI, typename TC, int MODE, bool SPLIT, int EPI>
 __global__ void __launch_bounds__(256) gemm_kernel(Args g) {
   __shared__ float red[SPLIT ? (EPI == kSwigluFwd ? 2 : 1) * 1024 : 1];
-  body<TI, TC, MODE, VEC, SPLIT, EPI>(g, (int)blockIdx.x, red);
+  body<TI, TC, MODE, SPLIT, EPI>(g, (int)blockIdx.x, red);
 }
 // weight gradient (TN, fp32) and input gradient (NN) of a linear in one grid
-template <typename T, bool VEC, int EPI>
+template <typename T, int EPI>
 __global__ void __launch_bounds__(256) gemm_dual_kernel(Args g0, Args g1) {
   __shared__ float red[1024];
-  if ((int)blockIdx.x < g0.blocks) body<T, float, GEMM_TN, VEC, true, kPlain>(g0, (int)blockIdx.x, red);
-  else body<T, T, GEMM_NN, VEC, true, EPI>(g1, (int)blockIdx.x - g0.blocks, red);
+  if ((int)blockIdx.x < g0.blocks) body<T, float, GEMM_TN, true, kPlain>(g0, (int)blockIdx.x, red);
+  else body<T, T, GEMM_NN, true, EPI>(g1, (int)blockIdx.x - g0.blocks, red);
 }
 
-constexpr int64_t kSplitTiles = 4096;      // results of more 16 x 16 tiles than these fill the chip with 64 x 64 ones
+constexpr int64_t kSplitTiles = 4096;      // the paired backward splits up to this many 16 x 16 tiles of either product
 
-inline bool take_split(const Args& g) { return ((g.M + 15) / 16) * ((g.N + 15) / 16) <= kSplitTiles; }
+// Splitting pays while its workgroups, one per 16 x 16 tile, are few: us split / 64 x 64 (fp32, NT): 400 x 750 x 250 (1175 tiles) 6.5 / 10.7, 1024 x 512 x 512
+// (2048) 17 / 18, 1024 x 1024 x 256 (4096) 18 / 12; with a short contraction a workgroup is mostly overhead: 4096 x 64 x 64 (1024) 4.6 / 5.6,
+// 4096 x 176 x 64 (2816) 8.4 / 6.0.  A tile of 64 x 64 loads pairs of rows or columns, of which a single one has none.
+inline bool take_split(const Args& g) {
+  const int64_t tiles = ((g.M + 15) / 16) * ((g.N + 15) / 16);
+  return g.M < 2 || g.N < 2 || tiles <= (g.K <= 128 ? 1536 : 2048);
+}
 inline void tile_up(Args& g, bool split) {
   const int t = split ? 16 : 64;
   g.tiles_n = (int)((g.N + t - 1) / t);
   g.blocks = (int)((g.M + t - 1) / t) * g.tiles_n;
 }
-// 16-byte loads along k: only operands that are contiguous along k use them
-inline bool vec_ok(int mode, const Args& g) { return mode == GEMM_TN || (g.lda % 4 == 0 && (mode == GEMM_NN || g.ldb % 4 == 0)); }
-
 inline Args make(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, int accumulate,
                  const void* R, int64_t ldr) {
   return Args{M, N, K, A, lda, B, ldb, C, ldc, accumulate, R, ldr, 0, 0, nullptr, 1, 2, 0, nullptr, nullptr};
@@ -202,12 +236,10 @@ inline Args make(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, co
 
 template <typename TI, typename TC, int MODE, int EPI>
 int launch(Args g, hipStream_t st) {
-  const bool vec = vec_ok(MODE, g), split = take_split(g);
+  const bool split = take_split(g);
   tile_up(g, split);
-#define TAW_GEN(VEC, SPLIT) hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, VEC, SPLIT, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g)
-  if (split) { if (vec) TAW_GEN(true, true); else TAW_GEN(false, true); }
-  else { if (vec) TAW_GEN(true, false); else TAW_GEN(false, false); }
-#undef TAW_GEN
+  if (split) hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, true, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g);
+  else hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, false, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g);
   return (int)hipGetLastError();
 }
 template <typename TI, typename TC>
@@ -253,11 +285,9 @@ int launch_gemm_generic_linear_bwd(int dtype, int64_t T, int64_t N, int64_t K, c
   g1.gu = gu;
   gen::tile_up(g0, true);
   gen::tile_up(g1, true);
-  const bool vec = gen::vec_ok(GEMM_NN, g1);
   const dim3 grid((unsigned)(g0.blocks + g1.blocks));
-#define TAW_GEN(T_, VEC, EPI) hipLaunchKernelGGL((gen::gemm_dual_kernel<T_, VEC, gen::EPI>), grid, dim3(256), 0, st, g0, g1)
-#define TAW_GEN_T(T_) do { if (gu) { if (vec) TAW_GEN(T_, true, kSwigluBwd); else TAW_GEN(T_, false, kSwigluBwd); } \
-                           else { if (vec) TAW_GEN(T_, true, kPlain); else TAW_GEN(T_, false, kPlain); } } while (0)
+#define TAW_GEN(T_, EPI) hipLaunchKernelGGL((gen::gemm_dual_kernel<T_, gen::EPI>), grid, dim3(256), 0, st, g0, g1)
+#define TAW_GEN_T(T_) do { if (gu) TAW_GEN(T_, kSwigluBwd); else TAW_GEN(T_, kPlain); } while (0)
   if (dtype == DT_F32) TAW_GEN_T(float); else TAW_GEN_T(bf16_t);
 #undef TAW_GEN_T
 #undef TAW_GEN

@@ -495,7 +495,13 @@ def test_linear_backward_cut_contractions(taw, T, N, K, tile, cut_dx, cut_g):
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16])
 @pytest.mark.parametrize("mode", [0, 1, 2])
 def test_gemm_generic_large_tiles(taw, dtype, mode):
-    """More than 4096 tiles of 16 x 16: the generic product takes 64 x 64 ones, ragged at every edge and in K."""
+    """More than 2048 tiles of 16 x 16: the generic product takes 64 x 64 ones, ragged at every edge and in K, the result's last column or row alone
+    or one of a pair (operands contiguous along it are loaded in pairs)."""
+    _gemm_case(taw, dtype, mode, 1025, 1089, 131, taw.TAW_IMPL_GENERIC)
+    _gemm_case(taw, dtype, mode, 1026, 1090, 13, taw.TAW_IMPL_GENERIC)
+    _gemm_case(taw, dtype, mode, 1, 40000, 17, taw.TAW_IMPL_GENERIC)          # a single row or column has no pair
+    _gemm_case(taw, dtype, mode, 40000, 1, 17, taw.TAW_IMPL_GENERIC)
+    _gemm_case(taw, dtype, mode, 40001, 2, 5, taw.TAW_IMPL_GENERIC)
     _gemm_case(taw, dtype, mode, 1030, 1051, 70, taw.TAW_IMPL_GENERIC, residual=True)
     _gemm_case(taw, dtype, mode, 1030, 1052, 33, taw.TAW_IMPL_GENERIC, c_f32=True, accumulate=True)
 
