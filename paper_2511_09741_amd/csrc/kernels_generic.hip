@@ -296,23 +296,27 @@ int launch_gemm_generic_linear_bwd(int dtype, int64_t T, int64_t N, int64_t K, c
 
 // =============================================================================== attention, narrow heads
 // head_dim <= 32: one wavefront per (batch, head, row), a lane per row of the other side (keys of a query, queries of a key), which
-// it keeps in registers: DP = head_dim rounded up to 8, 16 or 32 values, loaded in pairs or fours (head_dim is even), so a wavefront has 64 rows
+// it keeps in registers: DP = head_dim rounded up to 8, 16 or 32 values, loaded in fours at any alignment (head_dim is even), so a wavefront has 64 rows
 // in flight and no serial chain over the sequence.  Each lane sums over its own rows; the DP sums then meet by halves: at step b a
-// lane keeps the half its bit b names and receives the other lane's, until lane l holds element l % DP.
-// V: values per load, 4 where head_dim is a multiple of 4, else 2
-template <int V, typename T, int DP>
+// lane keeps the half its bit b names and receives the other lane's, until lane l holds element l % DP.  (A loop over those steps is not
+// unrolled, and every access to the row becomes a search through its registers: 33 and 100 KB of code for the two kernels at 32
+// values instead of 7 and 14, most of it fetched once per wavefront: 16 sequences of 64 tokens, 8 heads of 24, forward / backward
+// 64 / 195 us, with them 15 / 45.)
+// FULL: d == DP, no value to leave out and no branch per load (backward at 3 sequences of 1000 tokens, 8 heads of 8 in bf16: 264 us with, 227 without)
+template <bool FULL, typename T, int DP>
 __device__ __forceinline__ void load_row(float (&v)[DP], const T* p, int d) {
-  typedef T vec __attribute__((ext_vector_type(V)));
 #pragma unroll
-  for (int i = 0; i < DP; i += V) {
-    if (i < d) {
-      const vec x = *reinterpret_cast<const vec*>(p + i);
-#pragma unroll
-      for (int e = 0; e < V; ++e) v[i + e] = (float)x[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < V; ++e) v[i + e] = 0.f;
+  for (int i = 0; i < DP; i += 4) {
+    gen::Run<T, 4> r{{(T)0.f, (T)0.f, (T)0.f, (T)0.f}};
+    if (FULL || i + 4 <= d) {
+      r = gen::load_run<4>(p + i);
+    } else if (i < d) {
+      const gen::Run<T, 2> h = gen::load_run<2>(p + i);
+      r.v[0] = h.v[0];
+      r.v[1] = h.v[1];
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[i + e] = (float)r.v[e];
   }
 }
 template <int DP> __device__ __forceinline__ float dot_row(const float (&a)[DP], const float (&b)[DP]) {
@@ -321,40 +325,54 @@ template <int DP> __device__ __forceinline__ float dot_row(const float (&a)[DP],
   for (int i = 0; i < DP; ++i) s += a[i] * b[i];
   return s;
 }
-template <int DP> __device__ __forceinline__ float sum_lanes(float (&v)[DP], int lane) {
+template <int N, int DP> __device__ __forceinline__ void sum_halves(float (&v)[DP], int lane) {
+  if constexpr (N > 0) {
+    const bool up = (lane & N) != 0;
 #pragma unroll
-  for (int n = DP / 2; n > 0; n /= 2) {
-    const bool up = (lane & n) != 0;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-      const float mine = up ? v[n + i] : v[i], other = up ? v[i] : v[n + i];
-      v[i] = mine + __shfl_xor(other, n, 64);
+    for (int i = 0; i < N; ++i) {
+      const float mine = up ? v[N + i] : v[i], other = up ? v[i] : v[N + i];
+      v[i] = mine + __shfl_xor(other, N, 64);
     }
+    sum_halves<N / 2>(v, lane);
   }
+}
+template <int DP> __device__ __forceinline__ float sum_lanes(float (&v)[DP], int lane) {
+  sum_halves<DP / 2>(v, lane);
 #pragma unroll
   for (int n = DP; n < 64; n *= 2) v[0] += __shfl_xor(v[0], n, 64);
   return v[0];
 }
 
-template <typename T, int DP, int V>
-__global__ void __launch_bounds__(256) attn_fwd_narrow_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int B, int S,
+// the wavefront's (batch, head, row); a launch has fewer than 2^26 of them (2^32 work-items), so 32-bit divisions do
+struct NarrowRow {
+  int b, h, t;
+};
+__device__ __forceinline__ NarrowRow narrow_row(int S, int nh) {
+  const unsigned gid = blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = gid / (unsigned)S, b = pair / (unsigned)nh;
+  return NarrowRow{(int)b, (int)(pair - b * (unsigned)nh), (int)(gid - pair * (unsigned)S)};
+}
+
+// No more wavefronts on a SIMD than the rows they stream (a cache line each, read in pieces) leave room for in the L1 cache: 3 sequences of
+// 1000 tokens, 8 heads of 10 in fp32, forward 184 us without the limit, 99 with; 1000 tokens, 4 heads of 8, backward 62 and 50.
+template <typename T, int DP, bool FULL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, DP == 32 ? 3 : 4))) attn_fwd_narrow_kernel(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int B, int S,
                                                               int nh, int d) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t gid = (int64_t)blockIdx.x * 4 + wave;  // (b, h, t)
-  if (gid >= (int64_t)B * nh * S) return;
-  const int t = (int)(gid % S), h = (int)((gid / S) % nh), b = (int)(gid / ((int64_t)S * nh));
+  const int lane = threadIdx.x & 63;
+  const NarrowRow row = narrow_row(S, nh);
+  if (row.b >= B) return;
+  const int t = row.t, h = row.h, b = row.b;
   const int64_t H = (int64_t)nh * d, ld = 3 * H;
   const T* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * d;
   const float scale = 1.0f / sqrtf((float)d);
   float q[DP], acc[DP], m = -INFINITY, z = 0.f;
-  load_row<V>(q, qbase + (int64_t)t * ld, d);
+  load_row<FULL>(q, qbase + (int64_t)t * ld, d);
 #pragma unroll
   for (int i = 0; i < DP; ++i) acc[i] = 0.f;
   for (int u = lane; u <= t; u += 64) {
     float k[DP], v[DP];
-    const T* row = qbase + (int64_t)u * ld;
-    load_row<V>(k, row + H, d);
-    load_row<V>(v, row + 2 * H, d);
+    const T* kv = qbase + (int64_t)u * ld;
+    load_row<FULL>(k, kv + H, d);
+    load_row<FULL>(v, kv + 2 * H, d);
     // a key whose score overflowed to -inf has weight 0, also where the lane has seen no other yet (expf(-inf + inf) is NaN)
     const float s = dot_row(q, k) * scale, mn = fmaxf(m, s);
     const float keep = m == -INFINITY ? 0.f : expf(m - mn), p = s == -INFINITY ? 0.f : expf(s - mn);
@@ -374,15 +392,15 @@ __global__ void __launch_bounds__(256) attn_fwd_narrow_kernel(const T* __restric
 
 // blockIdx.y = 0: dq of a query; 1: dk, dv of a key (along y, since a launch takes fewer than 2^32 work-items along x).  D[t] = dO[t] . o[t] is formed where it is needed.  The gradients of
 // rotated q and k are rotated back before they leave where a table is given.
-template <typename T, int DP, int V>
-__global__ void __launch_bounds__(256) attn_bwd_narrow_kernel(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dO,
+template <typename T, int DP, bool FULL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 5))) attn_bwd_narrow_kernel(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dO,
                                                               const float* __restrict__ lse, T* __restrict__ dqkv, int B, int S, int nh, int d,
                                                               const float* __restrict__ rope) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const bool keys = blockIdx.y != 0;
-  const int64_t gid = (int64_t)blockIdx.x * 4 + wave;
-  if (gid >= (int64_t)B * nh * S) return;
-  const int t = (int)(gid % S), h = (int)((gid / S) % nh), b = (int)(gid / ((int64_t)S * nh));
+  const NarrowRow row = narrow_row(S, nh);
+  if (row.b >= B) return;
+  const int t = row.t, h = row.h, b = row.b;
   const int64_t H = (int64_t)nh * d, ld = 3 * H;
   const T* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * d;
   const int64_t ooff = (int64_t)b * S * H + (int64_t)h * d;
@@ -402,28 +420,28 @@ __global__ void __launch_bounds__(256) attn_bwd_narrow_kernel(const T* __restric
 #pragma unroll
   for (int i = 0; i < DP; ++i) { acc[i] = 0.f; acc2[i] = 0.f; }
   if (!keys) {        // x = q[t], y = dO[t]
-    load_row<V>(x, qbase + (int64_t)t * ld, d);
-    load_row<V>(y, dO + ooff + (int64_t)t * H, d);
-    load_row<V>(acc2, o + ooff + (int64_t)t * H, d);
+    load_row<FULL>(x, qbase + (int64_t)t * ld, d);
+    load_row<FULL>(y, dO + ooff + (int64_t)t * H, d);
+    load_row<FULL>(acc2, o + ooff + (int64_t)t * H, d);
     const float Dt = dot_row(y, acc2), Lt = L[t];
     for (int u = lane; u <= t; u += 64) {
       float k[DP], v[DP];
-      const T* row = qbase + (int64_t)u * ld;
-      load_row<V>(k, row + H, d);
-      load_row<V>(v, row + 2 * H, d);
+      const T* kv = qbase + (int64_t)u * ld;
+      load_row<FULL>(k, kv + H, d);
+      load_row<FULL>(v, kv + 2 * H, d);
       const float ds = expf(dot_row(x, k) * scale - Lt) * (dot_row(y, v) - Dt);
 #pragma unroll
       for (int i = 0; i < DP; ++i) acc[i] += ds * k[i];
     }
     leave(sum_lanes(acc, lane) * scale, 0, true);
   } else {            // x = k[t], y = v[t]
-    load_row<V>(x, qbase + (int64_t)t * ld + H, d);
-    load_row<V>(y, qbase + (int64_t)t * ld + 2 * H, d);
+    load_row<FULL>(x, qbase + (int64_t)t * ld + H, d);
+    load_row<FULL>(y, qbase + (int64_t)t * ld + 2 * H, d);
     for (int u = t + lane; u < S; u += 64) {
       float q[DP], g[DP], ov[DP];
-      load_row<V>(q, qbase + (int64_t)u * ld, d);
-      load_row<V>(g, dO + ooff + (int64_t)u * H, d);
-      load_row<V>(ov, o + ooff + (int64_t)u * H, d);
+      load_row<FULL>(q, qbase + (int64_t)u * ld, d);
+      load_row<FULL>(g, dO + ooff + (int64_t)u * H, d);
+      load_row<FULL>(ov, o + ooff + (int64_t)u * H, d);
       const float p = expf(dot_row(q, x) * scale - L[u]), ds = p * (dot_row(g, y) - dot_row(g, ov));
 #pragma unroll
       for (int i = 0; i < DP; ++i) {
@@ -590,9 +608,9 @@ static int attn_fwd_generic_t(int B, int S, int nh, int d, const T* qkv, T* o, f
 template <typename T>
 static int attn_fwd_narrow_t(int B, int S, int nh, int d, const T* qkv, T* o, float* lse, hipStream_t st) {
   const dim3 grid((unsigned)(((int64_t)B * nh * S + 3) / 4));
-#define TAW_NARROW(DP, V) hipLaunchKernelGGL((attn_fwd_narrow_kernel<T, DP, V>), grid, dim3(256), 0, st, qkv, o, lse, B, S, nh, d)
-  if (d % 4 == 0) { if (d <= 8) TAW_NARROW(8, 4); else if (d <= 16) TAW_NARROW(16, 4); else TAW_NARROW(32, 4); }
-  else { if (d <= 8) TAW_NARROW(8, 2); else if (d <= 16) TAW_NARROW(16, 2); else TAW_NARROW(32, 2); }
+#define TAW_NARROW(DP, FULL) hipLaunchKernelGGL((attn_fwd_narrow_kernel<T, DP, FULL>), grid, dim3(256), 0, st, qkv, o, lse, B, S, nh, d)
+  if (d == 8) TAW_NARROW(8, true); else if (d == 16) TAW_NARROW(16, true); else if (d == 32) TAW_NARROW(32, true);
+  else if (d < 8) TAW_NARROW(8, false); else if (d < 16) TAW_NARROW(16, false); else TAW_NARROW(32, false);
 #undef TAW_NARROW
   return (int)hipGetLastError();
 }
@@ -626,9 +644,9 @@ static int attn_bwd_generic_t(int B, int S, int nh, int d, const T* qkv, const T
 template <typename T>
 static int attn_bwd_narrow_t(int B, int S, int nh, int d, const T* qkv, const T* o, const T* dO, const float* lse, T* dqkv, const float* rope, hipStream_t st) {
   const dim3 grid((unsigned)(((int64_t)B * nh * S + 3) / 4), 2);
-#define TAW_NARROW(DP, V) hipLaunchKernelGGL((attn_bwd_narrow_kernel<T, DP, V>), grid, dim3(256), 0, st, qkv, o, dO, lse, dqkv, B, S, nh, d, rope)
-  if (d % 4 == 0) { if (d <= 8) TAW_NARROW(8, 4); else if (d <= 16) TAW_NARROW(16, 4); else TAW_NARROW(32, 4); }
-  else { if (d <= 8) TAW_NARROW(8, 2); else if (d <= 16) TAW_NARROW(16, 2); else TAW_NARROW(32, 2); }
+#define TAW_NARROW(DP, FULL) hipLaunchKernelGGL((attn_bwd_narrow_kernel<T, DP, FULL>), grid, dim3(256), 0, st, qkv, o, dO, lse, dqkv, B, S, nh, d, rope)
+  if (d == 8) TAW_NARROW(8, true); else if (d == 16) TAW_NARROW(16, true); else if (d == 32) TAW_NARROW(32, true);
+  else if (d < 8) TAW_NARROW(8, false); else if (d < 16) TAW_NARROW(16, false); else TAW_NARROW(32, false);
 #undef TAW_NARROW
   return (int)hipGetLastError();
 }

@@ -197,7 +197,7 @@ def _attn_case(taw, dtype, B, S, nh, d, impl, seed=0, scale=1.0, bwd_impl=None):
 
 
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16])
-@pytest.mark.parametrize("B,S,nh,d", [(1, 128, 4, 16), (2, 67, 3, 8), (1, 1, 2, 16), (1, 130, 1, 128)])
+@pytest.mark.parametrize("B,S,nh,d", [(1, 128, 4, 16), (2, 67, 3, 8), (1, 1, 2, 16), (1, 130, 1, 128), (1, 40, 2, 2), (2, 65, 3, 18), (1, 70, 5, 30), (1, 200, 1, 32)])
 def test_attention_generic(taw, dtype, B, S, nh, d):
     _attn_case(taw, dtype, B, S, nh, d, taw.TAW_IMPL_GENERIC, seed=S)
 
