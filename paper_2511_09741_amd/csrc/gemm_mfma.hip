@@ -205,7 +205,10 @@ struct EpiArgs {
 // of the 16-byte chunk): loads clamped into C, stores predicated, a unit's values all formed before its first store so that its reads stay
 // in flight together.  (As a loop of four chunks at a time this cost an edge tile 5 - 6 us, 10 with a residual.  4503 x 3072 x 1024, one round of
 // tiles: 32.6 -> 27.0 us, with a residual 42.3 -> 30.0, with rotation 41.6 -> 30.3; 255 x 256 x 64 in fp32 18.5 -> 11.3.)
-template <bool C_F32, int EPI = kEpiNone, bool EDGE = false>
+//
+// EXTRAS: the result is combined with something (or rotated).  Without, the passes need no fetch and no line drawn between them; drawn all the same
+// they cost a fp32 tile 1 us (256 x 256 x 64 TN in fp32: 8.6 us; 7.0).
+template <bool C_F32, int EPI = kEpiNone, bool EDGE = false, bool EXTRAS = true>
 __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                                 int wm, int wn, void* __restrict__ Cv, int64_t ldc, int accumulate,
                                                 const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}, int rows = 128, int cols = 128) {
@@ -270,8 +273,8 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
     const float* sp = srow + it * RPP * SLD;
     if constexpr (C_F32) {
       f32x4_t v = *reinterpret_cast<const f32x4_t*>(sp);
-      if (rw) v += x.r[p];
-      if (accumulate) v += x.c[p];
+      if (EXTRAS && rw) v += x.r[p];
+      if (EXTRAS && accumulate) v += x.c[p];
       return v;
     } else {
       const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(sp), v1 = *reinterpret_cast<const f32x4_t*>(sp + 4);
@@ -302,7 +305,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
       return o;
     }
   };
-  fetch(extra[0], 0);
+  if constexpr (EXTRAS) fetch(extra[0], 0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     if (EDGE && 32 * i >= rows) break;
@@ -315,7 +318,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
 #pragma unroll
     for (int it = 0; it < NPASS; ++it) {
       const int u = i * UPS + it / UP, p = it % UP;
-      if (p == 0) {
+      if (EXTRAS && p == 0) {
         __builtin_amdgcn_sched_barrier(0);
         if (u + 1 < 4 * UPS) fetch(extra[(u + 1) & 1], u + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -478,7 +481,9 @@ __device__ __forceinline__ void store_tile(const f32x16_t (&acc)[4][4], unsigned
   constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
   const bool aligned = (ldc & V) == 0 && (!Rv || (ldr & V) == 0);      // workgroup-uniform, as everything here
   const bool full = m0 + BM <= M && n0 + BN <= N && aligned && (EPI == kEpiNone || ea.S >= 32);
-  if (full) {
+  if (C_F32 && full && !Rv && !accumulate) {
+    store_tile_full<C_F32, EPI, false, !C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, 0, nullptr, 0, ea);
+  } else if (full) {
     store_tile_full<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea);
   } else if (EPI != kEpiNone || (aligned && (N & V) == 0)) {
     const int64_t rows = M - m0 - wm, cols = N - n0 - wn;
