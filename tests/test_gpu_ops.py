@@ -64,7 +64,7 @@ def test_gemm_generic_epilogues(taw, dtype):
 
 
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16])
-@pytest.mark.parametrize("T,H", [(5, 64), (130, 4096), (33, 100), (7, 1000), (2, 8192 if True else 0)])
+@pytest.mark.parametrize("T,H", [(5, 64), (130, 4096), (33, 100), (7, 1000), (2, 8192 if True else 0), (64, 1022), (65, 1022)])
 def test_rmsnorm_fwd_bwd(taw, dtype, T, H):
     import torch
     if dtype == I.F32 and H > 4096:
@@ -499,6 +499,8 @@ def test_gemm_generic_large_tiles(taw, dtype, mode):
     or one of a pair (operands contiguous along it are loaded in pairs)."""
     _gemm_case(taw, dtype, mode, 1025, 1089, 131, taw.TAW_IMPL_GENERIC)
     _gemm_case(taw, dtype, mode, 1026, 1090, 13, taw.TAW_IMPL_GENERIC)
+    _gemm_case(taw, dtype, mode, 650, 641, 100, taw.TAW_IMPL_GENERIC)          # 1681 tiles: 64 x 64 up to K = 128, split beyond
+    _gemm_case(taw, dtype, mode, 650, 641, 129, taw.TAW_IMPL_GENERIC)
     _gemm_case(taw, dtype, mode, 1, 40000, 17, taw.TAW_IMPL_GENERIC)          # a single row or column has no pair
     _gemm_case(taw, dtype, mode, 40000, 1, 17, taw.TAW_IMPL_GENERIC)
     _gemm_case(taw, dtype, mode, 40001, 2, 5, taw.TAW_IMPL_GENERIC)
