@@ -116,8 +116,11 @@ __device__ __forceinline__ void finish(const Args& g, int64_t row, int64_t col, 
   *c = (TC)v;
 }
 
-template <typename TI, typename TC, int MODE, bool SPLIT, int EPI>
+// FORM: kSplit, or the number of chains of a 64 x 64 tile
+constexpr int kSplit = 0;
+template <typename TI, typename TC, int MODE, int FORM, int EPI>
 __device__ __forceinline__ void body(const Args& g, int block, float* red) {
+  constexpr bool SPLIT = FORM == kSplit;
   constexpr bool A_KC = MODE != GEMM_TN, B_KC = MODE == GEMM_NT;
   constexpr int R = SPLIT ? 1 : 2, NB = EPI == kSwigluFwd ? 2 : 1;        // R x R matrix tiles per wavefront; NB: B panels
   constexpr int U = SPLIT ? 4 : 2;                                        // groups of 16 k whose loads are in flight together
@@ -143,13 +146,18 @@ __device__ __forceinline__ void body(const Args& g, int block, float* red) {
     ar[i] = m0 + 16 * i + l16 < g.M ? m0 + 16 * i + l16 : g.M - 1;
     bc[i] = n0 + 16 * i + l16 < g.N ? n0 + 16 * i + l16 : g.N - 1;
   }
-  f32x4_t acc[NB][R][R];
+  // NA accumulators per output, matrix instruction e of a group adding to accumulator e % NA
+  constexpr int NA = SPLIT ? 1 : FORM;
+  static_assert(NA == 1 || NA == 4, "one accumulator, or one per matrix instruction of a group");
+  f32x4_t acc[NA][NB][R][R];
 #pragma unroll
-  for (int q = 0; q < NB; ++q)
+  for (int n = 0; n < NA; ++n)
 #pragma unroll
-    for (int i = 0; i < R; ++i)
+    for (int q = 0; q < NB; ++q)
 #pragma unroll
-      for (int j = 0; j < R; ++j) acc[q][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc[n][q][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int64_t k = k0; k < k1; k += 16 * U) {
     f32x4_t a[U][R], b[U][NB][R];
 #pragma unroll
@@ -175,14 +183,14 @@ __device__ __forceinline__ void body(const Args& g, int block, float* red) {
 #pragma unroll
           for (int i = 0; i < R; ++i)
 #pragma unroll
-            for (int j = 0; j < R; ++j) acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][q][j][e], acc[q][i][j], 0, 0, 0);
+            for (int j = 0; j < R; ++j) acc[e % NA][q][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][q][j][e], acc[e % NA][q][i][j], 0, 0, 0);
   }
   // accumulator register r of lane l: row 4 (l >> 4) + r, column l & 15
   if constexpr (SPLIT) {
 #pragma unroll
     for (int q = 0; q < NB; ++q)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[((q * 4 + wave) * 16 + g4 + r) * 16 + l16] = acc[q][0][0][r];
+      for (int r = 0; r < 4; ++r) red[((q * 4 + wave) * 16 + g4 + r) * 16 + l16] = acc[0][q][0][0][r];
     __syncthreads();
     float v[2] = {0.f, 0.f};
 #pragma unroll
@@ -196,34 +204,41 @@ __device__ __forceinline__ void body(const Args& g, int block, float* red) {
 #pragma unroll
       for (int j = 0; j < R; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          finish<TC, EPI>(g, m0 + (A_PAIR ? 2 * (g4 + r) + i : 16 * i + g4 + r), n0 + (B_PAIR ? 2 * l16 + j : 16 * j + l16), acc[0][i][j][r],
-                          acc[NB - 1][i][j][r]);
+        for (int r = 0; r < 4; ++r) {
+          auto sum = [&](int q) {
+            float v = acc[0][q][i][j][r];
+            if constexpr (NA == 4) v = (v + acc[1][q][i][j][r]) + (acc[2][q][i][j][r] + acc[3][q][i][j][r]);
+            return v;
+          };
+          finish<TC, EPI>(g, m0 + (A_PAIR ? 2 * (g4 + r) + i : 16 * i + g4 + r), n0 + (B_PAIR ? 2 * l16 + j : 16 * j + l16), sum(0), sum(NB - 1));
+        }
   }
 }
 
-template <typename TI, typename TC, int MODE, bool SPLIT, int EPI>
+template <typename TI, typename TC, int MODE, int FORM, int EPI>
 __global__ void __launch_bounds__(256) gemm_kernel(Args g) {
-  __shared__ float red[SPLIT ? (EPI == kSwigluFwd ? 2 : 1) * 1024 : 1];
-  body<TI, TC, MODE, SPLIT, EPI>(g, (int)blockIdx.x, red);
+  __shared__ float red[FORM == kSplit ? (EPI == kSwigluFwd ? 2 : 1) * 1024 : 1];
+  body<TI, TC, MODE, FORM, EPI>(g, (int)blockIdx.x, red);
 }
 // weight gradient (TN, fp32) and input gradient (NN) of a linear in one grid
 template <typename T, int EPI>
 __global__ void __launch_bounds__(256) gemm_dual_kernel(Args g0, Args g1) {
   __shared__ float red[1024];
-  if ((int)blockIdx.x < g0.blocks) body<T, float, GEMM_TN, true, kPlain>(g0, (int)blockIdx.x, red);
-  else body<T, T, GEMM_NN, true, EPI>(g1, (int)blockIdx.x - g0.blocks, red);
+  if ((int)blockIdx.x < g0.blocks) body<T, float, GEMM_TN, kSplit, kPlain>(g0, (int)blockIdx.x, red);
+  else body<T, T, GEMM_NN, kSplit, EPI>(g1, (int)blockIdx.x - g0.blocks, red);
 }
 
-constexpr int64_t kSplitTiles = 4096;      // the paired backward splits up to this many 16 x 16 tiles of either product
+constexpr int64_t kSplitTiles = 4096;      // the paired backward splits up to this many 16 x 16 tiles of either product, and results of no more sum in four chains
 
 // Splitting pays while its workgroups, one per 16 x 16 tile, are few: us split / 64 x 64 (fp32, NT): 400 x 750 x 250 (1175 tiles) 6.5 / 10.7, 1024 x 512 x 512
 // (2048) 17 / 18, 1024 x 1024 x 256 (4096) 18 / 12; with a short contraction a workgroup is mostly overhead: 4096 x 64 x 64 (1024) 4.6 / 5.6,
-// 4096 x 176 x 64 (2816) 8.4 / 6.0.  A tile of 64 x 64 loads pairs of rows or columns, of which a single one has none.
-inline bool take_split(const Args& g) {
-  const int64_t tiles = ((g.M + 15) / 16) * ((g.N + 15) / 16);
-  return g.M < 2 || g.N < 2 || tiles <= (g.K <= 128 ? 1536 : 2048);
-}
+// 4096 x 176 x 64 (2816) 8.4 / 6.2.  A tile of 64 x 64 loads pairs of rows or columns, of which a single one has none.
+inline int64_t small_tiles(const Args& g) { return ((g.M + 15) / 16) * ((g.N + 15) / 16); }
+inline bool take_split(const Args& g) { return g.M < 2 || g.N < 2 || small_tiles(g) <= (g.K <= 128 ? 1536 : 2048); }
+// The 64 x 64 form adds up all of K.  Up to kSplitTiles it does so in four chains, which round off as little as the four quarters of the split form
+// (layer of 3 x 400 tokens, 256 wide, I = 768: weight gradients 4.0e-7 from fp64 in both, 4.9e-7 with one chain); grids beyond are bound by how many
+// wavefronts a SIMD holds, and four chains' registers cost them up to half (4096 x 1024 x 1024 NT in bf16 154 us with one chain, 169 with four).
+inline bool take_chains(const Args& g) { return small_tiles(g) <= kSplitTiles; }
 inline void tile_up(Args& g, bool split) {
   const int t = split ? 16 : 64;
   g.tiles_n = (int)((g.N + t - 1) / t);
@@ -238,8 +253,9 @@ template <typename TI, typename TC, int MODE, int EPI>
 int launch(Args g, hipStream_t st) {
   const bool split = take_split(g);
   tile_up(g, split);
-  if (split) hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, true, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g);
-  else hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, false, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g);
+#define TAW_GEN(FORM) hipLaunchKernelGGL((gemm_kernel<TI, TC, MODE, FORM, EPI>), dim3((unsigned)g.blocks), dim3(256), 0, st, g)
+  if (split) TAW_GEN(kSplit); else if (take_chains(g)) TAW_GEN(4); else TAW_GEN(1);
+#undef TAW_GEN
   return (int)hipGetLastError();
 }
 template <typename TI, typename TC>
