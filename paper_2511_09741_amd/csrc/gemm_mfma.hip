@@ -1314,10 +1314,14 @@ static GemmPlan work_out_plan(int np, const GemmProblem (&pr)[2], size_t max_flo
 struct PlanMemory {
   static constexpr int kRows = 32, kWays = 16;
   struct Entry {
-    int64_t key[9];      // np = 0: never written
+    int64_t key[9];
     GemmPlan plan;
-  } entry[kRows][kWays];
-  unsigned next[kRows];
+  };
+  struct Row {
+    uint64_t hash[kWays];      // 0: never written; looked through before any key is
+    unsigned next;
+    Entry entry[kWays];
+  } row[kRows];
   int64_t planned;
 };
 static thread_local PlanMemory g_plans;
@@ -1327,14 +1331,16 @@ static GemmPlan remembered_plan(int np, const GemmProblem (&pr)[2], size_t max_f
   const int64_t key[9] = {np, pr[0].M, pr[0].N, pr[0].K, pr[1].M, pr[1].N, pr[1].K, pr[0].out_bytes, (int64_t)max_floats};
   uint64_t h = 0;
   for (int64_t k : key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
-  const int row = (int)(h >> 59);
-  for (const PlanMemory::Entry& e : mem.entry[row])
-    if (memcmp(e.key, key, sizeof(key)) == 0) return e.plan;
-  PlanMemory::Entry& e = mem.entry[row][mem.next[row]++ % PlanMemory::kWays];
-  memcpy(e.key, key, sizeof(key));
-  e.plan = work_out_plan(np, pr, max_floats);
+  h |= 1;
+  PlanMemory::Row& row = mem.row[h >> 59];
+  for (int i = 0; i < PlanMemory::kWays; ++i)
+    if (row.hash[i] == h && memcmp(row.entry[i].key, key, sizeof(key)) == 0) return row.entry[i].plan;
+  const int i = (int)(row.next++ % PlanMemory::kWays);
+  row.hash[i] = h;
+  memcpy(row.entry[i].key, key, sizeof(key));
+  row.entry[i].plan = work_out_plan(np, pr, max_floats);
   ++mem.planned;
-  return e.plan;
+  return row.entry[i].plan;
 }
 
 // The plan without a limit wherever its partial products fit (it is then also the cheapest within the limit): sizing the scratch and
