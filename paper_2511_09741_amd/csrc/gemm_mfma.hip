@@ -1,19 +1,25 @@
-// bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
+// bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16), fp32 accumulation.
 //
 //   NT  C[M,N] = A[M,K] B[N,K]^T      both operands K-contiguous        (forward linears)
 //   NN  C[M,N] = A[M,K] B[K,N]        B is N-contiguous                 (input gradients)
 //   TN  C[M,N] = A[K,M]^T B[K,N]      both operands contiguous along the output dim (weight gradients)
 //
 // One 256-thread workgroup (4 wavefronts, one per SIMD) owns an output tile: 256x256, each wavefront
-// 128x128 of it as 4x4 MFMA tiles (256 fp32 accumulators per lane), or, where those would leave the
-// chip idle, 128x256, 128x128 or 64x64 (work_out_plan).  K advances in steps of 64 (the 256x256 TN
-// product: 32) through an LDS ring filled by direct global->LDS loads.  Any K: the last step's loads
-// are clamped into the matrix and what lies beyond K is zeroed in LDS once it has landed.
+// 128x128 of it as 8x8 MFMA tiles (256 fp32 accumulators per lane), or, where those would leave the
+// chip idle, 128x256, 128x128 or 64x64 (work_out_plan).  K advances in steps of 64 through an LDS
+// ring filled by direct global->LDS loads.  Any K: the last step's loads are clamped into the matrix
+// and what lies beyond K is zeroed in LDS once it has landed.
+//
+// Why 16x16x32 and not 32x32x16: a full chip of these products is bound by power, and per product the
+// smaller tile draws less of it.  A loop of MFMAs on random bf16 operands, everything in registers:
+// 2010 TFLOP/s at 2.03 GHz against 1790 at 1.77 (8x8 tiles and 4x4 of the larger, one wavefront per
+// SIMD).  8192 x 8192 x 8192 NT: 1430 -> 1600 TFLOP/s, 32768 x 4096 x 11008 NT 1406 -> 1560, its weight
+// gradient 1368 -> 1470 (boxes differ by 5 %, both sides on one).
 //
 // LDS layouts.  A K-contiguous operand is stored [row][64] with its 16-byte chunks XOR-swizzled by
 // (row>>1)&7: every MFMA operand (8 consecutive k of one row) is one ds_read_b128 and 16
 // consecutive lanes touch 16 distinct bank groups.  An operand that is contiguous along the output
-// dimension is stored as it comes, [k][columns], chunks swizzled by (k&3)<<2, and read with
+// dimension is stored as it comes, [k][columns], chunks swizzled by bits 0, 1 and 3 of k, and read with
 // ds_read_b64_tr_b16, which hands each lane 4 consecutive k of one column: the transposition the
 // MFMA operand layout needs happens in the LDS read, not in a separate pass over HBM.
 //
@@ -22,6 +28,7 @@
 // sharing them in the memory-side cache.
 #include <string.h>
 #include <type_traits>
+#include <utility>
 
 #include "dev_common.h"
 #include "taw_internal.h"
@@ -33,31 +40,7 @@ namespace {
 constexpr int BM = 256, BN = 256;
 constexpr int kThreads = 256;
 
-// =============================================================================== 256 x 256 tiles, TN
-// K advances in steps of 32 through
-// a 4-stage ring of LDS tiles (4 x 32 KiB) filled by direct global->LDS loads
-// (global_load_lds_dwordx4: no staging registers, no LDS store instructions).  Each lane picks
-// the global chunk whose swizzled home is the LDS slot its lane number writes, so the swizzle
-// costs nothing.  Per K step a wavefront issues its 8 loads for the tile three steps ahead, waits
-// (vmcnt) until the tile two steps ahead has landed, and meets the other wavefronts at one raw
-// s_barrier.  The first operand fragments of the next tile are read before that barrier (the tile
-// became visible at the previous one), so no LDS latency is exposed after it.
-//
-// The instruction stream of a step is laid out by hand as 16 groups of {2 MFMA, 1 operand
-// fragment read, 1 direct load}, each closed by a scheduling barrier: one wavefront per SIMD
-// issues in order, so the matrix pipe only stays busy if the LDS reads, the loads and their few
-// scalar instructions sit in the shadow of the MFMAs instead of in front of them.
-// A K that is no multiple of the step: the k rows of the last tile beyond K are loaded from its last
-// valid one (clamp_tail, before that tile's loads are issued) and zeroed in LDS once it has landed (zero_tail),
-// so no step is changed.  (A separate kernel staged through registers served these K before: 44 tiles of a
-// 4503-token weight gradient took 212 us in it.)
 namespace v2 {
-
-constexpr int BK2 = 32;
-constexpr int kStages = 4;
-constexpr int kOpBytes = 256 * BK2 * 2;          // one operand tile: 16 KiB
-constexpr int kStageBytes = 2 * kOpBytes;        // 32 KiB
-constexpr size_t kLds2 = (size_t)kStages * kStageBytes;   // 128 KiB
 
 typedef __attribute__((address_space(3))) unsigned char lds_u8_t;
 
@@ -78,6 +61,11 @@ __device__ __forceinline__ void lds_dma16(uint64_t base, unsigned off, unsigned 
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
 }
 
+// the same to lds_addr + OFF, one scalar instruction fewer than adding it first
+template <int OFF> __device__ __forceinline__ void lds_dma16_at(uint64_t base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr), "n"(OFF) : "scc");
+}
+
 // workgroup barrier that also tells the compiler LDS contents changed (the DMA writes are not
 // visible to it): no LDS access may be moved across
 __device__ __forceinline__ void stage_barrier() {
@@ -86,71 +74,23 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// f(0), f(1), ... f(N - 1), each with its number as a compile-time constant
+template <class F, int... E> __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, E...>) { (f(std::integral_constant<int, E>{}), ...); }
+template <int N, class F> __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
 // zeroes [from, to) bytes of LDS at p, in 16-byte pieces, all threads of the workgroup together
 __device__ __forceinline__ void zero_lds(unsigned char* p, int from, int to, int tid) {
   for (int o = from + 16 * tid; o < to; o += 16 * kThreads) *reinterpret_cast<u32x4_t*>(p + o) = u32x4_t{0u, 0u, 0u, 0u};
 }
 
-// One operand of the tile, contiguous along its 256 columns: where its direct loads come from and where its MFMA fragments sit in LDS.
-//   Tile [32 k][256 cols] (512-byte rows): load instruction j = 4 i + wave covers k rows 2 j, 2 j + 1;
-//   lane l writes position (l & 31) of k row 2 j + (l >> 5); position p of row k holds chunk p ^ ((k & 3) << 2).
-// Column chunks outside the matrix are clamped to the last valid one: they feed output rows / columns that the epilogue does not store.
-struct Operand {
-  uint64_t base;          // tile origin at the current K position (bytes); wavefront-uniform
-  uint64_t kstep;         // bytes per K step
-  unsigned goff[4];       // per-lane byte offsets of the 4 loads of a step
-  unsigned rd[4];         // LDS byte offset (inside an operand tile) of fragment i; MFMA k-step ks adds 8192, the second transposing read 2048
-
-  __device__ __forceinline__ void init(const bf16_t* mat, int64_t ld, int64_t origin, int64_t extent, int w0, int lane, int wave) {
-    base = (uint64_t)(mat + origin);
-    kstep = (uint64_t)ld * (BK2 * 2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 2 * (4 * i + wave) + (lane >> 5);
-      int64_t col = ((lane & 31) ^ ((k & 3) << 2)) * 8;
-      if (origin + col >= extent) col = extent - 8 - origin;
-      goff[i] = (unsigned)((k * ld + col) * 2);
-    }
-    const int blk = lane >> 4, l16 = lane & 15;
-    const int k = 8 * (blk >> 1) + (l16 >> 2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int n = w0 + 32 * i + 16 * (blk & 1) + 4 * (l16 & 3);
-      rd[i] = k * 512 + (((n >> 3) ^ ((k & 3) << 2)) << 4) + (n & 7) * 2;
-    }
-  }
-  // the next loads are those of the last K step, of which only `rem` rows of k exist
-  __device__ __forceinline__ void clamp_tail(int rem, int64_t ld, int lane, int wave) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 2 * (4 * i + wave) + (lane >> 5);
-      if (k >= rem) goff[i] -= (unsigned)((k - (rem - 1)) * ld * 2);
-    }
-  }
-  // zeroes the k rows of the operand tile at op that are not among the first `rem`
-  static __device__ __forceinline__ void zero_tail(unsigned char* op, int rem, int tid) { zero_lds(op, rem * 512, kOpBytes, tid); }
-  // direct load number i (0..3) of the current K step into the operand tile at LDS address lds_op
-  __device__ __forceinline__ void dma(int i, unsigned lds_op, int wave) const { lds_dma16(base, goff[i], lds_op + (4 * i + wave) * 1024); }
-  __device__ __forceinline__ void advance() { base += kstep; }
-  // fragment i (32 columns starting at w0 + 32 i) of MFMA k-step ks from the operand tile at op
-  __device__ __forceinline__ bf16x8_t frag(const lds_u8_t* op, int i, int ks) const {
-    union { s16x4_t h[2]; bf16x8_t v; } u;
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-      u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + 8192 * ks + 2048 * r));
-    return u.v;
-  }
-};
-
 // Zeroes the accumulators here (in the shadow of the first loads) and hides from the compiler that they are zero: known zeros are
 // kept in a second set of registers for the loop that may not run, and every accumulator is copied after it (0.4 us per tile).
-__device__ __forceinline__ void zero_acc(f32x16_t (&acc)[4][4]) {
+__device__ __forceinline__ void zero_acc(f32x4_t (&acc)[8][8]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < 8; ++j) {
+      acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       asm volatile("" : "+a"(acc[i][j]));
     }
 }
@@ -162,24 +102,17 @@ __device__ __forceinline__ bool opaque_zero(int x) {
   return x == 0;
 }
 
-// order in which a half step multiplies its 4 x 4 fragment pairs, two per group, and the fragment
-// each group reads for the following half step (0..3 = A fragment, 4..7 = B fragment): every
-// fragment is read at least five groups before the first MFMA that needs it
-__device__ constexpr int kMfmaI[16] = {0, 0, 1, 1, 0, 1, 2, 2, 2, 0, 1, 2, 3, 3, 3, 3};
-__device__ constexpr int kMfmaJ[16] = {0, 1, 0, 1, 2, 2, 0, 1, 2, 3, 3, 3, 0, 1, 2, 3};
-__device__ constexpr int kReadOrder[8] = {0, 4, 5, 1, 6, 2, 7, 3};
-
-// ---- accumulator block -> staging rows.  The MFMAs multiply (B fragment) x (A fragment)^T, so a 32 x 32 block of
-// the result sits transposed in the accumulator registers: lane l holds ROW l & 31 of the block and, in registers
-// 4 g .. 4 g + 3, the four consecutive COLUMNS 8 g + 4 (l >> 5) + 0..3.  Four consecutive floats of a row are one
-// 16-byte LDS write: a block goes to the fp32 staging rows ([32][SLD], SLD * 4 a multiple of 16) in 4 writes per lane
-// instead of the 16 single-float writes the untransposed layout (a lane = a column) needs.
-template <int SLD>
-__device__ __forceinline__ void stage_rows(const f32x16_t& blk, float* stg_blk, int lane) {
-  float* row = stg_blk + (lane & 31) * SLD + 4 * (lane >> 5);
+// ---- accumulator blocks -> staging rows.  The MFMAs multiply (B fragment) x (A fragment)^T, so a 16 x 16 block of
+// the result sits transposed in the accumulator registers: lane l holds ROW l & 15 of the block and, in its four
+// registers, the consecutive COLUMNS 4 (l >> 4) + 0..3.  Four consecutive floats of a row are one 16-byte LDS write
+// ([32][SLD] staging rows, SLD * 4 a multiple of 16 and, mod 256, 16: the 16 rows of a write fall into 16 bank groups).
+template <int SLD, int NB>
+__device__ __forceinline__ void stage_rows(const f32x4_t (&top)[NB], const f32x4_t (&bottom)[NB], float* stg, int lane) {
+  float* row = stg + (lane & 15) * SLD + 4 * (lane >> 4);
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
-    *reinterpret_cast<f32x4_t*>(row + 8 * g) = f32x4_t{blk[4 * g], blk[4 * g + 1], blk[4 * g + 2], blk[4 * g + 3]};
+  for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4_t*>(row + 16 * j) = top[j];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4_t*>(row + 16 * SLD + 16 * j) = bottom[j];
 }
 
 // ---- the same for a tile that lies wholly inside C with 16-byte aligned row segments (all tiles of
@@ -209,7 +142,7 @@ struct EpiArgs {
 // EXTRAS: the result is combined with something (or rotated).  Without, the passes need no fetch and no line drawn between them; drawn all the same
 // they cost a fp32 tile 1 us (256 x 256 x 64 TN in fp32: 8.6 us; 7.0).
 template <bool C_F32, int EPI = kEpiNone, bool EDGE = false, bool EXTRAS = true>
-__device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
+__device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                                 int wm, int wn, void* __restrict__ Cv, int64_t ldc, int accumulate,
                                                 const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}, int rows = 128, int cols = 128) {
   constexpr int SLD = 132;
@@ -309,8 +242,7 @@ __device__ __forceinline__ void store_tile_full(const f32x16_t (&acc)[4][4], uns
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     if (EDGE && 32 * i >= rows) break;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) stage_rows<SLD>(acc[i][j], stg + 32 * j, lane);
+    stage_rows<SLD>(acc[2 * i], acc[2 * i + 1], stg, lane);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
     char* ci = cw + (int64_t)(32 * i) * ldc * ES;
@@ -366,7 +298,7 @@ struct RotPairs {
 // element, several at a time, where C's or R's rows are not 16-byte aligned (4503 x 3067 x 1024 with a residual, one at a time: 118 us; eight: 57).  Loops over the staged slice stay loops: unrolled, this path of the 256 x 256
 // tile would be most of a kernel's code.
 template <bool C_F32, int TM, int TN, int EPI = kEpiNone>
-__device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
+__device__ __forceinline__ void store_checked(const f32x4_t (&acc)[2 * TM][2 * TN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
                                               int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
                                               const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
   typedef typename std::conditional<C_F32, float, bf16_t>::type T;
@@ -378,8 +310,7 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
   const bool vec = EPI != kEpiNone || ((N & (V - 1)) == 0 && (ldc & (V - 1)) == 0 && (!R || (ldr & (V - 1)) == 0));      // uniform
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) stage_rows<SLD>(acc[i][j], stg + 32 * j, lane);
+    stage_rows<SLD>(acc[2 * i], acc[2 * i + 1], stg, lane);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
     const int64_t row0 = mw + 32 * i;
@@ -475,7 +406,7 @@ __device__ __forceinline__ void store_checked(const f32x16_t (&acc)[TM][TN], uns
 
 // ---- epilogue of a 256 x 256 tile
 template <bool C_F32, int EPI = kEpiNone>
-__device__ __forceinline__ void store_tile(const f32x16_t (&acc)[4][4], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
+__device__ __forceinline__ void store_tile(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                            int wm, int wn, int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
                                            const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
   constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
@@ -516,162 +447,31 @@ struct GemmArgs {
   float* part;
 };
 
-template <bool C_F32>
-__device__ __forceinline__ void gemm_tn_body(const GemmArgs& ga, int block) {
-  const int64_t M = ga.M, N = ga.N, lda = ga.lda, ldb = ga.ldb, ldr = ga.ldr;
-  int64_t K = ga.K, ldc = ga.ldc;
-  const bf16_t* __restrict__ A = ga.A;
-  const bf16_t* __restrict__ B = ga.B;
-  void* __restrict__ Cv = ga.C;
-  const void* __restrict__ Rv = ga.R;
-  int accumulate = ga.accumulate;
-  const int tiles_m = ga.tiles_m, tiles_n = ga.tiles_n;
-  if (C_F32 && ga.splits > 1) {      // workgroup-uniform: this workgroup's range of the contraction
-    const int ntl = tiles_m * tiles_n, sp = block / ntl;
-    block -= sp * ntl;
-    const int64_t k0 = (int64_t)sp * ga.k_chunk;
-    A += k0 * lda;
-    B += k0 * ldb;
-    K = K - k0 < ga.k_chunk ? K - k0 : ga.k_chunk;
-    Cv = ga.part + (int64_t)sp * M * N;
-    ldc = N;
-    accumulate = 0;
-  }
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
-  const lds_u8_t* lds = (const lds_u8_t*)lds2;
-  const unsigned lds0 = (unsigned)(size_t)lds;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // ---- XCD-aware tile id
-  int tm, tn;
-  gemm_tile_of_block(block, tiles_m, tiles_n, &tm, &tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-
-  const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  Operand oa, ob;
-  oa.init(A, lda, m0, M, wm, lane, wave);
-  ob.init(B, ldb, n0, N, wn, lane, wave);
-
-  const int nk = (int)((K + BK2 - 1) / BK2), rem = (int)(K - (int64_t)(nk - 1) * BK2);     // rem: k rows of the last step
-  // ---- prologue: tiles 0, 1, 2 in flight; tiles 0 and 1 landed and visible before the loop
-  for (int t = 0; t < 3 && t < nk; ++t) {
-    if (t + 1 == nk) {
-      oa.clamp_tail(rem, lda, lane, wave);
-      ob.clamp_tail(rem, ldb, lane, wave);
-    }
-    const unsigned st = lds0 + t * kStageBytes;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) oa.dma(i, st, wave);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ob.dma(i, st + kOpBytes, wave);
-    oa.advance();
-    ob.advance();
-  }
-  f32x16_t acc[4][4];
-  zero_acc(acc);
-  if (nk >= 3) wait_vmcnt<8>(); else wait_vmcnt<0>();
-  stage_barrier();
-  auto zero_last = [&]() {
-    unsigned char* st = lds2 + ((nk - 1) & (kStages - 1)) * kStageBytes;
-    oa.zero_tail(st, rem, tid);
-    ob.zero_tail(st + kOpBytes, rem, tid);
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    stage_barrier();
-  };
-  if (nk < 3 && rem != BK2) zero_last();
-  __builtin_amdgcn_sched_barrier(0);
-
-  bf16x8_t fa[2][4], fb[2][4];     // [MFMA k-step of the tile][fragment]
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    fa[0][i] = oa.frag(lds, i, 0);
-    fb[0][i] = ob.frag(lds + kOpBytes, i, 0);
-  }
-
-  // one K step.  First half: MFMAs of k-step 0 (fragments already in registers) with the loads
-  // of tile kt + 3 (its stage held tile kt - 1, which every wavefront finished before the barrier
-  // that ended the previous step) and the fragment reads of k-step 1.  Second half: MFMAs of
-  // k-step 1 with the first fragments of tile kt + 1 (visible since the previous barrier).
-  auto constexpr_mfma = [&](int e, int h) {
-    acc[kMfmaI[e]][kMfmaJ[e]] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[h][kMfmaJ[e]], fa[h][kMfmaI[e]], acc[kMfmaI[e]][kMfmaJ[e]], 0, 0, 0);
-  };
-  auto step = [&](int kt, auto load_c) {
-    constexpr bool LOAD = decltype(load_c)::value;
-    const lds_u8_t* cur = lds + (kt & (kStages - 1)) * kStageBytes;
-    const lds_u8_t* nxt = lds + ((kt + 1) & (kStages - 1)) * kStageBytes;
-    const unsigned dst = lds0 + ((kt + 3) & (kStages - 1)) * kStageBytes;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const lds_u8_t* src = h == 0 ? cur : nxt;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        constexpr_mfma(2 * q, h);
-        const int f = kReadOrder[q];
-        if (f < 4) fa[1 - h][f] = oa.frag(src, f, 1 - h);
-        else fb[1 - h][f - 4] = ob.frag(src + kOpBytes, f - 4, 1 - h);
-        __builtin_amdgcn_sched_barrier(0);
-        constexpr_mfma(2 * q + 1, h);
-        if (LOAD && h == 0) {
-          if (q < 4) oa.dma(q, dst, wave);
-          else ob.dma(q - 4, dst + kOpBytes, wave);
-        }
-        // The next step loads the last tile: asked here, between MFMAs, because after the step's barrier, where the matrix pipe has run dry, the
-        // question alone costs 3 % (1024 x 4096 x 11008, one tile on a quarter of the compute units: 169 us; 174).
-        if (LOAD && h == 1 && q == 3 && opaque_zero(kt + 5 - nk)) {
-          oa.clamp_tail(rem, lda, lane, wave);
-          ob.clamp_tail(rem, ldb, lane, wave);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    if (LOAD) {
-      oa.advance();
-      ob.advance();
-      wait_vmcnt<8>();      // tile kt + 2 has landed: only tile kt + 3's 8 loads may still be in flight
-    } else {
-      wait_vmcnt<0>();
-    }
-    stage_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  // the prologue's fragment reads have returned; with nothing outstanding at loop entry the
-  // compiler's lgkmcnt bookkeeping inside the loop only has the loop's own LDS reads to consider
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  int kt = 0;
-  if (nk == 4) {                         // the first step loads the last tile
-    oa.clamp_tail(rem, lda, lane, wave);
-    ob.clamp_tail(rem, ldb, lane, wave);
-  }
-  for (; kt + 3 < nk; ++kt) step(kt, std::true_type{});
-  if (nk > 2 && rem != BK2) {      // the last tile, on its way, first has to land
-    wait_vmcnt<0>();
-    stage_barrier();
-    zero_last();
-  }
-  for (; kt < nk; ++kt) step(kt, std::false_type{});
-
-  store_tile<C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, Cv, ldc, accumulate, Rv, ldr, ga.epi);
-}
-
-// =============================================================================== 64-deep K steps
-// The same pipeline with K advancing 64 at a time through a ring of two 64 KiB stages.  What it buys:
-// a K-contiguous operand row is 128 bytes per step, one full cache line fetched by 8 adjacent lanes,
-// instead of two 64-byte halves fetched in two different steps (the L2 serves either as one request,
-// and a layer's forward and input-gradient GEMMs were bound by that request rate).
+// =============================================================================== 256 x 256 tiles
+// K advances 64 at a time through an LDS ring of two A tiles and three B tiles (5 x 32 KiB, all of a compute unit's LDS), filled by
+// direct global->LDS loads (global_load_lds_dwordx4: no staging registers, no LDS store instructions).  Each lane picks the global chunk
+// whose swizzled home is the LDS slot its lane number writes, so the swizzle costs nothing.  64 deep, a row of a K-contiguous operand is one
+// full cache line fetched by 8 adjacent lanes.
 //
-// A step is four MFMA k-steps q0..q3 of 16 MFMAs.  Its workgroup barrier sits after q2, not at the
-// end: the fragments of k-step 3 are read during q2, so at that barrier the stage is no longer read
-// and the next stage (loaded during q3 of the previous step and q0 of this one) has landed.  q3 then
-// already reads the first fragments of the next stage and starts refilling the stage just finished.
+// A step is two MFMA k-steps of 64 MFMAs.  The first reads the fragments of the second; then the step's only barrier: the stage is no longer
+// read and the next one has landed; the second reads the first fragments of the next stage.  The B tile of stage kt + 2 is loaded in the first
+// half, into the third slot, its A tile in the second half, into the slot that the barrier freed: one load per eight MFMAs.  (With two B tiles all
+// sixteen loads of a step had to go into its second half, one per four MFMAs: 17.5 instead of 16.4 cycles per MFMA, and 1024 cycles less to
+// land in; 32768 x 4096 x 11008 NT 2010 -> 1843 us.)
+//
+// The instruction stream is laid out by hand, every MFMA and what is to be issued beside it closed by scheduling barriers: one wavefront
+// per SIMD issues in order, and between two MFMAs (16 cycles) there is room for one LDS read every other time (every time: 25 cycles per
+// MFMA), one load every eighth, and little else, so that fragment addresses are kept in registers and moved to the next stage where nothing else is
+// issued.  A tile on its own runs at 17.8 cycles per MFMA (all three forms).
+//
 //   KC tile [256 rows][64 k] (128-byte rows): load instruction j = 4 i + wave covers rows 8 j .. 8 j + 7;
 //      lane l writes slot (l & 7) of row 8 j + (l >> 3); slot s of row r holds chunk s ^ ((r >> 1) & 7)
 //      (16 consecutive rows of one chunk column then sit in 16 different bank groups).
-//   NC tile [64 k][256 cols]: as above with twice the k rows.
+//   NC tile [64 k][256 cols]: load instruction j covers k rows 2 j, 2 j + 1; position p of row k holds chunk p ^ swz(k).
+// Rows and column chunks outside the matrix are clamped to the last valid one: they feed output rows / columns that are not stored.
 constexpr int BK64 = 64;
-constexpr int kOp64 = 256 * BK64 * 2;            // one operand tile: 32 KiB
-constexpr int kStage64 = 2 * kOp64;              // 64 KiB
-constexpr size_t kLds64 = 2 * (size_t)kStage64;  // 128 KiB
+constexpr int kOp64 = 256 * BK64 * 2;            // one operand tile: 32 KiB; two of A, then three of B
+constexpr size_t kLds64 = 5 * (size_t)kOp64;     // 160 KiB
 
 // R = rows (KC) or columns (NC) of the operand tile: 256, or 128 / 64 in the small-tile kernel below.
 template <bool KC, int R>
@@ -683,13 +483,13 @@ struct Operand64 {
   uint64_t base;          // tile origin at the current K position (bytes); wavefront-uniform
   uint64_t kstep;         // bytes per K step
   unsigned goff[NL];      // per-lane byte offsets of the loads of a step
-  // KC: rd[ks] for MFMA k-step ks, fragment i is 4096 i bytes further (32 rows)
-  // NC: rd[i] for fragment i; MFMA k-step ks adds 16 tile rows, the second transposing read of a fragment 4
-  unsigned rd[4];
+  // KC: rd[ks] for MFMA k-step ks, fragment i is 2048 i bytes further (16 rows)
+  // NC: rd[i] for fragment i; MFMA k-step ks adds 32 tile rows, the second transposing read of a fragment 4
+  unsigned rd[KC ? 2 : R / 32];
 
-  // NC: which chunk of a k row sits where: 4 consecutive k rows x 64 bytes, what half a wavefront reads at a time, must fall into
+  // NC: which chunk of a k row sits where: k rows 0..3 and 8..11 x 32 bytes, what half a wavefront reads at a time, must fall into
   // different banks.  Rows of 512 and 256 bytes all start at the same bank; of two 128-byte rows the second starts half way.
-  static __device__ __forceinline__ int swz(int k) { return R >= 128 ? (k & 3) << 2 : (k & 2) << 1; }
+  static __device__ __forceinline__ int swz(int k) { return (R >= 128 ? (k & 3) << 2 : (k & 2) << 1) | (k >> 3 & 1) << 1; }
   static __device__ __forceinline__ int k_of_load(int i, int lane, int wave) { return kKpl * (4 * i + wave) + lane / (R / 8); }
 
   __device__ __forceinline__ void init(const bf16_t* mat, int64_t ld, int64_t origin, int64_t extent, int w0, int lane, int wave) {
@@ -704,9 +504,9 @@ struct Operand64 {
         const int c = (lane & 7) ^ ((rt >> 1) & 7);
         goff[i] = (unsigned)(r * ld * 2 + c * 16);
       }
-      const int r = w0 + (lane & 31);
+      const int r = w0 + (lane & 15);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) rd[ks] = r * 128 + (((2 * ks + (lane >> 5)) ^ ((r >> 1) & 7)) << 4);
+      for (int ks = 0; ks < 2; ++ks) rd[ks] = r * 128 + (((4 * ks + (lane >> 4)) ^ ((r >> 1) & 7)) << 4);
     } else {
       base = (uint64_t)(mat + origin);
       kstep = (uint64_t)ld * (BK64 * 2);
@@ -718,10 +518,10 @@ struct Operand64 {
         goff[i] = (unsigned)((k * ld + col) * 2);
       }
       const int blk = lane >> 4, l16 = lane & 15;
-      const int k = 8 * (blk >> 1) + (l16 >> 2);
+      const int k = 8 * blk + (l16 >> 2);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int n = w0 + 32 * i + 16 * (blk & 1) + 4 * (l16 & 3);
+      for (int i = 0; i < R / 32; ++i) {
+        const int n = w0 + 16 * i + 4 * (l16 & 3);
         rd[i] = k * kRow + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2;
       }
     }
@@ -750,21 +550,35 @@ struct Operand64 {
       zero_lds(op, rem * kRow, kBytes, tid);
     }
   }
+  // the same in kUnits LDS instructions: fragment u / kUnits, from rd with the operand tile's address added to it
+  static constexpr int kUnits = KC ? 1 : 2;
+  __device__ __forceinline__ void frag_unit(bf16x8_t (&f)[R / 32], int u, int ks) const {
+    if (KC) {
+      f[u] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>((size_t)(rd[ks] + 2048 * u));
+    } else {
+      typedef short s16x8_t __attribute__((ext_vector_type(8)));
+      const int i = u / 2, r = u & 1;
+      const s16x4_t h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(size_t)(rd[i] + (32 * ks + 4 * r) * kRow));
+      const s16x8_t w = __builtin_shufflevector(h, h, 0, 1, 2, 3, 0, 1, 2, 3), o = __builtin_bit_cast(s16x8_t, f[i]);
+      f[i] = __builtin_bit_cast(bf16x8_t, r == 0 ? __builtin_shufflevector(w, o, 0, 1, 2, 3, 12, 13, 14, 15) : __builtin_shufflevector(o, w, 0, 1, 2, 3, 12, 13, 14, 15));
+    }
+  }
   __device__ __forceinline__ bf16x8_t frag(const lds_u8_t* op, int i, int ks) const {
     if (KC) {
-      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(op + rd[ks] + 4096 * i);
+      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(op + rd[ks] + 2048 * i);
     } else {
       union { s16x4_t h[2]; bf16x8_t v; } u;
 #pragma unroll
       for (int r = 0; r < 2; ++r)
-        u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + (16 * ks + 4 * r) * kRow));
+        u.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(op + rd[i] + (32 * ks + 4 * r) * kRow));
       return u.v;
     }
   }
 };
 
 template <int MODE, bool C_F32, int EPI = kEpiNone>
-__device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) {
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
+  constexpr bool A_KC = (MODE != GEMM_TN), B_KC = (MODE == GEMM_NT);
   const int64_t M = ga.M, N = ga.N, lda = ga.lda, ldb = ga.ldb;
   int64_t K = ga.K;
   const bf16_t* __restrict__ A = ga.A;
@@ -776,11 +590,10 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
     sp = block / ntl;
     block -= sp * ntl;
     const int64_t k0 = (int64_t)sp * ga.k_chunk;
-    A += k0;
-    B += MODE == GEMM_NT ? k0 : k0 * ldb;
+    A += A_KC ? k0 : k0 * lda;
+    B += B_KC ? k0 : k0 * ldb;
     K = K - k0 < ga.k_chunk ? K - k0 : ga.k_chunk;
   }
-  static_assert(MODE != GEMM_TN, "A is K-contiguous here");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
   const lds_u8_t* lds = (const lds_u8_t*)lds2;
   const unsigned lds0 = (unsigned)(size_t)lds;
@@ -793,109 +606,118 @@ __device__ __forceinline__ void gemm_dlds64_body(const GemmArgs& ga, int block) 
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  Operand64<true, 256> oa;
-  Operand64<MODE == GEMM_NT, 256> ob;
+  Operand64<A_KC, 256> oa;
+  Operand64<B_KC, 256> ob;
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
   const int nk = (int)((K + BK64 - 1) / BK64), rem = (int)(K - (int64_t)(nk - 1) * BK64);     // rem: k values of the last step
-  // ---- prologue: stage 0 whole and the A half of stage 1 in flight; stage 0 landed and visible
-  if (nk == 1) {
+  const unsigned fill_a = lds0 + wave * 1024, fill_b = fill_a + 2 * kOp64;
+  auto dma_a = [&](auto i, unsigned fill) __attribute__((always_inline)) { lds_dma16_at<4096 * i>(oa.base, oa.goff[i], fill); };
+  auto dma_b = [&](auto i, unsigned fill) __attribute__((always_inline)) { lds_dma16_at<4096 * i>(ob.base, ob.goff[i], fill); };
+  auto clamp_tail = [&]() {
     oa.clamp_tail(rem, lda, lane, wave);
     ob.clamp_tail(rem, ldb, lane, wave);
+  };
+  // ---- prologue: stages 0 and 1 in flight; stage 0 landed and visible
+  f32x4_t acc[8][8];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t < nk) {
+      if (t + 1 == nk) clamp_tail();
+      static_for<8>([&](auto i) __attribute__((always_inline)) { dma_a(i, fill_a + t * kOp64); });
+      static_for<8>([&](auto i) __attribute__((always_inline)) { dma_b(i, fill_b + t * kOp64); });
+      oa.advance();
+      ob.advance();
+    }
+    if (t == 0) zero_acc(acc);
   }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) oa.dma(i, lds0, wave);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) ob.dma(i, lds0 + kOp64, wave);
-  oa.advance();
-  ob.advance();
-  f32x16_t acc[4][4];
-  zero_acc(acc);
-  if (nk > 1) {
-    if (nk == 2) oa.clamp_tail(rem, lda, lane, wave);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) oa.dma(i, lds0 + kStage64, wave);
-    oa.advance();
-    wait_vmcnt<8>();
-  } else {
-    wait_vmcnt<0>();
-  }
+  if (nk > 1) wait_vmcnt<16>(); else wait_vmcnt<0>();
   stage_barrier();
-  auto zero_last = [&](int t) {
-    unsigned char* st = lds2 + (t & 1) * kStage64;
-    oa.zero_tail(st, rem, tid);
-    ob.zero_tail(st + kOp64, rem, tid);
+  int slot_b = 0;                                // of the current stage
+  auto zero_last = [&](int kt) {                 // slot_b: of the stage before
+    oa.zero_tail(lds2 + (kt & 1) * kOp64, rem, tid);
+    ob.zero_tail(lds2 + (2 + slot_b) * kOp64, rem, tid);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     stage_barrier();
   };
   if (nk == 1 && rem != BK64) zero_last(0);
   __builtin_amdgcn_sched_barrier(0);
 
-  bf16x8_t fa[2][4], fb[2][4];     // [parity of the MFMA k-step][fragment]
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    fa[0][i] = oa.frag(lds, i, 0);
-    fb[0][i] = ob.frag(lds + kOp64, i, 0);
-  }
-  auto constexpr_mfma = [&](int e, int h) {
-    acc[kMfmaI[e]][kMfmaJ[e]] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[h][kMfmaJ[e]], fa[h][kMfmaI[e]], acc[kMfmaI[e]][kMfmaJ[e]], 0, 0, 0);
+  bf16x8_t fa[2][8] = {}, fb[2][8] = {};     // [MFMA k-step of the stage][fragment]
+  // the LDS instructions that read a k-step's fragments, the B fragments first: the first row of MFMAs needs them all
+  constexpr int UB = 8 * Operand64<B_KC, 256>::kUnits, UN = UB + 8 * Operand64<A_KC, 256>::kUnits;
+  auto read = [&](auto u, int ks) __attribute__((always_inline)) {
+    if constexpr (u < UB) ob.frag_unit(fb[ks], u, ks);
+    else oa.frag_unit(fa[ks], u - UB, ks);
   };
-  // one K step of 64.  LB: the B half of stage kt + 1 is still to be loaded (during q0); LA: stage
-  // kt + 2 exists, its A half is loaded during q3 into the stage this step has finished with;
-  // NEXT: stage kt + 1 exists, q3 reads its first fragments.
-  auto step = [&](int kt, auto lb_c, auto la_c, auto next_c) {
-    constexpr bool LB = decltype(lb_c)::value, LA = decltype(la_c)::value, NEXT = decltype(next_c)::value;
-    const lds_u8_t* cur = lds + (kt & 1) * kStage64;
-    const lds_u8_t* nxt = lds + ((kt + 1) & 1) * kStage64;
-    const unsigned dst_b = lds0 + ((kt + 1) & 1) * kStage64 + kOp64;
-    const unsigned dst_a = lds0 + (kt & 1) * kStage64;
+  // Fragment addresses go to the other stage between a fragment's last read of one and its first of the next: MFMA k-step 1's in the
+  // first half of a step, k-step 0's in the second; operands that are not K-contiguous have the same addresses for both, and change in the first.
+  constexpr int TB = B_KC ? 1 : 8, TN = TB + (A_KC ? 1 : 8);
+  auto move = [&](auto n, int ks, int by_b) __attribute__((always_inline)) {
+    if constexpr (n < TB) ob.rd[B_KC ? ks : n] += by_b;
+    else oa.rd[A_KC ? ks : n - TB] ^= kOp64;
+  };
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int h = q & 1;
-      const lds_u8_t* src = q < 3 ? cur : nxt;
-      const int ks = (q + 1) & 3;
-      auto read = [&](int f) {
-        if (f < 4) fa[1 - h][f] = oa.frag(src, f, ks);
-        else fb[1 - h][f - 4] = ob.frag(src + kOp64, f - 4, ks);
-      };
+  for (int i = 0; i < (A_KC ? 2 : 8); ++i) oa.rd[i] += lds0;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        constexpr_mfma(2 * e, h);
-        if (q == 2) {                    // all of k-step 3's fragments early: the barrier after q2 waits for them
-          if (e < 4) { read(kReadOrder[2 * e]); read(kReadOrder[2 * e + 1]); }
-        } else if (q < 3 || NEXT) {
-          read(kReadOrder[e]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        constexpr_mfma(2 * e + 1, h);
-        if (LB && q == 0) ob.dma(e, dst_b, wave);
-        if (LA && q == 3) oa.dma(e, dst_a, wave);
-        __builtin_amdgcn_sched_barrier(0);
+  for (int i = 0; i < (B_KC ? 2 : 8); ++i) ob.rd[i] += lds0 + 2 * kOp64;
+  static_for<UN>([&](auto u) __attribute__((always_inline)) { read(u, 0); });
+  if (A_KC) oa.rd[0] ^= kOp64;
+  if (B_KC) ob.rd[0] += kOp64;
+  // MFMA e of a k-step: row by row, every other row backwards, so that two in a row always share a fragment
+  auto mfma = [&](int e, int ks) __attribute__((always_inline)) {
+    const int i = e / 8, j = i & 1 ? 7 - e % 8 : e % 8;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+  };
+  // One K step of 64.  NEXT: stage kt + 1 exists, the second half reads its first fragments.  LOAD: stage kt + 2 exists; its B tile is loaded
+  // during the first half, into the slot of stage kt - 1, its A tile during the second, into the slot this step has finished with.
+  auto step = [&](int kt, auto load_c, auto next_c) __attribute__((always_inline)) {
+    constexpr bool LOAD = decltype(load_c)::value, NEXT = decltype(next_c)::value;
+    const unsigned fa_dst = fill_a + (kt & 1) * kOp64, fb_dst = fill_b + (slot_b == 0 ? 2 : slot_b - 1) * kOp64;
+    slot_b = slot_b == 2 ? 0 : slot_b + 1;       // from here on: of the next stage
+    const int by1 = slot_b == 0 ? -2 * kOp64 : kOp64, by2 = slot_b == 2 ? -2 * kOp64 : kOp64;      // to the next stage, and from there to the one after
+    static_for<64>([&](auto e) __attribute__((always_inline)) {
+      mfma(e, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (e < 48 && e * UN / 48 < (e + 1) * UN / 48) read(std::integral_constant<int, e * UN / 48>{}, 1);
+      if constexpr (NEXT && e >= 48 && e - 48 < TN) move(std::integral_constant<int, e - 48>{}, 1, by1);
+      if constexpr (LOAD && e % 8 == 0) dma_b(std::integral_constant<int, e / 8>{}, fb_dst);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if (LOAD) ob.advance();
+    __builtin_amdgcn_s_waitcnt(0xc07f);                   // this wavefront's last reads of the stage have returned
+    if (LOAD) wait_vmcnt<8>();                            // and its share of the next stage has landed
+    else if (NEXT) wait_vmcnt<0>();
+    stage_barrier();                                      // !NEXT: the epilogue stages through the ring
+    if (NEXT && !LOAD && rem != BK64) zero_last(kt + 1);  // stage kt + 1 is the last
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<64>([&](auto e) __attribute__((always_inline)) {
+      mfma(e, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (NEXT) {
+        if constexpr (e * UN / 64 < (e + 1) * UN / 64) read(std::integral_constant<int, e * UN / 64>{}, 0);
+        if constexpr (A_KC && e == 63) oa.rd[0] ^= kOp64;
+        if constexpr (B_KC && e == 62) ob.rd[0] += by2;
       }
-      if (LB && q == 0) ob.advance();
-      if (LA && q == 3) oa.advance();
-      if (q == 2) {
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // this wavefront's last reads of the stage have returned
-        wait_vmcnt<0>();                      // and its share of the next stage has landed
-        stage_barrier();
-        if (NEXT && !LA && rem != BK64) zero_last(kt + 1);      // stage kt + 1 is the last
-        __builtin_amdgcn_sched_barrier(0);
+      if constexpr (LOAD && e % 8 == 0) dma_a(std::integral_constant<int, e / 8>{}, fa_dst);
+      // the next step loads the last stage: asked between MFMAs, where the question costs nothing
+      if constexpr (LOAD && e == 60) {
+        oa.advance();
+        if (opaque_zero(kt + 4 - nk)) clamp_tail();
       }
-    }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
   __builtin_amdgcn_s_waitcnt(0xc07f);
   int kt = 0;
-  for (; kt + 2 < nk; ++kt) {
-    if (opaque_zero(kt + 3 - nk)) oa.clamp_tail(rem, lda, lane, wave);      // this step loads the A half of the last stage
-    step(kt, std::true_type{}, std::true_type{}, std::true_type{});
-  }
+  if (nk == 3) clamp_tail();                              // the first step loads the last stage
+  for (; kt + 2 < nk; ++kt) step(kt, std::true_type{}, std::true_type{});
   if (kt + 1 < nk) {
-    ob.clamp_tail(rem, ldb, lane, wave);
-    step(kt, std::true_type{}, std::false_type{}, std::true_type{});
+    step(kt, std::false_type{}, std::true_type{});
     ++kt;
   }
-  step(kt, std::false_type{}, std::false_type{}, std::false_type{});
+  step(kt, std::false_type{}, std::false_type{});
 
   if (ga.splits > 1)
     store_tile<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.part + (int64_t)sp * M * N, N, 0, nullptr, 0, ga.epi);
@@ -947,13 +769,12 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
-  f32x16_t acc[TM][TN];
+  constexpr int FM = 2 * TM, FN = 2 * TN;      // fragments of 16 rows, columns
+  f32x4_t acc[FM][FN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const int nk = (int)((K + BK64 - 1) / BK64), rem = (int)(K - (int64_t)(nk - 1) * BK64);     // rem: k values of the last step
   auto dma = [&](int i, unsigned st) {      // load i (0 ... LPS - 1) of a stage
@@ -994,13 +815,13 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
   // A step multiplies the fragments of stage kt, which sit in registers, and reads those of stage kt + 1 into a second set.  At its
   // barrier stage kt + 1 has landed, and every wavefront has read stage kt, whose slot takes the loads of stage kt + NST.
   struct Frags {
-    bf16x8_t a[4][TM], b[4][TN];      // [MFMA k-step]
+    bf16x8_t a[2][FM], b[2][FN];      // [MFMA k-step]
   } f0, f1;
-  constexpr int NF = 4 * (TM + TN), NM = 4 * TM * TN;      // fragments and MFMAs of a step
+  constexpr int NF = 2 * (FM + FN), NM = 2 * FM * FN;      // fragments and MFMAs of a step
   auto read = [&](Frags& f, const lds_u8_t* st, int e) {
-    const int ks = e / (TM + TN), i = e % (TM + TN);
-    if (i < TM) f.a[ks][i] = oa.frag(st, i, ks);
-    else f.b[ks][i - TM] = ob.frag(st + OpA::kBytes, i - TM, ks);
+    const int ks = e / (FM + FN), i = e % (FM + FN);
+    if (i < FN) f.b[ks][i] = ob.frag(st + OpA::kBytes, i, ks);
+    else f.a[ks][i - FN] = oa.frag(st, i - FN, ks);
   };
 #pragma unroll
   for (int e = 0; e < NF; ++e) read(f0, lds, e);
@@ -1021,8 +842,8 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int e = 0; e < NM; ++e) {
-      const int ks = e / (TM * TN), i = e % (TM * TN) / TN, j = e % TN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.b[ks][j], cur.a[ks][i], acc[i][j], 0, 0, 0);
+      const int ks = e / (FM * FN), i = e % (FM * FN) / FN, j = i & 1 ? FN - 1 - e % FN : e % FN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[ks][j], cur.a[ks][i], acc[i][j], 0, 0, 0);
       if (NEXT) {
 #pragma unroll
         for (int r = e * NF / NM; r < (e + 1) * NF / NM; ++r) read(nxt, st, r);
@@ -1065,8 +886,7 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
 // ---- kernels: one GEMM, or two independent ones in one grid (the first's tiles, then the second's)
 template <int MODE, bool C_F32, int EPI = kEpiNone>
 __global__ void __launch_bounds__(kThreads, 1) gemm_pipe_kernel(GemmArgs g) {
-  if constexpr (MODE != GEMM_TN) gemm_dlds64_body<MODE, C_F32, EPI>(g, (int)blockIdx.x);
-  else gemm_tn_body<C_F32>(g, (int)blockIdx.x);
+  gemm_tile_body<MODE, C_F32, EPI>(g, (int)blockIdx.x);
 }
 // The layer's backward has such pairs at every linear: the input gradient and the weight gradient
 // read the same incoming gradient and write different outputs.  Neither tile count is a multiple
@@ -1074,8 +894,8 @@ __global__ void __launch_bounds__(kThreads, 1) gemm_pipe_kernel(GemmArgs g) {
 // one grid leaves one.  n1 >= 0: the second's n1 workgroups go first (dual_order).
 __global__ void __launch_bounds__(kThreads, 1) gemm_dual_kernel(GemmArgs g0, GemmArgs g1, int n0, int n1) {
   const int b = (int)blockIdx.x, b0 = n1 < 0 ? b : b - n1;      // this workgroup's index within the first problem, if it is one of its
-  if (b0 >= 0 && b0 < n0) gemm_tn_body<true>(g0, b0);
-  else gemm_dlds64_body<GEMM_NN, false>(g1, n1 < 0 ? b - n0 : b);
+  if (b0 >= 0 && b0 < n0) gemm_tile_body<GEMM_TN, true>(g0, b0);
+  else gemm_tile_body<GEMM_NN, false>(g1, n1 < 0 ? b - n0 : b);
 }
 template <int MODE, bool C_F32, int TM, int TN, int NST, int EPI = kEpiNone>
 __global__ void __launch_bounds__(kThreads, NST == 2 ? 2 : 1) gemm_small_kernel(GemmArgs g) {
@@ -1106,12 +926,10 @@ inline GemmArgs make_args(int64_t M, int64_t N, int64_t K, const void* A, int64_
   return g;
 }
 
-static_assert(kLds64 == kLds2, "the two pipelined kernels share one LDS size");
-
 template <int MODE, bool C_F32, int EPI = kEpiNone>
 int launch_pipe(const GemmArgs& g, hipStream_t st) {
-  TAW_SET_LDS_LIMIT_ONCE((gemm_pipe_kernel<MODE, C_F32, EPI>), kLds2);
-  hipLaunchKernelGGL((gemm_pipe_kernel<MODE, C_F32, EPI>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(kThreads), kLds2, st, g);
+  TAW_SET_LDS_LIMIT_ONCE((gemm_pipe_kernel<MODE, C_F32, EPI>), kLds64);
+  hipLaunchKernelGGL((gemm_pipe_kernel<MODE, C_F32, EPI>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(kThreads), kLds64, st, g);
   return (int)hipGetLastError();
 }
 
@@ -1121,9 +939,9 @@ int launch_pipe(const GemmArgs& g, hipStream_t st) {
 inline int dual_order(const GemmArgs& g0, const GemmArgs& g1, int n1) { return g0.k_chunk >= g1.k_chunk || n1 >= 256 ? -1 : n1; }
 
 inline int launch_dual(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st) {
-  TAW_SET_LDS_LIMIT_ONCE(gemm_dual_kernel, kLds2);
+  TAW_SET_LDS_LIMIT_ONCE(gemm_dual_kernel, kLds64);
   const int n0 = g0.tiles_m * g0.tiles_n * g0.splits, n1 = g1.tiles_m * g1.tiles_n * g1.splits;
-  hipLaunchKernelGGL(gemm_dual_kernel, dim3((unsigned)(n0 + n1)), dim3(kThreads), kLds2, st, g0, g1, n0, dual_order(g0, g1, n1));
+  hipLaunchKernelGGL(gemm_dual_kernel, dim3((unsigned)(n0 + n1)), dim3(kThreads), kLds64, st, g0, g1, n0, dual_order(g0, g1, n1));
   return (int)hipGetLastError();
 }
 
