@@ -40,6 +40,7 @@ namespace {
 constexpr int BM = 256, BN = 256;
 constexpr int kThreads = 256;
 
+// =============================================================================== common to all tiles
 namespace v2 {
 
 typedef __attribute__((address_space(3))) unsigned char lds_u8_t;
@@ -102,6 +103,123 @@ __device__ __forceinline__ bool opaque_zero(int x) {
   return x == 0;
 }
 
+// ---- where a result element sits in the accumulators.  The MFMAs multiply (B fragment) x (A fragment)^T, so a 16 x 16 block of the
+// result sits transposed in the accumulator registers: lane l holds ROW l & 15 of the block and, in its four registers, places
+// 4 (l >> 4) + 0..3 of the B fragment.  Which column a place is, is the B operand's choice (which rows, or columns, of it a fragment reads):
+//   kColsPlain   fragment j: columns 16 j + place.  A lane's four registers are 16 bytes of an fp32 row.
+//   kColsPaired  fragments 2 p, 2 p + 1 share 32 columns so that a lane's eight registers are the consecutive columns 32 p + 8 (l >> 4) + 0..7,
+//                16 bytes of a bf16 row: the even fragment holds the first four of them, the odd one the other four.
+//   kColsSwapped the same with the two fragments' fours exchanged where l >> 4 is odd (what bank-conflict-free transposing reads need).
+// Plain for A operands, fp32 results and the 256 x 256 tile, which reorders its result in LDS.
+constexpr int kColsPlain = 0, kColsPaired = 1, kColsSwapped = 2;
+template <int COLS> __device__ __forceinline__ int block_col(int j, int lane) {      // column of register 0 of block j
+  const int g = lane >> 4;
+  return COLS == kColsPlain ? 16 * j + 4 * g : 32 * (j >> 1) + 8 * g + 4 * ((j & 1) ^ (COLS == kColsSwapped ? g & 1 : 0));
+}
+
+// EPI = kEpiRope (bf16 output only): the rotary embedding applied to the result before it is stored.
+// Columns below rot_cols are heads of 128 whose adjacent pairs (2i, 2i+1) are rotated by the angle of
+// (row % S, i); table [S][64][2] fp32 of (cos, sin).  A lane holds 8 consecutive columns of a row here,
+// i.e. 4 whole pairs, in fp32: the fused qkv projection then needs no rotary pass of its own, and q, k
+// are rounded to bf16 once.  rot_cols is a multiple of 128. round_first: rounded to bf16 before the rotation too, as the
+// separate rotary pass did that rotated q and k of these sizes before (launch_gemm_mfma_nt_rope).
+constexpr int kEpiNone = 0, kEpiRope = 1;
+struct EpiArgs {
+  const float* table;
+  int S;
+  int64_t rot_cols;
+  int round_first;
+};
+
+// the rotation of 8 consecutive columns col .. col + 7 of row `row`: the table's 4 pairs, and their use
+struct RotPairs {
+  f32x4_t cs[2];
+  __device__ __forceinline__ void load_at(unsigned pos, int64_t col, const EpiArgs& ea) {
+    const float* tb = ea.table + ((int64_t)pos * 64 + ((col & 127) >> 1)) * 2;
+    cs[0] = *reinterpret_cast<const f32x4_t*>(tb);
+    cs[1] = *reinterpret_cast<const f32x4_t*>(tb + 4);
+  }
+  __device__ __forceinline__ void load(int64_t row, int64_t col, const EpiArgs& ea) { load_at((unsigned)row % (unsigned)ea.S, col, ea); }      // token counts fit 32 bits
+  __device__ __forceinline__ void rotate(float (&v)[8], int round_first) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1], c = cs[e >> 1][2 * (e & 1)], sn = cs[e >> 1][2 * (e & 1) + 1];
+      v[2 * e] = a * c - b2 * sn;
+      v[2 * e + 1] = a * sn + b2 * c;
+    }
+  }
+};
+
+// ---- the same where C's or R's rows are not 16-byte aligned: 32-row slices -> fp32 staging rows in LDS (one region per wavefront, in the
+// ring, which every wavefront has finished reading) -> element by element along the rows, several at a time (4503 x 3067 x 1024 with a residual, one
+// at a time: 118 us; eight: 57).  Loops over the staged slice stay loops: unrolled, this path of the 256 x 256 tile would be most of a kernel's code.
+template <bool C_F32, int FM, int FN, int COLS>
+__device__ __forceinline__ void store_elements(const f32x4_t (&acc)[FM][FN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
+                                               int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
+                                               const void* __restrict__ Rv, int64_t ldr) {
+  typedef typename std::conditional<C_F32, float, bf16_t>::type T;
+  constexpr int TN = FN / 2, SLD = 32 * TN + 4;
+  constexpr int UE = FM * FN == 64 ? 8 : 1;      // single elements in flight per lane: the registers that a tile's main loop leaves
+  float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
+  T* C = static_cast<T*>(Cv);
+  const T* R = static_cast<const T*>(Rv);
+#pragma unroll
+  for (int i = 0; i < FM / 2; ++i) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) *reinterpret_cast<f32x4_t*>(stg + (16 * h + (lane & 15)) * SLD + block_col<COLS>(j, lane)) = acc[2 * i + h][j];
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+    const int64_t row0 = mw + 32 * i;
+    if constexpr (UE == 1) {
+#pragma unroll 1
+      for (int e = lane; e < 32 * 32 * TN; e += 64) {
+        const int64_t row = row0 + e / (32 * TN), col = nw + e % (32 * TN);
+        if (row < M && col < N) {
+          float x = stg[e / (32 * TN) * SLD + e % (32 * TN)];
+          if (R) x += (float)R[row * ldr + col];
+          if (accumulate) x += (float)C[row * ldc + col];
+          C[row * ldc + col] = (T)x;
+        }
+      }
+    } else {
+#pragma unroll 1
+      for (int e0 = lane; e0 < 32 * 32 * TN; e0 += 64 * UE) {
+        float x[UE];
+        T r[UE], c[UE];
+        int64_t row[UE], col[UE];
+#pragma unroll
+        for (int u = 0; u < UE; ++u) {
+          const int e = e0 + 64 * u;
+          row[u] = row0 + e / (32 * TN);
+          col[u] = nw + e % (32 * TN);
+          x[u] = stg[e / (32 * TN) * SLD + e % (32 * TN)];
+        }
+        // loads clamped into C, so that they need no branch and are in flight together
+        auto at = [&](const T* p, int u, int64_t ld) { return p[(row[u] < M ? row[u] : M - 1) * ld + (col[u] < N ? col[u] : N - 1)]; };
+        if (R) {
+#pragma unroll
+          for (int u = 0; u < UE; ++u) r[u] = at(R, u, ldr);
+        }
+        if (accumulate) {
+#pragma unroll
+          for (int u = 0; u < UE; ++u) c[u] = at(C, u, ldc);
+        }
+#pragma unroll
+        for (int u = 0; u < UE; ++u) {
+          if (R) x[u] += (float)r[u];
+          if (accumulate) x[u] += (float)c[u];
+          if (row[u] < M && col[u] < N) C[row[u] * ldc + col[u]] = (T)x[u];
+        }
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// =============================================================================== epilogue of a 256 x 256 tile
 // ---- accumulator blocks -> staging rows.  The MFMAs multiply (B fragment) x (A fragment)^T, so a 16 x 16 block of
 // the result sits transposed in the accumulator registers: lane l holds ROW l & 15 of the block and, in its four
 // registers, the consecutive COLUMNS 4 (l >> 4) + 0..3.  Four consecutive floats of a row are one 16-byte LDS write
@@ -119,20 +237,6 @@ __device__ __forceinline__ void stage_rows(const f32x4_t (&top)[NB], const f32x4
 // the layer's shapes): no per-element checks, 32-bit lane offsets from the wavefront's corner of C
 // The result is stored non-temporally: a round of tiles writes more than an L2 holds, and ordinary stores
 // push the operand panels out of it (1-3 % per GEMM).
-//
-// EPI = kEpiRope (bf16 output only): the rotary embedding applied to the result before it is stored.
-// Columns below rot_cols are heads of 128 whose adjacent pairs (2i, 2i+1) are rotated by the angle of
-// (row % S, i); table [S][64][2] fp32 of (cos, sin).  A lane holds 8 consecutive columns of a row here,
-// i.e. 4 whole pairs, in fp32: the fused qkv projection then needs no rotary pass of its own, and q, k
-// are rounded to bf16 once.  rot_cols is a multiple of 128. round_first: rounded to bf16 before the rotation too, as the
-// separate rotary pass did that rotated q and k of these sizes before (launch_gemm_mfma_nt_rope).
-constexpr int kEpiNone = 0, kEpiRope = 1;
-struct EpiArgs {
-  const float* table;
-  int S;
-  int64_t rot_cols;
-  int round_first;
-};
 //
 // EDGE: the same for a block that reaches over the edge of C (rows and columns of C: `rows`, `cols` from the block's corner on, cols a multiple
 // of the 16-byte chunk): loads clamped into C, stores predicated, a unit's values all formed before its first store so that its reads stay
@@ -273,144 +377,13 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
   }
 }
 
-// the rotation of 8 consecutive columns col .. col + 7 of row `row`: the table's 4 pairs, and their use
-struct RotPairs {
-  f32x4_t cs[2];
-  __device__ __forceinline__ void load(int64_t row, int64_t col, const EpiArgs& ea) {
-    const unsigned pos = (unsigned)row % (unsigned)ea.S;      // token counts fit 32 bits
-    const float* tb = ea.table + ((int64_t)pos * 64 + ((col & 127) >> 1)) * 2;
-    cs[0] = *reinterpret_cast<const f32x4_t*>(tb);
-    cs[1] = *reinterpret_cast<const f32x4_t*>(tb + 4);
-  }
-  __device__ __forceinline__ void rotate(float (&v)[8], int round_first) const {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1], c = cs[e >> 1][2 * (e & 1)], sn = cs[e >> 1][2 * (e & 1) + 1];
-      v[2 * e] = a * c - b2 * sn;
-      v[2 * e + 1] = a * sn + b2 * c;
-    }
-  }
-};
-
-// ---- epilogue of a wavefront's (32 TM) x (32 TN) block at (mw, nw), any part of it possibly outside C: 32-row slices -> fp32
-// staging rows in LDS (one region per wavefront, in the ring, which every wavefront has finished reading) -> 16-byte accesses that
-// cover whole row segments of C, four at a time so that what they read (residual, accumulated C) is fetched together; element by
-// element, several at a time, where C's or R's rows are not 16-byte aligned (4503 x 3067 x 1024 with a residual, one at a time: 118 us; eight: 57).  Loops over the staged slice stay loops: unrolled, this path of the 256 x 256
-// tile would be most of a kernel's code.
-template <bool C_F32, int TM, int TN, int EPI = kEpiNone>
-__device__ __forceinline__ void store_checked(const f32x4_t (&acc)[2 * TM][2 * TN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
-                                              int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
-                                              const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
-  typedef typename std::conditional<C_F32, float, bf16_t>::type T;
-  constexpr int SLD = 32 * TN + 4, V = C_F32 ? 4 : 8, CPR = 32 * TN / V, U = CPR / 2 < 4 ? CPR / 2 : 4;      // CPR: chunks of V columns per row
-  constexpr int UE = TM * TN == 16 ? 8 : 1;      // single elements in flight per lane: the registers that a tile's main loop leaves
-  float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
-  T* C = static_cast<T*>(Cv);
-  const T* R = static_cast<const T*>(Rv);
-  const bool vec = EPI != kEpiNone || ((N & (V - 1)) == 0 && (ldc & (V - 1)) == 0 && (!R || (ldr & (V - 1)) == 0));      // uniform
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    stage_rows<SLD>(acc[2 * i], acc[2 * i + 1], stg, lane);
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-    const int64_t row0 = mw + 32 * i;
-    if (vec) {
-#pragma unroll 1
-      for (int it = 0; it < CPR / 2; it += U) {
-        Vec<T, V> r[U], c[U];
-        RotPairs rot[U];
-        int64_t row[U], col[U];
-        bool in[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int idx = (it + u) * 64 + lane;
-          row[u] = row0 + idx / CPR;
-          col[u] = nw + idx % CPR * V;
-          in[u] = row[u] < M && col[u] < N;
-          if (in[u] && R) r[u].load(R + row[u] * ldr + col[u]);
-          if (in[u] && accumulate) c[u].load(C + row[u] * ldc + col[u]);
-          if (EPI == kEpiRope && in[u] && col[u] < ea.rot_cols) rot[u].load(row[u], col[u], ea);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (!in[u]) continue;
-          const int idx = (it + u) * 64 + lane;
-          const float* sp = stg + idx / CPR * SLD + idx % CPR * V;
-          float v[V];
-#pragma unroll
-          for (int e = 0; e < V; e += 4) {
-            const f32x4_t q = *reinterpret_cast<const f32x4_t*>(sp + e);
-            v[e] = q[0]; v[e + 1] = q[1]; v[e + 2] = q[2]; v[e + 3] = q[3];
-          }
-          if constexpr (EPI == kEpiRope) {
-            if (col[u] < ea.rot_cols) rot[u].rotate(v, ea.round_first);
-          }
-          Vec<T, V> o;
-#pragma unroll
-          for (int e = 0; e < V; ++e) {
-            if (R) v[e] += r[u].get(e);
-            if (accumulate) v[e] += c[u].get(e);
-            o.set(e, v[e]);
-          }
-          o.store(C + row[u] * ldc + col[u]);
-        }
-      }
-    } else {
-      if constexpr (UE == 1) {
-#pragma unroll 1
-        for (int e = lane; e < 32 * 32 * TN; e += 64) {
-          const int64_t row = row0 + e / (32 * TN), col = nw + e % (32 * TN);
-          if (row < M && col < N) {
-            float x = stg[e / (32 * TN) * SLD + e % (32 * TN)];
-            if (R) x += (float)R[row * ldr + col];
-            if (accumulate) x += (float)C[row * ldc + col];
-            C[row * ldc + col] = (T)x;
-          }
-        }
-      } else {
-#pragma unroll 1
-        for (int e0 = lane; e0 < 32 * 32 * TN; e0 += 64 * UE) {
-          float x[UE];
-          T r[UE], c[UE];
-          int64_t row[UE], col[UE];
-#pragma unroll
-          for (int u = 0; u < UE; ++u) {
-            const int e = e0 + 64 * u;
-            row[u] = row0 + e / (32 * TN);
-            col[u] = nw + e % (32 * TN);
-            x[u] = stg[e / (32 * TN) * SLD + e % (32 * TN)];
-          }
-          // loads clamped into C, so that they need no branch and are in flight together
-          auto at = [&](const T* p, int u, int64_t ld) { return p[(row[u] < M ? row[u] : M - 1) * ld + (col[u] < N ? col[u] : N - 1)]; };
-          if (R) {
-#pragma unroll
-            for (int u = 0; u < UE; ++u) r[u] = at(R, u, ldr);
-          }
-          if (accumulate) {
-#pragma unroll
-            for (int u = 0; u < UE; ++u) c[u] = at(C, u, ldc);
-          }
-#pragma unroll
-          for (int u = 0; u < UE; ++u) {
-            if (R) x[u] += (float)r[u];
-            if (accumulate) x[u] += (float)c[u];
-            if (row[u] < M && col[u] < N) C[row[u] * ldc + col[u]] = (T)x[u];
-          }
-        }
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// ---- epilogue of a 256 x 256 tile
+// a wavefront's 128 x 128 block at (mw, nw), whatever C looks like; everything asked here is wavefront-uniform
 template <bool C_F32, int EPI = kEpiNone>
-__device__ __forceinline__ void store_tile(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
-                                           int wm, int wn, int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
-                                           const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
+__device__ __forceinline__ void store_large(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
+                                            int wm, int wn, int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
+                                            const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
   constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
-  const bool aligned = (ldc & V) == 0 && (!Rv || (ldr & V) == 0);      // workgroup-uniform, as everything here
+  const bool aligned = (ldc & V) == 0 && (!Rv || (ldr & V) == 0);
   const bool full = m0 + BM <= M && n0 + BN <= N && aligned && (EPI == kEpiNone || ea.S >= 32);
   if (C_F32 && full && !Rv && !accumulate) {
     store_tile_full<C_F32, EPI, false, !C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, 0, nullptr, 0, ea);
@@ -422,9 +395,164 @@ __device__ __forceinline__ void store_tile(const f32x4_t (&acc)[8][8], unsigned 
       store_tile_full<C_F32, EPI, true>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea, rows < 128 ? (int)rows : 128,
                                         cols < 128 ? (int)cols : 128);
   } else {
-    store_checked<C_F32, 4, 4>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, Cv, ldc, accumulate, Rv, ldr, ea);
+    store_elements<C_F32, 8, 8, kColsPlain>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, Cv, ldc, accumulate, Rv, ldr);
   }
 }
+
+// =============================================================================== epilogue of a smaller tile
+// Result, residual and rotary table are accessed in whole 16-byte pieces straight from the registers.  What bounds a short grid of smaller tiles is one
+// tile's latency, and the way through LDS, slice by slice with a wait on either side, was a third of it: a step of 63 tokens at H = 3072 628 -> 490 us, of 128
+// at 7040 2374 -> 1707, backward of a 4503 x 3072 x 1024 linear 60.4 -> 56.6.  (256 x 256 tiles store no faster this way: a round of them is bound by
+// the 32 MB it writes, and rows in pieces of 256 and 512 bytes go out better than in 128: 65536 x 1024 forward 2287 us staged, 2323 direct.)
+//
+// ---- epilogue of a wavefront's (16 FM) x (16 FN) block at (mw, nw) of C, whose rows are 16-byte aligned (N, ldc and ldr multiples of
+// a piece).  EDGE: any part of it may lie outside C: loads are clamped into it, stores predicated.  EXTRAS: the result is combined with
+// something, fetched one row of blocks ahead of its use.
+template <bool C_F32, int FM, int FN, int EPI, int COLS, bool EDGE, bool EXTRAS>
+__device__ __forceinline__ void store_pieces(const f32x4_t (&acc)[FM][FN], int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
+                                             void* __restrict__ Cv, int64_t ldc, int accumulate, const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
+  static_assert((COLS == kColsPlain) == C_F32 && (EPI == kEpiNone || !C_F32), "a lane's columns are 16 bytes");
+  constexpr int ES = C_F32 ? 4 : 2;                        // bytes per element of C (and R)
+  constexpr int W = 16 / ES;                               // consecutive columns a lane holds at a time: a piece
+  constexpr int U = 4 * FN / W, CSTEP = 4 * W;             // pieces of a row of blocks, columns from one to the next
+  constexpr bool PAIR = U % 2 == 0;                        // pieces are exchanged between lanes in pairs
+  typedef typename std::conditional<C_F32, f32x4_t, bf16x8_t>::type piece_t;
+  const int r0 = lane & 15, c0 = W * (lane >> 4);          // this lane's row of a block, first column of unit 0
+  const int rows = M - mw < 16 * FM ? (int)(M - mw) : 16 * FM, cols = N - nw < 16 * FN ? (int)(N - nw) : 16 * FN;
+  if (EDGE && (rows <= 0 || cols <= 0)) return;            // wavefront-uniform
+  char* cw = static_cast<char*>(Cv) + (mw * ldc + nw) * ES;
+  const char* rw = Rv ? static_cast<const char*>(Rv) + (mw * ldr + nw) * ES : nullptr;
+  const bool rotate = EPI == kEpiRope && nw < ea.rot_cols;      // wavefront-uniform where 16 FN columns are part of one head
+  struct Extra {
+    piece_t r[EXTRAS && EPI == kEpiNone ? U : 1], c[EXTRAS && EPI == kEpiNone ? U : 1];
+    RotPairs rot[EPI == kEpiRope ? U : 1];
+  } extra[2];
+  unsigned pos = EPI == kEpiRope ? (unsigned)(mw + r0) % (unsigned)ea.S : 0;      // of this lane's row in the row of blocks fetched next
+  auto fetch = [&](Extra& x, int i) {
+    if constexpr (EPI == kEpiRope) {
+      if (!rotate) return;
+#pragma unroll
+      for (int u = 0; u < U; ++u) x.rot[u].load_at(pos, nw + c0 + CSTEP * u, ea);
+      pos += 16;
+      if (ea.S < 16) pos %= (unsigned)ea.S;
+      else pos = pos >= (unsigned)ea.S ? pos - ea.S : pos;
+    } else {
+      const int row = 16 * i + r0, rr = EDGE && row >= rows ? rows - 1 : row;
+      auto at = [&](const char* w, int64_t ld, int u) {
+        int c = c0 + CSTEP * u;
+        if (EDGE && c >= cols) c = cols - W;
+        return *reinterpret_cast<const piece_t*>(w + ((unsigned)(rr * ld) + c) * ES);
+      };
+      if (rw) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x.r[u] = at(rw, ldr, u);
+      }
+      if (accumulate) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x.c[u] = at(cw, ldc, u);
+      }
+    }
+  };
+  // Of a pair of pieces (a lane's row, CSTEP columns apart) lanes with rows 0..7 of the block give the second to the lane 8 rows down and
+  // take its first: each of the two stores then covers whole 128-byte lines of 8 rows instead of half lines of 16.
+  const int hi = PAIR ? r0 >> 3 : 0, sr = r0 - 8 * hi, sc = c0 + CSTEP * hi;      // row of the first store's piece, and its column
+  const unsigned off = (unsigned)(sr * ldc + sc) * ES;
+  if constexpr (EXTRAS) fetch(extra[0], 0);
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    if (EDGE && 16 * i >= rows) break;
+    if (EXTRAS && i + 1 < FM) fetch(extra[(i + 1) & 1], i + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    // the accumulators are read here and not above the branches between the variants of this function, where they would need registers
+    f32x4_t blk[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      blk[j] = acc[i][j];
+      asm volatile("" : "+v"(blk[j]));
+    }
+    const Extra& x = extra[i & 1];
+    piece_t o[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float v[W];
+      if constexpr (C_F32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = blk[u][e];
+      } else {
+        const bool swap = COLS == kColsSwapped && (lane & 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = blk[2 * u][e], b = blk[2 * u + 1][e];
+          v[e] = swap ? b : a;
+          v[4 + e] = swap ? a : b;
+        }
+      }
+      if constexpr (EPI == kEpiRope) {
+        if (rotate) x.rot[u].rotate(v, ea.round_first);
+      }
+      if constexpr (EXTRAS && EPI == kEpiNone) {
+        if (rw) {
+#pragma unroll
+          for (int e = 0; e < W; ++e) v[e] += (float)x.r[u][e];
+        }
+        if (accumulate) {
+#pragma unroll
+          for (int e = 0; e < W; ++e) v[e] += (float)x.c[u][e];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < W; ++e) {
+        if constexpr (C_F32) o[u][e] = v[e];
+        else o[u][e] = (bf16_t)v[e];
+      }
+    }
+    char* ci = cw + (int64_t)(16 * i) * ldc * ES;
+    auto put = [&](const piece_t& q, unsigned at, int row, int col) {
+      if (EDGE && !(row < rows && col < cols)) return;
+      *reinterpret_cast<piece_t*>(ci + at) = q;
+    };
+    if constexpr (PAIR) {
+#pragma unroll
+      for (int u = 0; u < U; u += 2) {
+        u32x4_t a = __builtin_bit_cast(u32x4_t, o[u]), b = __builtin_bit_cast(u32x4_t, o[u + 1]);
+        u32x4_t first, second;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          first[e] = __builtin_amdgcn_update_dpp((int)a[e], (int)b[e], 0x128, 0xf, 0xc, false);       // row_ror:8 into lanes 8..15 of 16
+          second[e] = __builtin_amdgcn_update_dpp((int)b[e], (int)a[e], 0x128, 0xf, 0x3, false);      // into lanes 0..7
+        }
+        put(__builtin_bit_cast(piece_t, first), off + CSTEP * u * ES, 16 * i + sr, sc + CSTEP * u);
+        put(__builtin_bit_cast(piece_t, second), off + (unsigned)(8 * ldc) * ES + CSTEP * u * ES, 16 * i + 8 + sr, sc + CSTEP * u);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) put(o[u], off + CSTEP * u * ES, 16 * i + sr, sc + CSTEP * u);
+    }
+  }
+}
+
+// the same whatever C looks like; everything asked here is wavefront-uniform
+template <bool C_F32, int FM, int FN, int EPI, int COLS>
+__device__ __forceinline__ void store_small(const f32x4_t (&acc)[FM][FN], unsigned char* lds2, int wave, int lane, int64_t mw, int64_t nw,
+                                            int64_t M, int64_t N, void* __restrict__ Cv, int64_t ldc, int accumulate,
+                                            const void* __restrict__ Rv, int64_t ldr, const EpiArgs& ea) {
+  constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
+  const bool aligned = EPI != kEpiNone || ((N & V) == 0 && (ldc & V) == 0 && (!Rv || (ldr & V) == 0));
+  const bool full = mw + 16 * FM <= M && nw + 16 * FN <= N;
+  constexpr bool X = EPI != kEpiNone;
+  if (!aligned) {
+    store_elements<C_F32, FM, FN, COLS>(acc, lds2, wave, lane, mw, nw, M, N, Cv, ldc, accumulate, Rv, ldr);
+  } else if (full && !X && !Rv && !accumulate) {
+    store_pieces<C_F32, FM, FN, EPI, COLS, false, X>(acc, lane, mw, nw, M, N, Cv, ldc, 0, nullptr, 0, ea);
+  } else if (full) {
+    store_pieces<C_F32, FM, FN, EPI, COLS, false, true>(acc, lane, mw, nw, M, N, Cv, ldc, accumulate, Rv, ldr, ea);
+  } else {
+    store_pieces<C_F32, FM, FN, EPI, COLS, true, true>(acc, lane, mw, nw, M, N, Cv, ldc, accumulate, Rv, ldr, ea);
+  }
+}
+
+// floats of a partial product's row: whole groups of 32 columns, inside which the places of two blocks are permuted
+__host__ __device__ inline int64_t part_row(int64_t N) { return (N + 31) / 32 * 32; }
 
 // one GEMM as the pipelined kernels take it
 struct GemmArgs {
@@ -441,10 +569,13 @@ struct GemmArgs {
   int tiles_m, tiles_n;
   EpiArgs epi;            // fused epilogues only
   // the contraction cut into `splits` ranges of k_chunk (a multiple of 64), one workgroup per (range, tile); range s writes its
-  // partial product, dense [M][N] fp32, to part + s * M * N, and a second kernel sums the ranges into C in a fixed order
+  // partial product, [M][part_ld] fp32, to part + s * M * part_ld, and a second kernel sums the ranges into C in a fixed order.  part_places: its columns
+  // lie as the accumulators hold them (block j, place), for fp32 stores of whole lines: the second kernel puts them in order.
   int splits;
   int64_t k_chunk;
   float* part;
+  int part_places;
+  __host__ __device__ int64_t part_ld() const { return part_row(N); }
 };
 
 // =============================================================================== 256 x 256 tiles
@@ -474,8 +605,10 @@ constexpr int kOp64 = 256 * BK64 * 2;            // one operand tile: 32 KiB; tw
 constexpr size_t kLds64 = 5 * (size_t)kOp64;     // 160 KiB
 
 // R = rows (KC) or columns (NC) of the operand tile: 256, or 128 / 64 in the small-tile kernel below.
-template <bool KC, int R>
+// COLS: which columns of the result a fragment stands for (B operands; A's are kColsPlain: rows).
+template <bool KC, int R, int COLS = kColsPlain>
 struct Operand64 {
+  static_assert(KC ? COLS != kColsSwapped : COLS != kColsPaired, "");
   static constexpr int NL = R / 32;                // direct loads per wavefront and step
   static constexpr int kBytes = R * BK64 * 2;      // one operand tile
   static constexpr int kRow = KC ? BK64 * 2 : R * 2;                 // bytes of a tile row
@@ -483,13 +616,17 @@ struct Operand64 {
   uint64_t base;          // tile origin at the current K position (bytes); wavefront-uniform
   uint64_t kstep;         // bytes per K step
   unsigned goff[NL];      // per-lane byte offsets of the loads of a step
-  // KC: rd[ks] for MFMA k-step ks, fragment i is 2048 i bytes further (16 rows)
+  // KC: rd[ks] for MFMA k-step ks, fragment i is frag_off(i) bytes further
   // NC: rd[i] for fragment i; MFMA k-step ks adds 32 tile rows, the second transposing read of a fragment 4
   unsigned rd[KC ? 2 : R / 32];
 
   // NC: which chunk of a k row sits where: k rows 0..3 and 8..11 x 32 bytes, what half a wavefront reads at a time, must fall into
   // different banks.  Rows of 512 and 256 bytes all start at the same bank; of two 128-byte rows the second starts half way.
-  static __device__ __forceinline__ int swz(int k) { return (R >= 128 ? (k & 3) << 2 : (k & 2) << 1) | (k >> 3 & 1) << 1; }
+  // kColsSwapped: four pieces of 8 bytes at a distance of 16, alternating halves: two rows interleave in 64 bytes.
+  static __device__ __forceinline__ int swz(int k) { return (R >= 128 ? (k & 3) << 2 : (k & 2) << 1) | (k >> 3 & 1) << (COLS == kColsSwapped ? 0 : 1); }
+  // KC: what the chunks of row r are swizzled by: the 16 rows a fragment reads (16 in a row, or 4 of every 8) must differ in it or in their lowest bit
+  static __device__ __forceinline__ int swr(int r) { return COLS == kColsPaired ? (r >> 1 & 1) | (r >> 3 & 3) << 1 : r >> 1 & 7; }
+  static constexpr __device__ __forceinline__ int frag_off(int i) { return COLS == kColsPaired ? 4096 * (i >> 1) + 512 * (i & 1) : 2048 * i; }
   static __device__ __forceinline__ int k_of_load(int i, int lane, int wave) { return kKpl * (4 * i + wave) + lane / (R / 8); }
 
   __device__ __forceinline__ void init(const bf16_t* mat, int64_t ld, int64_t origin, int64_t extent, int w0, int lane, int wave) {
@@ -501,12 +638,12 @@ struct Operand64 {
         const int rt = 8 * (4 * i + wave) + (lane >> 3);      // row of the tile this lane's 16 bytes land in
         int64_t r = rt;
         if (origin + r >= extent) r = extent - 1 - origin;
-        const int c = (lane & 7) ^ ((rt >> 1) & 7);
+        const int c = (lane & 7) ^ swr(rt);
         goff[i] = (unsigned)(r * ld * 2 + c * 16);
       }
-      const int r = w0 + (lane & 15);
+      const int r = w0 + (COLS == kColsPaired ? 8 * (lane >> 2 & 3) + (lane & 3) : lane & 15);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) rd[ks] = r * 128 + (((4 * ks + (lane >> 4)) ^ ((r >> 1) & 7)) << 4);
+      for (int ks = 0; ks < 2; ++ks) rd[ks] = r * 128 + (((4 * ks + (lane >> 4)) ^ swr(r)) << 4);
     } else {
       base = (uint64_t)(mat + origin);
       kstep = (uint64_t)ld * (BK64 * 2);
@@ -521,7 +658,7 @@ struct Operand64 {
       const int k = 8 * blk + (l16 >> 2);
 #pragma unroll
       for (int i = 0; i < R / 32; ++i) {
-        const int n = w0 + 16 * i + 4 * (l16 & 3);
+        const int q = l16 & 3, n = w0 + (COLS == kColsSwapped ? 32 * (i >> 1) + 8 * q + 4 * ((i ^ q) & 1) : 16 * i + 4 * q);
         rd[i] = k * kRow + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2;
       }
     }
@@ -530,7 +667,7 @@ struct Operand64 {
   __device__ __forceinline__ void advance() { base += kstep; }
   // the next loads are those of the last K step, of which only `rem` values of k exist (KC: a multiple of 8)
   __device__ __forceinline__ void clamp_tail(int rem, int64_t ld, int lane, int wave) {
-    const int c = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);        // KC: the chunk this lane loads, the same in all its loads
+    const int c = (lane & 7) ^ swr(8 * wave + (lane >> 3));        // KC: the chunk this lane loads, the same in all its loads
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       if (KC) {
@@ -545,7 +682,7 @@ struct Operand64 {
   static __device__ __forceinline__ void zero_tail(unsigned char* op, int rem, int tid) {
     if (KC) {
       for (int r = tid; r < R; r += kThreads)
-        for (int c = rem / 8; c < 8; ++c) *reinterpret_cast<u32x4_t*>(op + r * kRow + ((c ^ ((r >> 1) & 7)) << 4)) = u32x4_t{0u, 0u, 0u, 0u};
+        for (int c = rem / 8; c < 8; ++c) *reinterpret_cast<u32x4_t*>(op + r * kRow + ((c ^ swr(r)) << 4)) = u32x4_t{0u, 0u, 0u, 0u};
     } else {
       zero_lds(op, rem * kRow, kBytes, tid);
     }
@@ -554,7 +691,7 @@ struct Operand64 {
   static constexpr int kUnits = KC ? 1 : 2;
   __device__ __forceinline__ void frag_unit(bf16x8_t (&f)[R / 32], int u, int ks) const {
     if (KC) {
-      f[u] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>((size_t)(rd[ks] + 2048 * u));
+      f[u] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>((size_t)(rd[ks] + frag_off(u)));
     } else {
       typedef short s16x8_t __attribute__((ext_vector_type(8)));
       const int i = u / 2, r = u & 1;
@@ -565,7 +702,7 @@ struct Operand64 {
   }
   __device__ __forceinline__ bf16x8_t frag(const lds_u8_t* op, int i, int ks) const {
     if (KC) {
-      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(op + rd[ks] + 2048 * i);
+      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(op + rd[ks] + frag_off(i));
     } else {
       union { s16x4_t h[2]; bf16x8_t v; } u;
 #pragma unroll
@@ -606,8 +743,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
+  typedef Operand64<B_KC, 256> OpB;
   Operand64<A_KC, 256> oa;
-  Operand64<B_KC, 256> ob;
+  OpB ob;
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
 
@@ -646,7 +784,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
 
   bf16x8_t fa[2][8] = {}, fb[2][8] = {};     // [MFMA k-step of the stage][fragment]
   // the LDS instructions that read a k-step's fragments, the B fragments first: the first row of MFMAs needs them all
-  constexpr int UB = 8 * Operand64<B_KC, 256>::kUnits, UN = UB + 8 * Operand64<A_KC, 256>::kUnits;
+  constexpr int UB = 8 * OpB::kUnits, UN = UB + 8 * Operand64<A_KC, 256>::kUnits;
   auto read = [&](auto u, int ks) __attribute__((always_inline)) {
     if constexpr (u < UB) ob.frag_unit(fb[ks], u, ks);
     else oa.frag_unit(fa[ks], u - UB, ks);
@@ -720,9 +858,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   step(kt, std::false_type{}, std::false_type{});
 
   if (ga.splits > 1)
-    store_tile<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.part + (int64_t)sp * M * N, N, 0, nullptr, 0, ga.epi);
+    store_large<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, ga.part_ld(), ga.part + sp * M * ga.part_ld(), ga.part_ld(), 0, nullptr, 0, ga.epi);
   else
-    store_tile<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
+    store_large<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
 }
 
 // =============================================================================== small tiles
@@ -739,7 +877,8 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
   constexpr bool A_KC = (MODE != GEMM_TN);
   constexpr bool B_KC = (MODE == GEMM_NT);
   typedef Operand64<A_KC, 64 * TM> OpA;
-  typedef Operand64<B_KC, 64 * TN> OpB;
+  constexpr int COLS = C_F32 ? kColsPlain : B_KC ? kColsPaired : kColsSwapped;
+  typedef Operand64<B_KC, 64 * TN, COLS> OpB;
   constexpr int kStage = OpA::kBytes + OpB::kBytes, LPS = OpA::NL + OpB::NL;      // LPS: loads per wavefront and step
   const int64_t M = ga.M, N = ga.N, lda = ga.lda, ldb = ga.ldb;
   int64_t K = ga.K;
@@ -878,9 +1017,9 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
   step(kt, f0, f1, no, no);
   stage_barrier();                             // every wavefront has finished reading the ring: the epilogue stages through it
   if (ga.splits > 1)
-    store_checked<true, TM, TN>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, ga.part + (int64_t)sp * M * N, N, 0, nullptr, 0, ga.epi);
+    store_small<true, FM, FN, kEpiNone, kColsPlain>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, ga.part_ld(), ga.part + sp * M * ga.part_ld(), ga.part_ld(), 0, nullptr, 0, ga.epi);
   else
-    store_checked<C_F32, TM, TN, EPI>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
+    store_small<C_F32, FM, FN, EPI, COLS>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
 }
 
 // ---- kernels: one GEMM, or two independent ones in one grid (the first's tiles, then the second's)
@@ -923,6 +1062,7 @@ inline GemmArgs make_args(int64_t M, int64_t N, int64_t K, const void* A, int64_
   g.splits = 1;
   g.k_chunk = K;
   g.part = nullptr;
+  g.part_places = 0;
   return g;
 }
 
@@ -965,22 +1105,26 @@ int launch_small_dual(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st) {
 
 // C = rotated(part[0] + part[1] + ... + part[splits - 1]) + R + (accumulate ? C : 0), added in that order, the rotation where the GEMM asks for
 // it; two GEMMs' worth in one grid, 8 columns per thread (4 of fp32), blocks of the first first
-template <bool C_F32, bool ROPE>
+template <bool C_F32, bool ROPE, int COLS>
 __device__ __forceinline__ void reduce_parts(const GemmArgs& g, int64_t first, int64_t stride) {
+  static_assert((COLS == kColsPlain) == C_F32, "");
   constexpr int V = C_F32 ? 4 : 8;
   typedef typename std::conditional<C_F32, float, bf16_t>::type T;
-  const int64_t nv = g.N / V, total = g.M * nv;
+  const int64_t nv = g.N / V, total = g.M * nv, ld = g.part_ld();
   for (int64_t i = first; i < total; i += stride) {
     const int64_t r = i / nv, c = (i - r * nv) * V;
-    const float* pp = g.part + r * g.N + c;
+    const bool places = COLS != kColsPlain && g.part_places;
+    const int q = places ? (int)(c >> 3 & 3) : 0;                                 // l >> 4 of the lanes that held the 8 columns
+    const int half = places ? 16 : 4, odd = COLS == kColsSwapped ? q & 1 : 0;
+    const float* pp = g.part + r * ld + c - 4 * q;
     float v[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) v[e] = 0.f;
-    for (int s = 0; s < g.splits; ++s, pp += g.M * g.N) {
+    for (int s = 0; s < g.splits; ++s, pp += g.M * ld) {
 #pragma unroll
       for (int e = 0; e < V; e += 4) {
-        const f32x4_t q = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(pp + e));
-        v[e] += q[0]; v[e + 1] += q[1]; v[e + 2] += q[2]; v[e + 3] += q[3];
+        const f32x4_t q4 = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(pp + half * ((e >> 2) ^ odd)));
+        v[e] += q4[0]; v[e + 1] += q4[1]; v[e + 2] += q4[2]; v[e + 3] += q4[3];
       }
     }
     if constexpr (ROPE) {
@@ -1009,11 +1153,11 @@ __device__ __forceinline__ void reduce_parts(const GemmArgs& g, int64_t first, i
 }
 template <bool ROPE>
 __global__ void __launch_bounds__(256) splitk_reduce_bf16_kernel(GemmArgs g) {
-  reduce_parts<false, ROPE>(g, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+  reduce_parts<false, ROPE, kColsPaired>(g, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 __global__ void __launch_bounds__(256) splitk_reduce_dual_kernel(GemmArgs g0, GemmArgs g1, int n0) {
-  if ((int)blockIdx.x < n0) reduce_parts<true, false>(g0, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)n0 * 256);
-  else reduce_parts<false, false>(g1, (int64_t)(blockIdx.x - n0) * 256 + threadIdx.x, (int64_t)(gridDim.x - n0) * 256);
+  if ((int)blockIdx.x < n0) reduce_parts<true, false, kColsPlain>(g0, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)n0 * 256);
+  else reduce_parts<false, false, kColsSwapped>(g1, (int64_t)(blockIdx.x - n0) * 256 + threadIdx.x, (int64_t)(gridDim.x - n0) * 256);
 }
 inline int reduce_blocks(const GemmArgs& g, int v) {
   if (g.splits <= 1) return 0;
@@ -1106,7 +1250,7 @@ static GemmPlan work_out_plan(int np, const GemmProblem (&pr)[2], size_t max_flo
           p.splits[i] = (int)cdiv(pr[i].K, p.chunk[i]);
           // ranges of at least 256, and no cut where the tiles alone fill the chip twice
           ok = ok && p.splits[i] == want[i] && p.chunk[i] >= 256 && tiles[i] * want[i] < 4 * 256 * c.resident;
-          p.part_floats += (size_t)p.splits[i] * pr[i].M * pr[i].N;
+          p.part_floats += (size_t)p.splits[i] * pr[i].M * v2::part_row(pr[i].N);
           part_bytes += (double)pr[i].M * pr[i].N * (8.0 * p.splits[i] + pr[i].out_bytes);
         }
         if (!ok || p.part_floats > max_floats) continue;
@@ -1183,6 +1327,7 @@ static void apply_plan(v2::GemmArgs& g, const GemmPlan& p, int which, float* par
   g.splits = p.splits[which];
   g.k_chunk = p.chunk[which];
   g.part = g.splits > 1 ? part : nullptr;
+  g.part_places = p.tile != 256;      // large tiles store columns in order
 }
 
 template <int MODE, bool C_F32, int EPI = v2::kEpiNone>
@@ -1220,7 +1365,7 @@ int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, in
   v2::GemmArgs g1 = v2::make_args(M1, N1, K1, A1, lda1, B1, ldb1, C1, ldc1, 0, nullptr, 0);
   const GemmPlan p = plan_dual(M0, N0, K0, M1, N1, K1, scr.floats);
   apply_plan(g0, p, 0, scr.part);
-  apply_plan(g1, p, 1, scr.part + (p.splits[0] > 1 ? (size_t)p.splits[0] * M0 * N0 : 0));
+  apply_plan(g1, p, 1, scr.part + (p.splits[0] > 1 ? (size_t)p.splits[0] * M0 * v2::part_row(N0) : 0));
   int rc;
   if (p.tile == 256) rc = v2::launch_dual(g0, g1, st);
   else if (p.tile == 192) rc = v2::launch_small_dual<2, 4, 3>(g0, g1, st);
