@@ -3,9 +3,9 @@
 //
 // Layout of the operands: qkv [B*S, 3H] row-major, q | k | v, head h at columns h*128 of each part.
 //
-// All three kernels use v_mfma_f32_32x32x16_bf16.  Its accumulator layout gives lane l column
-// (l & 31) and rows 8(r/4) + 4(l>>5) + r%4 for register r; its operand layout gives lane l row or
-// column (l & 31) and k = 8(l>>5) + 0..7.  The kernels are arranged so that the accumulator of the
+// The backward kernels use v_mfma_f32_32x32x16_bf16, the forward v_mfma_f32_16x16x32_bf16 (LaneAddr16).  The former's
+// accumulator layout gives lane l column (l & 31) and rows 8(r/4) + 4(l>>5) + r%4 for register r; its operand layout gives lane l
+// row or column (l & 31) and k = 8(l>>5) + 0..7.  The kernels are arranged so that the accumulator of the
 // first product can be fed, converted to bf16 and nothing else, into the operand of the second:
 //
 //   forward / dQ kernel:  S^T[kv][q] = K Q^T  -> lane owns one query column: the softmax row
@@ -39,6 +39,10 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 __device__ __forceinline__ f32x16_t mfma(bf16x8_t a, bf16x8_t b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 // ---- row-major [rows][128] bf16 tile in LDS, 16-byte chunks XOR-swizzled ------------------------
@@ -117,6 +121,24 @@ struct LaneAddr {
     tr = rl * 256 + (swz(rl, d >> 3) << 4) + (d & 7) * 2;
   }
 };
+// ---- the fragments of 16x16x32 MFMAs from such a tile ------------------------------------------------
+// The operand layout gives lane l row or column l & 15 and k = 8 (l >> 4) + 0..7, the accumulator layout column l & 15 and rows
+// 4 (l >> 4) + r for register r.  Two accumulator blocks 16 rows apart, converted to bf16, are an operand whose k places
+// 8 g + 0..7 (g = l >> 4) stand for rows 4 g + 0..3 and 16 + 4 g + 0..3 of 32; the transposed fragment it meets is read in that order.
+// The swizzle differs from swz in which bit of the row goes where: a transposing read's half wavefront covers 8 rows x 2 chunks.
+__device__ __forceinline__ int swz16(int row, int chunk) { return chunk ^ (((row & 3) << 2) | (row >> 1 & 2) | (row >> 3 & 1)); }
+//   natural, rows 16 rb + (l & 15), d = 32 ks + 8 (l >> 4) + 0..7:     (nat ^ (ks << 6)) + 4096 rb
+//   transposed, d = 16 dt + (l & 15), rows 32 t + the 8 named above:   (tr ^ (dt << 5)) + 8192 t, and 4096 further
+struct LaneAddr16 {
+  unsigned nat, tr;
+  __device__ __forceinline__ void init(int lane) {
+    const int r = lane & 15, g = lane >> 4;
+    nat = r * 256 + (swz16(r, g) << 4);
+    const int rl = 4 * g + (r >> 2);
+    tr = rl * 256 + (swz16(rl, (r & 3) >> 1) << 4) + (r & 1) * 8;
+  }
+};
+
 // x ^ k.  OPAQUE: computed where it is written; as an opaque instruction the compiler can neither hoist the
 // eight variants of an address out of the loop nor keep them all alive (that costs the registers
 // that decide between two wavefronts per SIMD with or without spills in the dK/dV kernel)
@@ -144,6 +166,18 @@ __device__ __forceinline__ void frag_tr2x2(unsigned tr_t, bf16x8_t& f0, bf16x8_t
   }
   f0 = u0.v;
   if (OFF1 >= 0) f1 = u1.v;
+}
+
+// natural fragment ks of the 16 rows at byte offset OFF (4096 per 16 rows), transposed fragment dt of the 32 rows at OFF; nat_t / tr_t as above
+template <int KS, int OFF, bool OPAQUE = false> __device__ __forceinline__ bf16x8_t frag16_nat(unsigned nat_t) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>((size_t)(xor_here<(KS << 6), OPAQUE>(nat_t) + OFF));
+}
+template <int DT, int OFF, bool OPAQUE = false> __device__ __forceinline__ bf16x8_t frag16_tr(unsigned tr_t) {
+  union { s16x4_t h2[2]; bf16x8_t v; } u;
+  const unsigned a = xor_here<(DT << 5), OPAQUE>(tr_t) + OFF;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) u.h2[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(size_t)(a + 4096 * r));
+  return u.v;
 }
 
 __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& x, int t) {
@@ -190,13 +224,13 @@ constexpr int kTileBytes = 64 * D * 2;      // a [64][128] bf16 tile: 16 KiB
 // of a row-major matrix (row stride ld_bytes, rows clamped to limit-1) into the swizzled LDS tile at
 // lds_tile.  Piece j holds rows 4j..4j+3; lane l writes slot l&15 of row 4j + (l>>4), and slot s of
 // row r holds chunk s ^ swizzle(r): the lane fetches the chunk that belongs where it writes.
-template <int NW = kWaves8>
+template <int NW = kWaves8, bool M16 = false>
 __device__ __forceinline__ void tile_dma(uint64_t base, unsigned ld_bytes, int row0, int limit, unsigned lds_tile, int lane, int wave) {
 #pragma unroll
   for (int i = 0; i < 16 / NW; ++i) {
     const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
-    const int c = swz(r, lane & 15);
+    const int c = M16 ? swz16(r, lane & 15) : swz(r, lane & 15);
     int rg = row0 + r;
     rg = rg < limit ? rg : limit - 1;
     lds_dma16(base, (unsigned)rg * ld_bytes + c * 16, lds_tile + j * 1024);
@@ -259,6 +293,10 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // taken relative to the stale maximum (they stay below 2^kMaxSlack, harmless in fp32 / bf16) and
 // the 64 accumulator registers need no rescaling.  The final division by the row sum makes the
 // result independent of which maximum was used.
+//
+// 16x16x32 MFMAs draw less power per product than 32x32x16 ones (gemm_mfma.hip), and with them a row's scores lie in four lanes instead of two,
+// which only the rare raising of a maximum and the end need to bring together: 8 wavefronts, 8 x 8192 tokens of 16 heads 2219 -> 2134 us,
+// 16 x 4096 of 8 560 -> 543, 32768 of 32 7948 -> 7842; 4 wavefronts, bound by latency, 10.6 -> 10.9 at 2 x 333 of 2.
 constexpr float kMaxSlack = 8.0f;
 
 template <int NW>
@@ -270,9 +308,9 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
 
-  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  LaneAddr la;
+  LaneAddr16 la;
   la.init(lane);
   const int nqt = (S + BQ - 1) / BQ;
   int bh, rank;
@@ -290,26 +328,26 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   const int nkv = (kv_end + BKV - 1) / BKV;
   auto issue = [&](int t) {
     const unsigned st = lds0 + (t & (NS - 1)) * kStage;
-    tile_dma<NW>(kbase, ldb, t * BKV, S, st, lane, wave);
-    tile_dma<NW>(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
+    tile_dma<NW, true>(kbase, ldb, t * BKV, S, st, lane, wave);
+    tile_dma<NW, true>(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
   };
   for (int t = 0; t < NS - 2 && t < nkv; ++t) issue(t);
 
-  // Q as B operands, straight from global memory
-  bf16x8_t qf[8];
-  {
-    int row = q0w + (lane & 31);
+  // Q as B operands, straight from global memory: two blocks of 16 rows
+  bf16x8_t qf[2][4];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    int row = q0w + 16 * qb + (lane & 15);
     if (row >= S) row = S - 1;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_t*>(qbase + (int64_t)row * ld + 16 * ks + 8 * hh);
+    for (int ks = 0; ks < 4; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8_t*>(qbase + (int64_t)row * ld + 32 * ks + 8 * g);
   }
-  f32x16_t oacc[4];
-  float m = -INFINITY, l = 0.f;      // running maximum (scaled, log2 domain) and sum of this lane's half of the keys
+  f32x4_t oacc[2][8];
+  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};      // running maximum (scaled, log2 domain) and sum of this lane's quarter of the keys
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-  const int qidx = q0w + (lane & 31);
+    for (int dt = 0; dt < 8; ++dt) oacc[qb][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   // The two wavefronts of a SIMD (w and w + 4) run the three phases of a tile in different orders, so
   // that one's softmax arithmetic meets the other's MFMAs instead of both doing the same thing after
@@ -317,10 +355,10 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   // late ones 4..7 start a period with the O += V^T P of the previous tile (its P waits in registers,
   // its V stays in the ring one period longer, which is why tiles are issued two ahead, not three).
   const bool late = NW == kWaves8 && wave >= NW / 2;       // 4 wavefronts have a SIMD each
-  bf16x8_t pf[2][2];
+  bf16x8_t pf[2][2];                                       // [16 rows][32 keys]
   bool pend = false;
   unsigned pend_tr = 0;
-  // O^T += V^T P^T: 16 MFMAs, fragment i = (kb, t, dt) = (i / 8, (i / 4) % 2, i % 4).  The fragment reads run kAhead MFMAs
+  // O^T += V^T P^T: 32 MFMAs, fragment i = (t, dt) = (i / 8, i % 8) for both blocks of rows.  The fragment reads run kAhead fragments
   // ahead of their use, in registers of their own: an LDS read takes several MFMA issue slots to return, and a read placed
   // right in front of its MFMA leaves the matrix pipe idle for that long, sixteen times per tile.  The scheduling barriers
   // keep the compiler from moving the reads back next to their use.
@@ -329,8 +367,7 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
     bf16x8_t vfr[16];
     auto rd = [&](auto i_c) {
       TAW_CONST(i, i_c);
-      bf16x8_t unused;
-      frag_tr2x2<(i / 4) % 2, i % 4, kTileBytes + (i / 8) * 8192, -1>(tr_t, vfr[i], unused);
+      vfr[i] = frag16_tr<i % 8, kTileBytes + (i / 8) * 8192>(tr_t);
     };
     static_for<kAhead>(rd);
     __builtin_amdgcn_s_setprio(1);
@@ -338,7 +375,8 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
       TAW_CONST(i, i_c);
       if constexpr (i + kAhead < 16) rd(std::integral_constant<int, i + kAhead>{});
       __builtin_amdgcn_sched_barrier(0);
-      oacc[i % 4] = mfma(vfr[i], pf[i / 8][(i / 4) % 2], oacc[i % 4]);
+      oacc[0][i % 8] = mfma16(vfr[i], pf[0][i / 8], oacc[0][i % 8]);
+      oacc[1][i % 8] = mfma16(vfr[i], pf[1][i / 8], oacc[1][i % 8]);
       __builtin_amdgcn_sched_barrier(0);
     });
     __builtin_amdgcn_s_setprio(0);
@@ -362,16 +400,18 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
     const unsigned so = lds0 + (j & (NS - 1)) * kStage;
     const unsigned nat_t = la.nat + so, tr_t = la.tr + so;
 
-    // S^T = K Q^T: 16 MFMAs in two independent accumulation chains (the two 32-key halves of the tile), issued alternately;
-    // fragment reads kAhead MFMAs ahead, as in pv
-    f32x16_t s[2];
+    // S^T = K Q^T: 32 MFMAs in eight accumulation chains (16 rows x 16 keys), fragment i = (ks, kb) = (i / 4, i % 4) for both blocks of rows;
+    // fragment reads kAhead fragments ahead, as in pv
+    f32x4_t s[2][4];
     {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { s[0][r] = 0.f; s[1][r] = 0.f; }      // (folded into the first MFMA of each chain as the constant 0)
+      for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) s[qb][kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};      // (folded into the first MFMA of each chain as the constant 0)
       bf16x8_t kfr[16];
       auto rd = [&](auto i_c) {
         TAW_CONST(i, i_c);
-        kfr[i] = frag_nat2<i / 2, (i % 2) * 8192>(nat_t);
+        kfr[i] = frag16_nat<i / 4, (i % 4) * 4096>(nat_t);
       };
       static_for<kAhead>(rd);
       __builtin_amdgcn_s_setprio(1);
@@ -379,56 +419,70 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
         TAW_CONST(i, i_c);
         if constexpr (i + kAhead < 16) rd(std::integral_constant<int, i + kAhead>{});
         __builtin_amdgcn_sched_barrier(0);
-        s[i % 2] = mfma(kfr[i], qf[i / 2], s[i % 2]);
+        s[0][i % 4] = mfma16(kfr[i], qf[0][i / 4], s[0][i % 4]);
+        s[1][i % 4] = mfma16(kfr[i], qf[1][i / 4], s[1][i % 4]);
         __builtin_amdgcn_sched_barrier(0);
       });
       __builtin_amdgcn_s_setprio(0);
     }
     if (kv0 + BKV - 1 > q0w) {                         // tile crosses the diagonal (or the end of the sequence)
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kv = kv0 + kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-          s[kb][r] = kv > qidx ? -INFINITY : s[kb][r];
-        }
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int kv = kv0 + kb * 16 + 4 * g + r;
+            s[qb][kb][r] = kv > q0w + 16 * qb + (lane & 15) ? -INFINITY : s[qb][kb][r];
+          }
     }
     // v_max3_f32 by name: fmaxf on MFMA results makes the compiler quiet possible signalling NaNs first, one extra
     // instruction per score, and pair the maxima up with two-operand instructions (58 instructions for 32 scores instead of 16)
-    float mx = max3(s[0][0], s[1][0], s[0][0]);
+    float mx[2];
 #pragma unroll
-    for (int r = 1; r < 16; ++r) mx = max3(mx, s[0][r], s[1][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;      // (v_permlane32_swap instead of this LDS round trip measured 3 % slower)
-    if (__builtin_amdgcn_ballot_w64(mx > m + kMaxSlack) != 0) {    // wavefront-uniform: some row's maximum moved far
-      const float m_new = fmaxf(m, mx);
-      const float alpha = fast_exp2(m - m_new);        // m = -inf on the first tile: alpha = 0, the accumulators are 0
-      m = m_new;
-      l *= alpha;
+    for (int qb = 0; qb < 2; ++qb) {
+      mx[qb] = max3(s[qb][0][0], s[qb][0][1], s[qb][0][0]);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+      for (int i = 2; i < 16; i += 2) mx[qb] = max3(mx[qb], s[qb][i / 4][i % 4], s[qb][i / 4][i % 4 + 1]);
+      mx[qb] *= c;
+    }
+    // wavefront-uniform: some row's maximum moved far.  Each lane asks for its own quarter of the keys: only where one says yes
+    // are the quarters of a row brought together.
+    if (__builtin_amdgcn_ballot_w64(mx[0] > m[0] + kMaxSlack || mx[1] > m[1] + kMaxSlack) != 0) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+      for (int qb = 0; qb < 2; ++qb) {
+        float x = fmaxf(mx[qb], __shfl_xor(mx[qb], 16, 64));
+        x = fmaxf(x, __shfl_xor(x, 32, 64));
+        const float m_new = fmaxf(m[qb], x);
+        const float alpha = fast_exp2(m[qb] - m_new);    // m = -inf on the first tile: alpha = 0, the accumulators are 0
+        m[qb] = m_new;
+        l[qb] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) oacc[qb][dt] *= alpha;
+      }
     }
     // probabilities, packed to bf16 in pairs; the row sum is taken from the packed pairs (one dot
     // product instruction per pair): the sum of exactly what the second product multiplies by
-    float rs = 0.f;
     const bf16x2_t ones = {(bf16_t)1.0f, (bf16_t)1.0f};
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int qb = 0; qb < 2; ++qb) {
+      float rs = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         u32x4_t w;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float p0 = fast_exp2(__builtin_fmaf(s[kb][8 * t + 2 * j], c, -m));
-          const float p1 = fast_exp2(__builtin_fmaf(s[kb][8 * t + 2 * j + 1], c, -m));
+          const f32x4_t& x = s[qb][2 * t + j / 2];
+          const float p0 = fast_exp2(__builtin_fmaf(x[2 * (j & 1)], c, -m[qb]));
+          const float p1 = fast_exp2(__builtin_fmaf(x[2 * (j & 1) + 1], c, -m[qb]));
           const bf16x2_t pk = {(bf16_t)p0, (bf16_t)p1};
           rs = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, rs, false);
           w[j] = __builtin_bit_cast(unsigned, pk);
         }
-        pf[kb][t] = __builtin_bit_cast(bf16x8_t, w);
+        pf[qb][t] = __builtin_bit_cast(bf16x8_t, w);
       }
-    l += rs;
+      l[qb] += rs;
+    }
     if (late) {
       pend = true;
       pend_tr = tr_t;
@@ -442,20 +496,20 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   // ---- epilogue: O^T accumulators -> [q][136] bf16 staging in LDS -> coalesced rows of o
   constexpr int OLD = 136;
   bf16_t* ob = reinterpret_cast<bf16_t*>(lds_raw) + wave * (WQ * OLD);
-  {
-    const float lsum = l + __shfl_xor(l, 32, 64);
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    float lsum = l[qb] + __shfl_xor(l[qb], 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
     const float inv = 1.0f / lsum;
-    const int qrow = lane & 31;
+    const int qrow = 16 * qb + (lane & 15);
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < 8; ++dt) {
+      bf16x4_t pk;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4_t pk;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) pk[e] = (bf16_t)(oacc[dt][4 * r4 + e] * inv);
-        *reinterpret_cast<bf16x4_t*>(ob + qrow * OLD + dt * 32 + 8 * r4 + 4 * hh) = pk;
-      }
-    if (hh == 0 && qidx < S) lse[((int64_t)b * nh + h) * S + qidx] = m * kLn2 + logf(lsum);
+      for (int e = 0; e < 4; ++e) pk[e] = (bf16_t)(oacc[qb][dt][e] * inv);
+      *reinterpret_cast<bf16x4_t*>(ob + qrow * OLD + dt * 16 + 4 * g) = pk;
+    }
+    if (g == 0 && q0w + qrow < S) lse[((int64_t)b * nh + h) * S + q0w + qrow] = m[qb] * kLn2 + logf(lsum);
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this wavefront's LDS writes are done
   __builtin_amdgcn_wave_barrier();
