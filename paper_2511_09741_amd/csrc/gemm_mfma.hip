@@ -551,8 +551,9 @@ __device__ __forceinline__ void store_small(const f32x4_t (&acc)[FM][FN], unsign
   }
 }
 
-// floats of a partial product's row: whole groups of 32 columns, inside which the places of two blocks are permuted
-__host__ __device__ inline int64_t part_row(int64_t N) { return (N + 31) / 32 * 32; }
+// floats of a partial product's row.  Of a bf16 result: whole groups of 32 columns, inside which the places of two blocks are permuted; the partial
+// products of an fp32 result lie as the result does
+__host__ __device__ inline int64_t part_row(int64_t N, bool c_f32) { return c_f32 ? N : (N + 31) / 32 * 32; }
 
 // one GEMM as the pipelined kernels take it
 struct GemmArgs {
@@ -569,13 +570,12 @@ struct GemmArgs {
   int tiles_m, tiles_n;
   EpiArgs epi;            // fused epilogues only
   // the contraction cut into `splits` ranges of k_chunk (a multiple of 64), one workgroup per (range, tile); range s writes its
-  // partial product, [M][part_ld] fp32, to part + s * M * part_ld, and a second kernel sums the ranges into C in a fixed order.  part_places: its columns
+  // partial product, [M][part_row] fp32, to part + s * M * part_row, and a second kernel sums the ranges into C in a fixed order.  part_places: its columns
   // lie as the accumulators hold them (block j, place), for fp32 stores of whole lines: the second kernel puts them in order.
   int splits;
   int64_t k_chunk;
   float* part;
   int part_places;
-  __host__ __device__ int64_t part_ld() const { return part_row(N); }
 };
 
 // =============================================================================== 256 x 256 tiles
@@ -858,7 +858,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   step(kt, std::false_type{}, std::false_type{});
 
   if (ga.splits > 1)
-    store_large<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, ga.part_ld(), ga.part + sp * M * ga.part_ld(), ga.part_ld(), 0, nullptr, 0, ga.epi);
+    store_large<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, part_row(N, C_F32), ga.part + sp * M * part_row(N, C_F32), part_row(N, C_F32), 0, nullptr, 0, ga.epi);
   else
     store_large<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
 }
@@ -1017,7 +1017,8 @@ __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
   step(kt, f0, f1, no, no);
   stage_barrier();                             // every wavefront has finished reading the ring: the epilogue stages through it
   if (ga.splits > 1)
-    store_small<true, FM, FN, kEpiNone, kColsPlain>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, ga.part_ld(), ga.part + sp * M * ga.part_ld(), ga.part_ld(), 0, nullptr, 0, ga.epi);
+    store_small<true, FM, FN, kEpiNone, kColsPlain>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, part_row(N, C_F32), ga.part + sp * M * part_row(N, C_F32),
+                                                        part_row(N, C_F32), 0, nullptr, 0, ga.epi);
   else
     store_small<C_F32, FM, FN, EPI, COLS>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
 }
@@ -1110,7 +1111,7 @@ __device__ __forceinline__ void reduce_parts(const GemmArgs& g, int64_t first, i
   static_assert((COLS == kColsPlain) == C_F32, "");
   constexpr int V = C_F32 ? 4 : 8;
   typedef typename std::conditional<C_F32, float, bf16_t>::type T;
-  const int64_t nv = g.N / V, total = g.M * nv, ld = g.part_ld();
+  const int64_t nv = g.N / V, total = g.M * nv, ld = part_row(g.N, C_F32);
   for (int64_t i = first; i < total; i += stride) {
     const int64_t r = i / nv, c = (i - r * nv) * V;
     const bool places = COLS != kColsPlain && g.part_places;
@@ -1250,7 +1251,7 @@ static GemmPlan work_out_plan(int np, const GemmProblem (&pr)[2], size_t max_flo
           p.splits[i] = (int)cdiv(pr[i].K, p.chunk[i]);
           // ranges of at least 256, and no cut where the tiles alone fill the chip twice
           ok = ok && p.splits[i] == want[i] && p.chunk[i] >= 256 && tiles[i] * want[i] < 4 * 256 * c.resident;
-          p.part_floats += (size_t)p.splits[i] * pr[i].M * v2::part_row(pr[i].N);
+          p.part_floats += (size_t)p.splits[i] * pr[i].M * v2::part_row(pr[i].N, pr[i].out_bytes == 4);
           part_bytes += (double)pr[i].M * pr[i].N * (8.0 * p.splits[i] + pr[i].out_bytes);
         }
         if (!ok || p.part_floats > max_floats) continue;
@@ -1365,7 +1366,7 @@ int launch_gemm_mfma_dual(int64_t M0, int64_t N0, int64_t K0, const void* A0, in
   v2::GemmArgs g1 = v2::make_args(M1, N1, K1, A1, lda1, B1, ldb1, C1, ldc1, 0, nullptr, 0);
   const GemmPlan p = plan_dual(M0, N0, K0, M1, N1, K1, scr.floats);
   apply_plan(g0, p, 0, scr.part);
-  apply_plan(g1, p, 1, scr.part + (p.splits[0] > 1 ? (size_t)p.splits[0] * M0 * v2::part_row(N0) : 0));
+  apply_plan(g1, p, 1, scr.part + (p.splits[0] > 1 ? (size_t)p.splits[0] * M0 * v2::part_row(N0, true) : 0));
   int rc;
   if (p.tile == 256) rc = v2::launch_dual(g0, g1, st);
   else if (p.tile == 192) rc = v2::launch_small_dual<2, 4, 3>(g0, g1, st);
