@@ -117,7 +117,7 @@ struct Ctx {       // saved by the forward for the backward; scr: partial produc
   void *xn, *qkv, *o, *h, *hn, *gu, *a; float *lse, *r1, *r2; GemmScratch scr; size_t bytes;
 };
 struct Work {      // scratch of the backward
-  void *da, *dgu, *dhn, *dh, *dO, *dqkv, *dxn; float *D, *partials; GemmScratch scr; size_t bytes;
+  void *da, *dgu, *dhn, *dh, *dO, *dqkv, *dxn; float *D, *partials[2]; GemmScratch scr; size_t bytes;
 };
 
 // which form of the MFMA attention backward the layer runs
@@ -152,7 +152,7 @@ static Work carve_work(const taw_layer_desc* d, void* base) {
   w.da = c.take(T * I * e); w.dgu = c.take(T * 2 * I * e); w.dhn = c.take(T * H * e); w.dh = c.take(T * H * e);
   w.dO = c.take(T * H * e); w.dqkv = c.take(T * 3 * H * e); w.dxn = c.take(T * H * e);
   w.D = (float*)c.take(attn_bwd_mfma_scratch_floats(d->B, d->S, d->n_heads, attn_mfma_supported(d->dtype, d->S, d->n_heads, d->head_dim) ? attn_bwd_form_of(d) : ATTN_BWD_SPLIT) * 4);   // covers the generic kernel's B*nh*S too
-  w.partials = (float*)c.take((size_t)rmsnorm_bwd_partial_rows() * H * 4);
+  for (float*& p : w.partials) p = (float*)c.take((size_t)rmsnorm_bwd_partial_rows() * H * 4);
   w.scr.floats = 0;
   if (gemms_may_be_cut(d)) {
     const int64_t t = (int64_t)T, h = (int64_t)H, i = (int64_t)I;
@@ -319,8 +319,8 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
   }
   // gu = hn Wgu^T :  dhn = dgu Wgu ;  G.Wgu (+)= dgu^T hn
   TAW_LAUNCH(linear_bwd(p, dt, T, 2 * I, H, w.dgu, at(W_chunk, L.w_gate_up, dt), c.hn, w.dhn, G_shard + L.w_gate_up, acc, scr, st), "gemm dhn, G.w_gate_up");
-  // hn = rmsnorm(h) :  dh = dy + rmsnorm_bwd(dhn) ;  G.gamma_mlp
-  TAW_LAUNCH(launch_rmsnorm_bwd(dt, T, (int)H, w.dhn, c.h, c.r2, at(W_chunk, L.gamma_mlp, dt), dy, w.dh, G_shard + L.gamma_mlp, acc, w.partials, st), "rmsnorm_bwd(mlp)");
+  // hn = rmsnorm(h) :  dh = dy + rmsnorm_bwd(dhn)
+  TAW_LAUNCH(launch_rmsnorm_bwd(dt, T, (int)H, w.dhn, c.h, c.r2, at(W_chunk, L.gamma_mlp, dt), dy, w.dh, nullptr, acc, w.partials[0], st), "rmsnorm_bwd(mlp)");
   // h = x + o Wo^T :  do = dh Wo ;  G.Wo (+)= dh^T o
   TAW_LAUNCH(linear_bwd(p, dt, T, H, H, w.dh, at(W_chunk, L.w_o, dt), c.o, w.dO, G_shard + L.w_o, acc, scr, st), "gemm do, G.w_o");
   // attention backward
@@ -334,8 +334,9 @@ extern "C" int taw_layer_bwd(const taw_layer_desc* desc, const void* W_chunk, co
   }
   // qkv = xn Wqkv^T :  dxn = dqkv Wqkv ;  G.Wqkv (+)= dqkv^T xn
   TAW_LAUNCH(linear_bwd(p, dt, T, 3 * H, H, w.dqkv, at(W_chunk, L.w_qkv, dt), c.xn, w.dxn, G_shard + L.w_qkv, acc, scr, st), "gemm dxn, G.w_qkv");
-  // xn = rmsnorm(x) :  dx = dh + rmsnorm_bwd(dxn) ;  G.gamma_attn
-  TAW_LAUNCH(launch_rmsnorm_bwd(dt, T, (int)H, w.dxn, x, c.r1, at(W_chunk, L.gamma_attn, dt), w.dh, dx, G_shard + L.gamma_attn, acc, w.partials, st), "rmsnorm_bwd(attn)");
+  // xn = rmsnorm(x) :  dx = dh + rmsnorm_bwd(dxn) ;  then G.gamma_mlp, G.gamma_attn
+  TAW_LAUNCH(launch_rmsnorm_bwd(dt, T, (int)H, w.dxn, x, c.r1, at(W_chunk, L.gamma_attn, dt), w.dh, dx, nullptr, acc, w.partials[1], st), "rmsnorm_bwd(attn)");
+  TAW_LAUNCH(launch_rmsnorm_dgamma_pair(T, (int)H, w.partials[0], G_shard + L.gamma_mlp, w.partials[1], G_shard + L.gamma_attn, acc, st), "G.gamma_mlp, G.gamma_attn");
   return TAW_OK;
 }
 

@@ -31,10 +31,13 @@ int launch_rmsnorm_fwd(int dtype, int64_t T, int H, const void* x, const void* g
                        void* out, float* r, hipStream_t st);
 // number of fp32 partial-sum rows (each H wide) the backward needs as scratch
 int rmsnorm_bwd_partial_rows();
-// dz = (dres ? dres : 0) + rmsnorm_bwd(dout);  dgamma (=|+=) column sums
+// dz = (dres ? dres : 0) + rmsnorm_bwd(dout);  dgamma (=|+=) column sums.  dgamma == nullptr: they stay in `partials`, for
+// launch_rmsnorm_dgamma_pair, which sums two such calls' of the same T and H
 int launch_rmsnorm_bwd(int dtype, int64_t T, int H, const void* dout, const void* z, const float* r,
                        const void* gamma, const void* dres, void* dz, float* dgamma, int accumulate,
                        float* partials, hipStream_t st);
+int launch_rmsnorm_dgamma_pair(int64_t T, int H, const float* partials0, float* dgamma0, const float* partials1, float* dgamma1, int accumulate,
+                               hipStream_t st);
 int launch_rope_table(int S, int head_dim, double theta, float* table, hipStream_t st);
 // rotates columns [0, ncols) of the [B*S, ld] matrix z in place; column j belongs to pair (j % d)/2
 int launch_rope(int dtype, int B, int S, int ncols, int head_dim, void* z, int64_t ld,
