@@ -297,7 +297,7 @@ def test_weight_stage_double_buffer(taw):
 
 
 # ----------------------------------------------------------------------------- MFMA kernels (bf16)
-# 1, 2, 3 and many steps of K (64 deep; 32 in the TN form's large tile), the last one whole or not.  NT with bf16 results takes the tile its
+# 1, 2, 3 and many steps of K (64 deep), the last one whole or not.  NT with bf16 results takes the tile its
 # plan names, everything else 256 x 256
 MFMA_GEMM_SHAPES = {
     0: [(256, 256, 64), (8, 8, 8), (300, 520, 136), (257, 263, 72), (1000, 264, 4104), (512, 768, 1024), (1, 3, 8),
@@ -351,6 +351,35 @@ def test_attention_mfma(taw, B, S, nh, form):
 def test_attention_mfma_peaked_scores(taw, form):
     """Scores of order 10: the running maximum moves a lot between key tiles."""
     _attn_case(taw, I.BF16, 1, 700, 2, 128, taw.TAW_IMPL_MFMA, seed=9, scale=3.0, bwd_impl=BWD_FORMS[form])
+
+
+@pytest.mark.parametrize("B", [1, 75])                    # 128-row workgroups of 4 wavefronts; 256-row ones of 8
+@pytest.mark.parametrize("quarter", [0, 1, 2, 3])
+@pytest.mark.parametrize("rise", [5.0, 7.9, 12.0, 150.0])
+def test_attention_mfma_maximum_raised_by_one_quarter(taw, B, quarter, rise):
+    """A row's scores of a key tile lie in four lanes, keys 4 q ... 4 q + 3 of every 16 in quarter q.  Here only one quarter's lie above the running maximum:
+    by `rise` (log2) more in every tile, so it is raised in none, some or all of them.  Probabilities are rounded to bf16 (2^-9 of each) in
+    the sum as in the product, and the result once more: |o - exact| <= 3 * 2^-9 max |v|, and |lse - exact| <= 2^-8."""
+    import torch
+    S, nh, d = 333, 4, 128
+    H = nh * d
+    g = torch.Generator(device="cuda").manual_seed(quarter)
+    qkv = torch.empty(B, S, 3, nh, d, device="cuda").normal_(0.0, 0.1, generator=g)
+    qkv[:, :, 2].normal_(0.0, 1.0, generator=g)
+    kv = torch.arange(S, device="cuda")
+    qkv[:, :, 0, :, 0] = 1.0
+    up = torch.where((kv // 4 % 4 == quarter) & (kv % 4 == 1), (kv // 64 + 1.0) * rise * d ** 0.5 * np.log(2.0), 0.0)
+    qkv[:, :, 1, :, 0] = up[None, :, None]
+    qkv = qkv.bfloat16()
+    o = torch.full((B, S, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B, nh, S), float("nan"), dtype=torch.float32, device="cuda")
+    taw.taw_op_attn_fwd(I.BF16, B, S, nh, d, qkv, o, lse, taw.TAW_IMPL_MFMA)
+    q, k, v = qkv.double().permute(2, 0, 3, 1, 4).contiguous()
+    scores = (q @ k.transpose(-1, -2).contiguous()) * d ** -0.5
+    scores.masked_fill_(kv[None, :] > kv[:, None], -float("inf"))
+    ref = (torch.softmax(scores, -1) @ v).permute(0, 2, 1, 3).reshape(B, S, H)
+    assert float((o.double() - ref).abs().max()) <= 3 * 2.0 ** -9 * float(v.abs().max())
+    assert float((lse.double() - torch.logsumexp(scores, -1)).abs().max()) <= 2.0 ** -8
 
 
 @pytest.mark.parametrize("form", ["fused", "stored"])
@@ -421,6 +450,27 @@ def test_gemm_mfma_edges_of_large_tiles(taw, mode, f32, M, N, pad):
         want = ref + 7.0 * acc + (R[:, :N].double() if residual else 0.0)
         err = float((C[:M, :N].double() - want).abs().max() / want.abs().max())
         assert err < (2e-6 if f32 else 2.0 ** -8), (residual, acc, err)
+        assert bool((C[M:] == 7).all()) and bool((C[:, N:] == 7).all())
+
+
+@pytest.mark.parametrize("M,N", [(1, 1), (63, 8), (65, 24), (33, 40), (129, 130), (70, 63), (66, 263)])
+@pytest.mark.parametrize("pad", [0, 8, 3])
+def test_gemm_mfma_edges_of_small_tiles(taw, M, N, pad):
+    """64 x 64 tiles are stored from the accumulators, 8 columns of bf16 from a lane and a line from a pair of lanes: results that end inside a lane's columns,
+    a pair's and a group of 32, with aligned and unaligned rows; nothing outside them touched.  Bounds as in test_linear_tile_shapes."""
+    import torch
+    K = 136
+    p = taw.taw_diag_gemm_plan(0, M, N, K)
+    assert (p["tile_m"], p["tile_n"]) == (64, 64)
+    A, B = I.device_normal((M, K), seed=1, std=1.0), I.device_normal((N, K), seed=2, std=1.0)
+    ref = A.double() @ B.double().t()
+    for residual, acc in ((0, 0), (1, 0), (0, 1), (1, 1)):
+        C = torch.full((M + 2, N + pad), 7.0, dtype=torch.bfloat16, device="cuda")
+        R = I.device_normal((M, N + pad), seed=5, std=1.0) if residual else None
+        taw.taw_op_gemm(I.BF16, 0, M, N, K, A, K, B, K, C, N + pad, I.BF16, acc, R, N + pad, taw.TAW_IMPL_MFMA)
+        want = ref + 7.0 * acc + (R[:, :N].double() if residual else 0.0)
+        err = float((C[:M, :N].double() - want).abs().max() / want.abs().max())
+        assert err < 2.0 ** -8, (residual, acc, err)
         assert bool((C[M:] == 7).all()) and bool((C[:, N:] == 7).all())
 
 
