@@ -3,7 +3,7 @@
 //
 // Layout of the operands: qkv [B*S, 3H] row-major, q | k | v, head h at columns h*128 of each part.
 //
-// The backward kernels use v_mfma_f32_32x32x16_bf16, the forward v_mfma_f32_16x16x32_bf16 (LaneAddr16).  The former's
+// The forward and the dK/dV kernel use v_mfma_f32_16x16x32_bf16 (LaneAddr16), the others v_mfma_f32_32x32x16_bf16.  The latter's
 // accumulator layout gives lane l column (l & 31) and rows 8(r/4) + 4(l>>5) + r%4 for register r; its operand layout gives lane l
 // row or column (l & 31) and k = 8(l>>5) + 0..7.  The kernels are arranged so that the accumulator of the
 // first product can be fed, converted to bf16 and nothing else, into the operand of the second:
@@ -139,6 +139,21 @@ struct LaneAddr16 {
   }
 };
 
+// The dK/dV kernel's query rows: fragment rb of a 32-row group has rows 8 rb + 0..7 and 8 rb + 16..23, so that a lane's registers of both
+// blocks are rows 16 (g >> 1) + 4 (g & 1) + {0..3, 8..11}, the pieces stored dS consists of.  Row bit 4 takes bit 3's place in the swizzle.
+__device__ __forceinline__ int swz16q(int row, int chunk) { return chunk ^ (((row & 3) << 2) | (row >> 1 & 2) | (row >> 4 & 1)); }
+//   natural, the rows above, d = 32 ks + 8 g + 0..7:                    (nat ^ (ks << 6)) + 2048 rb
+//   transposed, d = 16 dt + (l & 15), the lane's 8 rows:                (tr ^ (dt << 5)), and 2048 further
+struct LaneAddr16Q {
+  unsigned nat, tr;
+  __device__ __forceinline__ void init(int lane) {
+    const int r = lane & 15, g = lane >> 4;
+    const int rn = 16 * (r >> 3) + (r & 7), rl = 16 * (g >> 1) + 4 * (g & 1) + (r >> 2);
+    nat = rn * 256 + (swz16q(rn, g) << 4);
+    tr = rl * 256 + (swz16q(rl, (r & 3) >> 1) << 4) + (r & 1) * 8;
+  }
+};
+
 // x ^ k.  OPAQUE: computed where it is written; as an opaque instruction the compiler can neither hoist the
 // eight variants of an address out of the loop nor keep them all alive (that costs the registers
 // that decide between two wavefronts per SIMD with or without spills in the dK/dV kernel)
@@ -177,6 +192,15 @@ template <int DT, int OFF, bool OPAQUE = false> __device__ __forceinline__ bf16x
   const unsigned a = xor_here<(DT << 5), OPAQUE>(tr_t) + OFF;
 #pragma unroll
   for (int r = 0; r < 2; ++r) u.h2[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(size_t)(a + 4096 * r));
+  return u.v;
+}
+
+// the transposed fragment of the 32 query rows at OFF; a: LaneAddr16Q's tr plus the stage, ^ (dt << 5)
+template <int OFF> __device__ __forceinline__ bf16x8_t frag16q_tr(unsigned a) {
+  union { s16x4_t h2[2]; bf16x8_t v; } u;
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+    u.h2[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(size_t)(a + OFF + 2048 * r));
   return u.v;
 }
 
@@ -224,13 +248,14 @@ constexpr int kTileBytes = 64 * D * 2;      // a [64][128] bf16 tile: 16 KiB
 // of a row-major matrix (row stride ld_bytes, rows clamped to limit-1) into the swizzled LDS tile at
 // lds_tile.  Piece j holds rows 4j..4j+3; lane l writes slot l&15 of row 4j + (l>>4), and slot s of
 // row r holds chunk s ^ swizzle(r): the lane fetches the chunk that belongs where it writes.
-template <int NW = kWaves8, bool M16 = false>
+// SW: the tile's swizzle, 0 swz, 1 swz16, 2 swz16q
+template <int NW = kWaves8, int SW = 0>
 __device__ __forceinline__ void tile_dma(uint64_t base, unsigned ld_bytes, int row0, int limit, unsigned lds_tile, int lane, int wave) {
 #pragma unroll
   for (int i = 0; i < 16 / NW; ++i) {
     const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
-    const int c = M16 ? swz16(r, lane & 15) : swz(r, lane & 15);
+    const int c = SW == 1 ? swz16(r, lane & 15) : SW == 2 ? swz16q(r, lane & 15) : swz(r, lane & 15);
     int rg = row0 + r;
     rg = rg < limit ? rg : limit - 1;
     lds_dma16(base, (unsigned)rg * ld_bytes + c * 16, lds_tile + j * 1024);
@@ -328,8 +353,8 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   const int nkv = (kv_end + BKV - 1) / BKV;
   auto issue = [&](int t) {
     const unsigned st = lds0 + (t & (NS - 1)) * kStage;
-    tile_dma<NW, true>(kbase, ldb, t * BKV, S, st, lane, wave);
-    tile_dma<NW, true>(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
+    tile_dma<NW, 1>(kbase, ldb, t * BKV, S, st, lane, wave);
+    tile_dma<NW, 1>(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
   };
   for (int t = 0; t < NS - 2 && t < nkv; ++t) issue(t);
 
@@ -579,6 +604,49 @@ __device__ __forceinline__ void rope_inverse_T(f32x16_t (&acc)[4], const float* 
     }
 }
 
+// the same two for 16x16 blocks: X^T[128 d][32 rows], block (rb, dt) = rows 16 rb + (lane & 15), d = 16 dt + 4 (lane >> 4) + register
+__device__ __forceinline__ void store_rows_T(const f32x4_t (&acc)[2][8], float mul, bf16_t* stage, bf16_t* out, int64_t ld_out, int row0,
+                                             int limit, int lane) {
+  constexpr int OLD = 136;
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      bf16x4_t pk;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pk[e] = (bf16_t)(acc[rb][dt][e] * mul);
+      *reinterpret_cast<bf16x4_t*>(stage + (16 * rb + (lane & 15)) * OLD + dt * 16 + 4 * (lane >> 4)) = pk;
+    }
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int idx = it * 64 + lane, row = idx >> 4, ch = idx & 15;
+    if (row0 + row < limit)
+      *reinterpret_cast<u32x4_t*>(out + (int64_t)(row0 + row) * ld_out + ch * 8) = *reinterpret_cast<const u32x4_t*>(stage + row * OLD + ch * 8);
+  }
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void rope_inverse_T(f32x4_t (&acc)[2][8], const float* __restrict__ table, int pos0, int limit, int lane) {
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    int pos = pos0 + 16 * rb + (lane & 15);
+    if (pos >= limit) pos = limit - 1;
+    const float* tb = table + (int64_t)pos * D;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      const f32x4_t cs = *reinterpret_cast<const f32x4_t*>(tb + 16 * dt + 4 * (lane >> 4));
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float a = acc[rb][dt][2 * e], bb = acc[rb][dt][2 * e + 1], c = cs[2 * e], sn = cs[2 * e + 1];
+        acc[rb][dt][2 * e] = a * c + bb * sn;
+        acc[rb][dt][2 * e + 1] = bb * c - a * sn;
+      }
+    }
+  }
+}
+
 // =============================================================================== backward: row statistics
 // prep [2][B*nh][Sp] fp32, Sp = S rounded up to 64:  prep[0] = lse * log2(e) (what the exp2-domain
 // recomputation subtracts), +inf for rows S..Sp-1 so that their probabilities come out as exactly 0;
@@ -620,8 +688,10 @@ __global__ void __launch_bounds__(256) attn_bwd_prep_kernel(const bf16_t* __rest
 // through a 2-stage LDS ring in blocks of 64 (Q and dO tiles plus the rows' lse and D), from the diagonal to the end
 // of the sequence, filled by direct global->LDS loads one block ahead (a block takes several microseconds to process,
 // more than a load takes to land).
-//   S = Q K^T and dP = dO V^T as two alternating accumulation chains;  P = exp(S/sqrt(d) - lse);  dS = P (dP - D)
+//   S = Q K^T and dP = dO V^T, 32 x 32 as four 16 x 16 blocks each (16x16x32 MFMAs: less power per product, gemm_mfma.hip), the fragments of the next
+//   step read one by one between the MFMAs of this one;  P = exp(S/sqrt(d) - lse);  dS = P (dP - D)
 //   dV^T += dO^T P;   dK^T += Q^T dS  (scaled by 1/sqrt(d) at the end)
+// Step of 32768 tokens, 32 heads 59.6 -> 59.0 ms, of 8192 9.15 -> 9.12; 4 wavefronts, bound by latency, 2 x 333 of 2 heads 106.0 -> 106.3 us.
 constexpr int kKvStage = 2 * kTileBytes + 2 * 64 * 4;                    // Q tile | dO tile | lse[64] | D[64]
 template <int NW> constexpr size_t kKvLds = NW * 8192 + 2 * kKvStage;     // key tile [32 NW][128] bf16 in front of the ring
 //
@@ -629,10 +699,10 @@ template <int NW> constexpr size_t kKvLds = NW * 8192 + 2 * kKvStage;     // key
 // a dQ kernel that then needs one matrix product instead of three (attn_bwd_dq_stored_kernel).  Layout of `ds`, per (batch,
 // head): for block ib of 256 query rows, and in it for each 32-row group s (the rows of one wavefront of the dQ kernel),
 // the units of the key groups g = 0 .. 8 (ib + 1) - 1 one after the other (ds_unit_offset).  A unit is what one wavefront
-// here holds after one block: dS[32 rows][32 keys], 2 KiB, as 128 slots of 16 bytes.  Lane (key kk, lane half hh) holds the
-// two pieces tt = 0, 1 = accumulator registers 8 tt .. 8 tt + 7 = query rows 16 tt + 4 hh + {0..3, 8..11} of the group
+// here holds after one block: dS[32 rows][32 keys], 2 KiB, as 128 slots of 16 bytes.  A lane holds, for each of two keys kk, the
+// piece (hh, tt) = (g & 1, g >> 1), g = lane >> 4: query rows 16 tt + 4 hh + {0..3, 8..11} of the group (LaneAddr16Q)
 // (ds_row_of_slot gives the row for the position 16 hh + 8 tt + e the dQ kernel sees it at).  Piece tt goes to slot
-// ds_slot(kk, hh, tt): the 64 lanes of one store instruction fill one contiguous KiB, and the dQ kernel, which copies
+// ds_slot(kk, hh, tt): the 64 lanes of one store instruction fill two runs of 512 bytes, and the dQ kernel, which copies
 // units into LDS as they are, reads them back by transposing reads without bank conflicts (the 16 slots one half-wavefront
 // reads - 4 keys x 2 lane halves x 2 pieces - differ in their low 4 bits).  Units whose 32 queries all lie in front of
 // their 32 keys (dS = 0 there) are never written; the dQ kernel copies the ones inside its diagonal block into LDS along
@@ -650,15 +720,16 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
                     const float* __restrict__ rope, unsigned char* __restrict__ ds, int64_t ds_pair_bytes) {
   constexpr int BKVW = NW * 32, BQ = 64, NS = 2, kKvOffRing = NW * 8192;
   constexpr int kStage = kKvStage;
-  constexpr int kA = 1;                                // fragment reads run this many MFMA steps ahead of their use (deeper costs registers this kernel does not have)
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
 
-  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  LaneAddr la;
+  LaneAddr16 la;                                       // of the key tile
   la.init(lane);
+  LaneAddr16Q lq;                                      // of the query rows' tiles
+  lq.init(lane);
   int bh, kt;                                          // key tile 0 meets every query block: longest first
   pair_tile_of_block<false>((int)blockIdx.x, B * nh, (S + BKVW - 1) / BKVW, bh, kt);
   const int b = bh / nh, h = bh % nh;
@@ -679,7 +750,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   for (int i = 0; i < 8; ++i) {
     const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
-    const int cc = swz(r, lane & 15);
+    const int cc = swz16(r, lane & 15);
     int rg = kv0 + r;
     rg = rg < S ? rg : S - 1;
     lds_dma16(k64, (unsigned)rg * ldb + cc * 16, lds0 + j * 1024);
@@ -687,27 +758,28 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   auto issue = [&](int t) {
     const unsigned st = lds0 + kKvOffRing + (t & (NS - 1)) * kStage;
     const int row0 = (jb + t) * BQ;
-    tile_dma<NW>(qb64, ldb, row0, S, st, lane, wave);
-    tile_dma<NW>(do64, ldob, row0, S, st + kTileBytes, lane, wave);
+    tile_dma<NW, 2>(qb64, ldb, row0, S, st, lane, wave);
+    tile_dma<NW, 2>(do64, ldob, row0, S, st + kTileBytes, lane, wave);
     if (wave < 2)
       lds_dma4(wave == 0 ? l64 : d64, (unsigned)(row0 + lane) * 4u, st + 2 * kTileBytes + wave * (BQ * 4));
   };
   issue(0);
 
-  bf16x8_t vf[8];
-  {
-    int row = kv0w + (lane & 31);
+  bf16x8_t vf[2][4];                                   // [16 keys][32 d]
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    int row = kv0w + 16 * kb + (lane & 15);
     if (row >= S) row = S - 1;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) vf[ks] = *reinterpret_cast<const bf16x8_t*>(vbase + (int64_t)row * ld + 16 * ks + 8 * hh);
+    for (int ks = 0; ks < 4; ++ks) vf[kb][ks] = *reinterpret_cast<const bf16x8_t*>(vbase + (int64_t)row * ld + 32 * ks + 8 * g);
   }
-  f32x16_t dk[4], dv[4];
+  f32x4_t dk[2][8], dv[2][8];                          // [16 keys][16 d], transposed
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { dk[dt][r] = 0.f; dv[dt][r] = 0.f; }
-  const int kvi = kv0w + (lane & 31);
+    for (int dt = 0; dt < 8; ++dt) dk[kb][dt] = dv[kb][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const unsigned knat_t = la.nat + lds0 + wave * 8192;
+  const int qlane = 16 * (g >> 1) + 4 * (g & 1);       // block rb, register r: query row qlane + 8 rb + r of 32
   unsigned char* const ds_pair = STORE_DS ? ds + (int64_t)bh * ds_pair_bytes : nullptr;
   for (int t = 0; t < nblk; ++t) {
     wait_vmcnt<0>();                                     // block t (issued one iteration ago) has landed
@@ -716,8 +788,8 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
     const int qb0 = (jb + t) * BQ;
     if (qb0 + BQ - 1 < kv0w) continue;
     const unsigned so = lds0 + kKvOffRing + (t & (NS - 1)) * kStage;
-    const unsigned nat_t = la.nat + so, tr_t = la.tr + so;
-    const unsigned sl = so + 2 * kTileBytes + 16 * hh;
+    const unsigned nat_t = lq.nat + so, tr_t = lq.tr + so;
+    const unsigned sl = so + 2 * kTileBytes + 4 * qlane;
     static_for<2>([&](auto qb_c) {
       TAW_CONST(qb, qb_c);
       const int qrow0 = qb0 + qb * 32;
@@ -725,76 +797,109 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
       typedef const __attribute__((address_space(3))) f32x4_t* lds_f4_t;
       bf16x8_t pb[2], dsb[2];
       {
-        f32x16_t sacc, pacc;
+        f32x4_t sacc[2][2], pacc[2][2];                  // [16 rows][16 keys]
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { sacc[r] = 0.f; pacc[r] = 0.f; }
-        // step i: S MFMA needs Q(i) and K(i) from LDS, dP MFMA needs dO(i)
-        bf16x8_t fq[8], fk[8], fo[8];
-        auto rd = [&](auto i_c) {
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) sacc[rb][kb] = pacc[rb][kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // step i = 2 ks + rb: Q and dO of 16 rows meet K and V of both 16-key blocks; the K fragments of a ks come with its first step
+        bf16x8_t fq[8], fo[8], fk[4][2];
+        unsigned a[4], ak = 0;
+        // read n of a step, between its MFMAs of the step before: 0 Q, 1 dO, 2 and 3 the K fragments
+        auto rd = [&](auto i_c, auto n_c) {
           TAW_CONST(i, i_c);
-          // Q and dO fragments sit at the same place of their tiles: one address for both
-          const unsigned a = xor_here<(i << 5), true>(nat_t);
-          fq[i] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(a + qb * 8192);
-          fk[i] = frag_nat2<i, 0, true>(knat_t);
-          fo[i] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t*>(a + kTileBytes + qb * 8192);
+          TAW_CONST(n, n_c);
+          constexpr int ks = i / 2, rb = i % 2;
+          typedef const __attribute__((address_space(3))) bf16x8_t* lds_frag_t;
+          if constexpr (n == 0) {
+            // Q and dO fragments sit at the same place of their tiles: one address for both
+            if constexpr (rb == 0) a[ks] = xor_here<(ks << 6), true>(nat_t);
+            fq[i] = *reinterpret_cast<lds_frag_t>((size_t)(a[ks] + qb * 8192 + rb * 2048));
+          } else if constexpr (n == 1) {
+            fo[i] = *reinterpret_cast<lds_frag_t>((size_t)(a[ks] + kTileBytes + qb * 8192 + rb * 2048));
+          } else if constexpr (rb == 0) {
+            if constexpr (n == 2) ak = xor_here<(ks << 6), true>(knat_t);
+            fk[ks][n - 2] = *reinterpret_cast<lds_frag_t>((size_t)(ak + 4096 * (n - 2)));
+          }
         };
-        static_for<kA>(rd);
+        static_for<4>([&](auto n) { rd(std::integral_constant<int, 0>{}, n); });
         __builtin_amdgcn_s_setprio(1);
         static_for<8>([&](auto i_c) {
           TAW_CONST(i, i_c);
-          if constexpr (i + kA < 8) rd(std::integral_constant<int, i + kA>{});
-          __builtin_amdgcn_sched_barrier(0);
-          sacc = mfma(fq[i], fk[i], sacc);
-          pacc = mfma(fo[i], vf[i], pacc);
-          __builtin_amdgcn_sched_barrier(0);
+          constexpr int ks = i / 2, rb = i % 2;
+          static_for<4>([&](auto n_c) {
+            TAW_CONST(n, n_c);
+            if constexpr (i + 1 < 8) rd(std::integral_constant<int, i + 1>{}, n_c);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (n < 2) sacc[rb][n] = mfma16(fq[i], fk[ks][n], sacc[rb][n]);
+            else pacc[rb][n - 2] = mfma16(fo[i], vf[n - 2][ks], pacc[rb][n - 2]);
+            __builtin_amdgcn_sched_barrier(0);
+          });
         });
         __builtin_amdgcn_s_setprio(0);
         if (qrow0 < kv0w + 31) {
           asm volatile("" ::: "memory");
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int qi = qrow0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-            sacc[r] = kvi > qi ? -INFINITY : sacc[r];
-          }
+          for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                sacc[rb][kb][r] = kv0w + 16 * kb + (lane & 15) > qrow0 + qlane + 8 * rb + r ? -INFINITY : sacc[rb][kb][r];
         }
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const f32x4_t l4 = *reinterpret_cast<lds_f4_t>(sl + (qb * 32 + 8 * r4) * 4);
-          const f32x4_t d4 = *reinterpret_cast<lds_f4_t>(sl + (BQ + qb * 32 + 8 * r4) * 4);
+        for (int rb = 0; rb < 2; ++rb) {
+          const f32x4_t l4 = *reinterpret_cast<lds_f4_t>((size_t)(sl + (qb * 32 + 8 * rb) * 4));
+          const f32x4_t d4 = *reinterpret_cast<lds_f4_t>((size_t)(sl + (BQ + qb * 32 + 8 * rb) * 4));
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int r = 4 * r4 + e;
-            const float pr = fast_exp2(__builtin_fmaf(sacc[r], c, -l4[e]));
-            sacc[r] = pr;
-            pacc[r] = pr * (pacc[r] - d4[e]);
-          }
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float pr = fast_exp2(__builtin_fmaf(sacc[rb][kb][e], c, -l4[e]));
+              pb[kb][4 * rb + e] = (bf16_t)pr;
+              dsb[kb][4 * rb + e] = (bf16_t)(pr * (pacc[rb][kb][e] - d4[e]));
+            }
         }
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt) { pb[tt] = pack8(sacc, tt); dsb[tt] = pack8(pacc, tt); }
         if constexpr (STORE_DS) {
           unsigned char* unit = ds_pair + ds_unit_offset(qrow0 >> 8, (qrow0 >> 5) & 7, kv0w >> 5);      // wavefront-uniform
           int ln = lane;
           asm volatile("" : "+v"(ln));                     // the slot numbers are made here, from the lane id, not kept in registers through the loop
           // non-temporal: written once, read once by the next kernel, and 35 GB of it at S = 32768: nothing to keep in a cache
-          __builtin_nontemporal_store(dsb[0], reinterpret_cast<bf16x8_t*>(unit + ds_slot(ln & 31, ln >> 5, 0) * 16u));
-          __builtin_nontemporal_store(dsb[1], reinterpret_cast<bf16x8_t*>(unit + ds_slot(ln & 31, ln >> 5, 1) * 16u));
+          const unsigned slot = ds_slot(ln & 15, ln >> 4 & 1, ln >> 5);
+          __builtin_nontemporal_store(dsb[0], reinterpret_cast<bf16x8_t*>(unit + slot * 16u));
+          __builtin_nontemporal_store(dsb[1], reinterpret_cast<bf16x8_t*>(unit + slot * 16u + 512u));      // 16 keys on: bit 5 of the slot
         }
       }
       {
         bf16x8_t fq[8], fdo[8];
-        auto rd = [&](auto i_c) {
+        unsigned a = 0;
+        auto rd = [&](auto i_c, auto n_c) {                // one of the two fragments of step i
           TAW_CONST(i, i_c);
-          frag_tr2x2<i % 2, i / 2, qb * 8192, kTileBytes + qb * 8192, true>(tr_t, fq[i], fdo[i]);
+          TAW_CONST(n, n_c);
+          if constexpr (n == 0) {
+            a = xor_here<(i << 5), true>(tr_t);
+            fdo[i] = frag16q_tr<kTileBytes + qb * 8192>(a);
+          } else {
+            fq[i] = frag16q_tr<qb * 8192>(a);
+          }
         };
-        static_for<kA>(rd);
+        static_for<2>([&](auto n) { rd(std::integral_constant<int, 0>{}, n); });
         __builtin_amdgcn_s_setprio(1);
         static_for<8>([&](auto i_c) {
           TAW_CONST(i, i_c);
-          if constexpr (i + kA < 8) rd(std::integral_constant<int, i + kA>{});
-          __builtin_amdgcn_sched_barrier(0);
-          dv[i / 2] = mfma(fdo[i], pb[i % 2], dv[i / 2]);
-          dk[i / 2] = mfma(fq[i], dsb[i % 2], dk[i / 2]);
-          __builtin_amdgcn_sched_barrier(0);
+          static_for<2>([&](auto n_c) {
+            TAW_CONST(n, n_c);
+            if constexpr (i + 1 < 8) rd(std::integral_constant<int, i + 1>{}, n_c);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (n == 0) {
+              dv[0][i] = mfma16(fdo[i], pb[0], dv[0][i]);
+              dv[1][i] = mfma16(fdo[i], pb[1], dv[1][i]);
+            } else {
+              dk[0][i] = mfma16(fq[i], dsb[0], dk[0][i]);
+              dk[1][i] = mfma16(fq[i], dsb[1], dk[1][i]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          });
         });
         __builtin_amdgcn_s_setprio(0);
       }
@@ -808,7 +913,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   if (rope) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    rope_inverse_T(dk, rope, kv0w + (ln & 31), S, ln);
+    rope_inverse_T(dk, rope, kv0w, S, ln);
   }
   store_rows_T(dk, scale, stage, dkout, ld, kv0w, S, lane);
   store_rows_T(dv, 1.0f, stage, dvout, ld, kv0w, S, lane);

@@ -162,8 +162,8 @@ enum { ATTN_BWD_SPLIT = 0, ATTN_BWD_FUSED = 1, ATTN_BWD_FUSED_ATOMIC = 2, ATTN_B
 // ---- layout of the stored dS (ATTN_BWD_STORED), shared by the kernel that writes it, the kernel that reads it and the host
 // Per (batch, head): block ib of 256 query rows holds 256 (ib + 1) keys x 256 rows bf16, blocks one after the other; inside a
 // block, per 32-row group s, the 2 KiB units dS[32 rows][32 keys] of the key groups g = 0 .. 8 (ib + 1) - 1 one after the
-// other.  Inside a unit, 128 slots of 16 bytes: lane (key kk, lane half hh) of the writing wavefront puts its piece tt
-// (8 bf16 = accumulator registers 8 tt .. 8 tt + 7) at slot ds_slot(kk, hh, tt); position p = 16 hh + 8 tt + e of a
+// other.  Inside a unit, 128 slots of 16 bytes: piece (hh, tt) of key kk (8 bf16,
+// rows 16 tt + 4 hh + {0..3, 8..11}) is at slot ds_slot(kk, hh, tt); position p = 16 hh + 8 tt + e of a
 // key's 32 values is query row ds_row_of_slot(p) of the group.
 constexpr int64_t kDsBlockBytes = 256 * 256 * 2;       // one (256 keys, 256 query rows) block
 __host__ __device__ inline int64_t ds_block_offset(int ib) { return (int64_t)ib * (ib + 1) / 2 * kDsBlockBytes; }

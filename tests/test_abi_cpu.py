@@ -356,9 +356,9 @@ def test_stored_ds_layout(lib, S):
     """The dS hand-over of the default attention backward, as the kernels address it: the 2 KiB units of a (batch, head) tile
     its region exactly (no gap, no overlap, query block ib holding 256 (ib + 1) keys x 256 rows), and a wavefront of the reading
     kernel (one 32-row group) finds its units for consecutive key groups at consecutive addresses; the 128 slots of a unit are a
-    permutation, each store instruction (one piece of all 64 lanes) fills one contiguous KiB, and the 16 slots a
+    permutation, the pieces tt of all keys fill one contiguous KiB, and the 16 slots a
     half-wavefront of the reader touches in one transposing read (4 consecutive keys x 2 lane halves x 2 pieces) fall into 16
-    different 16-byte bank groups; positions map back to the accumulator's row order."""
+    different 16-byte bank groups; positions map back to rows."""
     L = taw.taw_diag_attn_ds_layout(S)
     nqt = (S + 255) // 256
     assert L["pair_bytes"] == sum(256 * (ib + 1) * 256 * 2 for ib in range(nqt))
@@ -377,7 +377,7 @@ def test_stored_ds_layout(lib, S):
     for k4 in range(8):
         group = [slots[(2 * tt + hh) * 32 + 4 * k4 + j] for tt in range(2) for hh in range(2) for j in range(4)]
         assert sorted(x % 16 for x in group) == list(range(16))
-    # position p = 16 hh + 8 tt + e holds accumulator register 8 tt + e of lane half hh, i.e. row 8 (r // 4) + 4 hh + r % 4
+    # position p = 16 hh + 8 tt + e holds row 8 (r // 4) + 4 hh + r % 4 with r = 8 tt + e
     for hh in range(2):
         for tt in range(2):
             for e in range(8):
