@@ -221,18 +221,19 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // into LDS at lds_addr + 16 * lane (lds_addr wavefront-uniform).  Inline assembly so that the
 // compiler's wait-count insertion does not see the load: it would put s_waitcnt vmcnt(0) in front
 // of every transposing LDS read that follows.  The kernels order these loads themselves (vmcnt
-// wait + workgroup barrier before a stage is read, barrier after its last read before a refill).
+// wait + workgroup barrier before a stage is read, barrier after its last read before a refill),
+// and the wait state the load needs after the write of m0 is theirs too (s_nop).
 __device__ __forceinline__ void lds_dma16(uint64_t base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
 }
 // the same with the non-temporal hint: for data read exactly once (it is not worth a place in the caches that the
 // re-read K / V / Q / dO tiles live in)
 __device__ __forceinline__ void lds_dma16_nt(uint64_t base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds_addr));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds_addr));
 }
 // 4 bytes per lane, same addressing (LDS destination lds_addr + 4 * lane)
 __device__ __forceinline__ void lds_dma4(uint64_t base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
 }
 // workgroup barrier that also tells the compiler that LDS changed behind its back
 __device__ __forceinline__ void stage_barrier() {

@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(256, 1) mfma_loop_kernel(int iters, const unsi
         asm volatile("ds_read_b128 %0, %1" : "=v"(pend[slot]) : "v"(rd + ((u >> 1) & 7) * 1024 + ((it & 1) ? 8192 : 0)));
       }
       if (KIND == TAW_DIAG_MFMA_LDS_LOADS && (u & 3) == 0) {       // one direct load per four MFMAs
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(goff & src_mask), "s"((unsigned long long)src), "s"(dma_dst + (u >> 2) * 1024));
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(goff & src_mask), "s"((unsigned long long)src), "s"(dma_dst + (u >> 2) * 1024));
         goff += 1024u;
       }
       acc[u & 7] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[u & 1].v, fb[(u >> 1) & 1].v, acc[u & 7], 0, 0, 0);

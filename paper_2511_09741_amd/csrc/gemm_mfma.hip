@@ -58,13 +58,14 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // the ring.  Here the loads are invisible to it and the kernel orders them itself: vmcnt waits
 // plus a workgroup barrier before a stage is read, a barrier after its last read before it is
 // refilled.  m0 is not allocatable: the compiler sets it immediately before each use of its own.
+// s_nop: a load into LDS needs one wait state after the write of m0, which the compiler does not place inside the block.
 __device__ __forceinline__ void lds_dma16(uint64_t base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr));
 }
 
 // the same to lds_addr + OFF, one scalar instruction fewer than adding it first
 template <int OFF> __device__ __forceinline__ void lds_dma16_at(uint64_t base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr), "n"(OFF) : "scc");
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr), "n"(OFF) : "scc");
 }
 
 // workgroup barrier that also tells the compiler LDS contents changed (the DMA writes are not
