@@ -66,3 +66,12 @@ def test_loads_into_lds_wait_for_m0(kernels):
     loads = {name: d for name, d in ((name, m0_distances(text)) for name, text in kernels.items()) if d}
     assert any("gemm_pipe" in n for n in loads) and any("attn_fwd" in n for n in loads) and any("mfma_loop" in n for n in loads)
     assert {name: d for name, d in loads.items() if any(x is None or x < 1 for x in d)} == {}
+
+
+def test_large_tiles_move_between_stages_by_addition(kernels):
+    """The fragments of a 256 x 256 tile are read at absolute LDS addresses.  Flipping the bit of the stage's size (0x8000) in them would
+    hold only while the ring starts at a multiple of twice that, which nothing guarantees; adding the size holds for any start."""
+    large = {name: text for name, text in kernels.items() if "v216gemm_pipe" in name or "v216gemm_dual" in name}
+    assert len(large) == 8
+    for name, text in large.items():
+        assert not [t for t in text if t.startswith("v_xor") and "0x8000" in t], name
