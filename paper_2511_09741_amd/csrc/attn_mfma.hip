@@ -257,9 +257,17 @@ __device__ __forceinline__ void tile_dma(uint64_t base, unsigned ld_bytes, int r
     const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
     const int c = SW == 1 ? swz16(r, lane & 15) : SW == 2 ? swz16q(r, lane & 15) : swz(r, lane & 15);
-    int rg = row0 + r;
-    rg = rg < limit ? rg : limit - 1;
-    lds_dma16(base, (unsigned)rg * ld_bytes + c * 16, lds_tile + j * 1024);
+    if constexpr (NW == 4) {      // a wavefront alone on its SIMD pays for the s_nop: m0 is written first, forming the address is the wait state
+      int rg = row0;
+      asm volatile("s_mov_b32 m0, %1" : "+s"(rg) : "s"(lds_tile + j * 1024));
+      rg += r;
+      rg = rg < limit ? rg : limit - 1;
+      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"((unsigned)rg * ld_bytes + c * 16), "s"(base));
+    } else {
+      int rg = row0 + r;
+      rg = rg < limit ? rg : limit - 1;
+      lds_dma16(base, (unsigned)rg * ld_bytes + c * 16, lds_tile + j * 1024);
+    }
   }
 }
 
@@ -322,7 +330,9 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 //
 // 16x16x32 MFMAs draw less power per product than 32x32x16 ones (gemm_mfma.hip), and with them a row's scores lie in four lanes instead of two,
 // which only the rare raising of a maximum and the end need to bring together: 8 wavefronts, 8 x 8192 tokens of 16 heads 2219 -> 2134 us,
-// 16 x 4096 of 8 560 -> 543, 32768 of 32 7948 -> 7842; 4 wavefronts, bound by latency, 10.6 -> 10.9 at 2 x 333 of 2.
+// 16 x 4096 of 8 560 -> 543, 32768 of 32 7948 -> 7842.  4 wavefronts, one to a SIMD, are bound by the instructions between the MFMAs and not by power,
+// and every MFMA of the smaller kind costs one more issue: 2 x 333 of 2 10.6 -> 10.8, 2048 of 16 40.3 -> 40.9, 3 x 1501 of 8 32.0 -> 31.9, 4096 of 16
+// 86.7 -> 85.1, 32768 of 2 638 -> 610 (the maximum as a chain and s_nop in the loads: 11.0, 41.9, 32.7, 87.1, 628).
 constexpr float kMaxSlack = 8.0f;
 
 template <int NW>
@@ -463,14 +473,24 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
           }
     }
     // v_max3_f32 by name: fmaxf on MFMA results makes the compiler quiet possible signalling NaNs first, one extra
-    // instruction per score, and pair the maxima up with two-operand instructions (58 instructions for 32 scores instead of 16)
+    // instruction per score, and pair the maxima up with two-operand instructions (58 instructions for 32 scores instead of 16).  As a tree: between
+    // two such blocks of which one needs the other's result the compiler puts a wait state, in a chain 14 of them.
     float mx[2];
+    {
+      float t[2][5];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      mx[qb] = max3(s[qb][0][0], s[qb][0][1], s[qb][0][0]);
+      for (int i = 0; i < 5; ++i)
 #pragma unroll
-      for (int i = 2; i < 16; i += 2) mx[qb] = max3(mx[qb], s[qb][i / 4][i % 4], s[qb][i / 4][i % 4 + 1]);
-      mx[qb] *= c;
+        for (int qb = 0; qb < 2; ++qb) {
+          auto x = [&](int e) { return s[qb][e / 4][e % 4]; };
+          t[qb][i] = max3(x(3 * i), x(3 * i + 1), x(3 * i + 2));
+        }
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) t[qb][0] = max3(t[qb][0], t[qb][1], t[qb][2]);
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) t[qb][3] = max3(t[qb][3], t[qb][4], s[qb][3][3]);
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) mx[qb] = max3(t[qb][0], t[qb][3], t[qb][3]) * c;
     }
     // wavefront-uniform: some row's maximum moved far.  Each lane asks for its own quarter of the keys: only where one says yes
     // are the quarters of a row brought together.
