@@ -1,6 +1,7 @@
 // Measurement probes (include/taw_diag.h): short synthetic kernels that record what the part sustains.
 // Each entry point launches on the default stream, waits, and returns the figures in host memory.
 #include <hip/hip_runtime.h>
+#include <type_traits>
 
 #include "../../include/taw_diag.h"
 #include "dev_common.h"
@@ -53,10 +54,15 @@ __global__ void __launch_bounds__(256, 1) mfma_loop_kernel(int iters, const unsi
   // loads of kind 3 land in the second half of LDS (this wavefront's 16 KiB), a different KiB per load of a step
   const unsigned dma_dst = lds0 + 65536 + wave * 16384;
   unsigned goff = (unsigned)((blockIdx.x * 4 + wave) * 65536u + lane * 16u);
+  // LDS reads the compiler waits for itself; the empty block and a scheduling barrier per MFMA keep each where it is issued
+  auto read = [](unsigned at) {
+    asm volatile("" ::: "memory");
+    return *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t*>((size_t)at);
+  };
   u32x4_t pend[2];
   if (KIND >= TAW_DIAG_MFMA_LDS) {
-    asm volatile("ds_read_b128 %0, %1" : "=v"(pend[0]) : "v"(rd));
-    asm volatile("ds_read_b128 %0, %1" : "=v"(pend[1]) : "v"(rd + 1024));
+    pend[0] = read(rd);
+    pend[1] = read(rd + 1024);
   }
   const long long w0 = wall_clock64(), c0 = clock64();
   for (int it = 0; it < iters; ++it) {
@@ -64,16 +70,16 @@ __global__ void __launch_bounds__(256, 1) mfma_loop_kernel(int iters, const unsi
     for (int u = 0; u < 16; ++u) {
       if (KIND >= TAW_DIAG_MFMA_LDS && (u & 1) == 0) {             // one fragment read per two MFMAs, consumed four MFMAs after it was issued
         const int slot = (u >> 1) & 1;
-        asm volatile("s_waitcnt lgkmcnt(1)" ::: "memory");         // all but the newest read have returned: pend[slot] is the older of the two
         if ((u >> 1) & 2) fa[slot].v = __builtin_bit_cast(bf16x8_t, pend[slot]);
         else fb[slot].v = __builtin_bit_cast(bf16x8_t, pend[slot]);
-        asm volatile("ds_read_b128 %0, %1" : "=v"(pend[slot]) : "v"(rd + ((u >> 1) & 7) * 1024 + ((it & 1) ? 8192 : 0)));
+        pend[slot] = read(rd + ((u >> 1) & 7) * 1024 + ((it & 1) ? 8192 : 0));
       }
       if (KIND == TAW_DIAG_MFMA_LDS_LOADS && (u & 3) == 0) {       // one direct load per four MFMAs
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(goff & src_mask), "s"((unsigned long long)src), "s"(dma_dst + (u >> 2) * 1024));
         goff += 1024u;
       }
       acc[u & 7] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[u & 1].v, fb[(u >> 1) & 1].v, acc[u & 7], 0, 0, 0);
+      if (KIND >= TAW_DIAG_MFMA_LDS) __builtin_amdgcn_sched_barrier(0);
     }
     if (KIND == TAW_DIAG_MFMA_LDS_LOADS) {
       __builtin_amdgcn_s_waitcnt((4 & 15) | (7 << 4) | (15 << 8));  // vmcnt(4): the previous trip's loads have landed
@@ -99,23 +105,32 @@ __global__ void __launch_bounds__(WAVES * 64, 1) lds_rate_kernel(int iters, unsi
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned lds0 = (unsigned)(size_t)(const lds_u8_t*)lds_raw;
   const unsigned a = lds0 + (INSTR == 0 ? lane * 16 : lane * 8) + (wave & 3) * 4096;
-  u32x4_t acc4 = {0, 0, 0, 0};
   typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-  u32x2_t acc2 = {0, 0};
+  unsigned acc = 0;
   const long long w0 = wall_clock64(), c0 = clock64();
   for (int it = 0; it < iters; ++it) {
+    // the wait stands in the block of the reads: the compiler takes their registers as written when the block ends
+#define TAW_READS(OP)                                                                                                          \
+  OP " %0, %16\n\t" OP " %1, %16 offset:1024\n\t" OP " %2, %16 offset:2048\n\t" OP " %3, %16 offset:3072\n\t"                   \
+  OP " %4, %16 offset:16384\n\t" OP " %5, %16 offset:17408\n\t" OP " %6, %16 offset:18432\n\t" OP " %7, %16 offset:19456\n\t"     \
+  OP " %8, %16 offset:32768\n\t" OP " %9, %16 offset:33792\n\t" OP " %10, %16 offset:34816\n\t" OP " %11, %16 offset:35840\n\t"   \
+  OP " %12, %16 offset:49152\n\t" OP " %13, %16 offset:50176\n\t" OP " %14, %16 offset:51200\n\t" OP " %15, %16 offset:52224\n\t" \
+  "s_waitcnt lgkmcnt(0)"
+#define TAW_INTO "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]), "=&v"(v[8]), \
+                 "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]), "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
+    typename std::conditional<INSTR == 0, u32x4_t, u32x2_t>::type v[16];
+    if constexpr (INSTR == 0) asm volatile(TAW_READS("ds_read_b128") : TAW_INTO : "v"(a) : "memory");
+    else if constexpr (INSTR == 1) asm volatile(TAW_READS("ds_read_b64") : TAW_INTO : "v"(a) : "memory");
+    else asm volatile(TAW_READS("ds_read_b64_tr_b16") : TAW_INTO : "v"(a) : "memory");
+#undef TAW_READS
+#undef TAW_INTO
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const unsigned ad = a + (u % 4) * 1024 + (u / 4) * 16384;
-      if (INSTR == 0) { u32x4_t v; asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(ad)); acc4 += v; }
-      else if (INSTR == 1) { u32x2_t v; asm volatile("ds_read_b64 %0, %1" : "=v"(v) : "v"(ad)); acc2 += v; }
-      else { u32x2_t v; asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(v) : "v"(ad)); acc2 += v; }
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    for (int u = 0; u < 16; ++u) acc ^= v[u][0];
   }
+  __syncthreads();                                                  // the time of all wavefronts, not of the first to end
   const long long w1 = wall_clock64(), c1 = clock64();
   if (threadIdx.x == 0) { g_clk[2 * blockIdx.x] = w1 - w0; g_clk[2 * blockIdx.x + 1] = c1 - c0; }
-  if ((acc4[0] ^ acc4[1] ^ acc4[2] ^ acc4[3] ^ acc2[0] ^ acc2[1]) == 0x12345679u) sink[0] = 1;
+  if (acc == 0x12345679u) sink[0] = 1;
 }
 
 // workgroup (head, key block): from row 256 * key block down, 32 rows per step; wavefront w takes rows 4 w .. 4 w + 3 of the step,
@@ -197,6 +212,8 @@ __global__ void __launch_bounds__(512, 1) issue_kernel(int iters, float* sink) {
     }
   }
   const long long t1 = __builtin_readcyclecounter();
+  // the MFMAs above are invisible to the compiler, which reads their results at once: not before they are there
+  asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
   float sum = 0.f;
 #pragma unroll
   for (int a = 0; a < 4; ++a)

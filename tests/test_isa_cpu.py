@@ -75,3 +75,46 @@ def test_large_tiles_move_between_stages_by_addition(kernels):
     assert len(large) == 8
     for name, text in large.items():
         assert not [t for t in text if t.startswith("v_xor") and "0x8000" in t], name
+
+
+def registers(operand):
+    m = re.fullmatch(r"-?\|?([va])(\d+)\|?", operand) or re.fullmatch(r"-?([va])\[(\d+):(\d+)\]", operand)
+    return [(m[1], r) for r in range(int(m[2]), int(m[m.lastindex]) + 1)] if m else []
+
+
+def unwaited_reads(instructions):
+    """instructions that use what an LDS read returns before a wait for it; LDS reads return in order, lgkmcnt(n) leaves the last n"""
+    out, pending = [], []
+    for text in instructions:
+        op, _, args = text.partition(" ")
+        if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+            pending = []
+        elif op == "s_waitcnt":
+            n = re.search(r"lgkmcnt\((\d+)\)", args)
+            if n:
+                pending = pending[-int(n[1]):] if int(n[1]) else []
+        else:
+            operands = [a.split(" ")[0] for a in re.sub(r"offset\S*|nt\b", "", args).split(", ")]
+            busy = {r for regs in pending for r in regs}
+            if any(r in busy for a in operands for r in registers(a)):
+                out.append(text)
+            if op.startswith("ds_"):      # every LDS instruction counts, a write as one that returns nothing
+                pending.append(registers(operands[0]) if op.startswith(("ds_read", "ds_bpermute")) else [])
+            elif op.startswith(("s_load", "s_buffer_load", "s_memtime", "s_memrealtime")):
+                pending.append([])
+    return out
+
+
+def test_unwaited_reads():
+    read = "ds_read_b64 v[2:3], v1 offset:8"
+    assert unwaited_reads([read, "v_add_u32_e32 v4, v4, v3"]) == ["v_add_u32_e32 v4, v4, v3"]
+    assert unwaited_reads([read, "ds_read_b32 v5, v1", "s_waitcnt lgkmcnt(1)", "v_add_u32_e32 v4, v4, v3"]) == []
+    assert unwaited_reads([read, "ds_read_b32 v5, v1", "s_waitcnt lgkmcnt(1)", "v_mov_b32_e32 v6, v5"]) == ["v_mov_b32_e32 v6, v5"]
+    assert unwaited_reads([read, "s_waitcnt vmcnt(0)", "v_mov_b32_e32 v3, 0"]) == ["v_mov_b32_e32 v3, 0"]      # taken as free while the read is under way
+    assert unwaited_reads([read, "s_waitcnt vmcnt(0) lgkmcnt(0)", "v_mov_b32_e32 v3, 0"]) == []
+
+
+def test_lds_reads_are_waited_for(kernels):
+    """An LDS read in inline assembly counts as done when its block ends: the wait for it stands in the same block, or its register may be used,
+    or handed to something else, while the read is under way."""
+    assert {name: bad[:3] for name, bad in ((name, unwaited_reads(text)) for name, text in kernels.items()) if bad} == {}
