@@ -557,13 +557,16 @@ def run_c5(env, cfg, steps, warmup):
 def mfma_ceiling(env):
     """A loop of nothing but bf16 MFMAs on random operands (and on zeros): the rate the matrix cores sustain under the
     part's power limit, measured in this run.  Every roofline fraction is quoted against this as well as against the
-    published peak."""
+    published peak.  The instruction is the one most of the layer's products use; the larger one draws more power."""
     taw = env.taw
-    r = taw.taw_diag_mfma_loop(taw.TAW_DIAG_MFMA_RANDOM, 20000)
+    r = taw.taw_diag_mfma_loop(taw.TAW_DIAG_MFMA16_RANDOM, 20000)
+    r32 = taw.taw_diag_mfma_loop(taw.TAW_DIAG_MFMA_RANDOM, 20000)
     z = taw.taw_diag_mfma_loop(taw.TAW_DIAG_MFMA_ZERO, 20000)
     return {"mfma_loop_random_operands_TFLOPs": round(r["TFLOPs"], 1), "clock_GHz": round(r["clock_GHz"], 3),
             "mfma_loop_zero_operands_TFLOPs": round(z["TFLOPs"], 1), "clock_GHz_zero_operands": round(z["clock_GHz"], 3),
-            "what": "256 workgroups x 4 wavefronts issuing v_mfma_f32_32x32x16_bf16 back to back from registers (taw_diag_mfma_loop)"}
+            "mfma_loop_32x32x16_random_operands_TFLOPs": round(r32["TFLOPs"], 1), "clock_GHz_32x32x16": round(r32["clock_GHz"], 3),
+            "what": "256 workgroups x 4 wavefronts issuing v_mfma_f32_16x16x32_bf16 (the zero-operand and the named loop: v_mfma_f32_32x32x16_bf16) "
+                    "back to back from registers (taw_diag_mfma_loop)"}
 
 
 def run_diag(env):
@@ -571,7 +574,7 @@ def run_diag(env):
     torch, taw = env.torch, env.taw
     src = torch.empty(256 << 20, dtype=torch.uint8, device="cuda")
     src.view(torch.int32).random_(0, 1 << 30)
-    names = {taw.TAW_DIAG_MFMA_RANDOM: "mfma_only_random_operands", taw.TAW_DIAG_MFMA_ZERO: "mfma_only_zero_operands",
+    names = {taw.TAW_DIAG_MFMA16_RANDOM: "mfma_16x16x32_only_random_operands", taw.TAW_DIAG_MFMA_RANDOM: "mfma_only_random_operands", taw.TAW_DIAG_MFMA_ZERO: "mfma_only_zero_operands",
              taw.TAW_DIAG_MFMA_LDS: "mfma_plus_lds_fragment_reads", taw.TAW_DIAG_MFMA_LDS_LOADS: "mfma_plus_lds_reads_plus_global_to_lds_loads"}
     out = {"mfma_loop": {}, "lds_read_bytes_per_clock_per_cu": {}, "issue_cycles_per_mfma_slot": {}, "dq_update": {}, "gemm_by_tiles": []}
     # vector instructions beside MFMAs: cycles per slot of {1 MFMA + n vector instructions} (32 = the matrix pipe never idles)

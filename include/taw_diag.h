@@ -24,17 +24,19 @@ enum {
   TAW_DIAG_MFMA_RANDOM = 0,       /* v_mfma_f32_32x32x16_bf16 back to back, operands in registers, random bf16 values */
   TAW_DIAG_MFMA_ZERO = 1,         /* the same on all-zero operands (no switching activity: the clock stays up) */
   TAW_DIAG_MFMA_LDS = 2,          /* + one LDS fragment read (ds_read_b128) per two MFMAs, the ratio of a 128x128 wavefront tile */
-  TAW_DIAG_MFMA_LDS_LOADS = 3     /* + one direct global->LDS load (16 bytes per lane) per four MFMAs, the ratio of a 256x256x64 tile step */
+  TAW_DIAG_MFMA_LDS_LOADS = 3,    /* + one direct global->LDS load (16 bytes per lane) per four MFMAs, the ratio of a 256x256x64 tile step */
+  TAW_DIAG_MFMA16_RANDOM = 4      /* v_mfma_f32_16x16x32_bf16 back to back on random values: what the GEMM, the attention forward and dK/dV are made of */
 };
 
 typedef struct {
-  double tflops;      /* 2 * 32 * 32 * 16 flops per MFMA, all 256 compute units x 4 wavefronts */
+  double tflops;      /* 2 * 32 * 32 * 16 (2 * 16 * 16 * 32) flops per MFMA, all 256 compute units x 4 wavefronts */
   double clock_ghz;   /* shader clock inside the loop: core-clock ticks over wall-clock ticks */
-  double mfma_busy;   /* 32 cycles per MFMA over the cycles the loop took: 1.0 = the matrix pipe never idles */
+  double mfma_busy;   /* 32 (16) cycles per MFMA over the cycles the loop took: 1.0 = the matrix pipe never idles */
   double ms;          /* duration of the launch */
 } taw_diag_rate;
 
-/* kind: TAW_DIAG_MFMA_*.  iters: loop trips of 16 MFMAs per wavefront (>= 1; 20000 gives about 10 ms).
+/* kind: TAW_DIAG_MFMA*.  iters: loop trips of 16 MFMAs (32 of the 16x16x32 ones) per wavefront (>= 1; 20000 gives about 6 ms; the latter's come
+ * in pairs).
  * src / src_bytes: a device buffer the loads of TAW_DIAG_MFMA_LDS_LOADS stream from (>= 1 MiB, a multiple of
  * 64 KiB; ignored by the other kinds, may be NULL there).  Synchronises with the host. */
 int taw_diag_mfma_loop(int32_t kind, int32_t iters, const void* src, size_t src_bytes, taw_diag_rate* out);

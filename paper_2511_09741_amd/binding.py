@@ -316,7 +316,7 @@ def taw_op_linear_bwd(dtype, T, N, K, dy, W, x, dx, G, accumulate=0, impl=TAW_IM
 
 
 # ----------------------------------------------------------------------------- taw_diag.h (each call waits for its kernel)
-TAW_DIAG_MFMA_RANDOM, TAW_DIAG_MFMA_ZERO, TAW_DIAG_MFMA_LDS, TAW_DIAG_MFMA_LDS_LOADS = 0, 1, 2, 3
+TAW_DIAG_MFMA_RANDOM, TAW_DIAG_MFMA_ZERO, TAW_DIAG_MFMA_LDS, TAW_DIAG_MFMA_LDS_LOADS, TAW_DIAG_MFMA16_RANDOM = 0, 1, 2, 3, 4
 
 
 def taw_diag_mfma_loop(kind, iters=20000, src=None) -> dict:

@@ -97,6 +97,48 @@ __global__ void __launch_bounds__(256, 1) mfma_loop_kernel(int iters, const unsi
   if (s == 12345.678f) sink[0] = s;                                 // keeps the accumulators alive; never true in practice
 }
 
+// the same with v_mfma_f32_16x16x32_bf16, as the GEMM's 256 x 256 tiles use it: 8 x 8 accumulators from 8 + 8 fragments, row by row, every other row
+// backwards.  A trip is 64 MFMAs, the FLOPs of two of the loop above.
+__global__ void __launch_bounds__(256, 1) mfma16_loop_kernel(int trips, float* sink) {
+  const int tid = threadIdx.x;
+  union { unsigned u[4]; bf16x8_t v; } fa[8], fb[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned x = mix(tid * 32 + j * 4 + e + 1), y = mix(x);
+      fa[j].u[e] = rnd_bf16(x) | (rnd_bf16(y) << 16);
+      fb[j].u[e] = rnd_bf16(y ^ 0x9e3779b9u) | (rnd_bf16(x ^ 0x85ebca6bu) << 16);
+    }
+  f32x4_t acc[8][8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[i][j]));                            // known zeros would be kept beside the loop and copied
+    }
+  const long long w0 = wall_clock64(), c0 = clock64();
+  for (int it = 0; it < trips; ++it) {
+#pragma unroll
+    for (int e = 0; e < 64; ++e) {
+      const int i = e / 8, j = i & 1 ? 7 - e % 8 : e % 8;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j].v, fa[i].v, acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  const long long w1 = wall_clock64(), c1 = clock64();
+  if (tid == 0) { g_clk[2 * blockIdx.x] = w1 - w0; g_clk[2 * blockIdx.x + 1] = c1 - c0; }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s += acc[i][j][r];
+  if (s == 12345.678f) sink[0] = s;                                 // keeps the accumulators alive; never true in practice
+}
+
 template <int INSTR, int WAVES>
 __global__ void __launch_bounds__(WAVES * 64, 1) lds_rate_kernel(int iters, unsigned* sink) {
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
@@ -261,7 +303,7 @@ using namespace taw;
 
 extern "C" int taw_diag_mfma_loop(int32_t kind, int32_t iters, const void* src, size_t src_bytes, taw_diag_rate* out) {
   if (!out) return TAW_ERR_NULL;
-  if (kind < TAW_DIAG_MFMA_RANDOM || kind > TAW_DIAG_MFMA_LDS_LOADS || iters < 1) return TAW_ERR_SHAPE;
+  if (kind < TAW_DIAG_MFMA_RANDOM || kind > TAW_DIAG_MFMA16_RANDOM || iters < 1) return TAW_ERR_SHAPE;
   unsigned mask = 0;
   if (kind == TAW_DIAG_MFMA_LDS_LOADS) {
     if (!src) return TAW_ERR_NULL;
@@ -278,7 +320,7 @@ extern "C" int taw_diag_mfma_loop(int32_t kind, int32_t iters, const void* src, 
     if (e != hipSuccess) return TAW_ERR_HIP;
     sink = reinterpret_cast<float*>(p);
   }
-  const size_t lds = kind >= TAW_DIAG_MFMA_LDS ? 131072 : 0;
+  const size_t lds = kind == TAW_DIAG_MFMA_LDS || kind == TAW_DIAG_MFMA_LDS_LOADS ? 131072 : 0;
   float ms = 0.f;
   int rc;
   const unsigned char* s8 = static_cast<const unsigned char*>(src);
@@ -292,7 +334,12 @@ extern "C" int taw_diag_mfma_loop(int32_t kind, int32_t iters, const void* src, 
     case TAW_DIAG_MFMA_RANDOM: TAW_DIAG_RUN(TAW_DIAG_MFMA_RANDOM); break;
     case TAW_DIAG_MFMA_ZERO: TAW_DIAG_RUN(TAW_DIAG_MFMA_ZERO); break;
     case TAW_DIAG_MFMA_LDS: TAW_DIAG_RUN(TAW_DIAG_MFMA_LDS); break;
-    default: TAW_DIAG_RUN(TAW_DIAG_MFMA_LDS_LOADS); break;
+    case TAW_DIAG_MFMA_LDS_LOADS: TAW_DIAG_RUN(TAW_DIAG_MFMA_LDS_LOADS); break;
+    default:
+      if (iters & 1) --iters;                                        // trips of two
+      if (iters == 0) iters = 2;
+      rc = timed([&] { hipLaunchKernelGGL(mfma16_loop_kernel, dim3(256), dim3(256), 0, 0, iters / 2, sink); }, &ms);
+      break;
   }
 #undef TAW_DIAG_RUN
   if (rc) return TAW_ERR_HIP;
