@@ -712,7 +712,10 @@ __global__ void __launch_bounds__(256) attn_bwd_prep_kernel(const bf16_t* __rest
 //   S = Q K^T and dP = dO V^T, 32 x 32 as four 16 x 16 blocks each (16x16x32 MFMAs: less power per product, gemm_mfma.hip), the fragments of the next
 //   step read one by one between the MFMAs of this one;  P = exp(S/sqrt(d) - lse);  dS = P (dP - D)
 //   dV^T += dO^T P;   dK^T += Q^T dS  (scaled by 1/sqrt(d) at the end)
-// Step of 32768 tokens, 32 heads 59.6 -> 59.0 ms, of 8192 9.15 -> 9.12; 4 wavefronts, bound by latency, 2 x 333 of 2 heads 106.0 -> 106.3 us.
+// What 16x16x32 gives depends on how long the chip is full, us of a layer's backward with 32x32x16 -> 16x16x32, both on the same buffers: 32768 tokens of 32 heads
+// (step) 63.2 -> 61.2 ms, 16384 of 64 53.5 -> 52.4, 8192 of 32 6658 -> 6645, 4096 of 32 3106 -> 3111, 2048 of 40 2495 -> 2495, 5 x 777 of 13 673 -> 678.  In a loop of its
+// own, away from the products that bring the chip to its power limit, the attention backward is 1 - 3 % slower below about 8192 tokens of 32 heads
+// (2048 of 48 194 -> 197, 4096 of 32 420 -> 426) and 3 - 4 % faster above.
 constexpr int kKvStage = 2 * kTileBytes + 2 * 64 * 4;                    // Q tile | dO tile | lse[64] | D[64]
 template <int NW> constexpr size_t kKvLds = NW * 8192 + 2 * kKvStage;     // key tile [32 NW][128] bf16 in front of the ring
 //
@@ -1097,8 +1100,8 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
 // 3-stage ring filled by direct global->LDS loads two tiles ahead: the K tile [64][128], shared, and per wavefront the two
 // dS units (32 keys each) of its own row group, 4 KiB copied as they lie in memory (consecutive tiles are consecutive
 // there: eight sequential streams per workgroup).  Both operands are transposing reads: K^T as in the kernel above, dS^T
-// from the wavefront's units at the slots ds_slot() gave them.  The 32 rows of a group come in the order the dK/dV kernel's
-// accumulators had them (ds_row_of_slot); only the epilogue needs to know.  With 16 MFMAs per wavefront and 48 KiB per
+// from the wavefront's units at the slots ds_slot() gave them.  The 32 rows of a group come in the order of the stored pieces
+// (ds_row_of_slot), for which the dK/dV kernel picks the rows of its fragments (LaneAddr16Q); only the epilogue needs to know.  With 16 MFMAs per wavefront and 48 KiB per
 // tile the kernel is bound by the rate the dS matrix streams in from memory.
 template <int NW> constexpr int kDqsStage = kTileBytes + NW * 4096;        // K tile | NW wavefronts x (2 units of 2 KiB)
 constexpr int kDqsStages = 3;
@@ -1591,12 +1594,14 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(f32x4_t* __restrict__ p, 
 // the longest one over its 64-row blocks: with two wavefronts per SIMD a block takes their matrix instructions twice over
 // (forward 1.6 us, alone 1.2), and with 256 compute units the halves have somewhere to go.  Both measured, us
 // forward / backward, 8 wavefronts -> 4 (n8 = 256-row tiles of all (batch, head) pairs):
-//   n8 = 8    2 x 333 tokens, 2 heads     12.6 / 31.1 -> 10.6 / 25.2
-//   n8 = 144  3 x 1501 tokens, 8 heads    41.5 / 103  -> 33.7 / 83
-//   n8 = 256  2048 tokens, 32 heads       56.4 / 151  -> 48.7 / 128;   32768 tokens, 2 heads   757 / 1987 -> 630 / 1752
-//   n8 = 384  2048 tokens, 48 heads       60.3 / 177  -> 76.7 / 202: two wavefronts overlap better once the chip is full
+//   n8 = 8    2 x 333 tokens, 2 heads     13.5 / 32.3 -> 10.8 / 25.5
+//   n8 = 144  3 x 1501 tokens, 8 heads    42.4 / 112  -> 32.3 / 88
+//   n8 = 256  2048 tokens, 32 heads       56.7 / 169  -> 48.9 / 143;   32768 tokens, 2 heads   794 / 2301 -> 633 / 1871
+//   n8 = 384  2048 tokens, 48 heads       60.9 / 192  -> 76.5 / 220: two wavefronts overlap better once the chip is full
 // With more than 256 of the halves the gain is the finer causal triangle, which one or two tiles per pair don't have:
-//   n8 = 256  8 x 200 tokens, 32 heads    15.2 / 38.7 -> 17.8 / 44.3;  2 x 512 tokens, 64 heads  23.0 / 56.1 -> 22.8 / 57.7
+//   n8 = 256  8 x 200 tokens, 32 heads    15.5 / 39.4 -> 18.2 / 44.6;  2 x 512 tokens, 64 heads  21.1 / 60.1 -> 22.4 / 60.5
+// The line is wrong between 256 and 512 halves where the pairs are no multiple of 8, so that some XCD gets a second round of them:
+//   n8 = 240  2 x 1000 tokens, 30 heads   31.9 / 94   -> 44.6 / 119;   5 x 777 tokens, 12 heads  26.9 / 78 -> 36.1 / 95
 bool few_tiles(int B, int S, int nh) {
   const int64_t pairs = (int64_t)B * nh, n8 = ((int64_t)S + 255) / 256 * pairs, n4 = ((int64_t)S + 127) / 128 * pairs;
   return n4 <= 256 || (n8 <= 256 && S > 512);

@@ -11,9 +11,8 @@
 // and what lies beyond K is zeroed in LDS once it has landed.
 //
 // Why 16x16x32 and not 32x32x16: a full chip of these products is bound by power, and per product the
-// smaller tile draws less of it.  A loop of MFMAs on random bf16 operands, everything in registers:
-// 2010 TFLOP/s at 2.03 GHz against 1790 at 1.77 (8x8 tiles and 4x4 of the larger, one wavefront per
-// SIMD).  8192 x 8192 x 8192 NT: 1430 -> 1600 TFLOP/s, 32768 x 4096 x 11008 NT 1406 -> 1560, its weight
+// smaller tile draws less of it.  A loop of MFMAs on random bf16 operands, everything in registers
+// (taw_diag_mfma_loop): 1932 TFLOP/s at 1.94 GHz against 1725 at 1.72, on a better box 2010 and 1790.  8192 x 8192 x 8192 NT: 1430 -> 1600 TFLOP/s, 32768 x 4096 x 11008 NT 1406 -> 1560, its weight
 // gradient 1368 -> 1470 (boxes differ by 5 %, both sides on one).
 //
 // LDS layouts.  A K-contiguous operand is stored [row][64] with its 16-byte chunks XOR-swizzled by
@@ -135,11 +134,11 @@ struct EpiArgs {
 // the rotation of 8 consecutive columns col .. col + 7 of row `row`: the table's 4 pairs, and their use
 struct RotPairs {
   f32x4_t cs[2];
-  __device__ __forceinline__ void load_at(unsigned pos, int64_t col, const EpiArgs& ea) {
-    const float* tb = ea.table + ((int64_t)pos * 64 + ((col & 127) >> 1)) * 2;
+  __device__ __forceinline__ void load_from(const float* tb) {
     cs[0] = *reinterpret_cast<const f32x4_t*>(tb);
     cs[1] = *reinterpret_cast<const f32x4_t*>(tb + 4);
   }
+  __device__ __forceinline__ void load_at(unsigned pos, int64_t col, const EpiArgs& ea) { load_from(ea.table + ((int64_t)pos * 64 + ((col & 127) >> 1)) * 2); }
   __device__ __forceinline__ void load(int64_t row, int64_t col, const EpiArgs& ea) { load_at((unsigned)row % (unsigned)ea.S, col, ea); }      // token counts fit 32 bits
   __device__ __forceinline__ void rotate(float (&v)[8], int round_first) const {
 #pragma unroll
@@ -270,7 +269,7 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
   constexpr bool COMBINE = EPI == kEpiNone;                 // the rotary projection has neither residual nor accumulation
   struct Extra {
     chunk_t r[COMBINE ? UP : 1], c[COMBINE ? UP : 1];
-    f32x4_t cs[EPI == kEpiRope ? 2 * UP : 1];      // (cos, sin) of the 4 pairs of every pass
+    RotPairs rot[EPI == kEpiRope ? UP : 1];        // of every pass
   } extra[2];
   const bool rotate = EPI == kEpiRope && n0 + wn < ea.rot_cols;                              // wavefront-uniform: 128 columns are one head
   int pos0 = EPI == kEpiRope ? (int)((unsigned)(m0 + wm + rr0) % (unsigned)ea.S) : 0;        // this lane's row in pass 0 (token counts fit 32 bits)
@@ -298,8 +297,7 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
         int pos = pos0 + it * RPP;
         if (EDGE && ea.S < 32) pos = (int)((unsigned)pos % (unsigned)ea.S);
         else pos = pos >= ea.S ? pos - ea.S : pos;      // 32 rows never span more than one sequence boundary (S >= 32)
-        x.cs[2 * it] = *reinterpret_cast<const f32x4_t*>(tab + (int64_t)pos * 128);
-        x.cs[2 * it + 1] = *reinterpret_cast<const f32x4_t*>(tab + (int64_t)pos * 128 + 4);
+        x.rot[it].load_from(tab + (int64_t)pos * 128);
       }
       pos0 += 32;
       if (EDGE && ea.S < 32) pos0 = (int)((unsigned)pos0 % (unsigned)ea.S);
@@ -318,15 +316,7 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
       const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(sp), v1 = *reinterpret_cast<const f32x4_t*>(sp + 4);
       float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
       if constexpr (!COMBINE) {
-        if (rotate) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float c = x.cs[2 * p + (e >> 1)][2 * (e & 1)], sn = x.cs[2 * p + (e >> 1)][2 * (e & 1) + 1];
-            const float a = ea.round_first ? (float)(bf16_t)v[2 * e] : v[2 * e], b2 = ea.round_first ? (float)(bf16_t)v[2 * e + 1] : v[2 * e + 1];
-            v[2 * e] = a * c - b2 * sn;
-            v[2 * e + 1] = a * sn + b2 * c;
-          }
-        }
+        if (rotate) x.rot[p].rotate(v, ea.round_first);
       } else {
         if (rw) {
 #pragma unroll
@@ -871,9 +861,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
 // NST stages; a step's fragments are read into registers one step ahead, while the MFMAs of the step before run.  NST = 4: the deep
 // prefetch a short grid needs (nothing else covers the latency of its loads); NST = 2: two workgroups share a compute unit.
 // What bounds them: the latency of a step's loads and, in a full chip, L2 bandwidth (a 128 x 128 tile reads twice the bytes per product
-// of a 256 x 256 one).  C[T, N] = A B^T, 256 x 256 tiles -> the shape picked: 1024 x 4096, K = 11008: 208 -> 98 us; 1024 x 1024, K = 1024:
-// 21.4 -> 6.0; 64 x 4096, K = 11008: 203 -> 22.5 (64 x 64, contraction in four ranges); 666 x 768, K = 256: 14.7 -> 4.0.  Reading the
-// fragments inside the step they are used in costs a third (64 x 64, K = 4096: 0.31 us per step instead of 0.26; 128 x 128: 0.70, 0.42).
+// of a 256 x 256 one).  C[T, N] = A B^T, 256 x 256 tiles -> the shape picked: 1024 x 4096, K = 11008: 174 -> 89 us; 1024 x 1024, K = 1024:
+// 22.5 -> 6.0; 64 x 4096, K = 11008: 171 -> 23.3 (64 x 64, contraction in eight ranges); 666 x 768, K = 256: 11.2 -> 4.3.  Reading the
+// fragments inside the step they are used in cost a third with 32x32x16 MFMAs (64 x 64, K = 4096: 0.31 us per step instead of 0.26; 128 x 128: 0.70, 0.42).
 template <int MODE, bool C_F32, int TM, int TN, int NST, int EPI = kEpiNone>
 __device__ __forceinline__ void gemm_small_body(const GemmArgs& ga, int block) {
   constexpr bool A_KC = (MODE != GEMM_TN);
@@ -1199,8 +1189,10 @@ struct GemmPlan {
 
 // What a tile shape costs, in microseconds: `fixed` per workgroup, and per 64-deep step the larger of `lone` (one workgroup on a compute
 // unit: the latency of its loads) and `busy` x the workgroups that share the unit (`resident` at most).  Fitted over 1800
-// timings of the five shapes at 64 ... 8192 rows and 256 ... 22016 columns: 13 % off in the mean, and what it picks is 4 % slower than
-// the fastest of the shapes and cuts measured, 256 x 256 tiles alone 88 % (up to 9 times).
+// timings of the five shapes at 64 ... 8192 rows and 256 ... 22016 columns, with 32x32x16 MFMAs and every result stored through LDS.  Over 1838
+// timings of the kernels there are (66 products and their backwards, the same range) it is 10.6 % off in the mean, 9 % low for 64 x 64 tiles and 3 %
+// for the others, and what it picks is 3.3 % slower than the fastest of the shapes and cuts (products 1.4 %, pairs 5.2; one in eight by more than 10 %, the
+// backward of 333 x 4096 x 11008 by 31).  256 x 256 tiles alone are up to 7 times slower.
 struct TileCost {
   int tile, tm, tn, nst, resident;
   double fixed, lone, busy;
