@@ -722,8 +722,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
     B += B_KC ? k0 : k0 * ldb;
     K = K - k0 < ga.k_chunk ? K - k0 : ga.k_chunk;
   }
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds2[];
-  const lds_u8_t* lds = (const lds_u8_t*)lds2;
+  extern __shared__ __attribute__((aligned(2 * kOp64))) unsigned char lds64[];      // A's two stages differ in one bit of an absolute LDS address
+  const lds_u8_t* lds = (const lds_u8_t*)lds64;
   const unsigned lds0 = (unsigned)(size_t)lds;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -765,8 +765,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   stage_barrier();
   int slot_b = 0;                                // of the current stage
   auto zero_last = [&](int kt) {                 // slot_b: of stage kt, the last
-    oa.zero_tail(lds2 + (kt & 1) * kOp64, rem, tid);
-    ob.zero_tail(lds2 + (2 + slot_b) * kOp64, rem, tid);
+    oa.zero_tail(lds64 + (kt & 1) * kOp64, rem, tid);
+    ob.zero_tail(lds64 + (2 + slot_b) * kOp64, rem, tid);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     stage_barrier();
   };
@@ -783,16 +783,16 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   // Fragment addresses go to the other stage between a fragment's last read of one and its first of the next: MFMA k-step 1's in the
   // first half of a step, k-step 0's in the second; operands that are not K-contiguous have the same addresses for both, and change in the first.
   constexpr int TB = B_KC ? 1 : 8, TN = TB + (A_KC ? 1 : 8);
-  auto move = [&](auto n, int ks, int by_a, int by_b) __attribute__((always_inline)) {
+  auto move = [&](auto n, int ks, int by_b) __attribute__((always_inline)) {
     if constexpr (n < TB) ob.rd[B_KC ? ks : n] += by_b;
-    else oa.rd[A_KC ? ks : n - TB] += by_a;
+    else oa.rd[A_KC ? ks : n - TB] ^= kOp64;
   };
 #pragma unroll
   for (int i = 0; i < (A_KC ? 2 : 8); ++i) oa.rd[i] += lds0;
 #pragma unroll
   for (int i = 0; i < (B_KC ? 2 : 8); ++i) ob.rd[i] += lds0 + 2 * kOp64;
   static_for<UN>([&](auto u) __attribute__((always_inline)) { read(u, 0); });
-  if (A_KC) oa.rd[0] += kOp64;
+  if (A_KC) oa.rd[0] ^= kOp64;
   if (B_KC) ob.rd[0] += kOp64;
   // MFMA e of a k-step: row by row, every other row backwards, so that two in a row always share a fragment
   auto mfma = [&](int e, int ks) __attribute__((always_inline)) {
@@ -805,13 +805,12 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
     constexpr bool LOAD = decltype(load_c)::value, NEXT = decltype(next_c)::value;
     const unsigned fa_dst = fill_a + (kt & 1) * kOp64, fb_dst = fill_b + (slot_b == 0 ? 2 : slot_b - 1) * kOp64;
     slot_b = slot_b == 2 ? 0 : slot_b + 1;       // from here on: of the next stage
-    const int by1 = slot_b == 0 ? -2 * kOp64 : kOp64, by2 = slot_b == 2 ? -2 * kOp64 : kOp64;      // B: to the next stage, and from there to the one after
-    const int by_a = kt & 1 ? -kOp64 : kOp64;    // A: to the next stage; the one after lies where this one does
+    const int by1 = slot_b == 0 ? -2 * kOp64 : kOp64, by2 = slot_b == 2 ? -2 * kOp64 : kOp64;      // to the next stage, and from there to the one after
     static_for<64>([&](auto e) __attribute__((always_inline)) {
       mfma(e, 0);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (e < 48 && e * UN / 48 < (e + 1) * UN / 48) read(std::integral_constant<int, e * UN / 48>{}, 1);
-      if constexpr (NEXT && e >= 48 && e - 48 < TN) move(std::integral_constant<int, e - 48>{}, 1, by_a, by1);
+      if constexpr (NEXT && e >= 48 && e - 48 < TN) move(std::integral_constant<int, e - 48>{}, 1, by1);
       if constexpr (LOAD && e % 8 == 0) dma_b(std::integral_constant<int, e / 8>{}, fb_dst);
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -827,7 +826,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (NEXT) {
         if constexpr (e * UN / 64 < (e + 1) * UN / 64) read(std::integral_constant<int, e * UN / 64>{}, 0);
-        if constexpr (A_KC && e == 63) oa.rd[0] -= by_a;
+        if constexpr (A_KC && e == 63) oa.rd[0] ^= kOp64;
         if constexpr (B_KC && e == 62) ob.rd[0] += by2;
       }
       if constexpr (LOAD && e % 8 == 0) dma_a(std::integral_constant<int, e / 8>{}, fa_dst);
@@ -850,9 +849,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   step(kt, std::false_type{}, std::false_type{});
 
   if (ga.splits > 1)
-    store_large<true>(acc, lds2, wave, lane, m0, n0, wm, wn, M, part_row(N, C_F32), ga.part + sp * M * part_row(N, C_F32), part_row(N, C_F32), 0, nullptr, 0, ga.epi);
+    store_large<true>(acc, lds64, wave, lane, m0, n0, wm, wn, M, part_row(N, C_F32), ga.part + sp * M * part_row(N, C_F32), part_row(N, C_F32), 0, nullptr, 0, ga.epi);
   else
-    store_large<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
+    store_large<C_F32, EPI>(acc, lds64, wave, lane, m0, n0, wm, wn, M, N, ga.C, ga.ldc, ga.accumulate, ga.R, ga.ldr, ga.epi);
 }
 
 // =============================================================================== small tiles

@@ -15,8 +15,8 @@ OBJDUMP = next((p for p in (os.path.join(os.path.dirname(HIPCC), "..", "llvm", "
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{kernel: its instructions in order, as text}"""
+def code_objects(tmp_path_factory):
+    """the folder and names of the device code objects in the library"""
     if OBJDUMP is None:
         pytest.skip("no llvm-objdump beside hipcc")
     if not os.path.exists(taw.LIB_PATH):
@@ -24,10 +24,15 @@ def kernels(tmp_path_factory):
     d = tmp_path_factory.mktemp("isa")
     shutil.copy(taw.LIB_PATH, d / "libtaw.so")
     subprocess.run([OBJDUMP, "--offloading", "libtaw.so"], cwd=d, check=True, capture_output=True)
+    return d, [f for f in sorted(os.listdir(d)) if "amdgcn" in f]
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    """{kernel: its instructions in order, as text}"""
+    d, files = code_objects
     out = {}
-    for f in sorted(os.listdir(d)):
-        if "amdgcn" not in f:
-            continue
+    for f in files:
         name = None
         for line in subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", f], cwd=d, check=True, capture_output=True, text=True).stdout.splitlines():
             head = re.match(r"[0-9a-f]+ <(.*)>:", line)
@@ -37,6 +42,17 @@ def kernels(tmp_path_factory):
                 out[name] = []
             elif name and text:
                 out[name].append(text)
+    return out
+
+
+@pytest.fixture(scope="module")
+def static_lds(code_objects):
+    """{kernel: bytes of LDS beside what its launch asks for}"""
+    d, files = code_objects
+    out = {}
+    for f in files:
+        notes = subprocess.run([OBJDUMP.replace("objdump", "readelf"), "--notes", f], cwd=d, check=True, capture_output=True, text=True).stdout
+        out.update((name, int(size)) for size, name in re.findall(r"\.group_segment_fixed_size: (\d+)\n(?:.*\n)*?\s+\.name:\s+(_Z\S+)", notes))
     return out
 
 
@@ -68,13 +84,12 @@ def test_loads_into_lds_wait_for_m0(kernels):
     assert {name: d for name, d in loads.items() if any(x is None or x < 1 for x in d)} == {}
 
 
-def test_large_tiles_move_between_stages_by_addition(kernels):
-    """The fragments of a 256 x 256 tile are read at absolute LDS addresses.  Flipping the bit of the stage's size (0x8000) in them would
-    hold only while the ring starts at a multiple of twice that, which nothing guarantees; adding the size holds for any start."""
-    large = {name: text for name, text in kernels.items() if "v216gemm_pipe" in name or "v216gemm_dual" in name}
-    assert len(large) == 8
-    for name, text in large.items():
-        assert not [t for t in text if t.startswith("v_xor") and "0x8000" in t], name
+def test_flipped_stage_addresses(kernels, static_lds):
+    """The 256 x 256 tiles go from one stage of A to the other by flipping a bit (0x8000) of absolute LDS addresses, which holds while the ring starts at
+    a multiple of twice that: it is declared so, and whatever LDS a kernel has beside it is padded to that (and then too much to launch with)."""
+    flip = [name for name, text in kernels.items() if any(t.startswith("v_xor") and "0x8000," in t for t in text)]
+    assert len(flip) == 8
+    assert {name: static_lds[name] for name in flip if static_lds[name] % 0x10000} == {}
 
 
 def registers(operand):
