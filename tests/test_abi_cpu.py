@@ -356,7 +356,8 @@ def test_stored_ds_layout(lib, S):
     """The dS hand-over of the default attention backward, as the kernels address it: the 2 KiB units of a (batch, head) tile
     its region exactly (no gap, no overlap, query block ib holding 256 (ib + 1) keys x 256 rows), and a wavefront of the reading
     kernel (one 32-row group) finds its units for consecutive key groups at consecutive addresses; the 128 slots of a unit are a
-    permutation, the pieces tt of all keys fill one contiguous KiB, and the 16 slots a
+    permutation, the pieces tt of all keys fill one contiguous KiB, a store instruction (both pieces of both lane halves of 16 keys) fills two runs of
+    512 bytes and the other one of a unit the same 512 bytes further on, and the 16 slots a
     half-wavefront of the reader touches in one transposing read (4 consecutive keys x 2 lane halves x 2 pieces) fall into 16
     different 16-byte bank groups; positions map back to rows."""
     L = taw.taw_diag_attn_ds_layout(S)
@@ -374,6 +375,9 @@ def test_stored_ds_layout(lib, S):
     assert sorted(slots) == list(range(128))
     for tt in range(2):
         assert sorted(slots[(2 * tt + hh) * 32 + kk] for hh in range(2) for kk in range(32)) == list(range(64 * tt, 64 * tt + 64))
+    for k in range(4):                                        # (2 tt + hh)
+        assert [slots[32 * k + kk + 16] for kk in range(16)] == [slots[32 * k + kk] + 32 for kk in range(16)]
+    assert sorted(slots[32 * k + kk] for k in range(4) for kk in range(16)) == list(range(32)) + list(range(64, 96))
     for k4 in range(8):
         group = [slots[(2 * tt + hh) * 32 + 4 * k4 + j] for tt in range(2) for hh in range(2) for j in range(4)]
         assert sorted(x % 16 for x in group) == list(range(16))
