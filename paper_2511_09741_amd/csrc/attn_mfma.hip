@@ -473,10 +473,11 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
           }
     }
     // v_max3_f32 by name: fmaxf on MFMA results makes the compiler quiet possible signalling NaNs first, one extra
-    // instruction per score, and pair the maxima up with two-operand instructions (58 instructions for 32 scores instead of 16).  As a tree: between
-    // two such blocks of which one needs the other's result the compiler puts a wait state, in a chain 14 of them.
+    // instruction per score, and pair the maxima up with two-operand instructions (58 instructions for 32 scores instead of 16).  Between two such
+    // blocks of which one needs the other's result the compiler puts a wait state, in a chain 14 of them: a wavefront alone on its SIMD takes the
+    // maxima as a tree; with two the chain is no slower (32768 of 32 heads 7474 us, as a tree 7516).
     float mx[2];
-    {
+    if constexpr (NW == 4) {
       float t[2][5];
 #pragma unroll
       for (int i = 0; i < 5; ++i)
@@ -491,6 +492,14 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
       for (int qb = 0; qb < 2; ++qb) t[qb][3] = max3(t[qb][3], t[qb][4], s[qb][3][3]);
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) mx[qb] = max3(t[qb][0], t[qb][3], t[qb][3]) * c;
+    } else {
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        mx[qb] = max3(s[qb][0][0], s[qb][0][1], s[qb][0][0]);
+#pragma unroll
+        for (int i = 2; i < 16; i += 2) mx[qb] = max3(mx[qb], s[qb][i / 4][i % 4], s[qb][i / 4][i % 4 + 1]);
+        mx[qb] *= c;
+      }
     }
     // wavefront-uniform: some row's maximum moved far.  Each lane asks for its own quarter of the keys: only where one says yes
     // are the quarters of a row brought together.
