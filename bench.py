@@ -612,15 +612,15 @@ def run_diag(env):
             row = {f"{n} stores": round(taw.taw_diag_store_cost(buf, nb, waves, mf, n), 1) for n in (0, 1, 2, 4)}
             out["store_cost_ns_per_trip"][f"{waves} wavefronts per compute unit, {mf} MFMAs per trip"] = row
     del buf
-    # the product GEMM (NT, bf16, K = 4096) on 64, 256 and 1024 output tiles: the same kernel and the same work per tile; what changes
-    # is how many compute units draw power at once
+    # the GEMM (NT, fp32 results, which keep the 256 x 256 tile at every size, K = 4096) on 64, 256 and 1024 output tiles: the same kernel and
+    # the same work per tile; what changes is how many compute units draw power at once
     BF = taw.TAW_BF16
     for (M, N) in ((2048, 2048), (4096, 4096), (8192, 8192)):
         K = 4096
         A = torch.empty(M * K, dtype=torch.bfloat16, device="cuda").normal_()
         Bm = torch.empty(N * K, dtype=torch.bfloat16, device="cuda").normal_()
-        Cm = torch.empty(M * N, dtype=torch.bfloat16, device="cuda")
-        t = env.ev_time(lambda: taw.taw_op_gemm(BF, taw.TAW_GEMM_NT, M, N, K, A, K, Bm, K, Cm, N, BF, 0, None, 0, taw.TAW_IMPL_MFMA, env.compute), 20)
+        Cm = torch.empty(M * N, dtype=torch.float32, device="cuda")
+        t = env.ev_time(lambda: taw.taw_op_gemm(BF, taw.TAW_GEMM_NT, M, N, K, A, K, Bm, K, Cm, N, taw.TAW_F32, 0, None, 0, taw.TAW_IMPL_MFMA, env.compute), 20)
         tiles = (M // 256) * (N // 256)
         tf = 2.0 * M * N * K / t / 1e9
         out["gemm_by_tiles"].append({"M": M, "N": N, "K": K, "tiles": tiles, "ms": round(t, 4), "TFLOPs": round(tf, 1),
