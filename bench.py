@@ -574,7 +574,7 @@ def run_diag(env):
     torch, taw = env.torch, env.taw
     src = torch.empty(256 << 20, dtype=torch.uint8, device="cuda")
     src.view(torch.int32).random_(0, 1 << 30)
-    names = {taw.TAW_DIAG_MFMA16_RANDOM: "mfma_16x16x32_only_random_operands", taw.TAW_DIAG_MFMA_RANDOM: "mfma_only_random_operands", taw.TAW_DIAG_MFMA_ZERO: "mfma_only_zero_operands",
+    names = {taw.TAW_DIAG_MFMA_RANDOM: "mfma_only_random_operands", taw.TAW_DIAG_MFMA16_RANDOM: "mfma_16x16x32_only_random_operands", taw.TAW_DIAG_MFMA_ZERO: "mfma_only_zero_operands",
              taw.TAW_DIAG_MFMA_LDS: "mfma_plus_lds_fragment_reads", taw.TAW_DIAG_MFMA_LDS_LOADS: "mfma_plus_lds_reads_plus_global_to_lds_loads"}
     out = {"mfma_loop": {}, "lds_read_bytes_per_clock_per_cu": {}, "issue_cycles_per_mfma_slot": {}, "dq_update": {}, "gemm_by_tiles": []}
     # vector instructions beside MFMAs: cycles per slot of {1 MFMA + n vector instructions} (32 = the matrix pipe never idles)
