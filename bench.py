@@ -31,7 +31,7 @@ Prints ONE JSON line.  Besides the contract fields it carries
                 launch stream: at C3 the attention backward (credited and executed FLOP/s against the
                 2.5 PFLOP/s dense bf16 MFMA peak), at C2 the bf16 MFMA GEMM (the 12 GEMM shapes of a
                 step, one launch each); "rooflines" holds both, plus the attention forward
-  cpu_baseline  the fp64 CPU oracle timed on this box's host cores on one whole C2 layer
+  cpu_baseline  the fp64 CPU oracle timed on this machine's host cores on one whole C2 layer
   kernels       per-kernel-class rates measured the same way (attention, bandwidth kernels)
   overlap       step time with and without the staging copy running beside it, with the gradient
                 aggregation on the compute stream instead of its side stream, and the event timestamps

@@ -12,8 +12,9 @@
 //
 // Why 16x16x32 and not 32x32x16: a full chip of these products is bound by power, and per product the
 // smaller tile draws less of it.  A loop of MFMAs on random bf16 operands, everything in registers
-// (taw_diag_mfma_loop): 1932 TFLOP/s at 1.94 GHz against 1725 at 1.72, on a better box 2010 and 1790.  8192 x 8192 x 8192 NT: 1430 -> 1600 TFLOP/s, 32768 x 4096 x 11008 NT 1406 -> 1560, its weight
-// gradient 1368 -> 1470 (boxes differ by 5 %, both sides on one).
+// (taw_diag_mfma_loop): 1932 TFLOP/s at 1.94 GHz against 1725 at 1.72, on a better card 2010 and 1790.
+// 8192 x 8192 x 8192 NT: 1430 -> 1600 TFLOP/s, 32768 x 4096 x 11008 NT 1406 -> 1560, its weight
+// gradient 1368 -> 1470 (cards differ by 5 %, both sides on one).
 //
 // LDS layouts.  A K-contiguous operand is stored [row][64] with its 16-byte chunks XOR-swizzled by
 // (row>>1)&7: every MFMA operand (8 consecutive k of one row) is one ds_read_b128 and 16
