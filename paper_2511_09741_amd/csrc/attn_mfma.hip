@@ -278,35 +278,37 @@ __device__ __forceinline__ void tile_dma(uint64_t base, unsigned ld_bytes, int r
 // with `band` neighbouring tiles that stream the same operands (one fill of that L2 serves them), and 8 * 32 / band
 // pairs on the chip, whose operands (17 MB per pair at S = 32768) then fit the 256 MiB memory-side cache together;
 // all pairs side by side do not.  Long tiles still start before short ones (bands are walked in rank order), which
-// is what keeps the last round of workgroups short.  Pairs beyond the last multiple of 8 are dealt out tile by tile.
+// is what keeps the last round of workgroups short.  Pairs beyond the last multiple of 8 are dealt out tile by tile, and first: their long tiles
+// behind everybody's short ones would run on alone (8192 tokens of 20 heads, us forward / backward, last 431 / 1263, first 324 / 978; 16384 of 9 heads
+// 841 / 2398 and 564 / 1701; 2 x 1000 of 30 45 / 114 and 33 / 83).
 // Measured: the forward gains 2 - 5 % from bands at S >= 16384 and loses 3 % at S = 8192 (few tiles per pair: the finer
 // longest-first order of band = 1 matters more there); the two backward kernels lose 0.5 - 2 % at every size and keep
 // band = 1, every pair of the XCD side by side, rank by rank.
 __device__ __forceinline__ int pair_band(int nt) { return nt >= 128 ? 32 : nt >= 64 ? 16 : 1; }
 template <bool BANDS = true>
 __device__ __forceinline__ void pair_tile_of_block(int blk, int npairs, int nt, int& bh, int& rank) {
-  const int p8 = npairs & ~7;
-  if (blk < p8 * nt) {
-    const int P = p8 >> 3, band = BANDS ? pair_band(nt) : 1;
-    const int i = blk >> 3;
-    const int full = (nt / band) * band;               // ranks covered by whole bands
-    int pair, r;
-    if (i < P * full) {
-      const int bnd = i / (P * band), j = i - bnd * (P * band);
-      pair = j / band;
-      r = bnd * band + j % band;
-    } else {
-      const int last = nt - full, j = i - P * full;
-      pair = j / last;
-      r = full + j % last;
-    }
-    bh = (blk & 7) + 8 * pair;
-    rank = r;
-  } else {
-    const int r = blk - p8 * nt, pr = npairs - p8;
-    bh = p8 + r % pr;
-    rank = r / pr;
+  const int p8 = npairs & ~7, pr = npairs - p8;
+  if (blk < pr * nt) {
+    bh = p8 + blk % pr;
+    rank = blk / pr;
+    return;
   }
+  blk -= pr * nt;
+  const int P = p8 >> 3, band = BANDS ? pair_band(nt) : 1;
+  const int i = blk >> 3;
+  const int full = (nt / band) * band;               // ranks covered by whole bands
+  int pair, r;
+  if (i < P * full) {
+    const int bnd = i / (P * band), j = i - bnd * (P * band);
+    pair = j / band;
+    r = bnd * band + j % band;
+  } else {
+    const int last = nt - full, j = i - P * full;
+    pair = j / last;
+    r = full + j % last;
+  }
+  bh = (blk & 7) + 8 * pair;
+  rank = r;
 }
 
 // max of three without the canonicalising self-maximum the compiler puts in front of fmaxf on MFMA results
@@ -1609,8 +1611,6 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(f32x4_t* __restrict__ p, 
 //   n8 = 384  2048 tokens, 48 heads       60.9 / 192  -> 76.5 / 220: two wavefronts overlap better once the chip is full
 // With more than 256 of the halves the gain is the finer causal triangle, which one or two tiles per pair don't have:
 //   n8 = 256  8 x 200 tokens, 32 heads    15.5 / 39.4 -> 18.2 / 44.6;  2 x 512 tokens, 64 heads  21.1 / 60.1 -> 22.4 / 60.5
-// The line is wrong between 256 and 512 halves where the pairs are no multiple of 8, so that some XCD gets a second round of them:
-//   n8 = 240  2 x 1000 tokens, 30 heads   31.9 / 94   -> 44.6 / 119;   5 x 777 tokens, 12 heads  26.9 / 78 -> 36.1 / 95
 bool few_tiles(int B, int S, int nh) {
   const int64_t pairs = (int64_t)B * nh, n8 = ((int64_t)S + 255) / 256 * pairs, n4 = ((int64_t)S + 127) / 128 * pairs;
   return n4 <= 256 || (n8 <= 256 && S > 512);

@@ -582,3 +582,9 @@ def test_attn_mfma_few_and_many_tiles_agree(taw, S):
     for i in (0, B // 2, B - 1):
         for a, b in zip(both(qkv[i:i + 1].contiguous(), dO[i:i + 1].contiguous()), many):
             assert torch.equal(a[0], b[i])
+
+
+@pytest.mark.parametrize("B,S,nh", [(1, 700, 47), (1, 1024, 33), (3, 320, 7)])
+def test_attn_mfma_pairs_that_the_xcds_do_not_divide(taw, B, S, nh):
+    """(batch, head) pairs beyond the last multiple of 8 are dealt out tile by tile, in front of the others: every tile of every pair is done once."""
+    _attn_case(taw, I.BF16, B, S, nh, 128, taw.TAW_IMPL_MFMA, seed=S, bwd_impl=taw.TAW_IMPL_MFMA_STORED)
