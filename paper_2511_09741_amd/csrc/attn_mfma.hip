@@ -318,11 +318,51 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   return d;
 }
 
+// ---- where the wavefronts of a workgroup share rows (KS of them work on the same 32, each with its own part of what is summed over) ----
+// X^T[128 d][32 rows] as 16x16 blocks, (rb, dt) = rows 16 rb + (lane & 15), d = 16 dt + 4 (lane >> 4) + register.  Each of the KS wavefronts ends with a
+// share of the sum: 16 rows (block `part & 1`), all 128 columns (KS = 2) or one half of them (KS = 4, half `part >> 1`).  The blocks cross LDS as the
+// accumulators hold them, 16 bytes per lane: a wavefront's region is 16 KiB, block (rb, dt) at (8 rb + dt) KiB.
+template <int KS> struct Share {
+  static constexpr int kDt = 16 / KS;                                        // blocks of 16 columns
+  static __device__ __forceinline__ int rb(int part) { return part & 1; }
+  static __device__ __forceinline__ int dt0(int part) { return kDt * (part >> 1); }
+};
+__device__ __forceinline__ void give_blocks(const f32x4_t (&acc)[2][8], unsigned char* region, int lane) {
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4_t*>(region + (8 * rb + dt) * 1024 + lane * 16) = acc[rb][dt];
+}
+// the share's rows -> staging in LDS (16 rows of 16 N + 8) -> 16-byte stores of row segments; out: the share's first column, row0: its first row
+template <int N>
+__device__ __forceinline__ void store_share(const f32x4_t (&x)[N], float mul, bf16_t* stage, bf16_t* out, int64_t ld_out, int row0, int limit, int lane) {
+  constexpr int SLD = 16 * N + 8, CPR = 2 * N;                               // staging row; 16-byte pieces of a row
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    bf16x4_t pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pk[e] = (bf16_t)(x[j][e] * mul);
+    *reinterpret_cast<bf16x4_t*>(stage + (lane & 15) * SLD + 16 * j + 4 * (lane >> 4)) = pk;
+  }
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int it = 0; it < 16 * CPR / 64; ++it) {
+    const int idx = it * 64 + lane, row = idx / CPR, ch = idx % CPR;
+    if (row0 + row < limit)
+      *reinterpret_cast<u32x4_t*>(out + (int64_t)(row0 + row) * ld_out + ch * 8) = *reinterpret_cast<const u32x4_t*>(stage + row * SLD + ch * 8);
+  }
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_wave_barrier();
+}
+
 // =============================================================================== forward
 // Workgroup: NW = 8 wavefronts (two per SIMD, so one's softmax arithmetic overlaps the other's MFMAs) or, where there are
-// few tiles (few_tiles), 4; one (batch, head, 32 NW query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
+// few tiles (attn_shape), 4; one (batch, head, 32 NW / KS query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
 // through a 4-stage LDS ring of 64-key tiles filled by direct global->LDS loads issued three
 // tiles ahead; one workgroup barrier per tile.
+// KS > 1: KS wavefronts, w, w + 8 / KS, ..., own the same 32 rows, each with 32 keys of a tile (of 64; KS = 4: of 128, in 2 stages) and a maximum and
+// sums of its own, which meet at the end.
 //
 // Online softmax in the exp2 domain.  The running maximum of a row is only raised when a tile
 // exceeds it by more than kMaxSlack (in log2 units): until then the probabilities of the tile are
@@ -337,39 +377,45 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // 86.7 -> 85.1, 32768 of 2 638 -> 610 (the maximum as a chain and s_nop in the loads: 11.0, 41.9, 32.7, 87.1, 628).
 constexpr float kMaxSlack = 8.0f;
 
-template <int NW>
+template <int NW, int KS>
 __global__ void __launch_bounds__(NW * 64, 2)
 attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int B, int S, int nh, float scale) {
-  constexpr int WQ = 32, BQ = NW * WQ, BKV = 64, NS = 4;
-  constexpr int kStage = 2 * kTileBytes;   // K tile | V tile
+  constexpr int WQ = 32, RG = NW / KS, BQ = RG * WQ, BKV = KS == 4 ? 128 : 64, NS = KS == 4 ? 2 : 4, kIssue = KS == 4 ? 1 : NS - 2;
+  constexpr int WK = BKV / KS, NK = WK / 16;      // keys of a tile that a wavefront takes, in blocks of 16
+  static_assert(KS == 1 || ((KS == 2 || KS == 4) && NW == kWaves8), "");
+  constexpr int kV = BKV / 64 * kTileBytes, kStage = 2 * kV;   // K tile | V tile
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = KS == 1 ? 0 : wave / RG;            // which keys of a tile
   LaneAddr16 la;
   la.init(lane);
   const int nqt = (S + BQ - 1) / BQ;
   int bh, rank;
-  pair_tile_of_block<NW == kWaves8>((int)blockIdx.x, B * nh, nqt, bh, rank);
+  pair_tile_of_block<NW == kWaves8 && KS == 1>((int)blockIdx.x, B * nh, nqt, bh, rank);
   const int qt = nqt - 1 - rank;                       // longest rows first
   const int b = bh / nh, h = bh % nh;
   const int64_t H = (int64_t)nh * D, ld = 3 * H;
   const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * D;
   const uint64_t kbase = (uint64_t)(qbase + H), vbase = (uint64_t)(qbase + 2 * H);
   const unsigned ldb = (unsigned)(ld * 2);
-  const int q0 = qt * BQ, q0w = q0 + wave * WQ;
+  const int q0 = qt * BQ, q0w = q0 + (KS == 1 ? wave : wave % RG) * WQ;
   const float c = scale * kLog2e;
 
   const int kv_end = (q0 + BQ < S) ? q0 + BQ : S;
   const int nkv = (kv_end + BKV - 1) / BKV;
   auto issue = [&](int t) {
     const unsigned st = lds0 + (t & (NS - 1)) * kStage;
-    tile_dma<NW, 1>(kbase, ldb, t * BKV, S, st, lane, wave);
-    tile_dma<NW, 1>(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
+#pragma unroll
+    for (int i = 0; i < BKV / 64; ++i) {
+      tile_dma<NW, 1>(kbase, ldb, t * BKV + 64 * i, S, st + i * kTileBytes, lane, wave);
+      tile_dma<NW, 1>(vbase, ldb, t * BKV + 64 * i, S, st + kV + i * kTileBytes, lane, wave);
+    }
   };
-  for (int t = 0; t < NS - 2 && t < nkv; ++t) issue(t);
+  for (int t = 0; t < kIssue && t < nkv; ++t) issue(t);
 
   // Q as B operands, straight from global memory: two blocks of 16 rows
   bf16x8_t qf[2][4];
@@ -381,7 +427,10 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
     for (int ks = 0; ks < 4; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8_t*>(qbase + (int64_t)row * ld + 32 * ks + 8 * g);
   }
   f32x4_t oacc[2][8];
-  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};      // running maximum (scaled, log2 domain) and sum of this lane's quarter of the keys
+  // running maximum (scaled, log2 domain) and sum of this lane's quarter of the keys.  Half of the keys may hold none that a row sees: its maximum stays
+  // at a finite value then, which the other half's is above, and what it adds is zero.
+  constexpr float kNoMax = KS == 1 ? -INFINITY : -3.402823466e38f;
+  float m[2] = {kNoMax, kNoMax}, l[2] = {0.f, 0.f};
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -392,8 +441,8 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   // every barrier: wavefronts 0..3 do S = K Q^T, softmax, O += V^T P within the tile's period; the
   // late ones 4..7 start a period with the O += V^T P of the previous tile (its P waits in registers,
   // its V stays in the ring one period longer, which is why tiles are issued two ahead, not three).
-  const bool late = NW == kWaves8 && wave >= NW / 2;       // 4 wavefronts have a SIMD each
-  bf16x8_t pf[2][2];                                       // [16 rows][32 keys]
+  const bool late = NW == kWaves8 && KS != 4 && wave >= NW / 2;       // 4 wavefronts have a SIMD each
+  bf16x8_t pf[2][NK / 2];                                  // [16 rows][32 keys]
   bool pend = false;
   unsigned pend_tr = 0;
   // O^T += V^T P^T: 32 MFMAs, fragment i = (t, dt) = (i / 8, i % 8) for both blocks of rows.  The fragment reads run kAhead fragments
@@ -402,16 +451,17 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   // keep the compiler from moving the reads back next to their use.
   constexpr int kAhead = 4;
   auto pv = [&](unsigned tr_t) {
-    bf16x8_t vfr[16];
+    constexpr int NF = 4 * NK;
+    bf16x8_t vfr[NF];
     auto rd = [&](auto i_c) {
       TAW_CONST(i, i_c);
-      vfr[i] = frag16_tr<i % 8, kTileBytes + (i / 8) * 8192>(tr_t);
+      vfr[i] = frag16_tr<i % 8, kV + (i / 8) * 8192>(tr_t);
     };
     static_for<kAhead>(rd);
     __builtin_amdgcn_s_setprio(1);
-    static_for<16>([&](auto i_c) {
+    static_for<NF>([&](auto i_c) {
       TAW_CONST(i, i_c);
-      if constexpr (i + kAhead < 16) rd(std::integral_constant<int, i + kAhead>{});
+      if constexpr (i + kAhead < NF) rd(std::integral_constant<int, i + kAhead>{});
       __builtin_amdgcn_sched_barrier(0);
       oacc[0][i % 8] = mfma16(vfr[i], pf[0][i / 8], oacc[0][i % 8]);
       oacc[1][i % 8] = mfma16(vfr[i], pf[1][i / 8], oacc[1][i % 8]);
@@ -421,53 +471,56 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
   };
 
   // The register-resident operands loaded above have arrived: said here, once, so that the compiler
-  // does not wait for them (and with them for every tile load in flight) at their first use inside the loop.
+  // does not wait for them (and with them for every tile load in flight) at their first use inside the loop.  The same for the kernel's arguments that the
+  // epilogue needs: with their load still out, every wait for an LDS read in the loop would be one for all of them (5 %).
+  asm volatile("" ::"s"(o), "s"(lse));
   wait_vmcnt<0>();
   for (int j = 0; j < nkv; ++j) {
     // tile j has landed (each wavefront waits for its own pieces, the barrier collects them); the
     // barrier also says every wavefront is done with tile j-2, whose stage tile j+2 goes into
-    if (j + 1 < nkv) wait_vmcnt<2 * (16 / NW)>(); else wait_vmcnt<0>();
+    if (KS != 4 && j + 1 < nkv) wait_vmcnt<2 * (16 / NW)>(); else wait_vmcnt<0>();
     stage_barrier();
-    if (j + NS - 2 < nkv) issue(j + NS - 2);
+    if (j + kIssue < nkv) issue(j + kIssue);
     if (pend) {                                        // late wavefronts: the previous tile's O += V^T P
       pv(pend_tr);
       pend = false;
     }
-    const int kv0 = j * BKV;
-    if (kv0 > q0w + WQ - 1) continue;                  // no key of the tile is visible to this wavefront
-    const unsigned so = lds0 + (j & (NS - 1)) * kStage;
+    const int kv0 = j * BKV + part * WK;
+    if (kv0 > q0w + WQ - 1) continue;                  // no key of the tile (its half of it) is visible to this wavefront
+    const unsigned so = lds0 + (j & (NS - 1)) * kStage + part * (WK * D * 2);
     const unsigned nat_t = la.nat + so, tr_t = la.tr + so;
 
-    // S^T = K Q^T: 32 MFMAs in eight accumulation chains (16 rows x 16 keys), fragment i = (ks, kb) = (i / 4, i % 4) for both blocks of rows;
+    // S^T = K Q^T: 32 MFMAs in eight accumulation chains (16 rows x 16 keys), fragment i = (ks, kb) = (i / NK, i % NK) for both blocks of rows;
     // fragment reads kAhead fragments ahead, as in pv
-    f32x4_t s[2][4];
+    f32x4_t s[2][NK];
     {
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) s[qb][kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};      // (folded into the first MFMA of each chain as the constant 0)
-      bf16x8_t kfr[16];
+        for (int kb = 0; kb < NK; ++kb) s[qb][kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};      // (folded into the first MFMA of each chain as the constant 0)
+      constexpr int NF = 4 * NK;
+      bf16x8_t kfr[NF];
       auto rd = [&](auto i_c) {
         TAW_CONST(i, i_c);
-        kfr[i] = frag16_nat<i / 4, (i % 4) * 4096>(nat_t);
+        kfr[i] = frag16_nat<i / NK, (i % NK) * 4096>(nat_t);
       };
       static_for<kAhead>(rd);
       __builtin_amdgcn_s_setprio(1);
-      static_for<16>([&](auto i_c) {
+      static_for<NF>([&](auto i_c) {
         TAW_CONST(i, i_c);
-        if constexpr (i + kAhead < 16) rd(std::integral_constant<int, i + kAhead>{});
+        if constexpr (i + kAhead < NF) rd(std::integral_constant<int, i + kAhead>{});
         __builtin_amdgcn_sched_barrier(0);
-        s[0][i % 4] = mfma16(kfr[i], qf[0][i / 4], s[0][i % 4]);
-        s[1][i % 4] = mfma16(kfr[i], qf[1][i / 4], s[1][i % 4]);
+        s[0][i % NK] = mfma16(kfr[i], qf[0][i / NK], s[0][i % NK]);
+        s[1][i % NK] = mfma16(kfr[i], qf[1][i / NK], s[1][i % NK]);
         __builtin_amdgcn_sched_barrier(0);
       });
       __builtin_amdgcn_s_setprio(0);
     }
-    if (kv0 + BKV - 1 > q0w) {                         // tile crosses the diagonal (or the end of the sequence)
+    if (kv0 + WK - 1 > q0w) {                          // tile crosses the diagonal (or the end of the sequence)
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int kb = 0; kb < NK; ++kb)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int kv = kv0 + kb * 16 + 4 * g + r;
@@ -499,7 +552,7 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
       for (int qb = 0; qb < 2; ++qb) {
         mx[qb] = max3(s[qb][0][0], s[qb][0][1], s[qb][0][0]);
 #pragma unroll
-        for (int i = 2; i < 16; i += 2) mx[qb] = max3(mx[qb], s[qb][i / 4][i % 4], s[qb][i / 4][i % 4 + 1]);
+        for (int i = 2; i < 4 * NK; i += 2) mx[qb] = max3(mx[qb], s[qb][i / 4][i % 4], s[qb][i / 4][i % 4 + 1]);
         mx[qb] *= c;
       }
     }
@@ -525,7 +578,7 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
     for (int qb = 0; qb < 2; ++qb) {
       float rs = 0.f;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
+      for (int t = 0; t < NK / 2; ++t) {
         u32x4_t w;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -552,6 +605,46 @@ attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* _
 
   // ---- epilogue: O^T accumulators -> [q][136] bf16 staging in LDS -> coalesced rows of o
   constexpr int OLD = 136;
+  if constexpr (KS > 1) {
+    constexpr int N = Share<KS>::kDt, kStats = NW * 16384;      // behind the regions: [wavefront][maximum, row sum][32 rows]
+    unsigned char* const own = lds_raw + wave * 16384;
+    float* const stats = reinterpret_cast<float*>(lds_raw + kStats);
+    give_blocks(oacc, own, lane);
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      float lsum = l[qb] + __shfl_xor(l[qb], 16, 64);
+      lsum += __shfl_xor(lsum, 32, 64);
+      if (g == 0) {
+        stats[wave * 64 + 16 * qb + lane] = m[qb];
+        stats[wave * 64 + 32 + 16 * qb + lane] = lsum;
+      }
+    }
+    __syncthreads();
+    const int rb = Share<KS>::rb(part), dt0 = Share<KS>::dt0(part), rg = wave % RG, row0 = q0w + 16 * rb;
+    float f[KS], mm = -INFINITY, ls = 0.f;
+#pragma unroll
+    for (int p = 0; p < KS; ++p) {
+      f[p] = stats[(p * RG + rg) * 64 + 16 * rb + (lane & 15)];
+      mm = fmaxf(mm, f[p]);
+    }
+#pragma unroll
+    for (int p = 0; p < KS; ++p) {
+      f[p] = fast_exp2(f[p] - mm);
+      ls += f[p] * stats[(p * RG + rg) * 64 + 32 + 16 * rb + (lane & 15)];
+    }
+    f32x4_t x[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      x[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int p = 0; p < KS; ++p) x[j] += f[p] * *reinterpret_cast<const f32x4_t*>(lds_raw + (p * RG + rg) * 16384 + (8 * rb + dt0 + j) * 1024 + lane * 16);
+      x[j] *= 1.0f / ls;
+    }
+    if (g == 0 && dt0 == 0 && row0 + lane < S) lse[((int64_t)b * nh + h) * S + row0 + lane] = mm * kLn2 + logf(ls);
+    __syncthreads();                                            // the regions have been read: they are the staging area
+    store_share<N>(x, 1.0f, reinterpret_cast<bf16_t*>(own), o + (int64_t)b * S * H + (int64_t)h * D + 16 * dt0, H, row0, S, lane);
+    return;
+  }
   bf16_t* ob = reinterpret_cast<bf16_t*>(lds_raw) + wave * (WQ * OLD);
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
@@ -714,7 +807,8 @@ __global__ void __launch_bounds__(256) attn_bwd_prep_kernel(const bf16_t* __rest
 }
 
 // =============================================================================== backward: dK, dV
-// Workgroup: NW = 8 wavefronts (4 where few_tiles says so), one (batch, head, 32 NW keys); wavefront w owns keys 32w..32w+31.
+// Workgroup: NW = 8 wavefronts (4 where attn_shape says so), one (batch, head, 32 NW / KS keys); wavefront w owns keys 32w..32w+31.
+// KS > 1: KS wavefronts own the same 32 keys, each with 32 rows of a block of query rows (of 64; KS = 4: of 128); their sums meet at the end.
 // Their V rows stay in registers as B operands; their K rows are read from a copy of the key tile in LDS (8 NW KiB), which leaves the
 // registers for both score accumulators at once and for reading fragments ahead of the MFMAs.  Query rows stream
 // through a 2-stage LDS ring in blocks of 64 (Q and dO tiles plus the rows' lse and D), from the diagonal to the end
@@ -728,7 +822,11 @@ __global__ void __launch_bounds__(256) attn_bwd_prep_kernel(const bf16_t* __rest
 // own, away from the products that bring the chip to its power limit, the attention backward is 1 - 3 % slower below about 8192 tokens of 32 heads
 // (2048 of 48 194 -> 197, 4096 of 32 420 -> 426) and 3 - 4 % faster above.
 constexpr int kKvStage = 2 * kTileBytes + 2 * 64 * 4;                    // Q tile | dO tile | lse[64] | D[64]
-template <int NW> constexpr size_t kKvLds = NW * 8192 + 2 * kKvStage;     // key tile [32 NW][128] bf16 in front of the ring
+// KS > 1: blocks of 32 KS query rows, 32 to each of the KS wavefronts that share 32 keys
+template <int KS> constexpr int kKvRows = KS == 1 ? 64 : 32 * KS;
+template <int KS> constexpr int kKvStageOf = kKvRows<KS> / 64 * kKvStage;
+// key tile [32 NW / KS][128] bf16 in front of the ring; KS > 1 ends with 16 KiB per wavefront changing hands
+template <int NW, int KS = 1> constexpr size_t kKvLds = NW * 8192 / KS + 2 * kKvStageOf<KS> > (KS > 1 ? NW * 16384 : 0) ? NW * 8192 / KS + 2 * kKvStageOf<KS> : NW * 16384;
 //
 // STORE_DS: every dS block this kernel forms is also written to memory (bf16, exactly what the dK product multiplies by) for
 // a dQ kernel that then needs one matrix product instead of three (attn_bwd_dq_stored_kernel).  Layout of `ds`, per (batch,
@@ -748,19 +846,21 @@ template <int NW> constexpr size_t kKvLds = NW * 8192 + 2 * kKvStage;     // key
 // over and over to the same few KiB: it is the issue of the store instructions that costs, not the traffic.
 // (ds_block_offset, ds_unit_offset, ds_slot, ds_row_of_slot: taw_internal.h, where host code can check them)
 
-template <bool STORE_DS, int NW>
+template <bool STORE_DS, int NW, int KS>
 __global__ void __launch_bounds__(NW * 64, 2)
 attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
                     const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
                     const float* __restrict__ rope, unsigned char* __restrict__ ds, int64_t ds_pair_bytes) {
-  constexpr int BKVW = NW * 32, BQ = 64, NS = 2, kKvOffRing = NW * 8192;
-  constexpr int kStage = kKvStage;
+  constexpr int RG = NW / KS, BKVW = RG * 32, BQ = kKvRows<KS>, NS = 2, kKvOffRing = RG * 8192, kDO = BQ / 64 * kTileBytes;
+  static_assert(KS == 1 || ((KS == 2 || KS == 4) && NW == kWaves8 && kKvLds<NW, KS> <= 160 * 1024), "");
+  constexpr int kStage = kKvStageOf<KS>;      // Q tile | dO tile | lse | D
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = KS == 1 ? 0 : wave / RG;            // which 32 of a block's query rows
   LaneAddr16 la;                                       // of the key tile
   la.init(lane);
   LaneAddr16Q lq;                                      // of the query rows' tiles
@@ -775,14 +875,14 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   const uint64_t qb64 = (uint64_t)qbase, k64 = (uint64_t)kbase, do64 = (uint64_t)(dO + (int64_t)b * S * H + (int64_t)h * D);
   const uint64_t l64 = (uint64_t)(lse2 + ((int64_t)b * nh + h) * Sp), d64 = (uint64_t)(Dsum + ((int64_t)b * nh + h) * Sp);
   const unsigned ldb = (unsigned)(ld * 2), ldob = (unsigned)(H * 2);
-  const int kv0 = kt * BKVW, kv0w = kv0 + wave * 32;
+  const int kv0 = kt * BKVW, kv0w = kv0 + (KS == 1 ? wave : wave % RG) * 32;
   const float c = scale * kLog2e;
 
   const int jb = kv0 / BQ, je = (S + BQ - 1) / BQ;
   const int nblk = je - jb;
-  // key tile -> LDS (8 pieces of 4 rows per wavefront)
+  // key tile -> LDS (8 / KS pieces of 4 rows per wavefront)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 8 / KS; ++i) {
     const int j = wave + NW * i;
     const int r = 4 * j + (lane >> 4);
     const int cc = swz16(r, lane & 15);
@@ -793,10 +893,13 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   auto issue = [&](int t) {
     const unsigned st = lds0 + kKvOffRing + (t & (NS - 1)) * kStage;
     const int row0 = (jb + t) * BQ;
-    tile_dma<NW, 2>(qb64, ldb, row0, S, st, lane, wave);
-    tile_dma<NW, 2>(do64, ldob, row0, S, st + kTileBytes, lane, wave);
-    if (wave < 2)
-      lds_dma4(wave == 0 ? l64 : d64, (unsigned)(row0 + lane) * 4u, st + 2 * kTileBytes + wave * (BQ * 4));
+#pragma unroll
+    for (int i = 0; i < BQ / 64; ++i) {
+      tile_dma<NW, 2>(qb64, ldb, row0 + 64 * i, S, st + i * kTileBytes, lane, wave);
+      tile_dma<NW, 2>(do64, ldob, row0 + 64 * i, S, st + kDO + i * kTileBytes, lane, wave);
+    }
+    if (wave < BQ / 32 && row0 + 64 * (wave >> 1) < Sp)      // the statistics are padded to a multiple of 64
+      lds_dma4(wave & 1 ? d64 : l64, (unsigned)(row0 + 64 * (wave >> 1) + lane) * 4u, st + 2 * kDO + (wave & 1) * (BQ * 4) + (wave >> 1) * 256);
   };
   issue(0);
 
@@ -813,7 +916,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) dk[kb][dt] = dv[kb][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const unsigned knat_t = la.nat + lds0 + wave * 8192;
+  const unsigned knat_t = la.nat + lds0 + (KS == 1 ? wave : wave % RG) * 8192;
   const int qlane = 16 * (g >> 1) + 4 * (g & 1);       // block rb, register r: query row qlane + 8 rb + r of 32
   unsigned char* const ds_pair = STORE_DS ? ds + (int64_t)bh * ds_pair_bytes : nullptr;
   for (int t = 0; t < nblk; ++t) {
@@ -823,12 +926,12 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
     const int qb0 = (jb + t) * BQ;
     if (qb0 + BQ - 1 < kv0w) continue;
     const unsigned so = lds0 + kKvOffRing + (t & (NS - 1)) * kStage;
-    const unsigned nat_t = lq.nat + so, tr_t = lq.tr + so;
-    const unsigned sl = so + 2 * kTileBytes + 4 * qlane;
-    static_for<2>([&](auto qb_c) {
+    const unsigned nat_t = lq.nat + so + part * 8192, tr_t = lq.tr + so + part * 8192;
+    const unsigned sl = so + 2 * kDO + 4 * qlane + part * 128;
+    static_for<KS == 1 ? 2 : 1>([&](auto qb_c) {
       TAW_CONST(qb, qb_c);
-      const int qrow0 = qb0 + qb * 32;
-      if (qrow0 + 31 < kv0w) return;
+      const int qrow0 = qb0 + (KS == 1 ? qb : part) * 32;
+      if (qrow0 + 31 < kv0w || (KS == 4 && qrow0 >= Sp)) return;
       typedef const __attribute__((address_space(3))) f32x4_t* lds_f4_t;
       bf16x8_t pb[2], dsb[2];
       {
@@ -851,7 +954,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
             if constexpr (rb == 0) a[ks] = xor_here<(ks << 6), true>(nat_t);
             fq[i] = *reinterpret_cast<lds_frag_t>((size_t)(a[ks] + qb * 8192 + rb * 2048));
           } else if constexpr (n == 1) {
-            fo[i] = *reinterpret_cast<lds_frag_t>((size_t)(a[ks] + kTileBytes + qb * 8192 + rb * 2048));
+            fo[i] = *reinterpret_cast<lds_frag_t>((size_t)(a[ks] + kDO + qb * 8192 + rb * 2048));
           } else if constexpr (rb == 0) {
             if constexpr (n == 2) ak = xor_here<(ks << 6), true>(knat_t);
             fk[ks][n - 2] = *reinterpret_cast<lds_frag_t>((size_t)(ak + 4096 * (n - 2)));
@@ -913,7 +1016,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
           TAW_CONST(n, n_c);
           if constexpr (n == 0) {
             a = xor_here<(i << 5), true>(tr_t);
-            fdo[i] = frag16q_tr<kTileBytes + qb * 8192>(a);
+            fdo[i] = frag16q_tr<kDO + qb * 8192>(a);
           } else {
             fq[i] = frag16q_tr<qb * 8192>(a);
           }
@@ -942,16 +1045,48 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   }
   __syncthreads();
 
-  bf16_t* stage = reinterpret_cast<bf16_t*>(lds_raw) + wave * (32 * 136);
   bf16_t* dkout = dqkv + (int64_t)b * S * ld + H + (int64_t)h * D;
   bf16_t* dvout = dkout + H;
-  if (rope) {
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    rope_inverse_T(dk, rope, kv0w, S, ln);
+  if constexpr (KS > 1) {
+    constexpr int N = Share<KS>::kDt;
+    unsigned char* const own = lds_raw + wave * 16384;
+    const int rb = Share<KS>::rb(part), dt0 = Share<KS>::dt0(part), rg = wave % RG, row0 = kv0w + 16 * rb;
+    auto sum_up = [&](const f32x4_t (&acc)[2][8], f32x4_t (&x)[N]) {
+      give_blocks(acc, own, lane);
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        x[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < KS; ++p) x[j] += *reinterpret_cast<const f32x4_t*>(lds_raw + (p * RG + rg) * 16384 + (8 * rb + dt0 + j) * 1024 + lane * 16);
+      }
+      __syncthreads();                                   // the regions have been read: they are the staging area
+    };
+    f32x4_t x[N];
+    sum_up(dk, x);
+    if (rope) {
+      int pos = row0 + (lane & 15);
+      if (pos >= S) pos = S - 1;
+      const float* tb = rope + (int64_t)pos * D + 16 * dt0 + 4 * g;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const f32x4_t cs = *reinterpret_cast<const f32x4_t*>(tb + 16 * j), v = x[j];
+        x[j] = f32x4_t{v[0] * cs[0] + v[1] * cs[1], v[1] * cs[0] - v[0] * cs[1], v[2] * cs[2] + v[3] * cs[3], v[3] * cs[2] - v[2] * cs[3]};
+      }
+    }
+    store_share<N>(x, scale, reinterpret_cast<bf16_t*>(own), dkout + 16 * dt0, ld, row0, S, lane);
+    sum_up(dv, x);
+    store_share<N>(x, 1.0f, reinterpret_cast<bf16_t*>(own), dvout + 16 * dt0, ld, row0, S, lane);
+  } else {
+    bf16_t* stage = reinterpret_cast<bf16_t*>(lds_raw) + wave * (32 * 136);
+    if (rope) {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      rope_inverse_T(dk, rope, kv0w, S, ln);
+    }
+    store_rows_T(dk, scale, stage, dkout, ld, kv0w, S, lane);
+    store_rows_T(dv, 1.0f, stage, dvout, ld, kv0w, S, lane);
   }
-  store_rows_T(dk, scale, stage, dkout, ld, kv0w, S, lane);
-  store_rows_T(dv, 1.0f, stage, dvout, ld, kv0w, S, lane);
 }
 
 // =============================================================================== backward: dQ
@@ -1106,24 +1241,26 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
 // =============================================================================== backward: dQ from stored dS
 // dQ^T[d][q] += K^T[d][kv] dS^T[kv][q] with dS read back from what attn_bwd_dkv_kernel<true> wrote: one product per (query
 // block, key block) pair instead of three, paid for with S^2 bytes per (batch, head) written once and read once.  Same
-// workgroup shape as the kernel above (256 query rows, wavefront w owns the 32-row group w; 128 and 4 wavefronts where
-// few_tiles says so), keys in tiles of 64 through a
+// workgroup shape as the kernel above (256 query rows, wavefront w owns the 32-row group w; 128 and 4 wavefronts, or KS wavefronts to a row group with
+// one of the 32-key units of a tile each, where attn_shape says so), keys in tiles of 64 through a
 // 3-stage ring filled by direct global->LDS loads two tiles ahead: the K tile [64][128], shared, and per wavefront the two
 // dS units (32 keys each) of its own row group, 4 KiB copied as they lie in memory (consecutive tiles are consecutive
 // there: eight sequential streams per workgroup).  Both operands are transposing reads: K^T as in the kernel above, dS^T
 // from the wavefront's units at the slots ds_slot() gave them.  The 32 rows of a group come in the order of the stored pieces
 // (ds_row_of_slot), for which the dK/dV kernel picks the rows of its fragments (LaneAddr16Q); only the epilogue needs to know.  With 16 MFMAs per wavefront and 48 KiB per
 // tile the kernel is bound by the rate the dS matrix streams in from memory.
-template <int NW> constexpr int kDqsStage = kTileBytes + NW * 4096;        // K tile | NW wavefronts x (2 units of 2 KiB)
+// K tile (KS = 4: of 128 keys) | NW wavefronts x their units of 2 KiB
+template <int NW, int KS = 1> constexpr int kDqsStage = KS == 1 ? kTileBytes + NW * 4096 : KS / 2 * kTileBytes + NW * 2048;
 constexpr int kDqsStages = 3;
-template <int NW> constexpr size_t kDqsLds = (size_t)kDqsStages * kDqsStage<NW>;       // 144 KiB with 8 wavefronts
+template <int NW, int KS = 1> constexpr size_t kDqsLds = (size_t)kDqsStages * kDqsStage<NW, KS>;       // 144 KiB with 8 wavefronts
 static_assert(kDqsLds<kWaves8> <= 160 * 1024, "LDS budget");
-template <int NW>
+template <int NW, int KS>
 __global__ void __launch_bounds__(NW * 64, 2)
 attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* __restrict__ ds, int64_t ds_pair_bytes,
                           bf16_t* __restrict__ dqkv, int B, int S, int nh, float scale, const float* __restrict__ rope) {
-  constexpr int WQ = 32, BQ = NW * WQ, BKV = 64, NS = kDqsStages, kDmaPerTile = 16 / NW + 4;
-  constexpr int kStage = kDqsStage<NW>;
+  constexpr int WQ = 32, RG = NW / KS, BQ = RG * WQ, BKV = KS == 4 ? 128 : 64, NS = kDqsStages, kUnits = KS == 1 ? 2 : 1, kK = BKV / 64 * kTileBytes, kDmaPerTile = BKV / 64 * 16 / NW + 2 * kUnits;
+  constexpr int kStage = kDqsStage<NW, KS>;
+  static_assert(KS == 1 || ((KS == 2 || KS == 4) && NW == kWaves8 && kDqsLds<NW, KS> >= (KS - 1) * RG * 16384 && kDqsLds<NW, KS> <= 160 * 1024), "");
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
@@ -1141,18 +1278,20 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
   const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * D;
   const uint64_t kbase = (uint64_t)(qbase + H);
   // this wavefront's units of its block of 256 rows (ib), key group 0 first: 2 KiB per key group, 8 (ib + 1) of them
-  const uint64_t dsbase = (uint64_t)(ds + (int64_t)bh * ds_pair_bytes + ds_unit_offset(qt * BQ >> 8, (qt * BQ >> 5 & 7) + wave, 0));
+  const int part = KS == 1 ? 0 : wave / RG, rg = KS == 1 ? wave : wave % RG;      // which unit of a tile; which rows
+  const uint64_t dsbase = (uint64_t)(ds + (int64_t)bh * ds_pair_bytes + ds_unit_offset(qt * BQ >> 8, (qt * BQ >> 5 & 7) + rg, part));
   const unsigned ldb = (unsigned)(ld * 2);
-  const int q0 = qt * BQ, q0w = q0 + wave * WQ;
+  const int q0 = qt * BQ, q0w = q0 + rg * WQ;
 
   const int kv_end = (q0 + BQ < S) ? q0 + BQ : S;
   const int nkv = (kv_end + BKV - 1) / BKV;               // key groups 0 .. 2 nkv - 1 <= 8 (ib + 1) - 1: every unit read exists
   auto issue = [&](int t, int stage) {
     const unsigned st = lds0 + stage * kStage;
-    tile_dma<NW>(kbase, ldb, t * BKV, S, st, lane, wave);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      lds_dma16_nt(dsbase, (unsigned)(t * 4096 + i * 1024 + lane * 16), st + kTileBytes + wave * 4096 + i * 1024);      // (6.0 instead of 6.8 ms at S = 32768)
+    for (int i = 0; i < BKV / 64; ++i) tile_dma<NW>(kbase, ldb, t * BKV + 64 * i, S, st + i * kTileBytes, lane, wave);
+#pragma unroll
+    for (int i = 0; i < 2 * kUnits; ++i)
+      lds_dma16_nt(dsbase, (unsigned)(t * (BKV * 64) + i * 1024 + lane * 16), st + kK + wave * (kUnits * 2048) + i * 1024);      // (6.0 instead of 6.8 ms at S = 32768)
   };
   for (int t = 0; t < NS - 1 && t < nkv; ++t) issue(t, t);
 
@@ -1168,7 +1307,7 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
   unsigned trd;
   {
     const int blk = lane >> 4, i = lane & 15;
-    trd = ds_slot(4 * (blk >> 1) + (i >> 2), blk & 1, (i >> 1) & 1) * 16u + 8u * (i & 1) + (unsigned)kTileBytes + (unsigned)wave * 4096u;
+    trd = ds_slot(4 * (blk >> 1) + (i >> 2), blk & 1, (i >> 1) & 1) * 16u + 8u * (i & 1) + (unsigned)kK + (unsigned)(wave * (kUnits * 2048));
   }
 
   int stage = 0, stage_in = NS - 1;                     // stage of tile j; stage the next issue goes into
@@ -1180,10 +1319,10 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
     const unsigned so = lds0 + stage * kStage;
     stage = stage + 1 == NS ? 0 : stage + 1;
     stage_in = stage_in + 1 == NS ? 0 : stage_in + 1;
-    const int kv0 = j * BKV;
+    const int kv0 = j * BKV + part * 32;
     if (kv0 > q0w + WQ - 1) continue;                   // every key of the tile lies behind this wavefront's rows: dS = 0, never written
-    const unsigned tr_t = la.tr + so, trd_t = trd + so;
-    static_for<2>([&](auto kb_c) {
+    const unsigned tr_t = la.tr + so + part * 8192, trd_t = trd + so;
+    static_for<kUnits>([&](auto kb_c) {
       TAW_CONST(kb, kb_c);
       if (kv0 + kb * 32 > q0w + WQ - 1) return;         // wavefront-uniform; same for this half of the tile
       constexpr int kAheadK = 3;
@@ -1214,7 +1353,33 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
   }
   __syncthreads();          // the ring becomes the output staging area
 
-  bf16_t* stage_out = reinterpret_cast<bf16_t*>(lds_raw) + wave * (32 * 136);
+  bf16_t* stage_out = reinterpret_cast<bf16_t*>(lds_raw + rg * (KS == 1 ? 32 * 136 * 2 : 16384));
+  if constexpr (KS > 1) {       // the other wavefronts of a row group hand their sums to its first
+    if (part != 0) {
+      float* hand = reinterpret_cast<float*>(lds_raw + ((part - 1) * RG + rg) * 16384) + lane * 4;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          *reinterpret_cast<f32x4_t*>(hand + (4 * dt + r) * 256) = f32x4_t{dq[dt][4 * r], dq[dt][4 * r + 1], dq[dt][4 * r + 2], dq[dt][4 * r + 3]};
+    }
+    __syncthreads();
+    if (part != 0) return;
+#pragma unroll
+    for (int p = 0; p < KS - 1; ++p) {
+      const float* hand = reinterpret_cast<const float*>(lds_raw + (p * RG + rg) * 16384) + lane * 4;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const f32x4_t x = *reinterpret_cast<const f32x4_t*>(hand + (4 * dt + r) * 256);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dq[dt][4 * r + e] += x[e];
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);                 // what lay there is in registers: it is the staging area now
+    __builtin_amdgcn_wave_barrier();
+  }
   bf16_t* dqout = dqkv + (int64_t)b * S * ld + (int64_t)h * D;
   const int lrow = ds_row_of_slot(lane & 31);           // the query row (of the wavefront's 32) this lane's column of dQ^T is
   if (rope) rope_inverse_T(dq, rope, q0w + lrow, S, lane);
@@ -1600,48 +1765,64 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(f32x4_t* __restrict__ p, 
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (size_t)gridDim.x * 256) p[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
-// Whether the forward and the pair of backward kernels with stored dS run as 128-row workgroups of 4 wavefronts (one per SIMD)
-// instead of 256-row workgroups of 8.  Bound, where every workgroup has a compute unit to itself, by the serial chain of
-// the longest one over its 64-row blocks: with two wavefronts per SIMD a block takes their matrix instructions twice over
-// (forward 1.6 us, alone 1.2), and with 256 compute units the halves have somewhere to go.  Both measured, us
-// forward / backward, 8 wavefronts -> 4 (n8 = 256-row tiles of all (batch, head) pairs):
-//   n8 = 8    2 x 333 tokens, 2 heads     13.5 / 32.3 -> 10.8 / 25.5
-//   n8 = 144  3 x 1501 tokens, 8 heads    42.4 / 112  -> 32.3 / 88
-//   n8 = 256  2048 tokens, 32 heads       56.7 / 169  -> 48.9 / 143;   32768 tokens, 2 heads   794 / 2301 -> 633 / 1871
-//   n8 = 384  2048 tokens, 48 heads       60.9 / 192  -> 76.5 / 220: two wavefronts overlap better once the chip is full
-// With more than 256 of the halves the gain is the finer causal triangle, which one or two tiles per pair don't have:
-//   n8 = 256  8 x 200 tokens, 32 heads    15.5 / 39.4 -> 18.2 / 44.6;  2 x 512 tokens, 64 heads  21.1 / 60.1 -> 22.4 / 60.5
-bool few_tiles(int B, int S, int nh) {
-  const int64_t pairs = (int64_t)B * nh, n8 = ((int64_t)S + 255) / 256 * pairs, n4 = ((int64_t)S + 127) / 128 * pairs;
-  return n4 <= 256 || (n8 <= 256 && S > 512);
+// How the forward and the pair of backward kernels with stored dS share out the work: `rows` query rows (of the dK/dV kernel: keys) to a workgroup, 32 to
+// a wavefront, and the sum over keys (query rows) in `parts` to as many wavefronts.  Bound, where every workgroup has a compute unit to itself, by the
+// serial chain of the longest one over its steps, and beyond that by what a compute unit gets through: 64 x 128 pairs of rows and keys take about what
+// 128 x 64 and half of what 256 x 64 take (forward 0.9, 0.9 and 1.6 us a step), but read twice and four times the keys per row, 1.4 us where every unit
+// does so.  us forward / backward with 256 rows, 128, 128 in 2 parts, 64 in 4 parts (n = 64-row, n8 = 256-row tiles of all (batch, head) pairs):
+//   n =  128  1024 tokens,  8 heads       29.7 / 70.2    22.8 / 52.4    22.0 / 47.8    15.0 / 33.2
+//   n =  512  1024 tokens, 32 heads       30.5 / 75.7    23.7 / 59.4    23.0 / 56.2    21.4 / 53.9
+//   n =  512  4096 tokens,  8 heads        103 / 259     77.4 / 191     69.0 / 170     50.5 / 129
+//   n =  544  1024 tokens, 34 heads       30.7 / 76.9    23.9 / 60.6    23.2 / 57.7    27.7 / 64.8
+//   n =  576  3 x 1501 tokens, 8 heads    42.5 / 107     32.6 / 82.7    30.4 / 77.7    33.8 / 81.7
+//   n =  640  4096 tokens, 10 heads        103 / 261     77.9 / 194     69.8 / 175     68.3 / 165
+//   n =  640  2048 tokens, 20 heads       54.8 / 140     42.0 / 107     38.8 / 98.3    42.7 / 102
+//   n =  768  16384 tokens, 3 heads        392 / 1003     292 / 762      257 / 685      281 / 711
+//   n8 = 192  1024 tokens, 48 heads       31.1 / 82.2    25.7 / 66.8    27.3 / 68.1    32.3 / 79.8
+//   n8 = 240  5 x 777 tokens, 12 heads    25.9 / 71.5    27.2 / 64.6    28.5 / 65.4    34.3 / 78.0
+//   n8 = 256  4096 tokens, 16 heads        104 / 293     86.0 / 238     80.6 / 223     96.9 / 253
+//   n8 = 288  2048 tokens, 36 heads       56.3 / 161     58.1 / 150     57.9 / 145     70.6 / 171;   8192, 9  204 / 574  191 / 520  174 / 476  193 / 516
+//   n8 = 384  2048 tokens, 48 heads       58.4 / 176     76.0 / 200     73.3 / 193     91.0 / 221
+// Up to 640 tokens a row's sums are never parted: its results are then the same bits whatever else is in the batch (128 rows, 4 wavefronts, and 256, 8,
+// do the same arithmetic in the same order).  There the finer tiles gain from the finer causal triangle, which one or two tiles per pair don't have:
+//   n8 = 256  8 x 200 tokens, 32 heads    15.5 / 39.4    18.2 / 44.6;   n8 = 8  2 x 333 tokens, 2 heads  13.5 / 32.3    10.8 / 25.5
+struct AttnShape {
+  int rows, parts;
+};
+AttnShape attn_shape(int B, int S, int nh) {
+  const int64_t pairs = (int64_t)B * nh, n8 = ((int64_t)S + 255) / 256 * pairs, n4 = ((int64_t)S + 127) / 128 * pairs, n = ((int64_t)S + 63) / 64 * pairs;
+  if (S <= 640) return {n4 <= 256 || (n8 <= 256 && S > 512) ? 128 : 256, 1};
+  if (n <= 512 || (n <= 640 && S >= 4096)) return {64, 4};
+  if (n8 <= 288 && S > 1024) return {128, 2};
+  return {n8 <= 256 ? 128 : 256, 1};
 }
 
-
-template <int NW>
+template <int NW, int KS>
 int launch_fwd(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st) {
-  constexpr size_t lds = 4 * 2 * kTileBytes;      // the ring; the output staging (NW x 32 x 136 bf16) fits inside
-  static_assert(lds >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
-  TAW_SET_LDS_LIMIT_ONCE(attn_fwd_kernel<NW>, lds);
-  const int nqt = (S + 32 * NW - 1) / (32 * NW);
+  // the ring, in which the output staging (NW x 32 x 136 bf16) fits; KS > 1: what changes hands at the end
+  constexpr size_t lds = KS == 1 ? 4 * 2 * kTileBytes : NW * (16384 + 256);
+  static_assert(lds >= 4 * 2 * kTileBytes && lds >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE((attn_fwd_kernel<NW, KS>), lds);
+  const int rows = 32 * NW / KS, nqt = (S + rows - 1) / rows;
   const float scale = 1.0f / sqrtf((float)D);
-  hipLaunchKernelGGL(attn_fwd_kernel<NW>, dim3((unsigned)(nqt * B * nh)), dim3(NW * 64), lds, st, (const bf16_t*)qkv, (bf16_t*)o, lse, B, S, nh, scale);
+  hipLaunchKernelGGL((attn_fwd_kernel<NW, KS>), dim3((unsigned)(nqt * B * nh)), dim3(NW * 64), lds, st, (const bf16_t*)qkv, (bf16_t*)o, lse, B, S, nh, scale);
   return (int)hipGetLastError();
 }
 
-template <int NW>
+template <int NW, int KS>
 int launch_bwd_stored(int B, int S, int Sp, int nh, const void* qkv, const void* dO, const float* lse2, const float* Dv, void* dqkv,
                       unsigned char* ds, int64_t pair_bytes, const float* rope_table, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
-  const int nt = (S + 32 * NW - 1) / (32 * NW);
-  static_assert(kKvLds<NW> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
-  TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<true, NW>), kKvLds<NW>);
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<true, NW>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), kKvLds<NW>, st, (const bf16_t*)qkv, (const bf16_t*)dO,
+  const int rows = 32 * NW / KS, nt = (S + rows - 1) / rows;
+  static_assert(kKvLds<NW, KS> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<true, NW, KS>), (kKvLds<NW, KS>));
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<true, NW, KS>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), (kKvLds<NW, KS>), st, (const bf16_t*)qkv, (const bf16_t*)dO,
                      lse2, Dv, (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, ds, pair_bytes);
   const int rc = (int)hipGetLastError();
   if (rc) return rc;
-  static_assert(kDqsLds<NW> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
-  TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dq_stored_kernel<NW>, kDqsLds<NW>);
-  hipLaunchKernelGGL(attn_bwd_dq_stored_kernel<NW>, dim3((unsigned)(nt * B * nh)), dim3(NW * 64), kDqsLds<NW>, st, (const bf16_t*)qkv, ds, pair_bytes,
+  static_assert(KS != 1 || kDqsLds<NW> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dq_stored_kernel<NW, KS>), (kDqsLds<NW, KS>));
+  hipLaunchKernelGGL((attn_bwd_dq_stored_kernel<NW, KS>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), (kDqsLds<NW, KS>), st, (const bf16_t*)qkv, ds, pair_bytes,
                      (bf16_t*)dqkv, B, S, nh, scale, rope_table);
   return (int)hipGetLastError();
 }
@@ -1653,7 +1834,10 @@ bool attn_mfma_supported(int dtype, int S, int nh, int d) {
 }
 
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st) {
-  return few_tiles(B, S, nh) ? launch_fwd<4>(B, S, nh, qkv, o, lse, st) : launch_fwd<kWaves8>(B, S, nh, qkv, o, lse, st);
+  const AttnShape a = attn_shape(B, S, nh);
+  if (a.parts == 4) return launch_fwd<kWaves8, 4>(B, S, nh, qkv, o, lse, st);
+  if (a.parts == 2) return launch_fwd<kWaves8, 2>(B, S, nh, qkv, o, lse, st);
+  return a.rows == 128 ? launch_fwd<4, 1>(B, S, nh, qkv, o, lse, st) : launch_fwd<kWaves8, 1>(B, S, nh, qkv, o, lse, st);
 }
 
 // Workers per (batch, head) for the slot form: as many as fill the 256 compute units in whole rounds, preferring few (every
@@ -1733,15 +1917,18 @@ int launch_attn_bwd_mfma(int B, int S, int nh, const void* qkv, const void* o, c
     // the stored dS follows the row statistics (a multiple of 512 bytes in front of it)
     unsigned char* ds = reinterpret_cast<unsigned char*>(slots);
     const int64_t pair_bytes = attn_bwd_ds_pair_bytes(S);
-    return few_tiles(B, S, nh) ? launch_bwd_stored<4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st)
-                               : launch_bwd_stored<kWaves8>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
+    const AttnShape a = attn_shape(B, S, nh);
+    if (a.parts == 4) return launch_bwd_stored<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
+    if (a.parts == 2) return launch_bwd_stored<kWaves8, 2>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
+    return a.rows == 128 ? launch_bwd_stored<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st)
+                         : launch_bwd_stored<kWaves8, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
   }
   {
     constexpr size_t lds = kKvLds<kWaves8>;
     static_assert(lds >= 8 * 32 * 136 * sizeof(bf16_t), "staging area");
-    TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<false, kWaves8>), lds);
+    TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<false, kWaves8, 1>), lds);
     const int nkt = (S + 255) / 256;
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<false, kWaves8>), dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<false, kWaves8, 1>), dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
                        (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, nullptr, (int64_t)0);
     int rc = (int)hipGetLastError();
     if (rc) return rc;

@@ -588,3 +588,37 @@ def test_attn_mfma_few_and_many_tiles_agree(taw, S):
 def test_attn_mfma_pairs_that_the_xcds_do_not_divide(taw, B, S, nh):
     """(batch, head) pairs beyond the last multiple of 8 are dealt out tile by tile, in front of the others: every tile of every pair is done once."""
     _attn_case(taw, I.BF16, B, S, nh, 128, taw.TAW_IMPL_MFMA, seed=S, bwd_impl=taw.TAW_IMPL_MFMA_STORED)
+
+
+@pytest.mark.parametrize("B,S,nh", [(1, 641, 3), (1, 704, 1), (2, 705, 1), (1, 767, 2), (1, 897, 1), (1, 1000, 9), (1, 4096, 1), (1, 4161, 1),      # 64 rows, 4 parts
+                                    (3, 1025, 11), (1, 1100, 29), (1, 1153, 28)])                                                                # 128 rows, 2 parts
+def test_attn_mfma_parted_rows(taw, B, S, nh):
+    """Where there are few tiles several wavefronts share a row (a key): every row at the ends of tiles of 64 and 128, with parts that hold no key a row
+    sees, and head counts that the 8 XCDs do not divide."""
+    _attn_case(taw, I.BF16, B, S, nh, 128, taw.TAW_IMPL_MFMA, seed=S, bwd_impl=taw.TAW_IMPL_MFMA_STORED)
+
+
+@pytest.mark.parametrize("S", [700, 1088])
+def test_attn_mfma_parted_rows_far_scores(taw, S):
+    """One part of a row's keys far above or below the others, -inf among its scores: what the parts are scaled by when they meet is the row's maximum.
+    Head 0: the keys of every second block of 32 score about +-300; head 1: they overflow to -inf for the later half of the rows."""
+    import torch
+    nh = 2
+    H = nh * 128
+    rng = np.random.default_rng(S)
+    qkv, _ = draw(rng, (S, 3 * H), I.BF16)
+    q64 = I.to_f64(qkv, I.BF16)
+    part = (np.arange(S) // 32) % 2 == 1
+    q64[:, 0] = np.where(np.arange(S) % 3 == 0, 60.0, -60.0)
+    q64[:, H] = np.where(part, 60.0, 0.0)
+    q64[:, 128] = np.where(np.arange(S) >= S // 2, 2.0 ** 100, 0.0)
+    q64[:, H + 128] = np.where(part & (np.arange(S) < S // 2), -(2.0 ** 100), 0.0)
+    qkv = I.to_storage(q64.astype(np.float32), I.BF16)
+    q, k, v = (I.to_f64(qkv, I.BF16)[:, i * H:(i + 1) * H].reshape(S, nh, 128) for i in range(3))
+    o, lse = U.empty_dev((S, H), I.BF16), torch.empty(nh * S, dtype=torch.float32, device="cuda")
+    taw.taw_op_attn_fwd(I.BF16, 1, S, nh, 128, U.to_dev(qkv, I.BF16), o, lse, taw.TAW_IMPL_MFMA)
+    got_o, got_l = U.from_dev(o).reshape(S, nh, 128), U.from_dev(lse).reshape(nh, S)
+    for h in range(nh):
+        oref, lref = O.attention_fwd_rows(q[:, h], k[:, h], v[:, h], np.arange(S))      # exp(-2^196) is 0, as exp(-inf)
+        assert U.tensor_scale_err(got_o[:, h], oref) < U.TOL[I.BF16]
+        assert np.max(np.abs(got_l[h] - lref)) < 2e-2
