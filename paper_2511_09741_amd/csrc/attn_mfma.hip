@@ -847,10 +847,9 @@ template <int NW, int KS = 1> constexpr size_t kKvLds = NW * 8192 / KS + 2 * kKv
 // (ds_block_offset, ds_unit_offset, ds_slot, ds_row_of_slot: taw_internal.h, where host code can check them)
 
 template <bool STORE_DS, int NW, int KS>
-__global__ void __launch_bounds__(NW * 64, 2)
-attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
-                    const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
-                    const float* __restrict__ rope, unsigned char* __restrict__ ds, int64_t ds_pair_bytes) {
+__device__ __forceinline__ void attn_bwd_dkv_body(int blk, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
+                                                  const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
+                                                  const float* __restrict__ rope, unsigned char* __restrict__ ds, int64_t ds_pair_bytes) {
   constexpr int RG = NW / KS, BKVW = RG * 32, BQ = kKvRows<KS>, NS = 2, kKvOffRing = RG * 8192, kDO = BQ / 64 * kTileBytes;
   static_assert(KS == 1 || ((KS == 2 || KS == 4) && NW == kWaves8 && kKvLds<NW, KS> <= 160 * 1024), "");
   constexpr int kStage = kKvStageOf<KS>;      // Q tile | dO tile | lse | D
@@ -866,7 +865,7 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   LaneAddr16Q lq;                                      // of the query rows' tiles
   lq.init(lane);
   int bh, kt;                                          // key tile 0 meets every query block: longest first
-  pair_tile_of_block<false>((int)blockIdx.x, B * nh, (S + BKVW - 1) / BKVW, bh, kt);
+  pair_tile_of_block<false>(blk, B * nh, (S + BKVW - 1) / BKVW, bh, kt);
   const int b = bh / nh, h = bh % nh;
   const int64_t H = (int64_t)nh * D, ld = 3 * H;
   const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * D;
@@ -1089,28 +1088,69 @@ attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d
   }
 }
 
+template <bool STORE_DS, int NW, int KS>
+__global__ void __launch_bounds__(NW * 64, 2)
+attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
+                    const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
+                    const float* __restrict__ rope, unsigned char* __restrict__ ds, int64_t ds_pair_bytes) {
+  attn_bwd_dkv_body<STORE_DS, NW, KS>((int)blockIdx.x, qkv, dO, lse2, Dsum, dqkv, B, S, Sp, nh, scale, rope, ds, ds_pair_bytes);
+}
+
+// KS > 1: the sums of the wavefronts that share 32 rows go to the first of them (part 0), through LDS that is free; false: this one is done.
+// The region its own staging rows may take is lds + rg * 16 KiB.
+template <int KS, int RG>
+__device__ __forceinline__ bool take_parts(f32x16_t (&acc)[4], unsigned char* lds, int part, int rg, int lane) {
+  if (part != 0) {
+    float* hand = reinterpret_cast<float*>(lds + ((part - 1) * RG + rg) * 16384) + lane * 4;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4_t*>(hand + (4 * dt + r) * 256) = f32x4_t{acc[dt][4 * r], acc[dt][4 * r + 1], acc[dt][4 * r + 2], acc[dt][4 * r + 3]};
+  }
+  __syncthreads();
+  if (part != 0) return false;
+#pragma unroll
+  for (int p = 0; p < KS - 1; ++p) {
+    const float* hand = reinterpret_cast<const float*>(lds + (p * RG + rg) * 16384) + lane * 4;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x4_t x = *reinterpret_cast<const f32x4_t*>(hand + (4 * dt + r) * 256);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[dt][4 * r + e] += x[e];
+      }
+  }
+  __builtin_amdgcn_s_waitcnt(0xc07f);                 // what lay there is in registers: it is the staging area now
+  __builtin_amdgcn_wave_barrier();
+  return true;
+}
+
 // =============================================================================== backward: dQ
-// Same workgroup shape and K/V ring as the forward: 8 wavefronts, 256 query rows, wavefront w owns
-// rows 32w..32w+31 and keeps their Q and dO rows in registers as B operands.
+// Same workgroup shapes and K/V ring as the forward: NW wavefronts, 32 NW / KS query rows, wavefront w owns
+// rows 32w..32w+31 and keeps their Q and dO rows in registers as B operands (KS > 1: of 32 keys of a tile each).
 //   S^T = K Q^T;  P^T = exp(S^T/sqrt(d) - lse);  dP^T = V dO^T;  dS^T = P^T (dP^T - D);
 //   dQ^T += K^T dS^T  (scaled by 1/sqrt(d) at the end)
-__global__ void __launch_bounds__(kThreads8, 1)
-attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
-                   const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
-                   const float* __restrict__ rope) {
-  constexpr int BQ = 256, WQ = 32, BKV = 64, NS = 4;
-  constexpr int kStage = 2 * kTileBytes;   // K tile | V tile
+template <int NW, int KS>
+__device__ __forceinline__ void attn_bwd_dq_body(int blk, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
+                                                 const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
+                                                 const float* __restrict__ rope) {
+  constexpr int WQ = 32, RG = NW / KS, BQ = RG * WQ, BKV = KS == 4 ? 128 : 64, NS = KS == 4 ? 2 : 4;
+  constexpr int kV = BKV / 64 * kTileBytes, kStage = 2 * kV, kDma = BKV / 32 * 16 / NW;   // K tile | V tile; loads per tile and wavefront
+  static_assert(KS == 1 || (KS == 4 && NW == kWaves8), "");
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
 
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = KS == 1 ? 0 : wave / RG, rg = KS == 1 ? wave : wave % RG;      // which 32 keys of a tile; which rows
   LaneAddr la;
   la.init(lane);
   const int nqt = (S + BQ - 1) / BQ;
   int bh, rank;
-  pair_tile_of_block<false>((int)blockIdx.x, B * nh, nqt, bh, rank);
+  pair_tile_of_block<false>(blk, B * nh, nqt, bh, rank);
   const int qt = nqt - 1 - rank;
   const int b = bh / nh, h = bh % nh;
   const int64_t H = (int64_t)nh * D, ld = 3 * H;
@@ -1118,15 +1158,18 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
   const uint64_t kbase = (uint64_t)(qbase + H), vbase = (uint64_t)(qbase + 2 * H);
   const bf16_t* dobase = dO + (int64_t)b * S * H + (int64_t)h * D;
   const unsigned ldb = (unsigned)(ld * 2);
-  const int q0 = qt * BQ, q0w = q0 + wave * WQ;
+  const int q0 = qt * BQ, q0w = q0 + rg * WQ;
   const float c = scale * kLog2e;
 
   const int kv_end = (q0 + BQ < S) ? q0 + BQ : S;
   const int nkv = (kv_end + BKV - 1) / BKV;
   auto issue = [&](int t) {
     const unsigned st = lds0 + (t & (NS - 1)) * kStage;
-    tile_dma(kbase, ldb, t * BKV, S, st, lane, wave);
-    tile_dma(vbase, ldb, t * BKV, S, st + kTileBytes, lane, wave);
+#pragma unroll
+    for (int i = 0; i < BKV / 64; ++i) {
+      tile_dma<NW>(kbase, ldb, t * BKV + 64 * i, S, st + i * kTileBytes, lane, wave);
+      tile_dma<NW>(vbase, ldb, t * BKV + 64 * i, S, st + kV + i * kTileBytes, lane, wave);
+    }
   };
   for (int t = 0; t < NS - 1 && t < nkv; ++t) issue(t);
 
@@ -1155,15 +1198,15 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
   wait_vmcnt<0>();
   for (int j = 0; j < nkv; ++j) {
     const int ahead = nkv - 1 - j;
-    if (ahead >= 2) wait_vmcnt<8>(); else if (ahead == 1) wait_vmcnt<4>(); else wait_vmcnt<0>();
+    if (NS > 2 && ahead >= 2) wait_vmcnt<2 * kDma>(); else if (NS > 2 && ahead == 1) wait_vmcnt<kDma>(); else wait_vmcnt<0>();
     stage_barrier();
     if (j + NS - 1 < nkv) issue(j + NS - 1);
-    const int kv0 = j * BKV;
+    const int kv0 = j * BKV + part * 32;
     if (kv0 > q0w + WQ - 1) continue;
-    const unsigned so = lds0 + (j & (NS - 1)) * kStage;
+    const unsigned so = lds0 + (j & (NS - 1)) * kStage + part * 8192;
     const unsigned nat_t = la.nat + so, tr_t = la.tr + so;
-    const bool need_mask = kv0 + BKV - 1 > q0w;
-    static_for<2>([&](auto kb_c) {
+    const bool need_mask = kv0 + (KS == 1 ? BKV : 32) - 1 > q0w;
+    static_for<KS == 1 ? 2 : 1>([&](auto kb_c) {
       TAW_CONST(kb, kb_c);
       f32x16_t sacc, pacc;
 #pragma unroll
@@ -1176,7 +1219,7 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
         bf16x8_t fr[16];
         auto rd = [&](auto i_c) {
           TAW_CONST(i, i_c);
-          fr[i] = frag_nat2<i / 2, (i % 2) * kTileBytes + kb * 8192>(nat_t);
+          fr[i] = frag_nat2<i / 2, (i % 2) * kV + kb * 8192>(nat_t);
         };
         static_for<kAheadDq>(rd);
         __builtin_amdgcn_s_setprio(1);
@@ -1228,7 +1271,10 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
   }
   __syncthreads();          // the ring becomes the output staging area
 
-  bf16_t* stage = reinterpret_cast<bf16_t*>(lds_raw) + wave * (32 * 136);
+  if constexpr (KS > 1) {
+    if (!take_parts<KS, RG>(dq, lds_raw, part, rg, lane)) return;
+  }
+  bf16_t* stage = reinterpret_cast<bf16_t*>(lds_raw + rg * (KS == 1 ? 32 * 136 * 2 : 16384));
   bf16_t* dqout = dqkv + (int64_t)b * S * ld + (int64_t)h * D;
   if (rope) {
     int ln = lane;
@@ -1236,6 +1282,25 @@ attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO
     rope_inverse_T(dq, rope, q0w + (ln & 31), S, ln);
   }
   store_rows_T(dq, scale, stage, dqout, ld, q0w, S, lane);
+}
+
+__global__ void __launch_bounds__(kThreads8, 1)
+attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
+                   const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
+                   const float* __restrict__ rope) {
+  attn_bwd_dq_body<kWaves8, 1>((int)blockIdx.x, qkv, dO, lse2, Dsum, dqkv, B, S, Sp, nh, scale, rope);
+}
+
+// Both of the above in one grid, dQ's workgroups after the n of dK/dV: where all of them find a compute unit of their own, the products that dQ forms again
+// cost no time, a launch less, and no dS has to be stored.
+template <int NW, int KS>
+__global__ void __launch_bounds__(NW * 64, 2)
+attn_bwd_pair_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
+                     const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int n, int B, int S, int Sp, int nh, float scale,
+                     const float* __restrict__ rope) {
+  const int b = (int)blockIdx.x;
+  if (b < n) attn_bwd_dkv_body<false, NW, KS>(b, qkv, dO, lse2, Dsum, dqkv, B, S, Sp, nh, scale, rope, nullptr, 0);
+  else attn_bwd_dq_body<NW, KS>(b - n, qkv, dO, lse2, Dsum, dqkv, B, S, Sp, nh, scale, rope);
 }
 
 // =============================================================================== backward: dQ from stored dS
@@ -1354,31 +1419,8 @@ attn_bwd_dq_stored_kernel(const bf16_t* __restrict__ qkv, const unsigned char* _
   __syncthreads();          // the ring becomes the output staging area
 
   bf16_t* stage_out = reinterpret_cast<bf16_t*>(lds_raw + rg * (KS == 1 ? 32 * 136 * 2 : 16384));
-  if constexpr (KS > 1) {       // the other wavefronts of a row group hand their sums to its first
-    if (part != 0) {
-      float* hand = reinterpret_cast<float*>(lds_raw + ((part - 1) * RG + rg) * 16384) + lane * 4;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          *reinterpret_cast<f32x4_t*>(hand + (4 * dt + r) * 256) = f32x4_t{dq[dt][4 * r], dq[dt][4 * r + 1], dq[dt][4 * r + 2], dq[dt][4 * r + 3]};
-    }
-    __syncthreads();
-    if (part != 0) return;
-#pragma unroll
-    for (int p = 0; p < KS - 1; ++p) {
-      const float* hand = reinterpret_cast<const float*>(lds_raw + (p * RG + rg) * 16384) + lane * 4;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const f32x4_t x = *reinterpret_cast<const f32x4_t*>(hand + (4 * dt + r) * 256);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dq[dt][4 * r + e] += x[e];
-        }
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);                 // what lay there is in registers: it is the staging area now
-    __builtin_amdgcn_wave_barrier();
+  if constexpr (KS > 1) {
+    if (!take_parts<KS, RG>(dq, lds_raw, part, rg, lane)) return;
   }
   bf16_t* dqout = dqkv + (int64_t)b * S * ld + (int64_t)h * D;
   const int lrow = ds_row_of_slot(lane & 31);           // the query row (of the wavefront's 32) this lane's column of dQ^T is
@@ -1797,6 +1839,14 @@ AttnShape attn_shape(int B, int S, int nh) {
   return {n8 <= 256 ? 128 : 256, 1};
 }
 
+// Whether the backward of the default form runs as one grid of both kernels, dQ forming the scores again (attn_bwd_pair_kernel), instead of storing dS: as
+// long as both kinds of workgroups find a compute unit each, and up to 256 of each, where the second ones follow the short ones of the first.  us with dS
+// stored -> in one grid: 64 tokens of 1 head 11.8 -> 8.6, 2 x 333 of 2 25.5 -> 18.7, 640 of 40 (200 tiles) 42.1 -> 32.2, 4 x 200 of 32 (256) 26.9 -> 25.5,
+// 1024 of 8 (128) 32.8 -> 23.8, 1024 of 16 (256) 36.8 -> 32.2, 16384 of 1 (256) 349 -> 266, 1024 of 24 (384) 45.8 -> 48.6.
+bool attn_bwd_in_one_grid(const AttnShape& a, int B, int S, int nh) {
+  return (a.parts == 4 || (a.parts == 1 && a.rows == 128)) && ((int64_t)S + a.rows - 1) / a.rows * B * nh <= 256;
+}
+
 template <int NW, int KS>
 int launch_fwd(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st) {
   // the ring, in which the output staging (NW x 32 x 136 bf16) fits; KS > 1: what changes hands at the end
@@ -1824,6 +1874,18 @@ int launch_bwd_stored(int B, int S, int Sp, int nh, const void* qkv, const void*
   TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dq_stored_kernel<NW, KS>), (kDqsLds<NW, KS>));
   hipLaunchKernelGGL((attn_bwd_dq_stored_kernel<NW, KS>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), (kDqsLds<NW, KS>), st, (const bf16_t*)qkv, ds, pair_bytes,
                      (bf16_t*)dqkv, B, S, nh, scale, rope_table);
+  return (int)hipGetLastError();
+}
+
+template <int NW, int KS>
+int launch_bwd_pair(int B, int S, int Sp, int nh, const void* qkv, const void* dO, const float* lse2, const float* Dv, void* dqkv,
+                    const float* rope_table, hipStream_t st) {
+  constexpr size_t ring = 4 * 2 * kTileBytes, lds = kKvLds<NW, KS> > ring ? kKvLds<NW, KS> : ring;
+  static_assert(lds >= NW * 32 * 136 * sizeof(bf16_t) && lds >= (KS - 1) * (NW / KS) * 16384, "staging area");
+  const int rows = 32 * NW / KS, n = (S + rows - 1) / rows * B * nh;
+  TAW_SET_LDS_LIMIT_ONCE((attn_bwd_pair_kernel<NW, KS>), lds);
+  hipLaunchKernelGGL((attn_bwd_pair_kernel<NW, KS>), dim3((unsigned)(2 * n)), dim3(NW * 64), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
+                     (bf16_t*)dqkv, n, B, S, Sp, nh, 1.0f / sqrtf((float)D), rope_table);
   return (int)hipGetLastError();
 }
 
@@ -1918,6 +1980,9 @@ int launch_attn_bwd_mfma(int B, int S, int nh, const void* qkv, const void* o, c
     unsigned char* ds = reinterpret_cast<unsigned char*>(slots);
     const int64_t pair_bytes = attn_bwd_ds_pair_bytes(S);
     const AttnShape a = attn_shape(B, S, nh);
+    if (attn_bwd_in_one_grid(a, B, S, nh))
+      return a.parts == 4 ? launch_bwd_pair<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st)
+                          : launch_bwd_pair<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);
     if (a.parts == 4) return launch_bwd_stored<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
     if (a.parts == 2) return launch_bwd_stored<kWaves8, 2>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
     return a.rows == 128 ? launch_bwd_stored<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st)

@@ -591,7 +591,8 @@ def test_attn_mfma_pairs_that_the_xcds_do_not_divide(taw, B, S, nh):
 
 
 @pytest.mark.parametrize("B,S,nh", [(1, 641, 3), (1, 704, 1), (2, 705, 1), (1, 767, 2), (1, 897, 1), (1, 1000, 9), (1, 4096, 1), (1, 4161, 1),      # 64 rows, 4 parts
-                                    (3, 1025, 11), (1, 1100, 29), (1, 1153, 28)])                                                                # 128 rows, 2 parts
+                                    (3, 1025, 11), (1, 1100, 29), (1, 1153, 28),                                                                 # 128 rows, 2 parts
+                                    (1, 1100, 14), (1, 1100, 15), (1, 641, 23), (1, 600, 51), (1, 600, 52)])      # 252 and 270 tiles: dQ in dK/dV's grid, or from stored dS
 def test_attn_mfma_parted_rows(taw, B, S, nh):
     """Where there are few tiles several wavefronts share a row (a key): every row at the ends of tiles of 64 and 128, with parts that hold no key a row
     sees, and head counts that the 8 XCDs do not divide."""
