@@ -221,60 +221,60 @@ __device__ __forceinline__ void store_elements(const f32x4_t (&acc)[FM][FN], uns
 }
 
 // =============================================================================== epilogue of a 256 x 256 tile
-// ---- accumulator blocks -> staging rows.  The MFMAs multiply (B fragment) x (A fragment)^T, so a 16 x 16 block of
-// the result sits transposed in the accumulator registers: lane l holds ROW l & 15 of the block and, in its four
-// registers, the consecutive COLUMNS 4 (l >> 4) + 0..3.  Four consecutive floats of a row are one 16-byte LDS write
-// ([32][SLD] staging rows, SLD * 4 a multiple of 16 and, mod 256, 16: the 16 rows of a write fall into 16 bank groups).
-template <int SLD, int NB>
-__device__ __forceinline__ void stage_rows(const f32x4_t (&top)[NB], const f32x4_t (&bottom)[NB], float* stg, int lane) {
-  float* row = stg + (lane & 15) * SLD + 4 * (lane >> 4);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4_t*>(row + 16 * j) = top[j];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4_t*>(row + 16 * SLD + 16 * j) = bottom[j];
-}
-
-// ---- the same for a tile that lies wholly inside C with 16-byte aligned row segments (all tiles of
-// the layer's shapes): no per-element checks, 32-bit lane offsets from the wavefront's corner of C
+// Accumulator blocks -> staging rows in LDS -> 16-byte pieces of whole row segments -> C.  The MFMAs multiply (B fragment) x (A fragment)^T, so a
+// 16 x 16 block of the result sits transposed in the accumulator registers: lane l holds ROW l & 15 of the block and, in its four registers, the
+// consecutive COLUMNS 4 (l >> 4) + 0..3: one 16-byte LDS write ([32][SLD] staging rows, SLD * 4 a multiple of 16 and, mod 256, 16: the 16 rows of a
+// write fall into 16 bank groups).
+//
 // The result is stored non-temporally: a round of tiles writes more than an L2 holds, and ordinary stores
 // push the operand panels out of it (1-3 % per GEMM).
 //
-// EDGE: the same for a block that reaches over the edge of C (rows and columns of C: `rows`, `cols` from the block's corner on, cols a multiple
-// of the 16-byte chunk): loads clamped into C, stores predicated, a unit's values all formed before its first store so that its reads stay
-// in flight together.  (As a loop of four chunks at a time this cost an edge tile 5 - 6 us, 10 with a residual.  4503 x 3072 x 1024, one round of
-// tiles: 32.6 -> 27.0 us, with a residual 42.3 -> 30.0, with rotation 41.6 -> 30.3; 255 x 256 x 64 in fp32 18.5 -> 11.3.)
+// Two things bound it, 2 us each: LDS moves 512 KiB at 128 bytes a clock, and a compute unit's 128 KiB of stores leave at about 32.  So a wavefront
+// works on three passes (4 rows of bf16, 2 of fp32) at once: the staging rows are there twice, and while pass q is converted and stored, pass q + kAhead is
+// being read and a few blocks of the next slice of 32 rows are written.  Nothing waits: LDS instructions of one wavefront are carried out in
+// order.  (Slice by slice, write - wait - read - store, with the
+// questions what the result is combined with asked in every pass, us: 4503 x 5632 x 1024 52.6, now 51.6, 4503 x 3072 x 1024 with a residual 31.7 and 30.9, the backward of 65536 x 2048 x 5632
+// into the shard 2191 and 2164, of 16384 x 8192 x 8192 2942 and 2925.  The rest is the stores': 2.6 us of a bf16 tile's 27 at K = 1024, whatever else is in
+// flight - a chip full of tiles is bound by power, and bytes moved beside products are not free.)
 //
-// EXTRAS: the result is combined with something (or rotated).  Without, the passes need no fetch and no line drawn between them; drawn all the same
-// they cost a fp32 tile 1 us (256 x 256 x 64 TN in fp32: 8.6 us; 7.0).
-template <bool C_F32, int EPI = kEpiNone, bool EDGE = false, bool EXTRAS = true>
+// EDGE: the same for a block that reaches over the edge of C (rows and columns of C: `rows`, `cols` from the block's corner on, cols a multiple
+// of the 16-byte chunk): loads clamped into C, stores predicated.  (As a loop of four chunks at a time this cost an edge tile 5 - 6 us, 10 with a residual.)
+//
+// X: what the result is combined with, known here or (kXAny) asked in every pass.
+constexpr int kXNone = 0, kXResidual = 1, kXAccumulate = 2, kXAny = 3;
+template <bool C_F32, int EPI = kEpiNone, bool EDGE = false, int X = kXAny>
 __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                                 int wm, int wn, void* __restrict__ Cv, int64_t ldc, int accumulate,
                                                 const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}, int rows = 128, int cols = 128) {
-  constexpr int SLD = 132;
+  constexpr int SLD = 132, kAhead = 2;
   constexpr int ES = C_F32 ? 4 : 2;                       // bytes per element of C (and R)
-  float* stg = reinterpret_cast<float*>(lds2) + wave * (32 * SLD);
+  constexpr bool COMBINE = EPI == kEpiNone;               // the rotary projection has neither residual nor accumulation
+  constexpr bool ROTATE = !COMBINE && X != kXNone;        // and X says whether these 128 columns (one head) are rotated
+  const bool add_r = COMBINE && (X == kXAny ? Rv != nullptr : X == kXResidual), add_c = COMBINE && (X == kXAny ? accumulate != 0 : X == kXAccumulate);
+  float* stg = reinterpret_cast<float*>(lds2) + wave * (2 * 32 * SLD);
   char* cw = static_cast<char*>(Cv) + ((m0 + wm) * ldc + n0 + wn) * ES;
-  const char* rw = Rv ? static_cast<const char*>(Rv) + ((m0 + wm) * ldr + n0 + wn) * ES : nullptr;
+  const char* rw = static_cast<const char*>(Rv) + ((m0 + wm) * ldr + n0 + wn) * ES;
   // read-back: a lane takes 16 bytes of a row; C_F32: 32 lanes per row (2 rows per pass), else 16 lanes per row (4 rows per pass)
   constexpr int LPR = C_F32 ? 32 : 16, RPP = 64 / LPR, NPASS = 32 / RPP;
   const int rr0 = lane / LPR, ch = lane % LPR;
   const unsigned coff0 = (unsigned)(rr0 * ldc) * ES + ch * 16, roff0 = (unsigned)(rr0 * ldr) * ES + ch * 16;
   const unsigned cstep = (unsigned)(RPP * ldc) * ES, rstep = (unsigned)(RPP * ldr) * ES;
-  const float* srow = stg + rr0 * SLD + ch * (16 / ES);
+  float* const wrow = stg + (lane & 15) * SLD + 4 * (lane >> 4);
+  const float* const srow = stg + rr0 * SLD + ch * (16 / ES);
   const int chc = EDGE && ch * 16 >= cols * ES ? cols * ES / 16 - 1 : ch;       // EDGE: the chunk column this lane loads
   typedef typename std::conditional<C_F32, f32x4_t, bf16x8_t>::type chunk_t;
-  // What the result is combined with is fetched one unit ahead: a 32-row slice, or half of one where fp32 rows would not fit the
-  // registers.  (Fetched pass by pass, each store behind its own load, every pass waits for memory: the forward of the 1024-wide layer on 65536 tokens took 6 % longer, a 4096-wide step
+  // What the result is combined with is fetched kDeep units ahead: a 32-row slice, or half of one where fp32 rows would not fit the
+  // registers.  (Two instead of one: weight gradient of 1024 x 22016 x 4096 into the shard 259 -> 242 us; three: 245.)  (Fetched pass by pass, each store behind its own load, every pass waits for memory: the forward of the 1024-wide layer on 65536 tokens took 6 % longer, a 4096-wide step
   // on 8192 tokens, whose contractions are four times as long, no longer.)
   constexpr int UPS = C_F32 ? 2 : 1, UP = NPASS / UPS;      // units per slice, passes per unit
-  constexpr bool COMBINE = EPI == kEpiNone;                 // the rotary projection has neither residual nor accumulation
+  constexpr bool FETCH = COMBINE ? X != kXNone : ROTATE;
+  constexpr int kDeep = COMBINE && X != kXAny && !EDGE ? 2 : 1;
   struct Extra {
-    chunk_t r[COMBINE ? UP : 1], c[COMBINE ? UP : 1];
-    RotPairs rot[EPI == kEpiRope ? UP : 1];        // of every pass
-  } extra[2];
-  const bool rotate = EPI == kEpiRope && n0 + wn < ea.rot_cols;                              // wavefront-uniform: 128 columns are one head
-  int pos0 = EPI == kEpiRope ? (int)((unsigned)(m0 + wm + rr0) % (unsigned)ea.S) : 0;        // this lane's row in pass 0 (token counts fit 32 bits)
-  const float* tab = EPI == kEpiRope ? ea.table + (((wn + ch * 8) & 127) >> 1) * 2 : nullptr;      // first of its 4 pairs inside the head
+    chunk_t r[COMBINE && (X & kXResidual) ? UP : 1], c[COMBINE && (X & kXAccumulate) ? UP : 1];
+    RotPairs rot[ROTATE ? UP : 1];        // of every pass
+  } extra[kDeep + 1];
+  int pos0 = ROTATE ? (int)((unsigned)(m0 + wm + rr0) % (unsigned)ea.S) : 0;        // this lane's row in pass 0 (token counts fit 32 bits)
+  const float* tab = ROTATE ? ea.table + (((wn + ch * 8) & 127) >> 1) * 2 : nullptr;      // first of its 4 pairs inside the head
   auto fetch = [&](Extra& x, int u) {
     const int row = (u / UPS) * 32 + (u % UPS) * (32 / UPS);
     if constexpr (COMBINE) {
@@ -282,17 +282,21 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
         const int r = row + it * RPP + rr0;
         return (unsigned)((r < rows ? r : rows - 1) * ld) * ES + chc * 16;
       };
-      if (rw) {
-        const char* ri = rw + (int64_t)row * ldr * ES;
+      if constexpr ((X & kXResidual) != 0) {
+        if (add_r) {
+          const char* ri = rw + (int64_t)row * ldr * ES;
 #pragma unroll
-        for (int it = 0; it < UP; ++it) x.r[it] = *reinterpret_cast<const chunk_t*>(EDGE ? rw + edge_off(it, ldr) : ri + roff0 + it * rstep);
+          for (int it = 0; it < UP; ++it) x.r[it] = *reinterpret_cast<const chunk_t*>(EDGE ? rw + edge_off(it, ldr) : ri + roff0 + it * rstep);
+        }
       }
-      if (accumulate) {
-        const char* ci = cw + (int64_t)row * ldc * ES;
+      if constexpr ((X & kXAccumulate) != 0) {
+        if (add_c) {
+          const char* ci = cw + (int64_t)row * ldc * ES;
 #pragma unroll
-        for (int it = 0; it < UP; ++it) x.c[it] = *reinterpret_cast<const chunk_t*>(EDGE ? cw + edge_off(it, ldc) : ci + coff0 + it * cstep);
+          for (int it = 0; it < UP; ++it) x.c[it] = *reinterpret_cast<const chunk_t*>(EDGE ? cw + edge_off(it, ldc) : ci + coff0 + it * cstep);
+        }
       }
-    } else if (rotate) {
+    } else if constexpr (ROTATE) {
 #pragma unroll
       for (int it = 0; it < UP; ++it) {
         int pos = pos0 + it * RPP;
@@ -305,25 +309,42 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
       else pos0 = pos0 >= ea.S ? pos0 - ea.S : pos0;
     }
   };
-  // pass `it` of a slice: the staged chunk with everything added to it or done to it
-  auto value = [&](int it, const Extra& x, int p) -> chunk_t {
-    const float* sp = srow + it * RPP * SLD;
+  // block n (0 .. 7: the upper 16 rows', 8 .. 15: the lower ones') of slice i to its staging rows
+  auto stage = [&](int i, int n) {
+    *reinterpret_cast<f32x4_t*>(wrow + (i & 1) * (32 * SLD) + (n >> 3) * (16 * SLD) + 16 * (n & 7)) = acc[2 * i + (n >> 3)][n & 7];
+  };
+  struct Raw {
+    f32x4_t v[C_F32 ? 1 : 2];
+  } raw[kAhead + 1];
+  auto read = [&](int q) {      // pass q of the block's 4 NPASS
+    const float* sp = srow + (q / NPASS & 1) * (32 * SLD) + q % NPASS * (RPP * SLD);
+    Raw& w = raw[q % (kAhead + 1)];
+    w.v[0] = *reinterpret_cast<const f32x4_t*>(sp);
+    if constexpr (!C_F32) w.v[1] = *reinterpret_cast<const f32x4_t*>(sp + 4);
+  };
+  // the chunk with everything added to it or done to it
+  auto value = [&](const Raw& w, const Extra& x, int p) -> chunk_t {
     if constexpr (C_F32) {
-      f32x4_t v = *reinterpret_cast<const f32x4_t*>(sp);
-      if (EXTRAS && rw) v += x.r[p];
-      if (EXTRAS && accumulate) v += x.c[p];
+      f32x4_t v = w.v[0];
+      if constexpr ((X & kXResidual) != 0) {
+        if (add_r) v += x.r[p];
+      }
+      if constexpr ((X & kXAccumulate) != 0) {
+        if (add_c) v += x.c[p];
+      }
       return v;
     } else {
-      const f32x4_t v0 = *reinterpret_cast<const f32x4_t*>(sp), v1 = *reinterpret_cast<const f32x4_t*>(sp + 4);
+      const f32x4_t v0 = w.v[0], v1 = w.v[1];
       float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-      if constexpr (!COMBINE) {
-        if (rotate) x.rot[p].rotate(v, ea.round_first);
-      } else {
-        if (rw) {
+      if constexpr (ROTATE) x.rot[p].rotate(v, ea.round_first);
+      if constexpr (COMBINE && (X & kXResidual) != 0) {
+        if (add_r) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] += (float)x.r[p][e];
         }
-        if (accumulate) {
+      }
+      if constexpr (COMBINE && (X & kXAccumulate) != 0) {
+        if (add_c) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] += (float)x.c[p][e];
         }
@@ -334,39 +355,42 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
       return o;
     }
   };
-  if constexpr (EXTRAS) fetch(extra[0], 0);
+  if constexpr (FETCH) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (EDGE && 32 * i >= rows) break;
-    stage_rows<SLD>(acc[2 * i], acc[2 * i + 1], stg, lane);
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-    char* ci = cw + (int64_t)(32 * i) * ldc * ES;
-    chunk_t out[EDGE ? UP : 1];
-#pragma unroll
-    for (int it = 0; it < NPASS; ++it) {
-      const int u = i * UPS + it / UP, p = it % UP;
-      if (EXTRAS && p == 0) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (u + 1 < 4 * UPS) fetch(extra[(u + 1) & 1], u + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (EDGE) {
-        out[p] = value(it, extra[u & 1], p);
-        if (p + 1 == UP) {
-#pragma unroll
-          for (int q = 0; q < UP; ++q) {
-            const int pass = it + 1 - UP + q;
-            if (ch == chc && 32 * i + pass * RPP + rr0 < rows) *reinterpret_cast<chunk_t*>(ci + coff0 + pass * cstep) = out[q];
-          }
-        }
-      } else {
-        __builtin_nontemporal_store(value(it, extra[u & 1], p), reinterpret_cast<chunk_t*>(ci + coff0 + it * cstep));
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
+    for (int u = 0; u < kDeep; ++u) fetch(extra[u], u);
+    __builtin_amdgcn_sched_barrier(0);
   }
+#pragma unroll
+  for (int n = 0; n < 16; ++n) stage(0, n);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int q = 0; q < kAhead; ++q) read(q);
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<4>([&](auto i_c) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_c)::value;
+    if (EDGE && 32 * i >= rows) return;
+    static_for<NPASS>([&](auto it_c) __attribute__((always_inline)) {
+      constexpr int it = decltype(it_c)::value, q = i * NPASS + it, u = i * UPS + it / UP, p = it % UP;
+      if constexpr (FETCH && p == 0 && u + kDeep < 4 * UPS) fetch(extra[(u + kDeep) % (kDeep + 1)], u + kDeep);
+      // the next slice's blocks: all of them before its first pass is read
+      constexpr int kOver = NPASS - kAhead;
+      if constexpr (i < 3 && it < kOver) {
+#pragma unroll
+        for (int n = it * 16 / kOver; n < (it + 1) * 16 / kOver; ++n) stage(i + 1, n);
+      }
+      __builtin_amdgcn_wave_barrier();
+      if constexpr (q + kAhead < 4 * NPASS) read(q + kAhead);
+      __builtin_amdgcn_sched_barrier(0);
+      const chunk_t o = value(raw[q % (kAhead + 1)], extra[u % (kDeep + 1)], p);
+      chunk_t* const dst = reinterpret_cast<chunk_t*>(cw + (int64_t)(32 * i) * ldc * ES + coff0 + it * cstep);
+      if constexpr (EDGE) {
+        if (ch == chc && 32 * i + it * RPP + rr0 < rows) *dst = o;
+      } else {
+        __builtin_nontemporal_store(o, dst);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  });
 }
 
 // a wavefront's 128 x 128 block at (mw, nw), whatever C looks like; everything asked here is wavefront-uniform
@@ -377,15 +401,28 @@ __device__ __forceinline__ void store_large(const f32x4_t (&acc)[8][8], unsigned
   constexpr int V = C_F32 ? 3 : 7;                      // elements per 16 bytes, minus one
   const bool aligned = (ldc & V) == 0 && (!Rv || (ldr & V) == 0);
   const bool full = m0 + BM <= M && n0 + BN <= N && aligned && (EPI == kEpiNone || ea.S >= 32);
-  if (C_F32 && full && !Rv && !accumulate) {
-    store_tile_full<C_F32, EPI, false, !C_F32>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, 0, nullptr, 0, ea);
-  } else if (full) {
-    store_tile_full<C_F32, EPI>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea);
+  const bool plain = EPI == kEpiNone ? !Rv && !accumulate : n0 + wn >= ea.rot_cols;      // 128 columns are one head: all of them are rotated, or none
+  // what a layer's products of this type are combined with: forward products a residual, weight gradients the shard
+  constexpr int XL = EPI != kEpiNone ? kXAny : C_F32 ? kXAccumulate : kXResidual;
+  const bool usual = EPI != kEpiNone || (C_F32 ? !Rv : !accumulate);
+  auto put = [&](auto x, auto edge, int rows, int cols) __attribute__((always_inline)) {
+    store_tile_full<C_F32, EPI, decltype(edge)::value, decltype(x)::value>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea, rows, cols);
+  };
+  constexpr std::integral_constant<int, kXNone> none{};
+  constexpr std::integral_constant<int, XL> with{};
+  constexpr std::integral_constant<int, kXAny> any{};
+  if (full) {
+    if (plain) put(none, std::false_type{}, 128, 128);
+    else if (usual) put(with, std::false_type{}, 128, 128);
+    else put(any, std::false_type{}, 128, 128);
   } else if (EPI != kEpiNone || (aligned && (N & V) == 0)) {
     const int64_t rows = M - m0 - wm, cols = N - n0 - wn;
-    if (rows > 0 && cols > 0)
-      store_tile_full<C_F32, EPI, true>(acc, lds2, wave, lane, m0, n0, wm, wn, Cv, ldc, accumulate, Rv, ldr, ea, rows < 128 ? (int)rows : 128,
-                                        cols < 128 ? (int)cols : 128);
+    if (rows > 0 && cols > 0) {
+      const int r = rows < 128 ? (int)rows : 128, c = cols < 128 ? (int)cols : 128;
+      if (plain) put(none, std::true_type{}, r, c);
+      else if (usual) put(with, std::true_type{}, r, c);
+      else put(any, std::true_type{}, r, c);
+    }
   } else {
     store_elements<C_F32, 8, 8, kColsPlain>(acc, lds2, wave, lane, m0 + wm, n0 + wn, M, N, Cv, ldc, accumulate, Rv, ldr);
   }
