@@ -66,6 +66,12 @@ template <typename T> struct VecWidth;
 template <> struct VecWidth<float> { static constexpr int value = 4; };
 template <> struct VecWidth<bf16_t> { static constexpr int value = 8; };
 
+// ---- SwiGLU: silu(g) u, wherever it is formed
+__device__ __forceinline__ float swiglu(float g, float u) {
+  const float sig = 1.0f / (1.0f + __expf(-g));
+  return g * sig * u;
+}
+
 // ---- wavefront reductions (64 lanes, xor butterfly: every lane ends with the result) ----------
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll

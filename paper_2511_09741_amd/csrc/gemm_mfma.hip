@@ -124,12 +124,18 @@ template <int COLS> __device__ __forceinline__ int block_col(int j, int lane) { 
 // i.e. 4 whole pairs, in fp32: the fused qkv projection then needs no rotary pass of its own, and q, k
 // are rounded to bf16 once.  rot_cols is a multiple of 128. round_first: rounded to bf16 before the rotation too, as the
 // separate rotary pass did that rotated q and k of these sizes before (launch_gemm_mfma_nt_rope).
+//
+// act != nullptr (NT with a bf16 result, EPI = kEpiNone, 256 x 256 tiles): the product is gate | up, [M, 2 half], and act [M, half] = silu(gate) up is stored
+// beside it, formed from the rounded values like the separate pass does.  A tile takes 128 gate columns and the same 128 up columns, each wavefront
+// 64 of both, so that a pair is in one lane.
 constexpr int kEpiNone = 0, kEpiRope = 1;
 struct EpiArgs {
   const float* table;
   int S;
   int64_t rot_cols;
   int round_first;
+  int64_t half;
+  bf16_t* act;
 };
 
 // the rotation of 8 consecutive columns col .. col + 7 of row `row`: the table's 4 pairs, and their use
@@ -245,7 +251,7 @@ constexpr int kXNone = 0, kXResidual = 1, kXAccumulate = 2, kXAny = 3;
 template <bool C_F32, int EPI = kEpiNone, bool EDGE = false, int X = kXAny>
 __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, int64_t m0, int64_t n0,
                                                 int wm, int wn, void* __restrict__ Cv, int64_t ldc, int accumulate,
-                                                const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0}, int rows = 128, int cols = 128) {
+                                                const void* __restrict__ Rv, int64_t ldr, EpiArgs ea = EpiArgs{nullptr, 1, 0, 0, 0, nullptr}, int rows = 128, int cols = 128) {
   constexpr int SLD = 132, kAhead = 2;
   constexpr int ES = C_F32 ? 4 : 2;                       // bytes per element of C (and R)
   constexpr bool COMBINE = EPI == kEpiNone;               // the rotary projection has neither residual nor accumulation
@@ -388,6 +394,84 @@ __device__ __forceinline__ void store_tile_full(const f32x4_t (&acc)[8][8], unsi
       } else {
         __builtin_nontemporal_store(o, dst);
       }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  });
+}
+
+// The same for gate | up: columns 0 .. 63 of the block are 64 gate columns from C on, 64 .. 127 the up columns `half` further, and act gets silu(gate) up.
+// A pass is 8 rows of both, 8 lanes to a row.  The separate pass reads 4 half bytes a row that this tile has in hand and writes 2; the epilogue gets half as
+// many stores again and the arithmetic, a lone wavefront's 5 cycles an instruction: forward of 65536 tokens at H = 1024 (K = 1024, where it weighs most)
+// 2184 -> 2106 us, a checkpointed step of 16384 at 2048 6606 -> 6519, a step of 8192 at 4096 9225 -> 9194.
+template <bool EDGE>
+__device__ __forceinline__ void store_tile_swiglu(const f32x4_t (&acc)[8][8], unsigned char* lds2, int wave, int lane, bf16_t* __restrict__ C, int64_t ldc,
+                                                  bf16_t* __restrict__ act, int64_t half, int rows) {
+  constexpr int SLD = 132, NPASS = 4, kAhead = 1;
+  float* stg = reinterpret_cast<float*>(lds2) + wave * (2 * 32 * SLD);
+  float* const wrow = stg + (lane & 15) * SLD + 4 * (lane >> 4);
+  const int rr0 = lane >> 3, ch = lane & 7;
+  const float* const srow = stg + rr0 * SLD + ch * 8;
+  const unsigned coff = (unsigned)(rr0 * ldc) + ch * 8, aoff = (unsigned)(rr0 * half) + ch * 8;
+  auto stage = [&](int i, int n) {
+    *reinterpret_cast<f32x4_t*>(wrow + (i & 1) * (32 * SLD) + (n >> 3) * (16 * SLD) + 16 * (n & 7)) = acc[2 * i + (n >> 3)][n & 7];
+  };
+  f32x4_t raw[kAhead + 1][4];      // gate, up
+  auto read = [&](int q) {
+    const float* sp = srow + (q / NPASS & 1) * (32 * SLD) + q % NPASS * (8 * SLD);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) raw[q % (kAhead + 1)][e] = *reinterpret_cast<const f32x4_t*>(sp + 64 * (e >> 1) + 4 * (e & 1));
+  };
+#pragma unroll
+  for (int n = 0; n < 16; ++n) stage(0, n);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int q = 0; q < kAhead; ++q) read(q);
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<4>([&](auto i_c) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_c)::value;
+    if (EDGE && 32 * i >= rows) return;
+    static_for<NPASS>([&](auto it_c) __attribute__((always_inline)) {
+      constexpr int it = decltype(it_c)::value, q = i * NPASS + it, kOver = NPASS - kAhead;
+      if constexpr (i < 3 && it < kOver) {
+#pragma unroll
+        for (int n = it * 16 / kOver; n < (it + 1) * 16 / kOver; ++n) stage(i + 1, n);
+      }
+      __builtin_amdgcn_wave_barrier();
+      if constexpr (q + kAhead < 4 * NPASS) read(q + kAhead);
+      __builtin_amdgcn_sched_barrier(0);
+      const f32x4_t* w = raw[q % (kAhead + 1)];
+      bf16x8_t g, u, a;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        g[e] = (bf16_t)w[e >> 2][e & 3];
+        u[e] = (bf16_t)w[2 + (e >> 2)][e & 3];
+      }
+      bf16_t* const cr = C + (int64_t)(32 * i + it * 8) * ldc;
+      bf16_t* const ar = act + (int64_t)(32 * i + it * 8) * half;
+      const bool in = !EDGE || 32 * i + it * 8 + rr0 < rows;
+      if (in) {
+        __builtin_nontemporal_store(g, reinterpret_cast<bf16x8_t*>(cr + coff));
+        __builtin_nontemporal_store(u, reinterpret_cast<bf16x8_t*>(cr + half + coff));
+      }
+      // 1 / (1 + exp(-g)) by the reciprocal instruction and a Newton step: 5 instructions where the division takes 10, between stores and products (forward of
+      // 65536 tokens at H = 1024 2124 us with the division, 2090 without).  The same bits while the result is no denormal number, which is asked.
+      float d[8], dmax = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        d[e] = 1.0f + __expf(-(float)g[e]);
+        dmax = fmaxf(dmax, d[e]);
+      }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(dmax > 8.0e37f) != 0, 0)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] = (bf16_t)swiglu((float)g[e], (float)u[e]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float r = __builtin_amdgcn_rcpf(d[e]);
+          a[e] = (bf16_t)((float)g[e] * __builtin_fmaf(r, __builtin_fmaf(-d[e], r, 1.0f), r) * (float)u[e]);
+        }
+      }
+      if (in) __builtin_nontemporal_store(a, reinterpret_cast<bf16x8_t*>(ar + aoff));
       __builtin_amdgcn_sched_barrier(0);
     });
   });
@@ -692,6 +776,16 @@ struct Operand64 {
       }
     }
   }
+  // KC: tile rows 64 q .. 64 q + 63 are to be rows 64 (q >> 1) .. from the origin on (q even) or those `half` rows further (q odd), all inside the matrix
+  __device__ __forceinline__ void pair_rows(int64_t ld, int64_t half, int lane, int wave) {
+    static_assert(KC, "");
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int rt = 8 * (4 * i + wave) + (lane >> 3);
+      const int64_t r = (rt >> 6 & 1) * half + (rt >> 7) * 64 + (rt & 63);
+      goff[i] = (unsigned)(r * ld * 2 + ((lane & 7) ^ swr(rt)) * 16);
+    }
+  }
   __device__ __forceinline__ void dma(int i, unsigned lds_op, int wave) const { lds_dma16(base, goff[i], lds_op + (4 * i + wave) * 1024); }
   __device__ __forceinline__ void advance() { base += kstep; }
   // the next loads are those of the last K step, of which only `rem` values of k exist (KC: a multiple of 8)
@@ -769,7 +863,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   // ---- XCD-aware tile id
   int tm, tn;
   gemm_tile_of_block(block, tiles_m, tiles_n, &tm, &tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  constexpr bool CAN_PAIR = MODE == GEMM_NT && !C_F32 && EPI == kEpiNone;
+  const bool pairs = CAN_PAIR && ga.epi.act != nullptr;
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * (pairs ? BN / 2 : BN);
 
   const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
   typedef Operand64<B_KC, 256> OpB;
@@ -777,6 +873,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   OpB ob;
   oa.init(A, lda, m0, M, wm, lane, wave);
   ob.init(B, ldb, n0, N, wn, lane, wave);
+  if constexpr (CAN_PAIR) {
+    if (pairs) ob.pair_rows(ldb, ga.epi.half, lane, wave);
+  }
 
   const int nk = (int)((K + BK64 - 1) / BK64), rem = (int)(K - (int64_t)(nk - 1) * BK64);     // rem: k values of the last step
   const unsigned fill_a = lds0 + wave * 1024, fill_b = fill_a + 2 * kOp64;
@@ -886,6 +985,16 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, int block) {
   }
   step(kt, std::false_type{}, std::false_type{});
 
+  if constexpr (CAN_PAIR) {
+    if (pairs) {
+      const int64_t rows = M - m0 - wm, half = ga.epi.half;
+      bf16_t* C = static_cast<bf16_t*>(ga.C) + (m0 + wm) * ga.ldc + n0 + wn / 2;
+      bf16_t* act = ga.epi.act + (m0 + wm) * half + n0 + wn / 2;
+      if (rows >= 128) store_tile_swiglu<false>(acc, lds64, wave, lane, C, ga.ldc, act, half, 128);
+      else if (rows > 0) store_tile_swiglu<true>(acc, lds64, wave, lane, C, ga.ldc, act, half, (int)rows);
+      return;
+    }
+  }
   if (ga.splits > 1)
     store_large<true>(acc, lds64, wave, lane, m0, n0, wm, wn, M, part_row(N, C_F32), ga.part + sp * M * part_row(N, C_F32), part_row(N, C_F32), 0, nullptr, 0, ga.epi);
   else
@@ -1088,7 +1197,7 @@ inline GemmArgs make_args(int64_t M, int64_t N, int64_t K, const void* A, int64_
   g.R = R; g.ldr = ldr;
   g.tiles_m = (int)((M + BM - 1) / BM);
   g.tiles_n = (int)((N + BN - 1) / BN);
-  g.epi = EpiArgs{nullptr, 1, 0, 0};
+  g.epi = EpiArgs{nullptr, 1, 0, 0, 0, nullptr};
   g.splits = 1;
   g.k_chunk = K;
   g.part = nullptr;
@@ -1414,6 +1523,19 @@ GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int6
   return GemmPlanInfo{p.tile == 192 ? 128 : p.tile, p.tile == 192 ? 256 : p.tile, p.nst, {p.splits[0], p.splits[1]}, p.part_floats, g_plans.planned};
 }
 
+// The product goes to 256 x 256 tiles, uncut, that take whole blocks of 128 gate columns; 32-bit offsets reach from a gate row of W to its up row
+bool gemm_mfma_swiglu_supported(int64_t M, int64_t half, int64_t K, int64_t lda, int64_t ldb, size_t floats) {
+  if (half % 128 != 0 || half * ldb >= ((int64_t)1 << 31) - ((int64_t)1 << 23) || !gemm_mfma_supported(DT_BF16, GEMM_NT, M, 2 * half, K, lda, ldb, 2 * half, DT_BF16, 0)) return false;
+  const GemmPlan p = plan_gemm(M, 2 * half, K, nt_scratch_limit(2 * half, 2 * half, 0, floats));
+  return p.tile == 256 && p.splits[0] == 1;
+}
+int launch_gemm_mfma_nt_swiglu(int64_t M, int64_t half, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* gu, void* act, hipStream_t st) {
+  v2::GemmArgs g = v2::make_args(M, 2 * half, K, A, lda, W, ldw, gu, 2 * half, 0, nullptr, 0);
+  g.epi.half = half;
+  g.epi.act = static_cast<bf16_t*>(act);
+  return v2::launch_pipe<GEMM_NT, false>(g, st);
+}
+
 bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols) { return N % 8 == 0 && rot_cols % 128 == 0; }
 
 int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
@@ -1422,7 +1544,7 @@ int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int
   // Sizes outside this condition were rotated by a pass of their own once, after a rounding to bf16, and keep that rounding: without it their
   // error against fp64 is lower (dx, 1000 tokens at H = 8192: 1.39 % instead of 1.56 %; 666 at 4096: 0.71 instead of 0.75), but q and k reach
   // dx through the scores, and it moves by more than bf16 results are held to (1.5 and 0.8 %).  With it everywhere the others would lose.
-  g.epi = v2::EpiArgs{rope_table, S, rot_cols, !(M % BM == 0 && N % BN == 0 && S >= 32)};
+  g.epi = v2::EpiArgs{rope_table, S, rot_cols, !(M % BM == 0 && N % BN == 0 && S >= 32), 0, nullptr};
   const GemmPlan p = plan_gemm(M, N, K, scr.floats);
   apply_plan(g, p, 0, scr.part);
   const int rc = launch_planned<GEMM_NT, false, v2::kEpiRope>(g, p, st);

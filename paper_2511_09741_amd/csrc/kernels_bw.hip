@@ -280,11 +280,7 @@ __global__ void __launch_bounds__(256) swiglu_fwd_kernel(const T* __restrict__ g
   g.load_nt(gu + row * 2 * (int64_t)I + col);
   u.load_nt(gu + row * 2 * (int64_t)I + I + col);
 #pragma unroll
-  for (int j = 0; j < V; ++j) {
-    const float gg = g.get(j);
-    const float sig = 1.0f / (1.0f + __expf(-gg));
-    o.set(j, gg * sig * u.get(j));
-  }
+  for (int j = 0; j < V; ++j) o.set(j, swiglu(g.get(j), u.get(j)));
   o.store_nt(a + row * (int64_t)I + col);
 }
 

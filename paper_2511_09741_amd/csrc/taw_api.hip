@@ -247,6 +247,8 @@ static int run_fwd(const taw_layer_desc* desc, const Plan& p, const taw_weight_l
   // gu = hn Wgu^T ; a = silu(g) u
   if (!p.mfma_gemm) {
     TAW_LAUNCH(launch_gemm_generic_swiglu(dt, T, I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, c.a, st), "gemm gate/up + swiglu (generic)");
+  } else if (dt == DT_BF16 && gemm_mfma_swiglu_supported(T, I, H, H, H, scr.floats)) {
+    TAW_LAUNCH(launch_gemm_mfma_nt_swiglu(T, I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, c.a, st), "gemm gate/up + swiglu");
   } else {
     TAW_LAUNCH(gemm(p, dt, GEMM_NT, T, 2 * I, H, c.hn, H, at(W_chunk, L.w_gate_up, dt), H, c.gu, 2 * I, dt, 0, nullptr, 0, scr, st), "gemm gate/up");
     TAW_LAUNCH(launch_swiglu_fwd(dt, T, (int)I, c.gu, c.a, st), "swiglu_fwd");

@@ -146,6 +146,10 @@ GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int6
 bool gemm_mfma_rope_supported(int64_t N, int64_t rot_cols);
 int launch_gemm_mfma_nt_rope(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
                              const float* rope_table, int S, int64_t rot_cols, const GemmScratch& scr, hipStream_t st);
+// gu[M, 2 half] = A W^T (W [2 half, K] = gate | up) and act[M, half] = silu(gate) up in one launch, where the product takes 256 x 256 tiles (`floats`: of scratch
+// that the product alone would be given)
+bool gemm_mfma_swiglu_supported(int64_t M, int64_t half, int64_t K, int64_t lda, int64_t ldb, size_t floats);
+int launch_gemm_mfma_nt_swiglu(int64_t M, int64_t half, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* gu, void* act, hipStream_t st);
 // bf16, head_dim 128, and S * 3 * n_heads * head_dim * 2 bytes below 4 GiB (32-bit row offsets inside one batch element)
 bool attn_mfma_supported(int dtype, int S, int nh, int d);
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st);

@@ -382,3 +382,39 @@ def test_kernel_level_qkv_projection_is_the_layers(taw, dtype, B, S, nh, d, I_):
     taw.taw_op_qkv_rope(dtype, B, S, nh, d, xn, L.chunk[lo:lo + 3 * H * H], out, L.rope, impl)
     torch.cuda.synchronize()
     assert torch.equal(out, qkv)
+
+
+@pytest.mark.parametrize("T,H,I_", [(4503, 1024, 2816), (16385, 1024, 2816), (16300, 1152, 1152), (8192, 2048, 2816)])
+def test_gate_up_projection_with_swiglu_in_its_epilogue(taw, T, H, I_):
+    """Where the gate/up product takes 256 x 256 tiles (and I is a multiple of 128) its epilogue stores silu(gate) up too.  The cached gate and up are the
+    product's, and the cached a is the separate pass's on them, bit for bit: tiles over the last row, saturated and tiny sigmoids, infinities and NaN."""
+    import torch
+    cfg = I.LayerConfig("swi", I.BF16, 1, T, H, H // 128, 128, I_, sigma_w=0.2)
+    L = U.DeviceLayer(taw, cfg)
+    info = taw.taw_diag_gemm_plan(False, T, 2 * I_, H)
+    assert (info["tile_m"], info["tile_n"], info["splits"]) == (256, 256, 1)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    w = torch.empty(L.layout["total_elems"], device="cuda").normal_(0, 0.05, generator=g)
+    lay = L.layout
+    w[lay["gamma_attn"]:lay["gamma_attn"] + H] = 1.0
+    w[lay["gamma_mlp"]:lay["gamma_mlp"] + H] = 1.0
+    gate = w[lay["w_gate_up"]:lay["w_gate_up"] + I_ * H].view(I_, H)
+    gate[3::8] *= 60.0                                    # gates of +-100: exp overflows, sigmoids are denormal numbers or 1
+    gate[5], gate[6] = float("inf"), float("nan")
+    gate[7, 0] = 3e38
+    L.chunk = w.bfloat16()
+    x = torch.empty(1, T, H, device="cuda").normal_(generator=g).bfloat16()
+    L.fwd(x)
+    up = lambda n: -(-n // 256) * 256
+    at, off = 0, {}
+    for name, n in (("xn", H), ("qkv", 3 * H), ("o", H), ("h", H), ("hn", H), ("gu", 2 * I_), ("a", I_)):      # each from a multiple of 256 bytes
+        off[name] = L.ctx[at:at + 2 * T * n].view(torch.bfloat16).view(T, n)
+        at += up(2 * T * n)
+    gu, a = torch.empty_like(off["gu"]), torch.empty_like(off["a"])
+    lo = lay["w_gate_up"]
+    taw.taw_op_gemm(I.BF16, taw.TAW_GEMM_NT, T, 2 * I_, H, off["hn"], H, L.chunk[lo:lo + 2 * I_ * H], H, gu, 2 * I_, I.BF16, 0, None, 0, taw.TAW_IMPL_MFMA)
+    taw.taw_op_swiglu_fwd(I.BF16, T, I_, off["gu"], a)
+    torch.cuda.synchronize()
+    assert torch.equal(gu.view(torch.int16), off["gu"].view(torch.int16))
+    assert torch.equal(a.isnan(), off["a"].isnan())
+    assert torch.equal(torch.nan_to_num(a, 0.0), torch.nan_to_num(off["a"], 0.0))
