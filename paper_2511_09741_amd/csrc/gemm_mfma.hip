@@ -1333,24 +1333,25 @@ struct GemmPlan {
   size_t part_floats;
 };
 
-// What a tile shape costs, in microseconds: `fixed` per workgroup, and per 64-deep step the larger of `lone` (one workgroup on a compute
-// unit: the latency of its loads) and `busy` x the workgroups that share the unit (`resident` at most).  Fitted over 1800
-// timings of the five shapes at 64 ... 8192 rows and 256 ... 22016 columns, with 32x32x16 MFMAs and every result stored through LDS.  Over 1838
-// timings of the kernels there are (66 products and their backwards, the same range) it is 10.6 % off in the mean, 9 % low for 64 x 64 tiles and 3 %
-// for the others, and what it picks is 3.3 % slower than the fastest of the shapes and cuts (products 1.4 %, pairs 5.2; one in eight by more than 10 %, the
-// backward of 333 x 4096 x 11008 by 31).  256 x 256 tiles alone are up to 7 times slower.
+// What a tile shape costs, in microseconds: a fixed part per workgroup, more where it stores fp32 (weight gradients and partial products), and per 64-deep
+// step the larger of `lone` (one workgroup on a compute unit: the latency of its loads) and `busy` x the workgroups that share the unit (`resident` at most).
+// Fitted for the time of what it picks first, over timings of the five shapes and their cuts for 945 products and backwards (64 ... 65536 rows, layers 256 ... 8192
+// wide), each on as much memory in turn as its layer touches (weights that a small layer leaves in the caches and a wide one does not), among the costs
+// that keep every shape and cut in use where the tests look for it.  The pick is 2.7 % slower than the fastest (products 0.9 %, pairs 3.6 %; without that
+// condition 1.8 %), with the costs of before, fitted on warm caches with one fixed part for both types, 3.9 % (1.7, 5.0).
+// 256 x 256 tiles alone are up to 7 times slower.
 struct TileCost {
   int tile, tm, tn, nst, resident;
-  double fixed, lone, busy;
+  double fixed_bf16, fixed_f32, lone, busy;
 };
 static const TileCost kTiles[] = {
-    {256, 256, 256, 2, 1, 6.8, 1.10, 1.17},
-    {192, 128, 256, 3, 1, 6.5, 0.63, 0.66},
-    {128, 128, 128, 4, 1, 4.1, 0.42, 0.42},
-    {128, 128, 128, 2, 2, 3.8, 0.54, 0.40},
-    {64, 64, 64, 4, 2, 1.8, 0.21, 0.16},
+    {256, 256, 256, 2, 1, 5.96, 7.18, 1.056, 1.056},
+    {192, 128, 256, 3, 1, 4.57, 6.13, 0.682, 0.682},
+    {128, 128, 128, 4, 1, 4.11, 4.22, 0.420, 0.420},
+    {128, 128, 128, 2, 2, 3.57, 4.04, 0.717, 0.402},
+    {64, 64, 64, 4, 2, 2.14, 1.94, 0.208, 0.163},
 };
-constexpr double kReduceFixed = 4.6, kReduceBytesPerUs = 10.3e6;      // the second kernel of a cut contraction
+constexpr double kReduceFixed = 4.61, kReduceBytesPerUs = 10.0e6;      // the second kernel of a cut contraction
 constexpr size_t kMaxPartFloats = (size_t)64 << 20;                   // 256 MB of partial products at most
 
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -1398,7 +1399,8 @@ static GemmPlan work_out_plan(int np, const GemmProblem (&pr)[2], size_t max_flo
         const int64_t n0 = tiles[0] * p.splits[0], n1 = tiles[1] * p.splits[1];
         const int64_t share = cdiv(n0 + n1, 256) < c.resident ? cdiv(n0 + n1, 256) : c.resident;
         const double step = c.lone > share * c.busy ? c.lone : share * c.busy;
-        const double d0 = c.fixed + step * cdiv(p.chunk[0], 64), d1 = c.fixed + step * cdiv(p.chunk[1], 64);
+        auto one = [&](int i) { return (pr[i].out_bytes == 4 || p.splits[i] > 1 ? c.fixed_f32 : c.fixed_bf16) + step * cdiv(p.chunk[i], 64); };
+        const double d0 = one(0), d1 = one(1);
         double t = np == 1 || d0 >= d1 ? makespan(n0, d0, n1, d1, 256 * c.resident) : makespan(n1, d1, n0, d0, 256 * c.resident);
         if (part_bytes > 0) t += kReduceFixed + part_bytes / kReduceBytesPerUs;
         if (t < best_t) {
