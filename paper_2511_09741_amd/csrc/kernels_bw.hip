@@ -359,12 +359,14 @@ __global__ void __launch_bounds__(256) grad_accum_kernel(float* __restrict__ G, 
 // AdamW with decoupled weight decay over a whole shard, one pass: reads G, m, v and the fp32 master
 // weights, writes m, v, the master weights and the weight chunk in its storage type; optionally
 // leaves G zeroed for the next mini-batch.  b1c = 1 - beta1^t, b2c = 1 - beta2^t come from the host.
-constexpr int kAdamRows = 2;
-template <typename TW>
+// STREAM: a chunk that the memory-side cache cannot hold is stored past the caches, and a workgroup takes one row instead of two.
+template <bool STREAM> constexpr int kAdamRowsOf = STREAM ? 1 : 2;
+template <typename TW, bool STREAM>
 __global__ void __launch_bounds__(256) adamw_kernel(TW* __restrict__ chunk, float* __restrict__ master, float* __restrict__ m,
                                                      float* __restrict__ v, float* __restrict__ G, size_t n, float lr, float beta1,
                                                      float beta2, float eps, float wd, float b1c, float b2c, float gscale,
                                                      int zero_grad) {
+  constexpr int kAdamRows = kAdamRowsOf<STREAM>;
   const size_t nvec = n / 4;
   auto upd = [&](float g, float& mm, float& vv, float& w) {
     g *= gscale;
@@ -401,14 +403,13 @@ __global__ void __launch_bounds__(256) adamw_kernel(TW* __restrict__ chunk, floa
     __builtin_nontemporal_store(m4[u], reinterpret_cast<f32x4_t*>(m + 4 * i));
     __builtin_nontemporal_store(v4[u], reinterpret_cast<f32x4_t*>(v + 4 * i));
     __builtin_nontemporal_store(w4[u], reinterpret_cast<f32x4_t*>(master + 4 * i));
-    if constexpr (sizeof(TW) == 4) {
-      *reinterpret_cast<f32x4_t*>(chunk + 4 * i) = w4[u];       // the chunk is what the next forward reads: ordinary store
-    } else {
-      bf16x4_t o;
+    // the chunk is what the next forward reads: ordinary store where a cache can keep it
+    typedef TW tw4_t __attribute__((ext_vector_type(4)));
+    tw4_t o;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] = (bf16_t)w4[u][j];
-      *reinterpret_cast<bf16x4_t*>(chunk + 4 * i) = o;
-    }
+    for (int j = 0; j < 4; ++j) o[j] = (TW)w4[u][j];
+    if constexpr (STREAM) __builtin_nontemporal_store(o, reinterpret_cast<tw4_t*>(chunk + 4 * i));
+    else *reinterpret_cast<tw4_t*>(chunk + 4 * i) = o;
     if (zero_grad) __builtin_nontemporal_store(f32x4_t{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4_t*>(G + 4 * i));
   }
   if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {
@@ -622,18 +623,28 @@ int launch_grad_accum(float* G, const void* g, int src_dtype, size_t n, float sc
   return last_err();
 }
 
+template <typename TW, bool STREAM>
+static int launch_adamw_as(void* chunk, float* master, float* m, float* v, float* G, size_t n, float lr, float beta1, float beta2, float eps, float wd, float b1c,
+                           float b2c, float gscale, int zero_grad, hipStream_t st) {
+  constexpr size_t per = kAdamRowsOf<STREAM> * 256;
+  size_t want = (n / 4 + per - 1) / per;
+  if (want == 0) want = 1;
+  if (want > 0x7fffffffu) return (int)hipErrorInvalidValue;
+  hipLaunchKernelGGL((adamw_kernel<TW, STREAM>), dim3((unsigned)want), dim3(256), 0, st, (TW*)chunk, master, m, v, G, n, lr, beta1, beta2, eps, wd, b1c, b2c, gscale,
+                     zero_grad);
+  return last_err();
+}
+
+// The line is the 256 MiB of the memory-side cache: a smaller chunk stays in it while the update runs, and storing past it costs.  us with ordinary stores and
+// two rows -> past the caches and one row, G zeroed: bf16 chunk of 800 MB 2495 -> 2390, 405 MB 1247 -> 1175 (1265 -> 1258 where the arrays lay elsewhere), 300 MB
+// 948 -> 933, 266 MB 772 -> 830, 99 MB 278 -> 306.
 int launch_adamw(int w_dtype, void* chunk, float* master, float* m, float* v, float* G, size_t n, float lr, float beta1, float beta2,
                  float eps, float wd, float b1c, float b2c, float gscale, int zero_grad, hipStream_t st) {
   if (n == 0) return 0;
-  size_t want = (n / 4 + kAdamRows * 256 - 1) / (kAdamRows * 256);
-  if (want == 0) want = 1;
-  if (want > 0x7fffffffu) return (int)hipErrorInvalidValue;
-  const unsigned grid = (unsigned)want;
-  if (w_dtype == DT_BF16)
-    hipLaunchKernelGGL((adamw_kernel<bf16_t>), dim3(grid), dim3(256), 0, st, (bf16_t*)chunk, master, m, v, G, n, lr, beta1, beta2, eps, wd, b1c, b2c, gscale, zero_grad);
-  else
-    hipLaunchKernelGGL((adamw_kernel<float>), dim3(grid), dim3(256), 0, st, (float*)chunk, master, m, v, G, n, lr, beta1, beta2, eps, wd, b1c, b2c, gscale, zero_grad);
-  return last_err();
+  const bool stream = n * (w_dtype == DT_BF16 ? 2 : 4) > ((size_t)256 << 20);
+  const auto f = w_dtype == DT_BF16 ? (stream ? launch_adamw_as<bf16_t, true> : launch_adamw_as<bf16_t, false>)
+                                    : (stream ? launch_adamw_as<float, true> : launch_adamw_as<float, false>);
+  return f(chunk, master, m, v, G, n, lr, beta1, beta2, eps, wd, b1c, b2c, gscale, zero_grad, st);
 }
 
 int launch_stage_copy(void* dst, const void* src, size_t bytes, hipStream_t st) {

@@ -433,6 +433,35 @@ def test_optimizer_step(taw, dtype, n):
         assert np.array_equal(I.to_storage(master.cpu().numpy(), dtype), chunk.view(torch.int16).cpu().numpy().view(np.uint16))
 
 
+@pytest.mark.parametrize("dtype,n", [(I.BF16, (1 << 27) + 2050), (I.F32, (1 << 26) + 1027)], ids=["bf16", "fp32"])
+def test_optimizer_step_on_a_chunk_past_the_cache(taw, dtype, n):
+    """A chunk of more than 256 MiB is stored past the caches, a row of 256 x 16 bytes to a workgroup: the first and last elements against the oracle (bounds as in
+    test_optimizer_step), and the whole of it against the same update of its halves, which take the other way: each within 1e-6 of the exact update, so
+    within 2e-6 of each other."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    w, m, v, G = (torch.empty(n, device="cuda").normal_(0, s, generator=gen) for s in (1.0, 0.1, 0.1, 1.0))
+    v.square_()
+    tdt = torch.bfloat16 if dtype == I.BF16 else torch.float32
+    hp = dict(lr=1e-2, beta1=0.9, beta2=0.95, eps=1e-6, weight_decay=0.1, grad_scale=0.25)
+    at = torch.cat([torch.arange(4100), torch.arange(n - 4100, n)]).cuda()
+    before = [x[at].double().cpu().numpy() for x in (w, m, v, G)]
+    halves = [x.clone() for x in (w, m, v, G)] + [torch.empty(n, dtype=tdt, device="cuda")]
+    chunk = torch.empty(n, dtype=tdt, device="cuda")
+    taw.taw_optimizer_step(chunk, dtype, w, m, v, G, n, 3, zero_grad=True, **hp)
+    cut = n // 2 // 1024 * 1024
+    for lo, hi in ((0, cut), (cut, n)):
+        hw, hm, hv, hG, hc = (x[lo:hi] for x in halves)
+        taw.taw_optimizer_step(hc, dtype, hw, hm, hv, hG, hi - lo, 3, zero_grad=True, **hp)
+    torch.cuda.synchronize()
+    for x, y in zip((w, m, v), halves):
+        assert float((x - y).abs().max()) < 2e-6 * float(y.abs().max())
+    ref = O.adamw_step(*before, 3, hp["lr"], hp["beta1"], hp["beta2"], hp["eps"], hp["weight_decay"], hp["grad_scale"])
+    for x, r in zip((w, m, v), ref):
+        assert U.tensor_scale_err(x[at].double().cpu().numpy(), r) < 1e-6
+    assert torch.count_nonzero(G).item() == 0 and torch.equal(chunk, w.to(tdt))
+
+
 @pytest.mark.parametrize("mode,f32,M,N", [(0, 1, 300, 264), (0, 1, 257, 263), (0, 1, 129, 130), (1, 0, 300, 264), (1, 0, 385, 520), (1, 1, 513, 8), (2, 0, 264, 136),
                                           (2, 1, 8, 392)])
 @pytest.mark.parametrize("pad", [0, 8, 3])
