@@ -384,12 +384,13 @@ def test_kernel_level_qkv_projection_is_the_layers(taw, dtype, B, S, nh, d, I_):
     assert torch.equal(out, qkv)
 
 
-@pytest.mark.parametrize("T,H,I_", [(4503, 1024, 2816), (16385, 1024, 2816), (16300, 1152, 1152), (8192, 2048, 2816)])
-def test_gate_up_projection_with_swiglu_in_its_epilogue(taw, T, H, I_):
+@pytest.mark.parametrize("B,S,H,d,I_", [(1, 4503, 1024, 128, 2816), (1, 16385, 1024, 128, 2816), (1, 16300, 1152, 128, 1152), (1, 8192, 2048, 128, 2816), (32, 512, 1032, 24, 2816)])
+def test_gate_up_projection_with_swiglu_in_its_epilogue(taw, B, S, H, d, I_):
     """Where the gate/up product takes 256 x 256 tiles (and I is a multiple of 128) its epilogue stores silu(gate) up too.  The cached gate and up are the
-    product's, and the cached a is the separate pass's on them, bit for bit: tiles over the last row, saturated and tiny sigmoids, infinities and NaN."""
+    product's, and the cached a is the separate pass's on them, bit for bit: tiles over the last row, a last step of the contraction that is not whole (the last case), saturated and tiny sigmoids, infinities and NaN."""
     import torch
-    cfg = I.LayerConfig("swi", I.BF16, 1, T, H, H // 128, 128, I_, sigma_w=0.2)
+    T = B * S
+    cfg = I.LayerConfig("swi", I.BF16, B, S, H, H // d, d, I_, sigma_w=0.2)
     L = U.DeviceLayer(taw, cfg)
     info = taw.taw_diag_gemm_plan(False, T, 2 * I_, H)
     assert (info["tile_m"], info["tile_n"], info["splits"]) == (256, 256, 1)
@@ -403,7 +404,7 @@ def test_gate_up_projection_with_swiglu_in_its_epilogue(taw, T, H, I_):
     gate[5], gate[6] = float("inf"), float("nan")
     gate[7, 0] = 3e38
     L.chunk = w.bfloat16()
-    x = torch.empty(1, T, H, device="cuda").normal_(generator=g).bfloat16()
+    x = torch.empty(B, S, H, device="cuda").normal_(generator=g).bfloat16()
     L.fwd(x)
     up = lambda n: -(-n // 256) * 256
     at, off = 0, {}
