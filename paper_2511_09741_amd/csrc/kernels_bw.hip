@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(256) grad_accum_kernel(float* __restrict__ G, 
 // AdamW with decoupled weight decay over a whole shard, one pass: reads G, m, v and the fp32 master
 // weights, writes m, v, the master weights and the weight chunk in its storage type; optionally
 // leaves G zeroed for the next mini-batch.  b1c = 1 - beta1^t, b2c = 1 - beta2^t come from the host.
-// STREAM: a chunk that the memory-side cache cannot hold is stored past the caches, and a workgroup takes one row instead of two.
+// STREAM (bf16): a chunk that the memory-side cache cannot hold is stored past the caches, and a workgroup takes one row instead of two.
 template <bool STREAM> constexpr int kAdamRowsOf = STREAM ? 1 : 2;
 template <typename TW, bool STREAM>
 __global__ void __launch_bounds__(256) adamw_kernel(TW* __restrict__ chunk, float* __restrict__ master, float* __restrict__ m,
@@ -368,12 +368,16 @@ __global__ void __launch_bounds__(256) adamw_kernel(TW* __restrict__ chunk, floa
                                                      int zero_grad) {
   constexpr int kAdamRows = kAdamRowsOf<STREAM>;
   const size_t nvec = n / 4;
-  auto upd = [&](float g, float& mm, float& vv, float& w) {
+  // Which product of a sum is fused with it is written out, as the kernel has always had it (by type, and for the up to three elements behind the last
+  // vector): left to the compiler, m and v of an instantiation for large chunks came out in other bits than those of the same shard updated in parts.
+  auto upd = [&](float g, float& mm, float& vv, float& w, bool behind) {
+#pragma clang fp contract(off)
     g *= gscale;
-    mm = beta1 * mm + (1.f - beta1) * g;
-    vv = beta2 * vv + (1.f - beta2) * g * g;
+    const float g1 = (1.f - beta1) * g, g2 = (1.f - beta2) * g;
+    mm = behind ? __builtin_fmaf(beta1, mm, g1) : __builtin_fmaf(1.f - beta1, g, beta1 * mm);
+    vv = behind || sizeof(TW) == 2 ? __builtin_fmaf(beta2, vv, g2 * g) : __builtin_fmaf(g, g2, beta2 * vv);
     const float mh = mm / b1c, vh = vv / b2c;
-    w = w - lr * (mh / (sqrtf(vh) + eps) + wd * w);
+    w = __builtin_fmaf(-lr, __builtin_fmaf(wd, w, mh / (sqrtf(vh) + eps)), w);
   };
   // a workgroup takes kAdamRows consecutive rows of 256 x 16 bytes of each array, once (as grad_accum_kernel does)
   const size_t i0 = (size_t)blockIdx.x * (kAdamRows * 256) + threadIdx.x;
@@ -397,7 +401,7 @@ __global__ void __launch_bounds__(256) adamw_kernel(TW* __restrict__ chunk, floa
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       float mm = m4[u][j], vv = v4[u][j], w = w4[u][j];
-      upd(g4[u][j], mm, vv, w);
+      upd(g4[u][j], mm, vv, w, false);
       m4[u][j] = mm; v4[u][j] = vv; w4[u][j] = w;
     }
     __builtin_nontemporal_store(m4[u], reinterpret_cast<f32x4_t*>(m + 4 * i));
@@ -415,7 +419,7 @@ __global__ void __launch_bounds__(256) adamw_kernel(TW* __restrict__ chunk, floa
   if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {
     const size_t i = nvec * 4 + threadIdx.x;
     float mm = m[i], vv = v[i], w = master[i];
-    upd(G[i], mm, vv, w);
+    upd(G[i], mm, vv, w, true);
     m[i] = mm; v[i] = vv; master[i] = w;
     chunk[i] = (TW)w;
     if (zero_grad) G[i] = 0.f;
@@ -635,15 +639,15 @@ static int launch_adamw_as(void* chunk, float* master, float* m, float* v, float
   return last_err();
 }
 
-// The line is the 256 MiB of the memory-side cache: a smaller chunk stays in it while the update runs, and storing past it costs.  us with ordinary stores and
-// two rows -> past the caches and one row, G zeroed: bf16 chunk of 800 MB 2495 -> 2390, 405 MB 1247 -> 1175 (1265 -> 1258 where the arrays lay elsewhere), 300 MB
-// 948 -> 933, 266 MB 772 -> 830, 99 MB 278 -> 306.
+// The line is a little above the 256 MiB of the memory-side cache: a smaller chunk stays in it while the update runs, and storing past it costs.  bf16, G zeroed,
+// us with ordinary stores and two rows -> past the caches and one row, mean of six placements of the arrays (they move a time by up to 4 %): 256 MiB of chunk
+// 766 -> 827, 261 MiB 802 -> 833, 267 MiB 855 -> 861, 273 MiB 895 -> 871, 286 MiB 944 -> 910, 343 MiB 1132 -> 1095, 386 MiB 1276 -> 1245 (single places -5 .. +1 %),
+// 763 MiB 2546 -> 2431.  fp32 chunks have next to nothing from it (256 MiB 375 -> 434, 286 MiB 495 -> 493, 381 MiB 654 -> 655, 572 MiB 999 -> 984).
+constexpr size_t kAdamStreamBytes = (size_t)272 << 20;
 int launch_adamw(int w_dtype, void* chunk, float* master, float* m, float* v, float* G, size_t n, float lr, float beta1, float beta2,
                  float eps, float wd, float b1c, float b2c, float gscale, int zero_grad, hipStream_t st) {
   if (n == 0) return 0;
-  const bool stream = n * (w_dtype == DT_BF16 ? 2 : 4) > ((size_t)256 << 20);
-  const auto f = w_dtype == DT_BF16 ? (stream ? launch_adamw_as<bf16_t, true> : launch_adamw_as<bf16_t, false>)
-                                    : (stream ? launch_adamw_as<float, true> : launch_adamw_as<float, false>);
+  const auto f = w_dtype != DT_BF16 ? launch_adamw_as<float, false> : 2 * n > kAdamStreamBytes ? launch_adamw_as<bf16_t, true> : launch_adamw_as<bf16_t, false>;
   return f(chunk, master, m, v, G, n, lr, beta1, beta2, eps, wd, b1c, b2c, gscale, zero_grad, st);
 }
 
