@@ -62,11 +62,13 @@ typedef enum { TAW_F32 = 0, TAW_BF16 = 1 } taw_dtype;
 
 /* Forms of the attention backward on the matrix-core path.  Default: a dK/dV kernel that forms the scores once and also
    writes dS (bf16) to the workspace, and a dQ kernel that reads it back: five matrix products per tile pair, no atomics,
-   reproducible; the workspace holds about S*S bytes per (batch, head) for it (35 GB at S = 32768 with 32 heads). */
+   reproducible; the workspace holds about S*S bytes per (batch, head) for it (35 GB at S = 32768 with 32 heads).  With so
+   few tokens that the chip has room for both kernels at once, one launch recomputes the scores instead (seven products). */
 #define TAW_ATTN_BWD_FUSED 4u /* one kernel that forms the scores once and keeps dQ partial sums in private fp32 slots
                                  (the workspace holds those slots instead of dS) */
 #define TAW_ATTN_BWD_RECOMPUTE 8u /* the pair of kernels with a dQ kernel that recomputes the scores (seven products):
-                                     needs neither dS nor slots in the workspace; about 12 % slower at S = 32768 */
+                                     needs neither dS nor slots in the workspace; the default's bits at every size; about
+                                     12 % slower at S = 32768 */
 
 /* One decoder layer and the micro-batch it is applied to (B, S, H as in the paper's Table 1). */
 typedef struct {

@@ -23,14 +23,14 @@ extern "C" {
 
 enum { TAW_IMPL_AUTO = 0, TAW_IMPL_GENERIC = 1, TAW_IMPL_MFMA = 2,
        /* taw_op_attn_bwd only: the forms of the MFMA backward.  TAW_IMPL_MFMA is the pair of kernels (dK/dV, then dQ) that
-          each recompute the scores: 7 matrix products per tile pair, nothing but the row statistics in the scratch.
+          each recompute the scores: 7 matrix products per tile pair, nothing but the row statistics in the scratch (one
+          launch where the chip has room for both at once: few tokens).
           TAW_IMPL_AUTO takes TAW_IMPL_MFMA_STORED where the MFMA kernels apply, as taw_layer_bwd does by default. */
        TAW_IMPL_MFMA_FUSED = 3,   /* one kernel, 5 products; dQ partial sums in private fp32 slots, one per worker, summed by a last pass: no atomics, reproducible */
        TAW_IMPL_MFMA_ATOMIC = 4,  /* one kernel, 5 products; dQ added with fp32 atomics into one buffer (not bit-reproducible) */
        TAW_IMPL_MFMA_STORED = 5   /* two kernels, 5 products: the dK/dV kernel also writes dS (bf16) to the scratch and the dQ kernel reads it
-                                     back instead of recomputing it; no atomics; the fastest on this part.  Where the chip has room for both at once (few
-                                     tokens) one launch does both and nothing is stored.  Up to 640 tokens and from about 300 tiles of 256 rows on
-                                     the bits of TAW_IMPL_MFMA, between them sums in another order */ };
+                                     back instead of recomputing it; no atomics; the fastest on this part.  Where the chip has room for both at once
+                                     nothing is stored: it is TAW_IMPL_MFMA there.  The bits of TAW_IMPL_MFMA at every size */ };
 enum { TAW_GEMM_NT = 0, TAW_GEMM_NN = 1, TAW_GEMM_TN = 2 };
 
 /* The three products of a linear layer y = x W^T (W is [out, in]):

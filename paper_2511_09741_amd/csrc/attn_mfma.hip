@@ -1138,7 +1138,7 @@ __device__ __forceinline__ void attn_bwd_dq_body(int blk, const bf16_t* __restri
                                                  const float* __restrict__ rope) {
   constexpr int WQ = 32, RG = NW / KS, BQ = RG * WQ, BKV = KS == 4 ? 128 : 64, NS = KS == 4 ? 2 : 4;
   constexpr int kV = BKV / 64 * kTileBytes, kStage = 2 * kV, kDma = BKV / 32 * 16 / NW;   // K tile | V tile; loads per tile and wavefront
-  static_assert(KS == 1 || (KS == 4 && NW == kWaves8), "");
+  static_assert(KS == 1 || ((KS == 2 || KS == 4) && NW == kWaves8), "");
   extern __shared__ __attribute__((aligned(256))) unsigned char lds_raw[];
   const lds_u8_t* L = (const lds_u8_t*)lds_raw;
   const unsigned lds0 = (unsigned)(size_t)L;
@@ -1284,11 +1284,12 @@ __device__ __forceinline__ void attn_bwd_dq_body(int blk, const bf16_t* __restri
   store_rows_T(dq, scale, stage, dqout, ld, q0w, S, lane);
 }
 
+template <int KS>
 __global__ void __launch_bounds__(kThreads8, 1)
 attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, const float* __restrict__ lse2,
                    const float* __restrict__ Dsum, bf16_t* __restrict__ dqkv, int B, int S, int Sp, int nh, float scale,
                    const float* __restrict__ rope) {
-  attn_bwd_dq_body<kWaves8, 1>((int)blockIdx.x, qkv, dO, lse2, Dsum, dqkv, B, S, Sp, nh, scale, rope);
+  attn_bwd_dq_body<kWaves8, KS>((int)blockIdx.x, qkv, dO, lse2, Dsum, dqkv, B, S, Sp, nh, scale, rope);
 }
 
 // Both of the above in one grid, dQ's workgroups after the n of dK/dV: where all of them find a compute unit of their own, the products that dQ forms again
@@ -1839,7 +1840,7 @@ AttnShape attn_shape(int B, int S, int nh) {
   return {n8 <= 256 ? 128 : 256, 1};
 }
 
-// Whether the backward of the default form runs as one grid of both kernels, dQ forming the scores again (attn_bwd_pair_kernel), instead of storing dS: as
+// Whether the backward (the default form and the recomputing pair) runs as one grid of both kernels, dQ forming the scores again (attn_bwd_pair_kernel), instead of storing dS: as
 // long as both kinds of workgroups find a compute unit each, and up to 256 of each, where the second ones follow the short ones of the first.  us with dS
 // stored -> in one grid: 64 tokens of 1 head 11.8 -> 8.6, 2 x 333 of 2 25.5 -> 18.7, 640 of 40 (200 tiles) 42.1 -> 32.2, 4 x 200 of 32 (256) 26.9 -> 25.5,
 // 1024 of 8 (128) 32.8 -> 23.8, 1024 of 16 (256) 36.8 -> 32.2, 16384 of 1 (256) 349 -> 266, 1024 of 24 (384) 45.8 -> 48.6.
@@ -1874,6 +1875,28 @@ int launch_bwd_stored(int B, int S, int Sp, int nh, const void* qkv, const void*
   TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dq_stored_kernel<NW, KS>), (kDqsLds<NW, KS>));
   hipLaunchKernelGGL((attn_bwd_dq_stored_kernel<NW, KS>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), (kDqsLds<NW, KS>), st, (const bf16_t*)qkv, ds, pair_bytes,
                      (bf16_t*)dqkv, B, S, nh, scale, rope_table);
+  return (int)hipGetLastError();
+}
+
+// The recomputing pair, in parts where the default form takes them: the bits of both are the same.  Unparted it keeps 256 rows: 128 do the same arithmetic in
+// the same order.
+template <int KS>
+int launch_bwd_split(int B, int S, int Sp, int nh, const void* qkv, const void* dO, const float* lse2, const float* Dv, void* dqkv,
+                     const float* rope_table, hipStream_t st) {
+  constexpr int NW = kWaves8;
+  const float scale = 1.0f / sqrtf((float)D);
+  const int rows = 32 * NW / KS, nt = (S + rows - 1) / rows;
+  static_assert(kKvLds<NW, KS> >= NW * 32 * 136 * sizeof(bf16_t), "staging area");
+  TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<false, NW, KS>), (kKvLds<NW, KS>));
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<false, NW, KS>), dim3((unsigned)(nt * B * nh)), dim3(NW * 64), (kKvLds<NW, KS>), st, (const bf16_t*)qkv, (const bf16_t*)dO,
+                     lse2, Dv, (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, nullptr, (int64_t)0);
+  const int rc = (int)hipGetLastError();
+  if (rc) return rc;
+  constexpr size_t ring = 4 * 2 * kTileBytes;
+  static_assert(ring >= NW * 32 * 136 * sizeof(bf16_t) && ring >= (KS - 1) * (NW / KS) * 16384, "staging area");
+  TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dq_kernel<KS>, ring);
+  hipLaunchKernelGGL(attn_bwd_dq_kernel<KS>, dim3((unsigned)(nt * B * nh)), dim3(NW * 64), ring, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv, (bf16_t*)dqkv,
+                     B, S, Sp, nh, scale, rope_table);
   return (int)hipGetLastError();
 }
 
@@ -1975,37 +1998,23 @@ int launch_attn_bwd_mfma(int B, int S, int nh, const void* qkv, const void* o, c
                        (int)H, scale, rope_table);
     return (int)hipGetLastError();
   }
+  // the default form and the recomputing pair: the same shapes, so the same sums in the same order
+  const AttnShape a = attn_shape(B, S, nh);
+  if (attn_bwd_in_one_grid(a, B, S, nh))
+    return a.parts == 4 ? launch_bwd_pair<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st)
+                        : launch_bwd_pair<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);
   if (form == ATTN_BWD_STORED) {
     // the stored dS follows the row statistics (a multiple of 512 bytes in front of it)
     unsigned char* ds = reinterpret_cast<unsigned char*>(slots);
     const int64_t pair_bytes = attn_bwd_ds_pair_bytes(S);
-    const AttnShape a = attn_shape(B, S, nh);
-    if (attn_bwd_in_one_grid(a, B, S, nh))
-      return a.parts == 4 ? launch_bwd_pair<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st)
-                          : launch_bwd_pair<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);
     if (a.parts == 4) return launch_bwd_stored<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
     if (a.parts == 2) return launch_bwd_stored<kWaves8, 2>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
     return a.rows == 128 ? launch_bwd_stored<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st)
                          : launch_bwd_stored<kWaves8, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, ds, pair_bytes, rope_table, st);
   }
-  {
-    constexpr size_t lds = kKvLds<kWaves8>;
-    static_assert(lds >= 8 * 32 * 136 * sizeof(bf16_t), "staging area");
-    TAW_SET_LDS_LIMIT_ONCE((attn_bwd_dkv_kernel<false, kWaves8, 1>), lds);
-    const int nkt = (S + 255) / 256;
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<false, kWaves8, 1>), dim3((unsigned)(nkt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
-                       (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table, nullptr, (int64_t)0);
-    int rc = (int)hipGetLastError();
-    if (rc) return rc;
-  }
-  {
-    constexpr size_t lds = 4 * 2 * kTileBytes;
-    TAW_SET_LDS_LIMIT_ONCE(attn_bwd_dq_kernel, lds);
-    const int nqt = (S + 255) / 256;
-    hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3((unsigned)(nqt * B * nh)), dim3(kThreads8), lds, st, (const bf16_t*)qkv, (const bf16_t*)dO, lse2, Dv,
-                       (bf16_t*)dqkv, B, S, Sp, nh, scale, rope_table);
-    return (int)hipGetLastError();
-  }
+  if (a.parts == 4) return launch_bwd_split<4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);
+  if (a.parts == 2) return launch_bwd_split<2>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);
+  return launch_bwd_split<1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);
 }
 
 }  // namespace taw

@@ -155,8 +155,8 @@ bool attn_mfma_supported(int dtype, int S, int nh, int d);
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st);
 // The MFMA backward exists in four forms.  STORED (the layer's default): a dK/dV kernel that forms S, dP and dS once and
 // also writes dS (bf16) to the scratch, and a dQ kernel that reads it back: 5 matrix products per tile pair, no atomics,
-// reproducible, about S * S bytes of scratch per (batch, head) (left alone where few tokens let one launch form everything at once).  SPLIT: the same pair with a dQ kernel that recomputes
-// S and dP instead (7 products), same bits, no dS in the scratch.  FUSED: one key-stationary kernel forms S and dP
+// reproducible, about S * S bytes of scratch per (batch, head) (left alone where few tokens let one launch form everything at once, as SPLIT does).
+// SPLIT: the same pair with a dQ kernel that recomputes S and dP instead (7 products), in workgroups of the same shape: same bits, no dS in the scratch.  FUSED: one key-stationary kernel forms S and dP
 // once and produces dK, dV and dQ (5 products); dQ partial sums go to private fp32 slots, one per worker, and a last
 // pass sums them: no atomics, reproducible.  FUSED_ATOMIC: the fused kernel adding dQ with fp32 atomics into one buffer.
 // S = 32768, 32 heads: 23.7 / 25.8 / 30.9 / 27.6 ms: the atomic units take 25.4 ms for the adds alone, the slots are 78 GB

@@ -651,3 +651,27 @@ def test_attn_mfma_parted_rows_far_scores(taw, S):
         oref, lref = O.attention_fwd_rows(q[:, h], k[:, h], v[:, h], np.arange(S))      # exp(-2^196) is 0, as exp(-inf)
         assert U.tensor_scale_err(got_o[:, h], oref) < U.TOL[I.BF16]
         assert np.max(np.abs(got_l[h] - lref)) < 2e-2
+
+
+@pytest.mark.parametrize("B,S,nh", [(1, 64, 1), (1, 600, 51), (1, 641, 3), (1, 1024, 16), (2, 700, 8), (1, 4161, 1),      # one grid, which recomputes in both forms
+                                    (1, 600, 52), (1, 1100, 15), (1, 4096, 5), (1, 1100, 29), (3, 1153, 11), (1, 700, 100), (2, 1301, 30)])   # stored by 128 rows, 4 and 2 parts, 256 rows
+@pytest.mark.parametrize("rotated", [False, True])
+def test_attn_bwd_stored_equals_recomputed(taw, B, S, nh, rotated):
+    """The default form and the pair that recomputes the scores form the same sums in the same order whatever shape the workgroups take: the same bits in dq, dk
+    and dv, over scratch of NaN."""
+    import torch
+    H = nh * 128
+    qkv, dO = I.device_normal((B * S, 3 * H), seed=S, std=1.0), I.device_normal((B * S, H), seed=nh, std=1.0)
+    table = None
+    if rotated:
+        table = torch.empty(S * 128, dtype=torch.float32, device="cuda")
+        taw.taw_rope_table_init(taw.make_desc(I.BF16, B, S, H, nh, 128, 8), table)
+    o, lse = torch.empty_like(dO), torch.empty(B * nh * S, dtype=torch.float32, device="cuda")
+    taw.taw_op_attn_fwd(I.BF16, B, S, nh, 128, qkv, o, lse, taw.TAW_IMPL_MFMA)
+    out = []
+    for form in (taw.TAW_IMPL_MFMA, taw.TAW_IMPL_MFMA_STORED):
+        dqkv = torch.full_like(qkv, float("nan"))
+        scratch = torch.full((taw.taw_op_attn_bwd_scratch_floats(B, S, nh),), float("nan"), dtype=torch.float32, device="cuda")
+        taw.taw_op_attn_bwd(I.BF16, B, S, nh, 128, qkv, o, dO, lse, dqkv, scratch, table, form)
+        out.append(dqkv)
+    assert torch.equal(*out)
