@@ -94,6 +94,15 @@ typedef struct {
 } taw_diag_gemm_plan_info;
 int taw_diag_gemm_plan(int32_t backward, int64_t M, int64_t N, int64_t K, int64_t ldc, int64_t ldr, taw_diag_gemm_plan_info* out);
 
+/* How the MFMA attention kernels share out a problem (bf16, heads of 128), on the host: workgroups of `rows` query rows (of the dK/dV
+ * kernel: keys), each row's sum in `parts` to as many wavefronts.
+ *   backward == 0   the forward; one_grid is 0
+ *   backward != 0   the default form and TAW_IMPL_MFMA; one_grid: both kernels in one launch, no dS stored */
+typedef struct {
+  int32_t rows, parts, one_grid;
+} taw_diag_attn_shape_info;
+int taw_diag_attn_shape(int32_t backward, int32_t B, int32_t S, int32_t n_heads, taw_diag_attn_shape_info* out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -49,6 +49,10 @@ class taw_diag_gemm_plan_info(C.Structure):
                 ("scratch_floats", C.c_int64), ("planned", C.c_int64)]
 
 
+class taw_diag_attn_shape_info(C.Structure):
+    _fields_ = [("rows", C.c_int32), ("parts", C.c_int32), ("one_grid", C.c_int32)]
+
+
 class taw_sched_desc(C.Structure):
     _fields_ = [("P", C.c_int32), ("D", C.c_int32), ("L", C.c_int32), ("N", C.c_int32)]
 
@@ -83,6 +87,7 @@ _SIGS = {
     "taw_diag_dq_update_rate": (C.c_int, [_vp, _i32, _i32, _i32, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     "taw_diag_gemm_tile_order": (C.c_int, [_i32, _i32, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "taw_diag_gemm_plan": (C.c_int, [_i32, _i64, _i64, _i64, _i64, _i64, C.POINTER(taw_diag_gemm_plan_info)]),
+    "taw_diag_attn_shape": (C.c_int, [_i32, _i32, _i32, _i32, C.POINTER(taw_diag_attn_shape_info)]),
     "taw_diag_issue_rate": (C.c_int, [_i32, _i32, _i32, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     "taw_diag_attn_ds_layout": (C.c_int, [_i32, C.POINTER(C.c_int64), C.POINTER(C.c_int64), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "taw_diag_store_cost_bytes": (C.c_size_t, []),
@@ -350,6 +355,13 @@ def taw_diag_gemm_plan(backward, M, N, K, ldc=0, ldr=0) -> dict:
     """What the MFMA GEMM launchers choose for C[M,N] = A[M,K] B[N,K]^T, or for the backward of the linear y[M,N] = x[M,K] W^T.  Host only."""
     out = taw_diag_gemm_plan_info()
     _check(load().taw_diag_gemm_plan(int(backward), M, N, K, ldc, ldr, C.byref(out)))
+    return {k: int(getattr(out, k)) for k, _ in out._fields_}
+
+
+def taw_diag_attn_shape(backward, B, S, n_heads) -> dict:
+    """How the MFMA attention forward (backward: the default form and TAW_IMPL_MFMA) shares out a problem.  Host only."""
+    out = taw_diag_attn_shape_info()
+    _check(load().taw_diag_attn_shape(int(backward), B, S, n_heads, C.byref(out)))
     return {k: int(getattr(out, k)) for k, _ in out._fields_}
 
 

@@ -358,7 +358,7 @@ __device__ __forceinline__ void store_share(const f32x4_t (&x)[N], float mul, bf
 
 // =============================================================================== forward
 // Workgroup: NW = 8 wavefronts (two per SIMD, so one's softmax arithmetic overlaps the other's MFMAs) or, where there are
-// few tiles (attn_shape), 4; one (batch, head, 32 NW / KS query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
+// few tiles (attn_fwd_shape), 4; one (batch, head, 32 NW / KS query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
 // through a 4-stage LDS ring of 64-key tiles filled by direct global->LDS loads issued three
 // tiles ahead; one workgroup barrier per tile.
 // KS > 1: KS wavefronts, w, w + 8 / KS, ..., own the same 32 rows, each with 32 keys of a tile (of 64; KS = 4: of 128, in 2 stages) and a maximum and
@@ -807,7 +807,7 @@ __global__ void __launch_bounds__(256) attn_bwd_prep_kernel(const bf16_t* __rest
 }
 
 // =============================================================================== backward: dK, dV
-// Workgroup: NW = 8 wavefronts (4 where attn_shape says so), one (batch, head, 32 NW / KS keys); wavefront w owns keys 32w..32w+31.
+// Workgroup: NW = 8 wavefronts (4 where attn_bwd_shape says so), one (batch, head, 32 NW / KS keys); wavefront w owns keys 32w..32w+31.
 // KS > 1: KS wavefronts own the same 32 keys, each with 32 rows of a block of query rows (of 64; KS = 4: of 128); their sums meet at the end.
 // Their V rows stay in registers as B operands; their K rows are read from a copy of the key tile in LDS (8 NW KiB), which leaves the
 // registers for both score accumulators at once and for reading fragments ahead of the MFMAs.  Query rows stream
@@ -1308,7 +1308,7 @@ attn_bwd_pair_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ 
 // dQ^T[d][q] += K^T[d][kv] dS^T[kv][q] with dS read back from what attn_bwd_dkv_kernel<true> wrote: one product per (query
 // block, key block) pair instead of three, paid for with S^2 bytes per (batch, head) written once and read once.  Same
 // workgroup shape as the kernel above (256 query rows, wavefront w owns the 32-row group w; 128 and 4 wavefronts, or KS wavefronts to a row group with
-// one of the 32-key units of a tile each, where attn_shape says so), keys in tiles of 64 through a
+// one of the 32-key units of a tile each, where attn_bwd_shape says so), keys in tiles of 64 through a
 // 3-stage ring filled by direct global->LDS loads two tiles ahead: the K tile [64][128], shared, and per wavefront the two
 // dS units (32 keys each) of its own row group, 4 KiB copied as they lie in memory (consecutive tiles are consecutive
 // there: eight sequential streams per workgroup).  Both operands are transposing reads: K^T as in the kernel above, dS^T
@@ -1808,36 +1808,61 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(f32x4_t* __restrict__ p, 
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (size_t)gridDim.x * 256) p[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
-// How the forward and the pair of backward kernels with stored dS share out the work: `rows` query rows (of the dK/dV kernel: keys) to a workgroup, 32 to
+// How the forward and the backward's kernels share out the work: `rows` query rows (of the dK/dV kernel: keys) to a workgroup, 32 to
 // a wavefront, and the sum over keys (query rows) in `parts` to as many wavefronts.  Bound, where every workgroup has a compute unit to itself, by the
 // serial chain of the longest one over its steps, and beyond that by what a compute unit gets through: 64 x 128 pairs of rows and keys take about what
 // 128 x 64 and half of what 256 x 64 take (forward 0.9, 0.9 and 1.6 us a step), but read twice and four times the keys per row, 1.4 us where every unit
-// does so.  us forward / backward with 256 rows, 128, 128 in 2 parts, 64 in 4 parts (n = 64-row, n8 = 256-row tiles of all (batch, head) pairs):
-//   n =  128  1024 tokens,  8 heads       29.7 / 70.2    22.8 / 52.4    22.0 / 47.8    15.0 / 33.2
-//   n =  512  1024 tokens, 32 heads       30.5 / 75.7    23.7 / 59.4    23.0 / 56.2    21.4 / 53.9
-//   n =  512  4096 tokens,  8 heads        103 / 259     77.4 / 191     69.0 / 170     50.5 / 129
-//   n =  544  1024 tokens, 34 heads       30.7 / 76.9    23.9 / 60.6    23.2 / 57.7    27.7 / 64.8
-//   n =  576  3 x 1501 tokens, 8 heads    42.5 / 107     32.6 / 82.7    30.4 / 77.7    33.8 / 81.7
-//   n =  640  4096 tokens, 10 heads        103 / 261     77.9 / 194     69.8 / 175     68.3 / 165
-//   n =  640  2048 tokens, 20 heads       54.8 / 140     42.0 / 107     38.8 / 98.3    42.7 / 102
-//   n =  768  16384 tokens, 3 heads        392 / 1003     292 / 762      257 / 685      281 / 711
-//   n8 = 192  1024 tokens, 48 heads       31.1 / 82.2    25.7 / 66.8    27.3 / 68.1    32.3 / 79.8
-//   n8 = 240  5 x 777 tokens, 12 heads    25.9 / 71.5    27.2 / 64.6    28.5 / 65.4    34.3 / 78.0
-//   n8 = 256  4096 tokens, 16 heads        104 / 293     86.0 / 238     80.6 / 223     96.9 / 253
-//   n8 = 288  2048 tokens, 36 heads       56.3 / 161     58.1 / 150     57.9 / 145     70.6 / 171;   8192, 9  204 / 574  191 / 520  174 / 476  193 / 516
-//   n8 = 384  2048 tokens, 48 heads       58.4 / 176     76.0 / 200     73.3 / 193     91.0 / 221
+// does so; dQ, with the least work per key read, feels that first.  The backward can also go in one grid (below), the forward cannot: a line for each.
+// n, n4, n8: tiles of 64, 128 and 256 rows of all (batch, head) pairs.
 // Up to 640 tokens a row's sums are never parted: its results are then the same bits whatever else is in the batch (128 rows, 4 wavefronts, and 256, 8,
-// do the same arithmetic in the same order).  There the finer tiles gain from the finer causal triangle, which one or two tiles per pair don't have:
-//   n8 = 256  8 x 200 tokens, 32 heads    15.5 / 39.4    18.2 / 44.6;   n8 = 8  2 x 333 tokens, 2 heads  13.5 / 32.3    10.8 / 25.5
+// do the same arithmetic in the same order).  There the finer tiles gain from the finer causal triangle, which one or two tiles per pair don't have
+// (us forward / backward with 256 rows -> 128):
+//   n8 = 256  8 x 200 tokens, 32 heads  15.5 / 39.4 -> 18.2 / 44.6;   n8 = 8  2 x 333 tokens, 2 heads  13.5 / 32.3 -> 10.8 / 25.5
 struct AttnShape {
   int rows, parts;
 };
-AttnShape attn_shape(int B, int S, int nh) {
-  const int64_t pairs = (int64_t)B * nh, n8 = ((int64_t)S + 255) / 256 * pairs, n4 = ((int64_t)S + 127) / 128 * pairs, n = ((int64_t)S + 63) / 64 * pairs;
-  if (S <= 640) return {n4 <= 256 || (n8 <= 256 && S > 512) ? 128 : 256, 1};
-  if (n <= 512 || (n <= 640 && S >= 4096)) return {64, 4};
-  if (n8 <= 288 && S > 1024) return {128, 2};
-  return {n8 <= 256 ? 128 : 256, 1};
+struct AttnTiles {
+  int64_t pairs, n, n4, n8;
+  AttnTiles(int B, int S, int nh) : pairs((int64_t)B * nh), n(((int64_t)S + 63) / 64 * pairs), n4(((int64_t)S + 127) / 128 * pairs), n8(((int64_t)S + 255) / 256 * pairs) {}
+  AttnShape whole_rows(int S) const { return {n4 <= 256 || (n8 <= 256 && S > 512) ? 128 : 256, 1}; }
+};
+
+// us of the forward inside the layer with 256 rows, 128, 128 in 2 parts, 64 in 4 parts:
+//   n  = 352  2 x 704 tokens, 16 heads    24.5   19.2   19.5   18.7        n  = 440  4 x 704 tokens, 10 heads    24.6   19.5   19.4   21.2
+//   n  = 416  2 x 1024 tokens, 13 heads   32.3   25.6   25.0   23.9        n  = 512  2 x 1024 tokens, 16 heads   32.4   25.6   25.5   26.7
+//   n  = 400  2 x 1280 tokens, 10 heads   37.2   29.1   27.8   25.0        n  = 480  2 x 1280 tokens, 12 heads   38.1   29.7   28.6   29.0
+//   n  = 512  4096 tokens, 8 heads        103    78.6   70.6   65.7        n  = 640  4096 tokens, 10 heads       104    79.5   71.8   78.0
+//   n4 = 324  4 x 1100 tokens, 9 heads    37.0   29.4   28.5   36.9        n4 = 360  4 x 1100 tokens, 10 heads   38.0   30.1   31.6   39.7
+//   n4 = 352  2 x 1400 tokens, 16 heads   43.9   34.6   33.7   41.6        n4 = 440  4 x 1400 tokens, 10 heads   45.8   40.1   41.0   53.4
+//   n8 = 224  2 x 1700 tokens, 16 heads   52.3   43.9   43.1   54.0        n8 = 256  4096 tokens, 16 heads       115    96.8   90.5   110
+//   n8 = 288  4 x 1501 tokens, 12 heads   48.8   53.7   54.7   68.9        n8 = 288  3 x 2048 tokens, 12 heads   63.0   63.4   62.6   81.5
+//   n8 = 288  8192 tokens, 9 heads        214    202    185    215         n8 = 280  5 x 1792 tokens, 8 heads    57.0   61.3   62.5   77.1
+AttnShape attn_fwd_shape(int B, int S, int nh) {
+  const AttnTiles t(B, S, nh);
+  if (S <= 640) return t.whole_rows(S);
+  if (t.n <= 512 && t.n <= 256 + S / 6) return {64, 4};
+  if (S > 1024 && t.n8 <= (S >= 2048 ? 288 : 256) && (S >= 1600 || t.n4 <= 256 + S / 12)) return {128, 2};
+  return t.whole_rows(S);
+}
+
+// us of the backward's two kernels inside the layer with 256 rows, 128 (* in one grid), 128 in 2 parts, 64 in 4 parts:
+//   n  = 264  2 x 704 tokens, 12 heads    58.4   31.7*  40.7   32.6        n  = 440  4 x 704 tokens, 10 heads    60.0   41.0*  44.1   44.7
+//   n  = 320  2 x 1024 tokens, 10 heads   76.7   41.3*  52.5   40.7        n  = 384  2 x 1024 tokens, 12 heads   77.9   41.6*  54.0   46.8
+//   n  = 512  2 x 1024 tokens, 16 heads   80.8   53.6*  57.7   58.5        n  = 480  2 x 1280 tokens, 12 heads   95.0   59.4*  66.0   60.3
+//   n  = 320  2 x 1280 tokens, 8 heads    91.4   48.6*  61.5   42.7        n  = 400  2 x 1280 tokens, 10 heads   92.1   51.6*  63.3   53.4
+//   n  = 480  2 x 1536 tokens, 10 heads   110    69.4*  75.5   67.9        n  = 512  4096 tokens, 8 heads        262    156*   169    123
+//   n  = 640  4096 tokens, 10 heads       263    194    171    166         n  = 640  2 x 2048 tokens, 10 heads   142    106    96.9   104
+//   n4 = 276  2 x 704 tokens, 23 heads    62.3   48.8   48.4   50.2        n8 = 195  3 x 1056 tokens, 13 heads   90.6   71.6   68.7   83.1
+//   n8 = 288  4 x 1400 tokens, 12 heads   130    123    125    147         n8 = 288  4 x 1501 tokens, 12 heads   129    135    131    157
+//   n8 = 288  4 x 1536 tokens, 12 heads   140    146    143    162         n8 = 280  2 x 1700 tokens, 20 heads   152    147    141    169
+//   n8 = 280  5 x 1792 tokens, 8 heads    155    153    154    175         n8 = 288  3 x 2048 tokens, 12 heads   166    161    152    186
+// (just above 256 tiles of 256 rows it matters how full the last one of a pair is: the tokens of all pairs decide, in 256s)
+AttnShape attn_bwd_shape(int B, int S, int nh) {
+  const AttnTiles t(B, S, nh);
+  if (S <= 640) return t.whole_rows(S);
+  if (t.n <= (S >= 4096 ? 640 : S >= 1536 ? 512 : 256 + (S - 640) / 6)) return {64, 4};
+  if (S > 1024 && t.n4 > 256 && t.n8 <= 288 && (S >= 2048 || S * t.pairs <= 272 * 256)) return {128, 2};
+  return t.whole_rows(S);
 }
 
 // Whether the backward (the default form and the recomputing pair) runs as one grid of both kernels, dQ forming the scores again (attn_bwd_pair_kernel), instead of storing dS: as
@@ -1919,10 +1944,15 @@ bool attn_mfma_supported(int dtype, int S, int nh, int d) {
 }
 
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st) {
-  const AttnShape a = attn_shape(B, S, nh);
+  const AttnShape a = attn_fwd_shape(B, S, nh);
   if (a.parts == 4) return launch_fwd<kWaves8, 4>(B, S, nh, qkv, o, lse, st);
   if (a.parts == 2) return launch_fwd<kWaves8, 2>(B, S, nh, qkv, o, lse, st);
   return a.rows == 128 ? launch_fwd<4, 1>(B, S, nh, qkv, o, lse, st) : launch_fwd<kWaves8, 1>(B, S, nh, qkv, o, lse, st);
+}
+
+AttnShapeInfo attn_shape_info(bool backward, int B, int S, int nh) {
+  const AttnShape a = backward ? attn_bwd_shape(B, S, nh) : attn_fwd_shape(B, S, nh);
+  return AttnShapeInfo{a.rows, a.parts, backward && attn_bwd_in_one_grid(a, B, S, nh)};
 }
 
 // Workers per (batch, head) for the slot form: as many as fill the 256 compute units in whole rounds, preferring few (every
@@ -1999,7 +2029,7 @@ int launch_attn_bwd_mfma(int B, int S, int nh, const void* qkv, const void* o, c
     return (int)hipGetLastError();
   }
   // the default form and the recomputing pair: the same shapes, so the same sums in the same order
-  const AttnShape a = attn_shape(B, S, nh);
+  const AttnShape a = attn_bwd_shape(B, S, nh);
   if (attn_bwd_in_one_grid(a, B, S, nh))
     return a.parts == 4 ? launch_bwd_pair<kWaves8, 4>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st)
                         : launch_bwd_pair<4, 1>(B, S, Sp, nh, qkv, dO, lse2, Dv, dqkv, rope_table, st);

@@ -483,6 +483,14 @@ extern "C" int taw_diag_gemm_plan(int32_t backward, int64_t M, int64_t N, int64_
   return TAW_OK;
 }
 
+extern "C" int taw_diag_attn_shape(int32_t backward, int32_t B, int32_t S, int32_t n_heads, taw_diag_attn_shape_info* out) {
+  if (B < 1 || n_heads < 1 || !taw::attn_mfma_supported(taw::DT_BF16, S, n_heads, 128)) return TAW_ERR_SHAPE;
+  if (!out) return TAW_ERR_NULL;
+  const taw::AttnShapeInfo a = taw::attn_shape_info(backward != 0, B, S, n_heads);
+  *out = taw_diag_attn_shape_info{a.rows, a.parts, a.one_grid};
+  return TAW_OK;
+}
+
 extern "C" int taw_diag_attn_ds_layout(int32_t S, int64_t* pair_bytes, int64_t* unit_offsets, int32_t* slots, int32_t* rows) {
   if (S < 1 || S > (1 << 20)) return TAW_ERR_SHAPE;
   if (!pair_bytes || !unit_offsets || !slots || !rows) return TAW_ERR_NULL;

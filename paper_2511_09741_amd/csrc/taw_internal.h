@@ -152,6 +152,12 @@ bool gemm_mfma_swiglu_supported(int64_t M, int64_t half, int64_t K, int64_t lda,
 int launch_gemm_mfma_nt_swiglu(int64_t M, int64_t half, int64_t K, const void* A, int64_t lda, const void* W, int64_t ldw, void* gu, void* act, hipStream_t st);
 // bf16, head_dim 128, and S * 3 * n_heads * head_dim * 2 bytes below 4 GiB (32-bit row offsets inside one batch element)
 bool attn_mfma_supported(int dtype, int S, int nh, int d);
+// how the forward, and the default and the recomputing form of the backward, share out the work
+struct AttnShapeInfo {
+  int rows, parts;
+  bool one_grid;
+};
+AttnShapeInfo attn_shape_info(bool backward, int B, int S, int nh);
 int launch_attn_fwd_mfma(int B, int S, int nh, const void* qkv, void* o, float* lse, hipStream_t st);
 // The MFMA backward exists in four forms.  STORED (the layer's default): a dK/dV kernel that forms S, dP and dS once and
 // also writes dS (bf16) to the scratch, and a dQ kernel that reads it back: 5 matrix products per tile pair, no atomics,

@@ -31,7 +31,7 @@ def declared_functions():
 
 def test_every_declared_symbol_is_exported(lib):
     names = declared_functions()
-    assert len(names) == 39
+    assert len(names) == 40
     for n in names:
         assert hasattr(lib, n), f"{n} declared in include/ but not exported"
     assert set(names) == set(taw.EXPORTS)
@@ -281,6 +281,30 @@ def test_gemm_plans(lib, T, N, K):
     with pytest.raises(taw.TawError) as e:
         taw.taw_diag_gemm_plan(0, T, 0, K)
     assert e.value.status == taw.TAW_ERR_SHAPE
+
+
+def test_attn_shapes(lib):
+    """A row's sum is parted by wavefronts in shapes that exist, never up to 640 tokens; the backward is one grid only where its tiles fit the chip.  The named
+    calls are the ones where one shape for all three kernels made the forward or dQ slower than unparted rows: they take those, and the backward of the
+    first three one grid of 128 rows."""
+    shape = lambda backward, B, S, nh: tuple(taw.taw_diag_attn_shape(backward, B, S, nh).values())
+    for pairs in (1, 2, 3, 7, 8, 16, 23, 33, 48, 100, 300, 1000):
+        for S in (1, 63, 64, 333, 512, 513, 640, 641, 704, 1000, 1024, 1025, 1100, 1501, 1600, 2048, 2305, 4096, 4161, 8192, 32768):
+            for backward in (0, 1):
+                rows, parts, one_grid = shape(backward, pairs, S, 1)
+                assert (rows, parts) in ({(256, 1), (128, 1)} if S <= 640 else {(256, 1), (128, 1), (128, 2), (64, 4)})
+                if S * 3 * pairs * 256 < 1 << 32:      # the 32-bit offsets inside one batch element
+                    assert shape(backward, 1, S, pairs) == (rows, parts, one_grid)
+                tiles = -(-S // rows) * pairs
+                assert one_grid == (backward and tiles <= 256 and (rows, parts) in {(128, 1), (64, 4)})
+                assert parts == 1 or tiles <= 640
+    for B, S, nh in ((1, 1024, 32), (4, 704, 10), (3, 768, 14)):
+        assert shape(0, B, S, nh) == (128, 1, 0) and shape(1, B, S, nh) == (128, 1, 1)
+    assert shape(0, 4, 1501, 12) == shape(1, 4, 1501, 12) == (256, 1, 0) and shape(0, 4, 1100, 12) == (128, 1, 0) and shape(1, 2, 704, 23) == (128, 1, 0)
+    for args in ((0, 64, 1), (1, 0, 1), (1, 64, 0), (1, 1 << 20, 8)):
+        with pytest.raises(taw.TawError) as e:
+            taw.taw_diag_attn_shape(0, *args)
+        assert e.value.status == taw.TAW_ERR_SHAPE
 
 
 def test_gemm_plans_are_worked_out_once(lib):

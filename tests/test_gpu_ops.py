@@ -156,7 +156,7 @@ def test_swiglu_fwd_bwd(taw, dtype, T, I_):
     assert U.tensor_scale_err(U.from_dev(dgu), np.concatenate([dg, du], axis=1)) < tol
 
 
-def _attn_case(taw, dtype, B, S, nh, d, impl, seed=0, scale=1.0, bwd_impl=None):
+def _attn_case(taw, dtype, B, S, nh, d, impl, seed=0, scale=1.0, bwd_impl=None, rotated=False):
     import torch
     rng = np.random.default_rng(seed)
     H = nh * d
@@ -183,8 +183,15 @@ def _attn_case(taw, dtype, B, S, nh, d, impl, seed=0, scale=1.0, bwd_impl=None):
     dref = np.concatenate([dq.reshape(B * S, H), dk.reshape(B * S, H), dv.reshape(B * S, H)], axis=1)
     lse_ref32 = torch.from_numpy(lref.astype(np.float32).reshape(-1)).cuda()
     dqkv = U.empty_dev((B * S, 3 * H), dtype)
-    scratch = torch.empty(taw.taw_op_attn_bwd_scratch_floats(B, S, nh), dtype=torch.float32, device="cuda")
-    taw.taw_op_attn_bwd(dtype, B, S, nh, d, qkvd, U.to_dev(o_st, dtype), U.to_dev(dO, dtype), lse_ref32, dqkv, scratch, None, impl if bwd_impl is None else bwd_impl)
+    scratch = torch.full((taw.taw_op_attn_bwd_scratch_floats(B, S, nh),), float("nan"), dtype=torch.float32, device="cuda")
+    table = None
+    if rotated:                                        # the gradients of q, k before their rotation
+        table = torch.empty(S * d, dtype=torch.float32, device="cuda")
+        taw.taw_rope_table_init(taw.make_desc(dtype, B, S, H, nh, d, 8), table)
+        phi = O.rope_angles(S, d, 10000.0)
+        for i, z in enumerate((dq, dk)):
+            dref[:, i * H:(i + 1) * H] = O.rope_apply(z, phi, inverse=True).reshape(B * S, H)
+    taw.taw_op_attn_bwd(dtype, B, S, nh, d, qkvd, U.to_dev(o_st, dtype), U.to_dev(dO, dtype), lse_ref32, dqkv, scratch, table, impl if bwd_impl is None else bwd_impl)
     got = U.from_dev(dqkv)
     # at S = 1 the exact dq and dk are identically zero: measure them on the scale of dv
     fl = 1e-3 * float(np.max(np.abs(dref[:, 2 * H:])))
@@ -382,26 +389,29 @@ def test_attention_mfma_maximum_raised_by_one_quarter(taw, B, quarter, rise):
     assert float((lse.double() - torch.logsumexp(scores, -1)).abs().max()) <= 2.0 ** -8
 
 
-@pytest.mark.parametrize("form", ["fused", "stored"])
-def test_attention_backward_forms_without_atomics_are_reproducible(taw, form):
+@pytest.mark.parametrize("form,B,S,nh,shape", [("fused", 2, 1500, 3, None), ("stored", 2, 1500, 3, (64, 4, 1)),      # one grid: nothing stored
+                                               ("stored", 1, 1100, 15, (64, 4, 0)), ("stored", 1, 1100, 29, (128, 2, 0)), ("stored", 1, 600, 52, (128, 1, 0)),
+                                               ("stored", 2, 700, 45, (256, 1, 0))])
+def test_attention_backward_forms_without_atomics_are_reproducible(taw, form, B, S, nh, shape):
     """The fused backward with slots adds its dQ partial sums in a fixed order, and the form with stored dS reads back only
-    what it wrote: two runs over scratch with different stale contents give the same bits."""
+    what it wrote: runs over scratch with different stale contents give the same bits."""
     import torch
-    B, S, nh, d = 2, 1500, 3, 128
+    d = 128
     H = nh * d
+    assert shape is None or tuple(taw.taw_diag_attn_shape(1, B, S, nh).values()) == shape
     qkv = I.device_normal((B * S, 3 * H), seed=5, std=0.7)
     dO = I.device_normal((B * S, H), seed=6, std=1.0)
     o = torch.empty((B * S, H), dtype=torch.bfloat16, device="cuda")
     lse = torch.empty(B * nh * S, dtype=torch.float32, device="cuda")
     taw.taw_op_attn_fwd(I.BF16, B, S, nh, d, qkv, o, lse, taw.TAW_IMPL_MFMA)
     outs = []
-    for fill in (0.0, 1e30):
+    for fill in (0.0, 1e30, float("nan")):
         scratch = torch.full((taw.taw_op_attn_bwd_scratch_floats(B, S, nh),), fill, dtype=torch.float32, device="cuda")   # stale contents must not matter
-        dqkv = torch.empty_like(qkv)
+        dqkv = torch.full_like(qkv, fill)
         taw.taw_op_attn_bwd(I.BF16, B, S, nh, d, qkv, o, dO, lse, dqkv, scratch, None, BWD_FORMS[form])
         torch.cuda.synchronize()
         outs.append(dqkv)
-    assert torch.equal(outs[0], outs[1])
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
 
 
 @pytest.mark.parametrize("dtype", [I.F32, I.BF16])
@@ -618,21 +628,30 @@ def test_attn_mfma_pairs_that_the_xcds_do_not_divide(taw, B, S, nh):
     _attn_case(taw, I.BF16, B, S, nh, 128, taw.TAW_IMPL_MFMA, seed=S, bwd_impl=taw.TAW_IMPL_MFMA_STORED)
 
 
-@pytest.mark.parametrize("B,S,nh", [(1, 641, 3), (1, 704, 1), (2, 705, 1), (1, 767, 2), (1, 897, 1), (1, 1000, 9), (1, 4096, 1), (1, 4161, 1),      # 64 rows, 4 parts
-                                    (3, 1025, 11), (1, 1100, 29), (1, 1153, 28),                                                                 # 128 rows, 2 parts
-                                    (1, 1100, 14), (1, 1100, 15), (1, 641, 23), (1, 600, 51), (1, 600, 52)])      # 252 and 270 tiles: dQ in dK/dV's grid, or from stored dS
-def test_attn_mfma_parted_rows(taw, B, S, nh):
+# shapes of the workgroups (rows, parts of a row's sum) and of the backward (both kernels in one grid, nothing stored): all that there are
+F256, F128, F128P, F64P = (256, 1, 0), (128, 1, 0), (128, 2, 0), (64, 4, 0)
+PAIR128, PAIR64P, ST256, ST128, ST128P, ST64P = (128, 1, 1), (64, 4, 1), (256, 1, 0), (128, 1, 0), (128, 2, 0), (64, 4, 0)
+
+
+@pytest.mark.parametrize("B,S,nh,fwd,bwd", [(1, 641, 3, F64P, PAIR64P), (1, 704, 1, F64P, PAIR64P), (2, 705, 1, F64P, PAIR64P), (1, 767, 2, F64P, PAIR64P), (1, 897, 1, F64P, PAIR64P),
+                                            (1, 1000, 9, F64P, PAIR64P), (1, 4096, 1, F64P, PAIR64P), (1, 4161, 1, F64P, PAIR64P), (1, 1100, 14, F64P, PAIR64P),
+                                            (1, 641, 23, F64P, PAIR64P), (1, 1100, 15, F64P, ST64P), (3, 1025, 11, F128P, ST128P), (1, 1100, 29, F128P, ST128P),
+                                            (1, 1153, 28, F128P, ST128P), (1, 1100, 48, F128, ST128P), (1, 1024, 24, F64P, PAIR128), (1, 600, 51, F128, PAIR128),
+                                            (1, 600, 52, F128, ST128), (2, 704, 23, F128, ST128), (2, 700, 45, F256, ST256)], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+@pytest.mark.parametrize("rotated", [False, True])
+def test_attn_mfma_parted_rows(taw, B, S, nh, fwd, bwd, rotated):
     """Where there are few tiles several wavefronts share a row (a key): every row at the ends of tiles of 64 and 128, with parts that hold no key a row
-    sees, and head counts that the 8 XCDs do not divide."""
-    _attn_case(taw, I.BF16, B, S, nh, 128, taw.TAW_IMPL_MFMA, seed=S, bwd_impl=taw.TAW_IMPL_MFMA_STORED)
+    sees, and head counts that the 8 XCDs do not divide; whole rows beyond 640 tokens; the rotary backward inside each."""
+    assert tuple(taw.taw_diag_attn_shape(0, B, S, nh).values()) == fwd and tuple(taw.taw_diag_attn_shape(1, B, S, nh).values()) == bwd
+    _attn_case(taw, I.BF16, B, S, nh, 128, taw.TAW_IMPL_MFMA, seed=S, bwd_impl=taw.TAW_IMPL_MFMA_STORED, rotated=rotated)
 
 
-@pytest.mark.parametrize("S", [700, 1088])
-def test_attn_mfma_parted_rows_far_scores(taw, S):
+@pytest.mark.parametrize("S,nh,shape", [(700, 2, F64P), (1088, 2, F64P), (1100, 29, F128P)], ids=["700", "1088", "1100-2parts"])
+def test_attn_mfma_parted_rows_far_scores(taw, S, nh, shape):
     """One part of a row's keys far above or below the others, -inf among its scores: what the parts are scaled by when they meet is the row's maximum.
     Head 0: the keys of every second block of 32 score about +-300; head 1: they overflow to -inf for the later half of the rows."""
     import torch
-    nh = 2
+    assert tuple(taw.taw_diag_attn_shape(0, 1, S, nh).values()) == shape
     H = nh * 128
     rng = np.random.default_rng(S)
     qkv, _ = draw(rng, (S, 3 * H), I.BF16)
@@ -647,18 +666,20 @@ def test_attn_mfma_parted_rows_far_scores(taw, S):
     o, lse = U.empty_dev((S, H), I.BF16), torch.empty(nh * S, dtype=torch.float32, device="cuda")
     taw.taw_op_attn_fwd(I.BF16, 1, S, nh, 128, U.to_dev(qkv, I.BF16), o, lse, taw.TAW_IMPL_MFMA)
     got_o, got_l = U.from_dev(o).reshape(S, nh, 128), U.from_dev(lse).reshape(nh, S)
-    for h in range(nh):
+    for h in range(2):
         oref, lref = O.attention_fwd_rows(q[:, h], k[:, h], v[:, h], np.arange(S))      # exp(-2^196) is 0, as exp(-inf)
         assert U.tensor_scale_err(got_o[:, h], oref) < U.TOL[I.BF16]
         assert np.max(np.abs(got_l[h] - lref)) < 2e-2
 
 
-@pytest.mark.parametrize("B,S,nh", [(1, 64, 1), (1, 600, 51), (1, 641, 3), (1, 1024, 16), (2, 700, 8), (1, 4161, 1),      # one grid, which recomputes in both forms
-                                    (1, 600, 52), (1, 1100, 15), (1, 4096, 5), (1, 1100, 29), (3, 1153, 11), (1, 700, 100), (2, 1301, 30)])   # stored by 128 rows, 4 and 2 parts, 256 rows
+@pytest.mark.parametrize("B,S,nh,shape", [(1, 64, 1, PAIR128), (1, 600, 51, PAIR128), (1, 1024, 24, PAIR128), (1, 641, 3, PAIR64P), (1, 1024, 16, PAIR64P), (2, 700, 8, PAIR64P),
+                                          (1, 4161, 1, PAIR64P), (1, 600, 52, ST128), (1, 1100, 15, ST64P), (1, 4096, 5, ST64P), (1, 1100, 29, ST128P),
+                                          (3, 1153, 11, ST128P), (1, 700, 100, ST256), (2, 1301, 30, ST256)], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 @pytest.mark.parametrize("rotated", [False, True])
-def test_attn_bwd_stored_equals_recomputed(taw, B, S, nh, rotated):
+def test_attn_bwd_stored_equals_recomputed(taw, B, S, nh, shape, rotated):
     """The default form and the pair that recomputes the scores form the same sums in the same order whatever shape the workgroups take: the same bits in dq, dk
     and dv, over scratch of NaN."""
+    assert tuple(taw.taw_diag_attn_shape(1, B, S, nh).values()) == shape
     import torch
     H = nh * 128
     qkv, dO = I.device_normal((B * S, 3 * H), seed=S, std=1.0), I.device_normal((B * S, H), seed=nh, std=1.0)
