@@ -1525,9 +1525,10 @@ GemmPlanInfo gemm_plan_info(bool backward, int64_t M, int64_t N, int64_t K, int6
   return GemmPlanInfo{p.tile == 192 ? 128 : p.tile, p.tile == 192 ? 256 : p.tile, p.nst, {p.splits[0], p.splits[1]}, p.part_floats, g_plans.planned};
 }
 
-// The product goes to 256 x 256 tiles, uncut, that take whole blocks of 128 gate columns; 32-bit offsets reach from a gate row of W to its up row
+// The product goes to 256 x 256 tiles, uncut, that take whole blocks of 128 gate columns; 32-bit offsets reach from a tile's
+// first gate row of W to its last up row, half + 127 further
 bool gemm_mfma_swiglu_supported(int64_t M, int64_t half, int64_t K, int64_t lda, int64_t ldb, size_t floats) {
-  if (half % 128 != 0 || half * ldb >= ((int64_t)1 << 31) - ((int64_t)1 << 23) || !gemm_mfma_supported(DT_BF16, GEMM_NT, M, 2 * half, K, lda, ldb, 2 * half, DT_BF16, 0)) return false;
+  if (half % 128 != 0 || (half + 128) * ldb >= ((int64_t)1 << 31) || !gemm_mfma_supported(DT_BF16, GEMM_NT, M, 2 * half, K, lda, ldb, 2 * half, DT_BF16, 0)) return false;
   const GemmPlan p = plan_gemm(M, 2 * half, K, nt_scratch_limit(2 * half, 2 * half, 0, floats));
   return p.tile == 256 && p.splits[0] == 1;
 }

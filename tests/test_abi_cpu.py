@@ -283,6 +283,21 @@ def test_gemm_plans(lib, T, N, K):
     assert e.value.status == taw.TAW_ERR_SHAPE
 
 
+def test_gate_up_pairs_within_32_bit_offsets(lib):
+    """A tile of the gate/up product with SwiGLU inside reaches from its first gate row of W to 64 + 63 rows behind the same up row, in bytes that have
+    to fit 32 bits, to the end of a 128-byte row segment."""
+    supported = lib._ZN3taw26gemm_mfma_swiglu_supportedElllllm       # (rows, I, K, row strides of the operands, floats of scratch)
+    supported.argtypes, supported.restype = [C.c_int64] * 5 + [C.c_size_t], C.c_bool
+    taken = 0
+    for ld in (1024, 8192, 22016, 65536, 66048, 99968, 131072, 200064, 262144, 1 << 20, 1 << 22):
+        edge = (1 << 31) // ld // 128 * 128
+        for half in {128, 2816, edge - 256, edge - 128, edge, edge + 128} - {0, -128, -256}:
+            ok = supported(65536, half, ld, ld, ld, 0)
+            assert not ok or (half + 127) * ld * 2 + 128 <= 1 << 32, (half, ld)
+            taken += ok
+    assert taken > 8 and supported(65536, 2816, 1024, 1024, 1024, 0) and supported(16384, 22016, 8192, 8192, 8192, 0)
+
+
 def test_attn_shapes(lib):
     """A row's sum is parted by wavefronts in shapes that exist, never up to 640 tokens; the backward is one grid only where its tiles fit the chip.  The named
     calls are the ones where one shape for all three kernels made the forward or dQ slower than unparted rows: they take those, and the backward of the
