@@ -63,7 +63,8 @@ typedef enum { TAW_F32 = 0, TAW_BF16 = 1 } taw_dtype;
 /* Forms of the attention backward on the matrix-core path.  Default: a dK/dV kernel that forms the scores once and also
    writes dS (bf16) to the workspace, and a dQ kernel that reads it back: five matrix products per tile pair, no atomics,
    reproducible; the workspace holds about S*S bytes per (batch, head) for it (35 GB at S = 32768 with 32 heads).  With so
-   few tokens that the chip has room for both kernels at once, one launch recomputes the scores instead (seven products). */
+   few tokens that the chip has room for both kernels at once, one launch recomputes the scores instead (seven products)
+   and leaves that part of the workspace, which is asked for at every size, alone. */
 #define TAW_ATTN_BWD_FUSED 4u /* one kernel that forms the scores once and keeps dQ partial sums in private fp32 slots
                                  (the workspace holds those slots instead of dS) */
 #define TAW_ATTN_BWD_RECOMPUTE 8u /* the pair of kernels with a dQ kernel that recomputes the scores (seven products):
@@ -117,7 +118,9 @@ int taw_rope_table_init(const taw_layer_desc* desc, float* rope_table, void* str
  *   x, y        [B, S, H] desc->dtype; y must not alias x
  *   ctx         taw_layer_ctx_bytes() bytes, written here, to be passed unchanged to taw_layer_bwd
  *   workspace   >= taw_layer_workspace_bytes() bytes of scratch (TAW_ERR_WORKSPACE otherwise)
- * bf16 layers compute with fp32 accumulation and store activations in bf16. */
+ * bf16 layers compute with fp32 accumulation and store activations in bf16.  A call repeated gives the same bits; in which
+ * order fp32 sums are taken (the products' from few tokens on, the attention's beyond 640 positions) is chosen from the
+ * descriptor's sizes, so a sequence in a larger or smaller batch may differ by such an order.  The same holds for the backward. */
 int taw_layer_fwd(const taw_layer_desc* desc, const void* W_chunk, const float* rope_table,
                   const void* x, void* y, void* ctx, void* workspace, size_t workspace_bytes,
                   void* stream);

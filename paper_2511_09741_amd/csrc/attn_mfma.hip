@@ -359,9 +359,9 @@ __device__ __forceinline__ void store_share(const f32x4_t (&x)[N], float mul, bf
 // =============================================================================== forward
 // Workgroup: NW = 8 wavefronts (two per SIMD, so one's softmax arithmetic overlaps the other's MFMAs) or, where there are
 // few tiles (attn_fwd_shape), 4; one (batch, head, 32 NW / KS query rows); wavefront w owns rows 32w .. 32w+31.  Keys/values stream
-// through a 4-stage LDS ring of 64-key tiles filled by direct global->LDS loads issued three
-// tiles ahead; one workgroup barrier per tile.
-// KS > 1: KS wavefronts, w, w + 8 / KS, ..., own the same 32 rows, each with 32 keys of a tile (of 64; KS = 4: of 128, in 2 stages) and a maximum and
+// through a 4-stage LDS ring of 64-key tiles filled by direct global->LDS loads issued two
+// tiles ahead (the late wavefronts below still read V of the tile before); one workgroup barrier per tile.
+// KS > 1: KS wavefronts, w, w + 8 / KS, ..., own the same 32 rows, each with 32 keys of a tile (of 64; KS = 4: of 128, in 2 stages, one ahead) and a maximum and
 // sums of its own, which meet at the end.
 //
 // Online softmax in the exp2 domain.  The running maximum of a row is only raised when a tile

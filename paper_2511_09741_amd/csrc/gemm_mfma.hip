@@ -454,7 +454,9 @@ __device__ __forceinline__ void store_tile_swiglu(const f32x4_t (&acc)[8][8], un
         __builtin_nontemporal_store(u, reinterpret_cast<bf16x8_t*>(cr + half + coff));
       }
       // 1 / (1 + exp(-g)) by the reciprocal instruction and a Newton step: 5 instructions where the division takes 10, between stores and products (forward of
-      // 65536 tokens at H = 1024 2124 us with the division, 2090 without).  The same bits while the result is no denormal number, which is asked.
+      // 65536 tokens at H = 1024 2124 us with the division, 2090 without).  The same bits while the result is no denormal number, which is asked: no property
+      // of the method (a reciprocal off by one in its last place can end beside the rounded quotient), but what this part's instruction gives: of all
+      // 1055964611 floats in [1, 8e37] none differs from the division (of the bare reciprocals 113040621 do).
       float d[8], dmax = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -1336,10 +1338,12 @@ struct GemmPlan {
 // What a tile shape costs, in microseconds: a fixed part per workgroup, more where it stores fp32 (weight gradients and partial products), and per 64-deep
 // step the larger of `lone` (one workgroup on a compute unit: the latency of its loads) and `busy` x the workgroups that share the unit (`resident` at most).
 // Fitted for the time of what it picks first, over timings of the five shapes and their cuts for 945 products and backwards (64 ... 65536 rows, layers 256 ... 8192
-// wide), each on as much memory in turn as its layer touches (weights that a small layer leaves in the caches and a wide one does not), among the costs
-// that keep every shape and cut in use where the tests look for it.  The pick is 2.7 % slower than the fastest (products 0.9 %, pairs 3.6 %; without that
-// condition 1.8 %), with the costs of before, fitted on warm caches with one fixed part for both types, 3.9 % (1.7, 5.0).
-// 256 x 256 tiles alone are up to 7 times slower.
+// wide), each in a loop of its own on as much memory in turn as its layer touches (weights that a small layer leaves in the caches and a wide one does not),
+// among the costs that keep every shape and cut in use where the tests look for it.  The pick is 2.7 % slower than the fastest (products 0.9 %, pairs 3.6 %;
+// without that condition 1.8 %), with the costs of before, fitted on warm caches with one fixed part for both types, 3.9 % (1.7, 5.0); against their pick one in
+// ten is more than 3 % faster and one in forty as much slower (666 x 1024 x 2816 backward into the shard 18.2 -> 21.0 us is the worst).
+// They rank, they don't predict: what a tile does beside the product is not in them, and inside a layer call a product takes 1.2 - 1.7 times its cost, most
+// where it rotates or forms SwiGLU.  256 x 256 tiles alone are up to 7 times slower.
 struct TileCost {
   int tile, tm, tn, nst, resident;
   double fixed_bf16, fixed_f32, lone, busy;
