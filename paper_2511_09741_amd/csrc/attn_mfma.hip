@@ -1856,12 +1856,13 @@ AttnShape attn_fwd_shape(int B, int S, int nh) {
 //   n8 = 288  4 x 1400 tokens, 12 heads   130    123    125    147         n8 = 288  4 x 1501 tokens, 12 heads   129    135    131    157
 //   n8 = 288  4 x 1536 tokens, 12 heads   140    146    143    162         n8 = 280  2 x 1700 tokens, 20 heads   152    147    141    169
 //   n8 = 280  5 x 1792 tokens, 8 heads    155    153    154    175         n8 = 288  3 x 2048 tokens, 12 heads   166    161    152    186
-// (just above 256 tiles of 256 rows it matters how full the last one of a pair is: the tokens of all pairs decide, in 256s)
+// (just above 256 tiles of 256 rows it matters how full the last one of a pair is: the tokens of all pairs decide, in 256s; in a loop of its own the backward
+// of 5 x 1792 tokens of 8 heads takes 157 and 150 with 256 rows and with 128 in 2 parts, of 4 x 1501 of 12 138 and 139, of 4 x 1153 of 14 115 and 111)
 AttnShape attn_bwd_shape(int B, int S, int nh) {
   const AttnTiles t(B, S, nh);
   if (S <= 640) return t.whole_rows(S);
   if (t.n <= (S >= 4096 ? 640 : S >= 1536 ? 512 : 256 + (S - 640) / 6)) return {64, 4};
-  if (S > 1024 && t.n4 > 256 && t.n8 <= 288 && (S >= 2048 || S * t.pairs <= 272 * 256)) return {128, 2};
+  if (S > 1024 && t.n4 > 256 && t.n8 <= 288 && (S >= 2048 || S * t.pairs <= 280 * 256)) return {128, 2};
   return t.whole_rows(S);
 }
 

@@ -240,7 +240,8 @@ __device__ __forceinline__ void store_elements(const f32x4_t (&acc)[FM][FN], uns
 // being read and a few blocks of the next slice of 32 rows are written.  Nothing waits: LDS instructions of one wavefront are carried out in
 // order.  (Slice by slice, write - wait - read - store, with the
 // questions what the result is combined with asked in every pass, us: 4503 x 5632 x 1024 52.6, now 51.6, 4503 x 3072 x 1024 with a residual 31.7 and 30.9, the backward of 65536 x 2048 x 5632
-// into the shard 2191 and 2164, of 16384 x 8192 x 8192 2942 and 2925.  The rest is the stores': 2.6 us of a bf16 tile's 27 at K = 1024, whatever else is in
+// into the shard 2191 and 2164, of 16384 x 8192 x 8192 2942 and 2925, each in a loop of its own; of a layer's backward at that size, 16.3 ms, nothing of it can be
+// told from noise, nor of a forward's products at H = 1024.  The rest is the stores': 2.6 us of a bf16 tile's 27 at K = 1024, whatever else is in
 // flight - a chip full of tiles is bound by power, and bytes moved beside products are not free.)
 //
 // EDGE: the same for a block that reaches over the edge of C (rows and columns of C: `rows`, `cols` from the block's corner on, cols a multiple
